@@ -1,118 +1,414 @@
 // Adversarial training step of a draft head (section 3.2, Algorithm 1, Eq. 5 and 6) in fp32: the
 // discriminator's forward and backward passes with its gradient-descent update, the draft-head loss and its
 // gradient at the logits, and the forward pass / backward pass / update of a Medusa-style head.  Dense
-// products run on the fp32 matrix pipe (16x16x4 MFMA); everything else is small row-wise kernels.
+// products run on the matrix pipe with fp32 operands cut into three bfloat16 pieces; the rest is small row-wise kernels.
 #include <math.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "koala_internal.h"
 
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+struct __attribute__((packed, aligned(4))) f32x4_any { float x, y, z, w; };   // 16 bytes at a 4-byte aligned address
+struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 
 // ---------------------------------------------------------------------------------------------
-// C[M,N] = alpha * sum_k A(m,k) B(k,n) + beta * C[m,n]; A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn],
-// C row-major with leading dimension ldc.  Workgroup = 4 waves on a 64 x 64 tile, each wave 32 x 32 as 2 x 2
-// MFMA tiles, K in chunks of 16 through LDS.  MFMA 16x16x4 operands: lane (i = l%16, k = l/16) holds A[i][k]
-// and B[k][i]; the result lane holds C[4*(l/16) + r][l%16], r = 0..3.
+// fp32 products on the 16-bit matrix pipe: C[M,N] (+)= alpha * sum_k Q(m,k) P(n,k).
+//
+// A float is the exact sum of three bfloat16 values (its 24 significant bits in three runs of eight: truncate,
+// subtract, truncate, subtract; every step is exact), so a product of two floats is the sum of nine bfloat16 products,
+// each exact in the fp32 accumulator of the MFMA.  Six of them are kept; the other three are below 2^-22 of the
+// product each and 2^-24 on average, one rounding of the fp32 sum.  Six 16x16x32 MFMAs (16 cycles each) do the work of
+// eight 16x16x4 fp32 MFMAs (32 cycles each), so the pipe is 2.7 times as fast as in fp32, and each accumulator is
+// rounded once per 32 terms and plane pair instead of once per four terms: the sums come out closer to the exact ones.
+//
+// Workgroup of 256 threads on a tile of 64 n x BM m; K in chunks of 32.  Both operands of a chunk go from memory to
+// registers (two chunks ahead, so that about 50 KB a compute unit are under way), are cut into their three planes there
+// and put into LDS as MFMA fragments, double-buffered with one barrier a chunk.  P is the MFMA's row operand: a lane then
+// holds four consecutive n of one m, a 16-byte piece of a row of C.
+//   operand k-contiguous (KS false): element (i, k) at i * ld + k;  8 threads x 16 B cover 128 B of a row
+//   operand k-strided    (KS true):  element (i, k) at k * ld + i;  a thread takes 8 consecutive k of one or two i, the
+//                                    eight values of a fragment lane
+// LDS plane of a 16-row tile: 64 slots of 16 B, lane (i, g = k/8) in slot (i ^ 4 g) + 16 g: the 8-byte stores of 32 lanes of
+// the k-contiguous form (four rows, all g) then fall into different banks.
+// Rows past the end re-read the last one (never stored); k past the end is zero in both operands.  A tile whose operands
+// hold an infinity or not-a-number is summed again in plain fp32, so that those come out as they do there.
+// grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  With part set the
+// split's sums go to part[split][M][N] for k_sum_parts, else to C.  ACC: C += alpha * sum, C fetched before the loop.
+// Measured, with the 64 x 64 fp32-MFMA kernel this replaced: 40 x 1024 from K = 32000 4063 -> 55 us (31 splits), 128 x 4096
+// from K = 32000 4396 -> 311 us (8 splits), 20 x 32000 from K = 4096 590 -> 152 us, 128 x 32000 816 -> 291 us, update of
+// 32000 x 4096 by 20 rows 326 -> 346 us (1 GB moved: 3 TB/s).  Splitting and LDS traffic bound the large ones.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_sgemm(const float *__restrict__ A, long sam, long sak,
-                                               const float *__restrict__ B, long sbk, long sbn, float *C, long ldc,
-                                               int M, int N, int K, float alpha, float beta) {
-    constexpr int LD = 17;
-    __shared__ float As[64 * LD], Bs[64 * LD];   // As[m][k], Bs[n][k]
-    const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64, wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        // 64 x 16 elements of each operand: 4 per thread; the faster-varying index follows the smaller stride
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = tid + 256 * i;
-            const int ma = sak <= sam ? e / 16 : e % 64, ka = sak <= sam ? e % 16 : e / 64;
-            As[ma * LD + ka] = (m0 + ma < M && k0 + ka < K) ? A[(long)(m0 + ma) * sam + (long)(k0 + ka) * sak] : 0.f;
-            const int nb = sbk <= sbn ? e / 16 : e % 64, kb = sbk <= sbn ? e % 16 : e / 64;
-            Bs[nb * LD + kb] = (n0 + nb < N && k0 + kb < K) ? B[(long)(k0 + kb) * sbk + (long)(n0 + nb) * sbn] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            float a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = As[(wm + 16 * i + li) * LD + 4 * kk + lk];
-                b[i] = Bs[(wn + 16 * i + li) * LD + 4 * kk + lk];
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
+enum { X3_BN = 64, X3_BK = 32 };
+
+__device__ __forceinline__ void split3(float a, uint32_t &h, uint32_t &m, uint32_t &l, bool &odd) {
+    h = __float_as_uint(a);
+    const float r = a - __uint_as_float(h & 0xFFFF0000u);
+    m = __float_as_uint(r);
+    l = __float_as_uint(r - __uint_as_float(m & 0xFFFF0000u));
+    odd |= !__builtin_isfinite(a);
+}
+// the upper halves of two words as one (first value in the lower half)
+__device__ __forceinline__ uint32_t upper_pair(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// One operand's share of a chunk in a thread's registers, and its way into LDS.  T rows (32, 64 or 128).
+template <int T, bool KS, int DEPTH>
+struct X3Loader {
+    static constexpr int PER = KS && T == 32 ? 8 : T * X3_BK / 256;   // floats per thread (KS, 32 rows: of half of them)
+    static constexpr int TILE = 64;                          // 16-byte units of a plane of one 16-row tile
+    const float *p;
+    long ld;
+    int rows, i0, K;
+    float v[DEPTH][PER];
+
+    __device__ __forceinline__ void init(const float *base, long ld_, int rows_, int i0_, int K_) {
+        p = base; ld = ld_; rows = rows_; i0 = i0_; K = K_;
     }
+    template <int SLOT>
+    __device__ __forceinline__ void load(int k0) {
+        const int t = threadIdx.x;
+        float *d = v[SLOT];
+        if (!KS) {
+            const int k = k0 + 4 * (t & 7);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int q = 0; q < T / 32; ++q) {
+                const float *src = p + (long)min(i0 + (t >> 3) + 32 * q, rows - 1) * ld + k;
+                if (k0 + X3_BK <= K) {
+                    const f32x4_any w = *(const f32x4_any *)src;
+                    d[4 * q] = w.x; d[4 * q + 1] = w.y; d[4 * q + 2] = w.z; d[4 * q + 3] = w.w;
+                } else {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm + 16 * i + 4 * lk + r, n = n0 + wn + 16 * j + li;
-                if (m < M && n < N) {
-                    float *c = C + (long)m * ldc + n;
-                    *c = alpha * acc[i][j][r] + (beta != 0.f ? beta * *c : 0.f);
+                    for (int e = 0; e < 4; ++e) d[4 * q + e] = k + e < K ? src[e] : 0.f;
                 }
             }
+        } else {
+            constexpr int W = T / 64 > 0 ? T / 64 : 1;       // consecutive i per thread
+            const int g = t / (T / W), i = (t % (T / W)) * W;
+            if (T / W * 4 < 256 && g > 3) return;            // T = 32: half of the threads
+            const bool whole = i0 + T <= rows;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = k0 + 8 * g + e;
+                const float *src = p + (long)min(k, K - 1) * ld;
+                if (W == 2 && whole) {
+                    const f32x2_any w = *(const f32x2_any *)(src + i0 + i);
+                    d[e] = k < K ? w.x : 0.f;
+                    d[(W - 1) * 8 + e] = k < K ? w.y : 0.f;
+                } else {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        const float x = src[min(i0 + i + w, rows - 1)];
+                        d[w * 8 + e] = k < K ? x : 0.f;
+                    }
+                }
+            }
+        }
+    }
+    template <int SLOT>
+    __device__ __forceinline__ void store(u32x4 *lds, bool &odd) const {   // planes [3][T/16][64]
+        const int t = threadIdx.x;
+        const float *d = v[SLOT];
+        if (!KS) {
+            const int g = (t & 7) >> 1;
+#pragma unroll
+            for (int q = 0; q < T / 32; ++q) {
+                const int i = (t >> 3) + 32 * q;
+                uint32_t h[4], m[4], l[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) split3(d[4 * q + e], h[e], m[e], l[e], odd);
+                unsigned char *dst = (unsigned char *)(lds + (i >> 4) * TILE + ((i & 15) ^ (4 * g)) + 16 * g) + 8 * (t & 1);
+                constexpr int PL = (T / 16) * TILE * 16;
+                *(u32x2 *)dst = (u32x2){upper_pair(h[0], h[1]), upper_pair(h[2], h[3])};
+                *(u32x2 *)(dst + PL) = (u32x2){upper_pair(m[0], m[1]), upper_pair(m[2], m[3])};
+                *(u32x2 *)(dst + 2 * PL) = (u32x2){upper_pair(l[0], l[1]), upper_pair(l[2], l[3])};
+            }
+        } else {
+            constexpr int W = T / 64 > 0 ? T / 64 : 1;
+            const int g = t / (T / W), i = (t % (T / W)) * W;
+            if (T / W * 4 < 256 && g > 3) return;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                uint32_t h[8], m[8], l[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) split3(d[w * 8 + e], h[e], m[e], l[e], odd);
+                u32x4 *dst = lds + ((i + w) >> 4) * TILE + (((i + w) & 15) ^ (4 * g)) + 16 * g;
+                dst[0] = (u32x4){upper_pair(h[0], h[1]), upper_pair(h[2], h[3]), upper_pair(h[4], h[5]), upper_pair(h[6], h[7])};
+                dst[(T / 16) * TILE] = (u32x4){upper_pair(m[0], m[1]), upper_pair(m[2], m[3]), upper_pair(m[4], m[5]), upper_pair(m[6], m[7])};
+                dst[2 * (T / 16) * TILE] = (u32x4){upper_pair(l[0], l[1]), upper_pair(l[2], l[3]), upper_pair(l[4], l[5]), upper_pair(l[6], l[7])};
+            }
+        }
+    }
+};
+
+template <int BM, bool PKS, bool QKS, bool ACC, int DEPTH>
+__global__ __launch_bounds__(256, 2) void k_gemm_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q,
+                                                    long ldq, float *C, long ldc, float *part, int M, int N, int K,
+                                                    float alpha, int vec) {
+    constexpr int WN = BM == 32 ? 4 : 2, WM = 4 / WN;        // waves along n and m
+    constexpr int TN = X3_BN / 16 / WN, TM = BM / 16 / WM;   // accumulator tiles of a wave
+    constexpr int PU = 3 * (X3_BN / 16) * 64, QU = 3 * (BM / 16) * 64;   // 16-byte units of a chunk's planes
+    extern __shared__ __attribute__((aligned(16))) u32x4 x3_lds[];   // [2][PU + QU]
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
+    const int wn = wave % WN, wm = wave / WN;
+    const int nmb = (M + BM - 1) / BM, ntile = (N + X3_BN - 1) / X3_BN;
+    const int die = blockIdx.x & 7, rnd = blockIdx.x >> 3;
+    const int nt = (rnd / nmb) * 8 + die, mb = rnd % nmb;
+    if (nt >= ntile) return;                                 // the grid is padded to whole rounds of eight
+    const int n0 = nt * X3_BN, m0 = mb * BM;
+    const int nch = (K + X3_BK - 1) / X3_BK, S = gridDim.y;
+    const int c0 = (int)((unsigned)(blockIdx.y * nch) / (unsigned)S), c1 = (int)((unsigned)((blockIdx.y + 1) * nch) / (unsigned)S);
+    X3Loader<X3_BN, PKS, DEPTH> lp;
+    X3Loader<BM, QKS, DEPTH> lq;
+    lp.init(P, ldp, N, n0, K);
+    lq.init(Q, ldq, M, m0, K);
+    f32x4 acc[TN][TM], old[ACC ? TN : 1][ACC ? TM : 1];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&](int c, auto sc) __attribute__((always_inline)) {
+        constexpr int B = decltype(sc)::value;
+        if (c < c1) { lp.template load<B>(c * X3_BK); lq.template load<B>(c * X3_BK); }
+    };
+    fetch(c0, std::integral_constant<int, 0>{});
+    fetch(c0 + 1, std::integral_constant<int, 1>{});
+    if constexpr (DEPTH == 4) {
+        fetch(c0 + 2, std::integral_constant<int, 2>{});
+        fetch(c0 + 3, std::integral_constant<int, 3>{});
+    }
+    if (ACC) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j) {
+                const int m = m0 + (wm * TM + j) * 16 + li, n = n0 + (wn * TN + i) * 16 + 4 * lg;
+                const float *c = C + (long)m * ldc + n;
+                old[ACC ? i : 0][ACC ? j : 0] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                if (m < M) {
+                    if (vec && n + 4 <= N) old[ACC ? i : 0][ACC ? j : 0] = *(const f32x4 *)c;
+                    else
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (n + r < N) old[ACC ? i : 0][ACC ? j : 0][r] = c[r];
+                }
+            }
+    }
+    const int slot = (li ^ (4 * lg)) + 16 * lg;
+    bool odd = false;   // an infinity or not-a-number was met
+    auto chunk = [&](int c, auto sc) __attribute__((always_inline)) {
+        constexpr int B = decltype(sc)::value;
+        u32x4 *lds = x3_lds + (B & 1) * (PU + QU);
+        lp.template store<B>(lds, odd);
+        lq.template store<B>(lds + PU, odd);
+        fetch(c + DEPTH, sc);
+        // a bare barrier behind this wave's LDS writes: the fence of __syncthreads would wait for the loads too
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        bf16x8 a[3][TN], b[3][TM];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+                a[pl][i] = __builtin_bit_cast(bf16x8, lds[(pl * (X3_BN / 16) + wn * TN + i) * 64 + slot]);
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+                b[pl][j] = __builtin_bit_cast(bf16x8, lds[PU + (pl * (BM / 16) + wm * TM + j) * 64 + slot]);
+        }
+        // small terms first
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+        for (int z = 0; z < 6; ++z)
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[z]][i], b[PB[z]][j], acc[i][j], 0, 0, 0);
+    };
+    static_assert(DEPTH == 2 || DEPTH == 4, "a chunk's registers and its LDS buffer go by the chunk number");
+    for (int c = c0; c < c1; c += DEPTH) {
+        chunk(c, std::integral_constant<int, 0>{});
+        if (c + 1 < c1) chunk(c + 1, std::integral_constant<int, 1>{});
+        if constexpr (DEPTH == 4) {
+            if (c + 2 < c1) chunk(c + 2, std::integral_constant<int, 2>{});
+            if (c + 3 < c1) chunk(c + 3, std::integral_constant<int, 3>{});
+        }
+    }
+    if (__syncthreads_or(odd)) {
+        // the pieces of an infinity times zero pieces would be no numbers: such a tile is summed in plain fp32 instead
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j) {
+                const int m = min(m0 + (wm * TM + j) * 16 + li, M - 1), n = n0 + (wn * TN + i) * 16 + 4 * lg;
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int k = c0 * X3_BK; k < min(K, c1 * X3_BK); ++k) {
+                    const float q = Q[QKS ? (long)k * ldq + m : (long)m * ldq + k];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const long nn = min(n + r, N - 1);
+                        v[r] = fmaf(q, P[PKS ? (long)k * ldp + nn : nn * ldp + k], v[r]);
+                    }
+                }
+                acc[i][j] = v;
+            }
+    }
+    float *out = part ? part + (long)blockIdx.y * M * N : C;
+    const long ldo = part ? N : ldc;
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            const int m = m0 + (wm * TM + j) * 16 + li, n = n0 + (wn * TN + i) * 16 + 4 * lg;
+            if (m >= M) continue;
+            f32x4 v = acc[i][j] * alpha;
+            if (ACC) v += old[ACC ? i : 0][ACC ? j : 0];
+            float *o = out + (long)m * ldo + n;
+            if (vec && n + 4 <= N) *(f32x4 *)o = v;
+            else
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (n + r < N) o[r] = v[r];
+        }
 }
 
-void sgemm(hipStream_t st, const float *A, long sam, long sak, const float *B, long sbk, long sbn, float *C, long ldc,
-           int M, int N, int K, float alpha, float beta) {
-    k_sgemm<<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, st>>>(A, sam, sak, B, sbk, sbn, C, ldc, M, N, K, alpha, beta);
+// How many K splits give about two workgroups a compute unit, at least four chunks each, and fit `room` floats of partial
+// sums (none: one split, straight into C)
+int x3_splits(int M, int N, int K, size_t room) {
+    const long bm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
+    const long tiles = (long)((N + X3_BN - 1) / X3_BN) * ((M + bm - 1) / bm), nch = (K + X3_BK - 1) / X3_BK;
+    long S = tiles >= 384 ? 1 : (512 + tiles / 2) / tiles;
+    S = std::min({S, nch / 4, (long)(room / ((size_t)M * N)), 32L});
+    return S < 2 ? 1 : (int)S;
+}
+
+template <int BM, bool PKS, bool QKS, bool ACC>
+void launch_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *C, long ldc, float *part, int S,
+               int M, int N, int K, float alpha) {
+    const size_t sm = (size_t)2 * 3 * (X3_BN + BM) / 16 * 64 * 16;
+    constexpr int DEPTH = !ACC && BM <= 64 ? 4 : 2;
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_gemm_x3<BM, PKS, QKS, ACC, DEPTH>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    (void)attr;   // a failure shows at the launch
+    const long ldo = part ? N : ldc;
+    const int vec = ldo % 4 == 0 && ((uintptr_t)(part ? part : C) & 15) == 0 && (!part || (size_t)M * N % 4 == 0);
+    const dim3 grid(((N + X3_BN - 1) / X3_BN + 7) / 8 * 8 * ((M + BM - 1) / BM), S);
+    k_gemm_x3<BM, PKS, QKS, ACC, DEPTH><<<grid, 256, sm, st>>>(P, ldp, Q, ldq, C, ldc, part, M, N, K, alpha, vec);
+}
+template <bool PKS, bool QKS, bool ACC>
+void gemm_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *C, long ldc, float *part, int S,
+             int M, int N, int K, float alpha) {
+    if (M <= 32) launch_x3<32, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
+    else if (M <= 64) launch_x3<64, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
+    else launch_x3<128, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
+}
+// C[M,N] = X[M,K] W[N,K]^T, split sums to part (S > 1) or straight to C
+void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
+    gemm_x3<false, false, false>(st, W, K, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
+}
+// C[M,N] = X[M,K] W[K,N]
+void gemm_nn(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
+    gemm_x3<true, false, false>(st, W, N, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
+}
+// W[M,N] -= lr * G[rows,M]^T X[rows,N]
+void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr) {
+    gemm_x3<true, true, true>(st, X, N, G, M, W, N, nullptr, 1, M, N, rows, -lr);
+}
+
+// The S split sums of element i added in split order, and the element-wise step that follows the product:
+//   SUM_ONLY  out = sum;  SUM_BASE  out = base + sum;
+//   SUM_RELU  out = sum + bias[column] (the pre-activation), out2 = max(out, 0);
+//   SUM_SILU  out = sum, out2 = base + SiLU(sum).
+// part may be out itself (S = 1).
+enum { SUM_ONLY = 0, SUM_BASE = 1, SUM_RELU = 2, SUM_SILU = 3 };
+template <int MODE>
+__global__ __launch_bounds__(256) void k_sum_parts(const float *part, int S, long count, int N, const float *base,
+                                                   float *out, float *out2) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= count) return;
+    float v = 0.f;
+    int s = 0;
+    for (; s + 8 <= S; s += 8) {
+        float t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = part[(long)(s + u) * count + i];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += t[u];
+    }
+    for (; s < S; ++s) v += part[(long)s * count + i];
+    if (MODE == SUM_BASE) v += base[i];
+    if (MODE == SUM_RELU) { v += base[i % N]; out2[i] = fmaxf(v, 0.f); }
+    if (MODE == SUM_SILU) out2[i] = base[i] + v / (1.0f + expf(-v));
+    out[i] = v;
+}
+template <int MODE>
+void sum_parts(hipStream_t st, const float *part, int S, int M, int N, const float *base, float *out, float *out2) {
+    const long count = (long)M * N;
+    k_sum_parts<MODE><<<(int)((count + 255) / 256), 256, 0, st>>>(part, S, count, N, base, out, out2);
 }
 
 __device__ __forceinline__ float softplus(float x) { return fmaxf(x, 0.f) + log1pf(expf(-fabsf(x))); }
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + expf(-x)); }
 
-// sum over the workgroup (256 threads); every thread gets the total
+// sum / maximum over the workgroup of NW waves; every thread gets it
+template <int NW = 4>
 __device__ __forceinline__ float block_sum(float v, float *sh) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    float t[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t[w] = sh[w];
+#pragma unroll
+    for (int h = NW / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int w = 0; w < h; ++w) t[w] += t[w + h];
+    return t[0];
 }
+template <int NW = 4>
 __device__ __forceinline__ float block_max(float v, float *sh) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+    float t = sh[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t = fmaxf(t, sh[w]);
+    return t;
 }
 
-// u[r][v] = z[r % n][v] + (r < n ? la : lb)[r % n][v]: the mapped hidden state joined to a logits row
-__global__ void k_join(const float *z, const float *la, const float *lb, float *u, int n, int V, int rows) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long)rows * V) return;
-    const int r = (int)(i / V), v = (int)(i % V), p = r % n;
-    u[i] = z[(long)p * V + v] + (r < n ? la : lb)[(long)p * V + v];
-}
-
-// y += bias (kept as the pre-activation), a = max(y, 0)
-__global__ void k_bias_relu(float *y, const float *bias, float *a, int rows, int W) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long)rows * W) return;
-    const float v = y[i] + bias[i % W];
-    y[i] = v;
-    a[i] = fmaxf(v, 0.f);
+// The mapped hidden state z[p][v], in two halves z0 + z1 (z1 may be null), joined to a logits row: u[p] = z + la[p] and,
+// with lb, u[n + p] = z + lb[p].  The halves may lie where u does (row p and row n + p).
+__global__ __launch_bounds__(256) void k_join(const float *z0, const float *z1, const float *la, const float *lb, float *u,
+                                              long nV) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= nV) return;
+    float z = z0[i];
+    if (z1) z += z1[i];
+    u[i] = z + la[i];
+    if (lb) u[nV + i] = z + lb[i];
 }
 
 // g[r][j] *= (pre[r][j] > 0)
 __global__ void k_relu_back(float *g, const float *pre, long n) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n && !(pre[i] > 0.f)) g[i] = 0.f;
+}
+
+// s[r] = a[r] . w: the width-1 layer.  One workgroup per row.
+__global__ __launch_bounds__(256) void k_row_dot(const float *a, const float *w, float *s, int W) {
+    __shared__ float sh[4];
+    const float *ar = a + (long)blockIdx.x * W;
+    float v = 0.f;
+    for (int j = threadIdx.x; j < W; j += 256) v += ar[j] * w[j];
+    v = block_sum(v, sh);
+    if (threadIdx.x == 0) s[blockIdx.x] = v;
 }
 
 // bias[j] -= lr * sum_r g[r][j]
@@ -148,11 +444,11 @@ __global__ __launch_bounds__(256) void k_score_loss(const float *s, const float 
     if (threadIdx.x == 0) loss[0] = tot / n;
 }
 
-// g[r][j] = ds[r] * w[j]   (backward of the width-1 layer towards its input)
-__global__ void k_outer(const float *ds, const float *w, float *g, int rows, int W) {
+// g[r][j] = ds[r] * w[j] (backward of the width-1 layer towards its input), zero where the unit was off (pre, if given)
+__global__ void k_outer(const float *ds, const float *w, const float *pre, float *g, int rows, int W) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long)rows * W) return;
-    g[i] = ds[i / W] * w[i % W];
+    g[i] = pre && !(pre[i] > 0.f) ? 0.f : ds[i / W] * w[i % W];
 }
 
 // gz[p][v] = gu[p][v] + gu[n + p][v]
@@ -162,32 +458,60 @@ __global__ void k_fold_rows(const float *gu, float *gz, int n, int V) {
 }
 
 // Distillation term (cross-entropy of softmax(d) against softmax(q)) of one row per workgroup:
-// ce[r] = lse(d) - sum_v softmax(q)_v d_v, and grad[r][v] (+)= (softmax(d)_v - softmax(q)_v) / n
-__global__ __launch_bounds__(256) void k_distill(const float *q, const float *d, float *grad, float *ce, int V, int n,
-                                                 int accumulate) {
-    __shared__ float sh[4];
-    const int r = blockIdx.x;
-    const float *qr = q + (long)r * V, *dr = d + (long)r * V;
+// ce[r] = lse(d) - sum_v softmax(q)_v d_v, and grad[r][v] = base[r][v] + (softmax(d)_v - softmax(q)_v) / n.
+// A row of both logits is read once into registers (up to 32 of each per thread, 32768 columns; longer rows read the
+// rest again) with all loads in flight; one workgroup of 256 threads reading a row three times took 182 us for 128 rows
+// of 32000, this form 40 us.
+__global__ __launch_bounds__(1024) void k_distill(const float *q, const float *d, const float *base, float *grad, float *ce,
+                                                  int V, int n) {
+    constexpr int NR = 32, NT = 1024;
+    __shared__ float sh[16];
+    const int r = blockIdx.x, t = threadIdx.x;
+    const float *qr = q + (long)r * V, *dr = d + (long)r * V, *br = base + (long)r * V;
+    float qv[NR], dv[NR];
     float mq = -INFINITY, md = -INFINITY;
-    for (int v = threadIdx.x; v < V; v += 256) { mq = fmaxf(mq, qr[v]); md = fmaxf(md, dr[v]); }
-    mq = block_max(mq, sh);
-    md = block_max(md, sh);
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        const unsigned v = t + u * NT;
+        qv[u] = v < (unsigned)V ? qr[v] : -INFINITY;
+        dv[u] = v < (unsigned)V ? dr[v] : -INFINITY;
+    }
+#pragma unroll
+    for (int u = 0; u < NR; ++u) { mq = fmaxf(mq, qv[u]); md = fmaxf(md, dv[u]); }
+    for (int v = NR * NT + t; v < V; v += NT) { mq = fmaxf(mq, qr[v]); md = fmaxf(md, dr[v]); }
+    mq = block_max<16>(mq, sh);
+    md = block_max<16>(md, sh);
     float sq = 0.f, sd = 0.f, qd = 0.f;
-    for (int v = threadIdx.x; v < V; v += 256) {
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        if (t + u * NT < V) {
+            const float eq = expf(qv[u] - mq), ed = expf(dv[u] - md);
+            sq += eq;
+            sd += ed;
+            qd += eq * dv[u];
+            qv[u] = eq;
+            dv[u] = ed;
+        }
+        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few at a time: the registers hold the row
+    }
+    for (int v = NR * NT + t; v < V; v += NT) {
         const float eq = expf(qr[v] - mq);
         sq += eq;
         sd += expf(dr[v] - md);
         qd += eq * dr[v];
     }
-    sq = block_sum(sq, sh);
-    sd = block_sum(sd, sh);
-    qd = block_sum(qd, sh);
-    if (threadIdx.x == 0) ce[r] = (md + logf(sd)) - qd / sq;
+    sq = block_sum<16>(sq, sh);
+    sd = block_sum<16>(sd, sh);
+    qd = block_sum<16>(qd, sh);
+    if (t == 0) ce[r] = (md + logf(sd)) - qd / sq;
     float *gr = grad + (long)r * V;
-    for (int v = threadIdx.x; v < V; v += 256) {
-        const float g = (expf(dr[v] - md) / sd - expf(qr[v] - mq) / sq) / n;
-        gr[v] = accumulate ? gr[v] + g : g;
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        const int v = t + u * NT;
+        if (v < V) gr[v] = br[v] + (dv[u] / sd - qv[u] / sq) / n;
+        if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
+    for (int v = NR * NT + t; v < V; v += NT) gr[v] = br[v] + (expf(dr[v] - md) / sd - expf(qr[v] - mq) / sq) / n;
 }
 
 // loss[0] = mean of ce[0..n)
@@ -197,12 +521,6 @@ __global__ __launch_bounds__(256) void k_mean(const float *ce, float *loss, int 
     for (int r = threadIdx.x; r < n; r += 256) t += ce[r];
     t = block_sum(t, sh);
     if (threadIdx.x == 0) loss[0] = t / n;
-}
-
-// x_next = x + SiLU(y)
-__global__ void k_res_silu(const float *x, const float *y, float *xn, long n) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) xn[i] = x[i] + y[i] / (1.0f + expf(-y[i]));
 }
 
 // gy = gx * SiLU'(y)
@@ -260,34 +578,53 @@ bool params_ok(const koala_disc_shape *s, const koala_disc_params *p) {
 inline int fc_in(const koala_disc_shape &s, int k) { return k == 0 ? s.vocab : s.fc_hidden; }
 inline int fc_out(const koala_disc_shape &s, int k) { return k == s.n_fc - 1 ? 1 : s.fc_hidden; }
 
-// scores of `rows` joined rows u: leaves every layer's input and pre-activation in the workspace, s = w_last . a
-void disc_forward(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int rows) {
+// z = h W_lin^T joined to one or two sets of logits rows.  Two K splits, whose sums lie where u will: twice the
+// workgroups, so twice the bytes under way (20 rows, 32000 x 4096: 169 us with one split, 152 us with two).
+void disc_join(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, const float *h,
+               const float *la, const float *lb) {
+    const long nV = (long)n * s.vocab;
+    const int S = n <= 64 && s.hidden >= 8 * X3_BK ? 2 : 1;
+    gemm_nt(st, h, p.w_lin, w.z, w.u, S, n, s.vocab, s.hidden);
+    k_join<<<blocks(nV), 256, 0, st>>>(S == 2 ? w.u : w.z, S == 2 ? w.u + nV : nullptr, la, lb, w.u, nV);
+}
+
+// scores of `rows` joined rows u: leaves every layer's input and pre-activation in the workspace, s = w_last . a.
+// g[0], which only the backward pass fills, holds the split sums of the inner layers.
+void disc_forward(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, int rows) {
     for (int k = 0; k < s.n_fc; ++k) {
         const int in = fc_in(s, k), out = fc_out(s, k);
-        if (k == s.n_fc - 1) {   // width 1: s[r] = a[r] . w (bias added where the score is used)
-            sgemm(st, w.a[k], in, 1, p.w_fc[k], 1, in, w.s, 1, rows, 1, in, 1.f, 0.f);
+        if (k == s.n_fc - 1) {   // width 1 (bias added where the score is used)
+            k_row_dot<<<rows, 256, 0, st>>>(w.a[k], p.w_fc[k], w.s, in);
         } else {
-            sgemm(st, w.a[k], in, 1, p.w_fc[k], 1, in, w.pre[k], out, rows, out, in, 1.f, 0.f);
-            k_bias_relu<<<blocks((long)rows * out), 256, 0, st>>>(w.pre[k], p.b_fc[k], w.a[k + 1], rows, out);
+            const int S = x3_splits(rows, out, in, (size_t)2 * n * s.vocab);
+            gemm_nt(st, w.a[k], p.w_fc[k], w.pre[k], w.g[0], S, rows, out, in);
+            sum_parts<SUM_RELU>(st, S > 1 ? w.g[0] : w.pre[k], S, rows, out, p.b_fc[k], w.pre[k], w.a[k + 1]);
         }
     }
 }
 
 // from ds (dL/ds per row) back to g[0] = dL/du; lr > 0: the parameters are updated on the way (each layer's
-// input gradient is taken with the layer's old weights first)
-void disc_backward(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int rows,
+// input gradient is taken with the layer's old weights first).  z (the mapped hidden state, no longer needed) holds the
+// split sums of the inner layers' input gradients.
+void disc_backward(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, int rows,
                    float lr) {
     for (int k = s.n_fc - 1; k >= 0; --k) {
         const int in = fc_in(s, k), out = fc_out(s, k);
         const float *gout = k == s.n_fc - 1 ? w.ds : w.g[k + 1];   // dL/d(pre of layer k): [rows, out]
-        if (k == s.n_fc - 1) k_outer<<<blocks((long)rows * in), 256, 0, st>>>(w.ds, p.w_fc[k], w.g[k], rows, in);
-        else sgemm(st, gout, out, 1, p.w_fc[k], in, 1, w.g[k], in, rows, in, out, 1.f, 0.f);
+        const float *pre = k > 0 ? w.pre[k - 1] : nullptr;
+        if (k == s.n_fc - 1) {
+            k_outer<<<blocks((long)rows * in), 256, 0, st>>>(w.ds, p.w_fc[k], pre, w.g[k], rows, in);
+        } else {
+            const int S = x3_splits(rows, in, out, (size_t)n * s.vocab);
+            gemm_nn(st, gout, p.w_fc[k], w.g[k], w.z, S, rows, in, out);
+            if (S > 1) sum_parts<SUM_ONLY>(st, w.z, S, rows, in, nullptr, w.g[k], nullptr);
+            if (pre) k_relu_back<<<blocks((long)rows * in), 256, 0, st>>>(w.g[k], pre, (long)rows * in);
+        }
         if (lr > 0.f) {
             // W_k[out, in] -= lr * gout^T a_k ;  b_k -= lr * column sums of gout
-            sgemm(st, gout, 1, out, w.a[k], in, 1, p.w_fc[k], in, out, in, rows, -lr, 1.f);
+            gemm_update(st, gout, w.a[k], p.w_fc[k], out, in, rows, lr);
             k_bias_update<<<blocks(out), 256, 0, st>>>(p.b_fc[k], gout, rows, out, lr);
         }
-        if (k > 0) k_relu_back<<<blocks((long)rows * in), 256, 0, st>>>(w.g[k], w.pre[k - 1], (long)rows * in);
     }
 }
 
@@ -314,15 +651,14 @@ koala_status koala_train_disc_step(const koala_disc_shape *shape, const koala_di
     hipStream_t st = (hipStream_t)hip_stream;
     const int n = n_rows, V = s.vocab, H = s.hidden, rows = 2 * n;
     // z = h W_lin^T, u = [z + d ; z + q]
-    sgemm(st, h, H, 1, params->w_lin, 1, H, w.z, V, n, V, H, 1.f, 0.f);
-    k_join<<<blocks((long)rows * V), 256, 0, st>>>(w.z, d_logits, q_logits, w.u, n, V, rows);
-    disc_forward(st, s, *params, w, rows);
+    disc_join(st, s, *params, w, n, h, d_logits, q_logits);
+    disc_forward(st, s, *params, w, n, rows);
     k_score_loss<<<1, 256, 0, st>>>(w.s, params->b_fc[s.n_fc - 1], w.ds, loss_out, n, 0, 0.f);
-    disc_backward(st, s, *params, w, rows, lr);
+    disc_backward(st, s, *params, w, n, rows, lr);
     if (lr > 0.f) {
         // u = W_lin h + logits for both halves: dL/dW_lin = (g_u[draft rows] + g_u[target rows])^T h
         k_fold_rows<<<blocks((long)n * V), 256, 0, st>>>(w.g[0], w.z, n, V);
-        sgemm(st, w.z, 1, V, h, H, 1, params->w_lin, H, V, H, n, -lr, 1.f);
+        gemm_update(st, w.z, h, params->w_lin, V, H, n, lr);
     }
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }
@@ -339,51 +675,76 @@ koala_status koala_train_gen_grad(const koala_disc_shape *shape, const koala_dis
     if (workspace_bytes < w.bytes) return KOALA_E_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     const int n = n_rows, V = s.vocab, H = s.hidden;
-    sgemm(st, h, H, 1, params->w_lin, 1, H, w.z, V, n, V, H, 1.f, 0.f);
-    k_join<<<blocks((long)n * V), 256, 0, st>>>(w.z, d_logits, d_logits, w.u, n, V, n);
-    disc_forward(st, s, *params, w, n);
+    disc_join(st, s, *params, w, n, h, d_logits, nullptr);
+    disc_forward(st, s, *params, w, n, n);
     k_score_loss<<<1, 256, 0, st>>>(w.s, params->b_fc[s.n_fc - 1], w.ds, loss_out, n, 1, lambda);
-    disc_backward(st, s, *params, w, n, 0.f);
+    disc_backward(st, s, *params, w, n, n, 0.f);
     // dL_G/dd = dL_adv/du (u = z + d) + the distillation term's gradient
-    if (hipMemcpyAsync(grad_d, w.g[0], (size_t)n * V * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return KOALA_E_DEVICE;
-    k_distill<<<n, 256, 0, st>>>(q_logits, d_logits, grad_d, w.ce, V, n, 1);
+    k_distill<<<n, 1024, 0, st>>>(q_logits, d_logits, w.g[0], grad_d, w.ce, V, n);
     k_mean<<<1, 256, 0, st>>>(w.ce, loss_out + 1, n);
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }
 
+// Medusa workspace, in slots of n_rows * hidden floats: x_1 .. x_K, y_0 .. y_{K-1}, gx, gx', gy and one spare, as many as
+// a call needs at least, then MED_PARTS slots of split sums.  A workspace without those is accepted as well: the
+// products then run unsplit, on fewer compute units.
+enum { MED_PARTS = 8 };
+static size_t med_slot(int n_rows, int hidden) { return up256((size_t)n_rows * hidden * sizeof(float)); }
+static size_t med_need(int n_rows, int hidden, int K) { return med_slot(n_rows, hidden) * (size_t)(2 * K + 4); }
+
 koala_status koala_train_medusa_workspace_bytes(int n_rows, int hidden, int K, size_t *out) {
     if (!out) return KOALA_E_NULL;
     if (n_rows < 1 || hidden < 1 || K < 1 || K > 8) return KOALA_E_SHAPE;
-    // x_0 .. x_K, y_0 .. y_{K-1}, gx, gx', gy
-    *out = up256((size_t)n_rows * hidden * sizeof(float)) * (size_t)(2 * K + 4);
+    *out = med_need(n_rows, hidden, K) + MED_PARTS * med_slot(n_rows, hidden);
     return KOALA_OK;
 }
 
-static void medusa_forward(hipStream_t st, int n, int H, int K, float *const *blocks_w, const float *h, float *xs,
-                           float *ys, size_t stride) {
-    (void)hipMemcpyAsync(xs, h, (size_t)n * H * sizeof(float), hipMemcpyDeviceToDevice, st);
+struct MedWs {
+    float *x[9], *y[8], *gx, *gx2, *gy, *part;
+    size_t room;   // floats at part
+};
+static MedWs med_carve(int n, int H, int K, const float *h, void *workspace, size_t bytes) {
+    const size_t slot = med_slot(n, H) / sizeof(float);
+    MedWs w{};
+    float *p = (float *)workspace;
+    w.x[0] = const_cast<float *>(h);
+    for (int k = 1; k <= K; ++k) w.x[k] = p + slot * k;
+    for (int k = 0; k < K; ++k) w.y[k] = p + slot * (K + 1 + k);
+    w.gx = p + slot * (2 * K + 1);
+    w.gx2 = w.gx + slot;
+    w.gy = w.gx2 + slot;
+    w.part = w.gy + slot;
+    w.room = (bytes - med_need(n, H, K)) / sizeof(float);
+    return w;
+}
+
+static void medusa_forward(hipStream_t st, int n, int H, int K, float *const *blocks_w, const MedWs &w) {
+    const int S = x3_splits(n, H, H, w.room);
     for (int k = 0; k < K; ++k) {
-        float *x = xs + stride * k, *y = ys + stride * k;
-        sgemm(st, x, H, 1, blocks_w[k], 1, H, y, H, n, H, H, 1.f, 0.f);
-        k_res_silu<<<blocks((long)n * H), 256, 0, st>>>(x, y, xs + stride * (k + 1), (long)n * H);
+        gemm_nt(st, w.x[k], blocks_w[k], w.y[k], w.part, S, n, H, H);
+        sum_parts<SUM_SILU>(st, S > 1 ? w.part : w.y[k], S, n, H, w.x[k], w.y[k], w.x[k + 1]);
     }
+}
+
+static koala_status med_check(int n_rows, int hidden, int vocab, int K, float *const *blocks_w, size_t workspace_bytes,
+                              float lr) {
+    if (n_rows < 1 || hidden < 1 || K < 1 || K > 8 || vocab < 1 || !(lr >= 0.f)) return KOALA_E_SHAPE;
+    if (workspace_bytes < med_need(n_rows, hidden, K)) return KOALA_E_WORKSPACE;
+    for (int k = 0; k < K; ++k)
+        if (!blocks_w[k]) return KOALA_E_NULL;
+    return KOALA_OK;
 }
 
 koala_status koala_train_medusa_head_forward(void *hip_stream, int n_rows, int hidden, int vocab, int K,
                                              float *const *blocks_w, const float *w_lm, const float *h,
                                              void *workspace, size_t workspace_bytes, float *d_logits) {
     if (!blocks_w || !w_lm || !h || !workspace || !d_logits) return KOALA_E_NULL;
-    size_t need = 0;
-    if (koala_train_medusa_workspace_bytes(n_rows, hidden, K, &need) != KOALA_OK || vocab < 1) return KOALA_E_SHAPE;
-    if (workspace_bytes < need) return KOALA_E_WORKSPACE;
-    for (int k = 0; k < K; ++k)
-        if (!blocks_w[k]) return KOALA_E_NULL;
+    const koala_status rc = med_check(n_rows, hidden, vocab, K, blocks_w, workspace_bytes, 0.f);
+    if (rc != KOALA_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
-    const size_t stride = up256((size_t)n_rows * hidden * sizeof(float)) / sizeof(float);
-    float *xs = (float *)workspace, *ys = xs + stride * (K + 1);
-    medusa_forward(st, n_rows, hidden, K, blocks_w, h, xs, ys, stride);
-    sgemm(st, xs + stride * K, hidden, 1, w_lm, 1, hidden, d_logits, vocab, n_rows, vocab, hidden, 1.f, 0.f);
+    const MedWs w = med_carve(n_rows, hidden, K, h, workspace, workspace_bytes);
+    medusa_forward(st, n_rows, hidden, K, blocks_w, w);
+    gemm_nt(st, w.x[K], w_lm, d_logits, nullptr, 1, n_rows, vocab, hidden);
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }
 
@@ -391,26 +752,23 @@ koala_status koala_train_medusa_head_step(void *hip_stream, int n_rows, int hidd
                                           float *const *blocks_w, const float *w_lm, const float *h,
                                           const float *grad_d, float lr, void *workspace, size_t workspace_bytes) {
     if (!blocks_w || !w_lm || !h || !grad_d || !workspace) return KOALA_E_NULL;
-    size_t need = 0;
-    if (koala_train_medusa_workspace_bytes(n_rows, hidden, K, &need) != KOALA_OK || vocab < 1 || !(lr >= 0.f))
-        return KOALA_E_SHAPE;
-    if (workspace_bytes < need) return KOALA_E_WORKSPACE;
-    for (int k = 0; k < K; ++k)
-        if (!blocks_w[k]) return KOALA_E_NULL;
+    const koala_status rc = med_check(n_rows, hidden, vocab, K, blocks_w, workspace_bytes, lr);
+    if (rc != KOALA_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     const int n = n_rows, H = hidden, V = vocab;
-    const size_t stride = up256((size_t)n * H * sizeof(float)) / sizeof(float);
-    float *xs = (float *)workspace, *ys = xs + stride * (K + 1), *gx = ys + stride * K, *gx2 = gx + stride,
-          *gy = gx2 + stride;
-    medusa_forward(st, n, H, K, blocks_w, h, xs, ys, stride);
-    sgemm(st, grad_d, V, 1, w_lm, H, 1, gx, H, n, H, V, 1.f, 0.f);                 // gx = grad_d W_lm
+    MedWs w = med_carve(n, H, K, h, workspace, workspace_bytes);
+    medusa_forward(st, n, H, K, blocks_w, w);
+    const int Sv = x3_splits(n, H, V, w.room), Sh = x3_splits(n, H, H, w.room);
+    gemm_nn(st, grad_d, w_lm, w.gx, w.part, Sv, n, H, V);                 // gx = grad_d W_lm
+    if (Sv > 1) sum_parts<SUM_ONLY>(st, w.part, Sv, n, H, nullptr, w.gx, nullptr);
     for (int k = K - 1; k >= 0; --k) {
-        k_silu_back<<<blocks((long)n * H), 256, 0, st>>>(gx, ys + stride * k, gy, (long)n * H);
-        // gx <- gx + gy W_k with the block's old weights, then W_k -= lr * gy^T x_k
-        (void)hipMemcpyAsync(gx2, gx, (size_t)n * H * sizeof(float), hipMemcpyDeviceToDevice, st);
-        sgemm(st, gy, H, 1, blocks_w[k], H, 1, gx2, H, n, H, H, 1.f, 1.f);
-        sgemm(st, gy, 1, H, xs + stride * k, H, 1, blocks_w[k], H, H, H, n, -lr, 1.f);
-        float *t = gx; gx = gx2; gx2 = t;
+        k_silu_back<<<blocks((long)n * H), 256, 0, st>>>(w.gx, w.y[k], w.gy, (long)n * H);
+        if (k > 0) {   // gx <- gx + gy W_k with the block's old weights, for the block below
+            gemm_nn(st, w.gy, blocks_w[k], w.gx2, w.part, Sh, n, H, H);
+            sum_parts<SUM_BASE>(st, Sh > 1 ? w.part : w.gx2, Sh, n, H, w.gx, w.gx2, nullptr);
+            std::swap(w.gx, w.gx2);
+        }
+        gemm_update(st, w.gy, w.x[k], blocks_w[k], H, H, n, lr);             // W_k -= lr * gy^T x_k
     }
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }

@@ -1,0 +1,142 @@
+"""The dense products of the training step at the edges of their tiles (rows 32 / 64 / 128 and one more, columns not
+a multiple of 64, contraction lengths around a chunk of 32, split and unsplit sums) against float64.
+
+Bound: the operands are represented exactly and each accumulator is rounded once per 32 terms and plane pair, so over
+K terms the relative error of a sum of random terms is about sqrt(6 K / 32) 2^-24 of the sum's typical size; four times
+that, at K = 1030, is 3.3e-6 in the 2-norm (the fp32 additions of the splits and of the residual block are fewer)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+TOL = 3.3e-6
+
+
+def _rel(got, ref):
+    got = got.double().cpu().numpy()
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+def _head(n, H, V, K, seed):
+    import torch
+    rng = np.random.default_rng(seed)
+    f32 = lambda a: a.astype(np.float32)
+    blocks = [f32(rng.normal(size=(H, H)) * 0.05) for _ in range(K)]
+    w_lm, h, g = f32(rng.normal(size=(V, H)) * 0.1), f32(rng.normal(size=(n, H))), f32(rng.normal(size=(n, V)) * 0.1)
+    dev = lambda a: torch.from_numpy(a.copy()).cuda()
+    return blocks, w_lm, h, g, dev
+
+
+def _head_ref(blocks, w_lm, h, g, lr):
+    from oracle import train as T
+    b64 = [b.astype(np.float64) for b in blocks]
+    logits, _ = T.medusa_head_forward(b64, w_lm.astype(np.float64), h.astype(np.float64))
+    new, grads = T.medusa_head_step(b64, w_lm.astype(np.float64), h.astype(np.float64), g.astype(np.float64), lr)
+    return logits, grads
+
+
+@pytest.mark.parametrize("n,H,V,K", [(1, 64, 100, 1), (16, 63, 129, 2), (32, 64, 512, 1), (33, 97, 1030, 2), (64, 128, 300, 1),
+                                     (65, 260, 1000, 2), (128, 96, 700, 1), (129, 130, 1030, 2), (300, 65, 260, 1)])
+def test_head_products(n, H, V, K):
+    import torch
+    import paper_2408_08146_amd as KO
+    blocks, w_lm, h, g, dev = _head(n, H, V, K, n + H)
+    lr = 0.5
+    logits, grads = _head_ref(blocks, w_lm, h, g, lr)
+    db = [dev(b) for b in blocks]
+    head = KO.MedusaHeadTrainer(db, dev(w_lm))
+    d = torch.zeros(n, V, device="cuda")
+    head.forward(dev(h), d)
+    assert _rel(d, logits) < TOL
+    head.step(dev(h), dev(g), lr)
+    for k in range(K):
+        # the update is seen through the rounding of the weights themselves: 2^-24 of a weight each
+        upd = db[k].double().cpu().numpy() - blocks[k]
+        floor = 2.0 ** -24 * np.linalg.norm(blocks[k])
+        assert np.linalg.norm(upd + lr * grads[k]) < TOL * 4 * np.linalg.norm(lr * grads[k]) + floor
+
+
+def test_head_with_the_smallest_workspace():
+    """A workspace without room for split sums is accepted (one byte less is not) and gives the same results to rounding."""
+    import torch
+    import paper_2408_08146_amd as KO
+    n, H, V, K = 20, 256, 600, 2
+    blocks, w_lm, h, g, dev = _head(n, H, V, K, 5)
+    slot = (n * H * 4 + 255) // 256 * 256
+    need = slot * (2 * K + 4)
+    head = KO.MedusaHeadTrainer([dev(b) for b in blocks], dev(w_lm))
+    full = torch.zeros(n, V, device="cuda")
+    head.forward(dev(h), full)
+    head._workspace = lambda rows: small
+    small = torch.empty(need, dtype=torch.uint8, device="cuda")
+    d = torch.zeros(n, V, device="cuda")
+    head.forward(dev(h), d)
+    head.step(dev(h), dev(g), 0.1)
+    logits, grads = _head_ref(blocks, w_lm, h, g, 0.1)
+    assert _rel(d, logits) < TOL and _rel(full, logits) < TOL
+    for k in range(K):
+        upd = head.blocks[k].double().cpu().numpy() - blocks[k]
+        assert np.linalg.norm(upd + 0.1 * grads[k]) < 1e-3 * np.linalg.norm(0.1 * grads[k])
+    small = torch.empty(need - 1, dtype=torch.uint8, device="cuda")
+    with pytest.raises(KO.KoalaError):
+        head.forward(dev(h), d)
+
+
+@pytest.mark.parametrize("n,H,V,DH,n_fc", [(1, 64, 100, 0, 1), (16, 33, 1030, 40, 2), (17, 256, 2000, 64, 3), (65, 300, 700, 129, 3)])
+def test_discriminator_products(n, H, V, DH, n_fc):
+    import torch
+    import paper_2408_08146_amd as KO
+    from oracle import train as T
+    rng = np.random.default_rng(n)
+    theta = T.disc_params(rng, H, V, max(DH, 1), n_fc, std=0.05)
+    r32 = lambda a: a.astype(np.float32).astype(np.float64)
+    theta = dict(w_lin=r32(theta["w_lin"]), w_fc=[r32(w) for w in theta["w_fc"]], b_fc=[r32(b) for b in theta["b_fc"]])
+    h, q = r32(rng.normal(size=(n, H))), r32(rng.normal(size=(n, V)))
+    d = r32(q + rng.normal(size=(n, V)))
+    loss_ref, _, grads = T.disc_step(theta, h, q, d, 0.3)
+    dev = lambda a: torch.from_numpy(a.astype(np.float32)).cuda()
+    w_lin, w_fc, b_fc = dev(theta["w_lin"]), [dev(w) for w in theta["w_fc"]], [dev(b) for b in theta["b_fc"]]
+    D = KO.Discriminator(w_lin, w_fc, b_fc, fc_hidden=DH)
+    loss = torch.zeros(1, device="cuda")
+    D.step(dev(h), dev(q), dev(d), 0.3, loss)
+    assert abs(loss.item() - loss_ref) < 1e-5 * abs(loss_ref)
+    for got, old, g in [(w_lin, theta["w_lin"], grads["w_lin"])] + list(zip(w_fc, theta["w_fc"], grads["w_fc"])):
+        upd = got.double().cpu().numpy() - old
+        floor = 2.0 ** -24 * np.linalg.norm(old)
+        # the gradient passes through up to four products and a sigmoid of a sum over V terms
+        assert np.linalg.norm(upd + 0.3 * g) < 3e-5 * np.linalg.norm(0.3 * g) + floor
+
+
+def test_infinite_operand_stays_infinite():
+    """One logit of minus infinity times a negative weight switches the only unit to +inf, whose negative score weight makes
+    the draft row's score -inf and its loss zero; a not-a-number on the way would give the loss of a silent unit."""
+    import torch
+    import paper_2408_08146_amd as KO
+    n, H, V = 4, 32, 96
+    z = lambda *s: torch.zeros(*s, device="cuda")
+    w_fc = [z(1, V), torch.full((1, 1), -1.0, device="cuda")]
+    w_fc[0][0, 5] = -2.0
+    w_fc[0][0, :5] = 0.25
+    d = z(n, V)
+    d[:, 5] = float("-inf")
+    D = KO.Discriminator(z(V, H), w_fc, [z(1), z(1)], fc_hidden=1)
+    loss = z(1)
+    # the zero weights beside column 5 meet finite logits only; target rows: score 0, loss log 2
+    D.step(z(n, H), z(n, V), d, 0.0, loss)
+    assert abs(loss.item() - np.log(2.0)) < 1e-6
+
+
+@pytest.mark.parametrize("V", [1, 1023, 1025, 32768, 33001])
+def test_distillation_rows_of_every_length(V):
+    import torch
+    import paper_2408_08146_amd as KO
+    n, H = 3, 8
+    g = torch.Generator(device="cuda").manual_seed(V)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q, d = rnd(n, V) * 3, rnd(n, V) * 3
+    D = KO.Discriminator(rnd(V, H), [rnd(1, V)], [rnd(1)])
+    loss, grad = torch.zeros(2, device="cuda"), torch.full((n, V), 7.0, device="cuda")
+    D.gen_grad(rnd(n, H), q, d, 0.0, loss, grad)
+    p, s = torch.softmax(q.double(), -1), torch.log_softmax(d.double(), -1)
+    assert abs(loss[1].item() + (p * s).sum(-1).mean().item()) < 2e-6 * (1 + abs(loss[1].item()))
+    assert (grad.double() - (s.exp() - p) / n).abs().max().item() < 1e-6
