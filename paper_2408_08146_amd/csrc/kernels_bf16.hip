@@ -185,13 +185,15 @@ __global__ __launch_bounds__(256 * RS, RS > 1 ? 1 : MT == 4 ? 2 : 3) void k_gemm
 //                MFMA fragments for the attention kernel, rotated keys and values to their cache slots (bf16).  W_q / W_k rows are stored pair-interleaved
 //                (koala.h), so the two halves of a rotary pair are neighbours in one lane;
 //   EPI_SWIGLU   row scale, SiLU(gate) * up (rows interleaved gate, up), written as fragments of the
-//                down projection's input.
+//                down projection's input;
+//   EPI_HEADS    EPI_PARTIAL of several matrices of one shape on the same input, matrix blockIdx.y into its own
+//                P[blockIdx.y][sp][row][n]: the residual blocks of a Medusa-style draft's heads in one launch.
 // Every compute unit can take in only so many bytes per second (about 53 GB/s measured, weights and
 // activations together), and with S = 1 every workgroup reads all activation fragments; U is therefore
 // chosen so that one launch is one workgroup per compute unit with equal shares of the weights.
 // RS > 1: RS waves share a tile position and split the MT * RS activation tiles between them.
 // ---------------------------------------------------------------------------------------------
-enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2 };
+enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_HEADS = 3 };
 
 // whether the wave accumulators of k_gemm_rows are combined in halving rounds (they do not all fit in LDS at once)
 constexpr bool gemm_rows_tree(int U, int MT, int NW) { return NW * U * MT > 96; }
@@ -209,6 +211,7 @@ struct GemmEpi {
     float qscale;
     uint32_t *Xo;       // EPI_SWIGLU: output fragments, F = out features / 2
     int F;
+    const void *heads[kb::GEMM_HEADS];   // EPI_HEADS: the matrices
 };
 
 template <int U, int MT, int RS, int NW, int PF, int EPI>
@@ -226,6 +229,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
     const int g = blockIdx.x % nwg, sp = blockIdx.x / nwg, ug0 = g * U;
     const int nkt = K / 64;
     const int kt0 = split_begin(sp, nkt, S), kt1 = split_begin(sp + 1, nkt, S);
+    if (EPI == EPI_HEADS) Wp = (const u32x4 *)e.heads[blockIdx.y];
     const u32x4 *w[U];   // unit j, tile kt, half s: w[j] + kt * 512 + s * 64 (a ragged last group re-reads its last unit)
 #pragma unroll
     for (int j = 0; j < U; ++j) {
@@ -253,7 +257,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
     // per-lane row data of the epilogue, fetched while the first tiles are in flight
     float rsc[MTT];
     int rslot[MTT], rbat[MTT];
-    if (EPI != EPI_PARTIAL) {
+    if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
 #pragma unroll
         for (int m = 0; m < MTT; ++m) {
             const int row = m * 16 + li;
@@ -353,8 +357,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             for (int q = 1; q < KW; ++q) v += red[((size_t)((q * RS + umh) * U + j) * MT + um) * 64 + l];
         }
         const int row = mtt * 16 + li, n = (ug0 + j) * 16 + 4 * lg;
-        if (EPI == EPI_PARTIAL) {
-            *(f32x4 *)(e.P + ((size_t)sp * (MTT * 16) + row) * Npad + n) = v;
+        if (EPI == EPI_PARTIAL || EPI == EPI_HEADS) {
+            const int part = EPI == EPI_HEADS ? blockIdx.y * S + sp : sp;
+            *(f32x4 *)(e.P + ((size_t)part * (MTT * 16) + row) * Npad + n) = v;
             continue;
         }
         if (row >= e.rows) continue;
@@ -936,13 +941,36 @@ __global__ __launch_bounds__(64) void k_silu_frag(const float *P, int S, int Mp,
     store_frag8(Xf, MT, r, g * 8, y);
 }
 
-// Medusa residual block: x += SiLU(sum of partials)
-__global__ void k_resblock_p(float *x, int ldx, const float *P, int S, int Mp, int ldp, int M, int H) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)M * H) return;
-    const int r = (int)(i / H), j = (int)(i % H);
-    const float v = psum(P, S, Mp, ldp, r, j);
-    x[(size_t)r * ldx + j] += v / (1.0f + __expf(-v));
+// Input of a Medusa-style draft's heads: row r of x, and its fragments, is the newest feature of sequence r % batch.
+// grid (ceil(H/512), rows), 64 threads x 8 columns
+__global__ __launch_bounds__(64) void k_medusa_in(const float *feat, float *x, u32x4 *Xf, int batch, int m, int H, int MT) {
+    const int r = blockIdx.y, j = (blockIdx.x * 64 + threadIdx.x) * 8;
+    if (j >= H) return;
+    const float *src = feat + ((size_t)(r % batch) * m + m - 1) * H + j;
+    const f32x4 a = *(const f32x4 *)src, b = *(const f32x4 *)(src + 4);
+    *(f32x4 *)(x + (size_t)r * H + j) = a;
+    *(f32x4 *)(x + (size_t)r * H + j + 4) = b;
+    const float y[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    store_frag8(Xf, MT, r, j, y);
+}
+
+// Medusa residual block: x += SiLU(sum of partials), and (Xf given) the fragments of the new x.  Row r0 + blockIdx.y belongs
+// to head number blockIdx.y / batch of the launch, whose partials are P[head][S][Mp][H], its row there r - p0.
+// grid (ceil(H/512), rows)
+__global__ __launch_bounds__(64) void k_resblock_p(float *x, u32x4 *Xf, const float *P, int S, int Mp, int batch, int r0,
+                                                   int p0, int H, int MT) {
+    const int r = r0 + blockIdx.y, j = (blockIdx.x * 64 + threadIdx.x) * 8;
+    if (j >= H) return;
+    float v[8];
+    psum8(P + (size_t)(blockIdx.y / batch) * S * Mp * H, S, Mp, H, r - p0, j, v);
+    float *xr = x + (size_t)r * H + j;
+    const f32x4 a = *(const f32x4 *)xr, b = *(const f32x4 *)(xr + 4);
+    float y[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] += v[e] / (1.0f + __expf(-v[e]));
+    *(f32x4 *)xr = (f32x4){y[0], y[1], y[2], y[3]};
+    *(f32x4 *)(xr + 4) = (f32x4){y[4], y[5], y[6], y[7]};
+    if (Xf) store_frag8(Xf, MT, r, j, y);
 }
 
 // logits[r][v] = sum of partials for v < V
@@ -1050,7 +1078,7 @@ inline int cdiv(size_t a, size_t b) { return (int)((a + b - 1) / b); }
 
 template <int U, int MT, int RS, int NW, int PF, int EPI>
 void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, int K, int S, const GemmEpi &e,
-                      hipEvent_t ev_start, hipEvent_t ev_stop) {
+                      hipEvent_t ev_start, hipEvent_t ev_stop, int n_heads = 1) {
     const size_t sm = (size_t)(gemm_rows_tree(U, MT, NW) ? NW / 2 : NW) * U * MT * 64 * 16 + (EPI == EPI_QKV ? (size_t)MT * RS * 16 * U * 8 * 2 * 4 : 0);
     static bool done = false;
     if (!done) {
@@ -1058,7 +1086,7 @@ void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, 
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
         done = true;
     }
-    const dim3 grid(((Npad / 16 + U - 1) / U) * S);
+    const dim3 grid(((Npad / 16 + U - 1) / U) * S, n_heads);
     if (ev_start || ev_stop)
         hipExtLaunchKernelGGL((k_gemm_rows<U, MT, RS, NW, PF, EPI>), grid, dim3(64 * NW), sm, st, ev_start, ev_stop, 0,
                               (const u32x4 *)Wp, (const u32x4 *)Xf, Npad, K, S, e);
@@ -1070,12 +1098,12 @@ void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, 
 // MTT = 1, 2 or 4 activation tiles
 template <int U, int EPI>
 void dispatch_gemm_rows_u(hipStream_t st, const void *Wp, const void *Xf, int Npad, int K, int MTT, int S,
-                          const GemmEpi &e, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                          const GemmEpi &e, hipEvent_t ev_start, hipEvent_t ev_stop, int n_heads = 1) {
     // tiles in flight per wave: two, or one where the registers do not hold a second (four tiles with more than
     // four groups)
-    if (MTT == 1) launch_gemm_rows<U, 1, 1, 8, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop);
-    else if (MTT == 2) launch_gemm_rows<U, 2, 1, 8, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop);
-    else launch_gemm_rows<U, 4, 1, 8, (U <= 4 ? 2 : 1), EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop);
+    if (MTT == 1) launch_gemm_rows<U, 1, 1, 8, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
+    else if (MTT == 2) launch_gemm_rows<U, 2, 1, 8, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
+    else launch_gemm_rows<U, 4, 1, 8, (U <= 4 ? 2 : 1), EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
 }
 
 // 16-row groups per workgroup for an S = 1 launch over Npad rows: the smallest supported count that covers the
@@ -1144,9 +1172,9 @@ int gemm_splits(int Npad, int K, int MTT) {
 }
 
 // K splits of gemm_rows_partial: about 256 workgroups of 64 weight rows each
-int rows_splits(int Npad, int K) {
+int rows_splits(int Npad, int K, int n_heads) {
     static const int target = env_int("KOALA_ROWS_WGS", 256);
-    const int nb = Npad / 64, nkt = K / 64;
+    const int nb = Npad / 64 * n_heads, nkt = K / 64;
     int S = (target + nb / 2) / nb;
     S = S < 1 ? 1 : S > 8 ? 8 : S;
     return S > nkt ? nkt : S;
@@ -1196,6 +1224,14 @@ void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P,
     GemmEpi e{};
     e.P = P;
     dispatch_gemm_rows_u<4, EPI_PARTIAL>(st, Wp, Xf, Npad, K, MTT, S, e, ev_start, ev_stop);
+}
+
+void gemm_rows_heads(hipStream_t st, const void *const *W, int n, const void *Xf, float *P, int Npad, int K, int MTT, int S,
+                     hipEvent_t ev_start, hipEvent_t ev_stop) {
+    GemmEpi e{};
+    e.P = P;
+    for (int h = 0; h < n; ++h) e.heads[h] = W[h];
+    dispatch_gemm_rows_u<4, EPI_HEADS>(st, W[0], Xf, Npad, K, MTT, S, e, ev_start, ev_stop, n);
 }
 
 void gemm_rows_qkv(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const NormScale &ns, int rows,
@@ -1346,8 +1382,13 @@ void silu_frag(hipStream_t st, const float *P, int S, int Mp, int ldp, const Nor
     k_silu_frag<<<dim3((F / 8 + 63) / 64, M), 64, 0, st>>>(P, S, Mp, ldp, mk_scale(ns), (u32x4 *)Xf, MT, F);
 }
 
-void resblock_p(hipStream_t st, float *x, int ldx, const float *P, int S, int Mp, int ldp, int M, int H) {
-    k_resblock_p<<<cdiv((size_t)M * H, 256), 256, 0, st>>>(x, ldx, P, S, Mp, ldp, M, H);
+void medusa_in(hipStream_t st, const float *feat, float *x, void *Xf, int batch, int m, int rows, int H, int MT) {
+    k_medusa_in<<<dim3((H + 511) / 512, rows), 64, 0, st>>>(feat, x, (u32x4 *)Xf, batch, m, H, MT);
+}
+
+void resblock_p(hipStream_t st, float *x, void *Xf, const float *P, int S, int Mp, int batch, int r0, int p0, int rows, int H,
+                int MT) {
+    k_resblock_p<<<dim3((H + 511) / 512, rows), 64, 0, st>>>(x, (u32x4 *)Xf, P, S, Mp, batch, r0, p0, H, MT);
 }
 
 // cand buffers: rows * ceil(V/1024) * k entries each
@@ -1356,7 +1397,7 @@ void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const N
     const int nchunk = (V + 1023) / 1024;
     k_topk_stage1<<<dim3(nchunk, rows), 256, 0, st>>>(P, S, Mp, ldp, mk_scale(ns), logits, ldl, V, k, cand_val,
                                                       cand_idx);
-    k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val);
+    if (k > 0) k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val);
 }
 
 void reduce_out(hipStream_t st, const float *P, int S, int Mp, int ldp, float *out, int ldo, int M, int N) {

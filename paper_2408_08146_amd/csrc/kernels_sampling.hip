@@ -7,9 +7,15 @@
 //
 // A draw is an inverse CDF over ascending token id: the first id at which the running sum of the weights
 // exceeds u * total.  The vocabulary is cut into segments of 256 consecutive ids; a wave sums a segment
-// with lane l holding ids 4l..4l+3 (fp64, fixed shuffle order), the segment sums are added in id order, and
+// with lane l holding ids 4l..4l+3 (fp64, fixed shuffle order), the segment sums are added up in a fixed order, and
 // inside the chosen segment a wave-wide inclusive scan in lane order finds the id.  All orders are fixed,
 // so a draw does not depend on scheduling.
+//
+// Two forms.  Up to 32768 tokens a workgroup holds its rows in registers (32 values of a row per thread): a row is read
+// once, every later pass over it is arithmetic, and the draws of a row exchange one number each through LDS.  Larger
+// vocabularies keep their rows in memory and read them again in every pass.  The register form of the acceptance walk took
+// 102 us where the memory form takes 278 us (eight sequences, 60 nodes, 32000 tokens), that of the draws (the children of
+// 208 nodes, a 64-node Medusa-style tree for eight sequences) 33 us where the memory form takes 427 us.
 #include "koala_internal.h"
 
 namespace {
@@ -209,27 +215,18 @@ __device__ void scale_by(float *w, int V, double total) {
     }
 }
 
-// dst row (b * n_level + li) = src row (src_row0 + b), for every li: the shared per-depth logits of a
-// Medusa-style head get one private copy per parent node.  grid: batch * n_level.
-__global__ __launch_bounds__(256) void k_repeat_rows(const float *src, int src_row0, float *dst, int V, int n_level) {
-    const int row = blockIdx.x, b = row / n_level;
-    const float *s = src + (size_t)(src_row0 + b) * V;
-    float *d = dst + (size_t)row * V;
-    for (int i = threadIdx.x; i < V; i += 256) d[i] = s[i];
-}
-
-// grid: batch * n_level rows.  z: [rows][V] draft logits of the level's nodes (overwritten by weights).
-__global__ __launch_bounds__(NT) void k_sample_children(float *z, const int32_t *level_nodes, int n_level,
-                                                         TreeTables tt, int T, int V, float inv_tau,
+// One workgroup per sequence and listed node.  The node's logits are row (stride_by_depth: depth * batch + sequence, the
+// heads of a Medusa-style draft; else the workgroup's own number) of src; z: [workgroup][V] scratch, may be src.
+__global__ __launch_bounds__(NT) void k_sample_children(const float *src, float *z, ks::NodeList nodes, int by_depth,
+                                                         int batch, TreeTables tt, int T, int V, float inv_tau,
                                                          const float *u_draw, int32_t *tree_tokens,
                                                          float *draft_logits) {
     __shared__ Shared sh;
-    const int row = blockIdx.x, b = row / n_level, li = row % n_level, tid = threadIdx.x;
-    const int p = level_nodes[li];
-    if (p < 0 || p >= T) return;   // uniform; never for tables the host built
+    const int row = blockIdx.x, b = row / nodes.n, p = nodes.node[row % nodes.n], tid = threadIdx.x;
     list_children(tt, T, p, sh);
     float *zr = z + (size_t)row * V;
-    (void)softmax_weights(zr, zr, draft_logits + ((size_t)b * T + p) * V, V, inv_tau, sh);
+    src += (size_t)(by_depth ? nodes.depth[row % nodes.n] * batch + b : row) * V;
+    (void)softmax_weights(src, zr, draft_logits + ((size_t)b * T + p) * V, V, inv_tau, sh);
     segment_sums(zr, V, sh);
     for (int j = 0; j < sh.nk; ++j) {
         const int c = sh.kids[j];
@@ -340,29 +337,416 @@ __global__ __launch_bounds__(NT) void k_accept_sample(TreeTables tt, int T, int 
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Register form.  Thread t holds ids (u * 1024 + t) * 4 + e, u < NQ, e < 4, of a row: group u of wave w is segment
+// u * 16 + w, lane l of it ids 4l..4l+3 of the segment.
+// ---------------------------------------------------------------------------------------------
+constexpr int REG_SEG = 128;                 // segments of a row held in registers, at most
+constexpr int REG_V = REG_SEG * SEG;         // vocabularies of the register form: up to 32768
+typedef __attribute__((ext_vector_type(4))) float f32q;
+struct __attribute__((packed, aligned(4))) f4_any { float v[4]; };   // 16 bytes at a 4-byte aligned address
+
+struct RegShared {
+    double seg[REG_SEG];
+    double red[2][NW];
+    float mx[2][NW];
+    double news[2];        // the sum a draw leaves its segment with, by parity of the draw
+    float qx[2], dx[2];    // probabilities of the child to be tried, by parity
+};
+
+template <int NQ>
+__device__ __forceinline__ void row_load(const float *row, int V, float (&w)[NQ][4]) {
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+        const int i = (u * NT + (int)threadIdx.x) * 4;
+        if (i + 4 <= V) {
+            const f4_any x = *(const f4_any *)(row + i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[u][e] = x.v[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[u][e] = i + e < V ? row[i + e] : -INFINITY;
+        }
+    }
+}
+template <int NQ>
+__device__ __forceinline__ float row_max(const float (&w)[NQ][4]) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) m = fmaxf(m, fmaxf(fmaxf(w[u][0], w[u][1]), fmaxf(w[u][2], w[u][3])));
+    return m;
+}
+// w <- exp((w - m) / tau) (past the vocabulary, where w is -inf, zero); returns this thread's sum
+template <int NQ>
+__device__ __forceinline__ double row_exp(float (&w)[NQ][4], float m, float inv_tau) {
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            w[u][e] = expf((w[u][e] - m) * inv_tau);
+            s += (double)w[u][e];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return s;
+}
+template <int NQ>
+__device__ __forceinline__ void row_scale(float (&w)[NQ][4], double f) {
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            asm volatile("" : "+v"(w[u][e]));   // widened again here: a row of doubles from the sums would not fit
+            w[u][e] = (float)((double)w[u][e] * f);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+// maxima / sums of two values over the workgroup; nobody may still be reading the arrays of an earlier call
+__device__ __forceinline__ void block_max2(float &a, float &b, RegShared &sh) {
+    for (int o = 32; o > 0; o >>= 1) { a = fmaxf(a, __shfl_xor(a, o)); b = fmaxf(b, __shfl_xor(b, o)); }
+    if ((threadIdx.x & 63) == 0) { sh.mx[0][threadIdx.x >> 6] = a; sh.mx[1][threadIdx.x >> 6] = b; }
+    __syncthreads();
+    const int l = threadIdx.x & 63;   // sixteen lanes a value
+    float v = sh.mx[(l >> 4) & 1][l & 15];
+    for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    a = __shfl(v, 0);
+    b = __shfl(v, 16);
+}
+__device__ __forceinline__ void block_sum2(double &a, double &b, RegShared &sh) {
+    for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
+    if ((threadIdx.x & 63) == 0) { sh.red[0][threadIdx.x >> 6] = a; sh.red[1][threadIdx.x >> 6] = b; }
+    __syncthreads();
+    const int l = threadIdx.x & 63;
+    double v = sh.red[(l >> 4) & 1][l & 15];
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    a = __shfl(v, 0);
+    b = __shfl(v, 16);
+}
+
+// The sums of segments 2l and 2l + 1 in lane l of every wave
+struct SegPair { double a, b; };
+template <int NQ>
+__device__ __forceinline__ SegPair segment_pairs(const float (&w)[NQ][4], RegShared &sh) {
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+    double t[NQ];
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) t[u] = seg_lane_sum(w[u]);
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) t[u] += __shfl_xor(t[u], o);
+    if (l == 0) {
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) sh.seg[u * NW + wave] = t[u];
+    }
+    __syncthreads();
+    SegPair p;
+    p.a = 2 * l < NQ * NW ? sh.seg[2 * l] : 0.0;
+    p.b = 2 * l + 1 < NQ * NW ? sh.seg[2 * l + 1] : 0.0;
+    return p;
+}
+__device__ __forceinline__ double wave_scan(double v, int l) {   // inclusive, in lane order
+    for (int o = 1; o < 64; o <<= 1) {
+        const double t = __shfl_up(v, o);
+        if (l >= o) v += t;
+    }
+    return v;
+}
+struct SegPick { int s; bool rounding; double base, target; };   // s: the segment that holds the id, -1 if nothing is positive
+// The first segment with anything in it at which the running sum exceeds u * total; the last one with anything if
+// rounding leaves none.  The same in every wave.
+__device__ __forceinline__ SegPick pick_segment(const SegPair &p, double u) {
+    const int l = threadIdx.x & 63;
+    const double incl = wave_scan(p.a + p.b, l);
+    double excl = __shfl_up(incl, 1);
+    if (l == 0) excl = 0.0;
+    SegPick r;
+    r.target = u * __shfl(incl, 63);
+    const bool first = p.a > 0.0 && excl + p.a > r.target, second = p.b > 0.0 && incl > r.target;
+    const unsigned long long hit = __ballot(first || second);
+    const double base = first ? excl : excl + p.a;
+    r.rounding = hit == 0;
+    r.base = 0.0;
+    if (hit) {
+        const int at = __ffsll((long long)hit) - 1;
+        r.s = 2 * at + (__shfl((int)first, at) ? 0 : 1);
+        r.base = __shfl(base, at);
+    } else {
+        const unsigned long long any = __ballot(p.a > 0.0 || p.b > 0.0);
+        if (any == 0) { r.s = -1; return r; }
+        const int at = 63 - __clzll((long long)any);
+        r.s = 2 * at + (__shfl((int)(p.b > 0.0), at) ? 1 : 0);
+    }
+    return r;
+}
+// The id inside the picked segment, by the wave that holds it in group x (every lane gets it)
+__device__ __forceinline__ int pick_in_segment(const float (&x)[4], const SegPick &r) {
+    const int l = threadIdx.x & 63;
+    const double own = seg_lane_sum(x), incl = wave_scan(own, l);
+    const double lo = r.base + (incl - own), hi = r.base + incl;
+    int pick = -1, last = -1;
+    double run = lo;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (x[e] > 0.f) {
+            last = r.s * SEG + 4 * l + e;
+            run += (double)x[e];
+            if (pick < 0 && run > r.target) pick = last;
+        }
+    }
+    const unsigned long long claims = __ballot(!r.rounding && lo <= r.target && hi > r.target && pick >= 0);
+    if (claims) return __shfl(pick, __ffsll((long long)claims) - 1);
+    for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
+    return max(last, 0);
+}
+
+// The children of node p as bits, from the tree held one node a lane, and the child of the j-th lowest rank (lowest id
+// among equal ranks, as the other form lists them)
+__device__ __forceinline__ unsigned long long children_of(int parent_of_lane, int p) { return __ballot(parent_of_lane == p); }
+__device__ __forceinline__ int child_order(unsigned long long kids, int rank_of_lane) {   // place of the lane's node among them
+    const int l = threadIdx.x & 63;
+    int place = 0;
+    for (unsigned long long m = kids; m; m &= m - 1) {
+        const int j = __ffsll((long long)m) - 1, rj = __builtin_amdgcn_readlane(rank_of_lane, j);
+        place += rj < rank_of_lane || (rj == rank_of_lane && j < l) ? 1 : 0;
+    }
+    return (kids >> l) & 1 ? place : -1;
+}
+__device__ __forceinline__ int child_at(int place_of_lane, int j) { return __ffsll((long long)__ballot(place_of_lane == j)) - 1; }
+
+template <int NQ>
+__global__ __launch_bounds__(NT) void k_sample_children_r(const float *src, ks::NodeList nodes, int by_depth, int batch,
+                                                          TreeTables tt, int T, int V, float inv_tau, const float *u_draw,
+                                                          int32_t *tree_tokens, float *draft_logits) {
+    __shared__ RegShared sh;
+    const int row = blockIdx.x, b = row / nodes.n, p = nodes.node[row % nodes.n];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    float w[NQ][4];
+    row_load<NQ>(src + (size_t)(by_depth ? nodes.depth[row % nodes.n] * batch + b : row) * V, V, w);
+    const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
+    const float u_lane = l < T ? u_draw[(size_t)b * T + l] : 0.f;
+    const unsigned long long kids = children_of(par, p);
+    const int nk = __popcll(kids), place = child_order(kids, rank);
+    float *copy = draft_logits + ((size_t)b * T + p) * V;
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+        const int i = (u * NT + (int)threadIdx.x) * 4;
+        if (i + 4 <= V) {
+            f4_any x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x.v[e] = w[u][e];
+            *(f4_any *)(copy + i) = x;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e < V) copy[i + e] = w[u][e];
+        }
+    }
+    float m = row_max<NQ>(w), unused = 0.f;
+    block_max2(m, unused, sh);
+    (void)row_exp<NQ>(w, m, inv_tau);
+    SegPair seg = segment_pairs<NQ>(w, sh);
+    for (int j = 0; j < nk; ++j) {
+        const int c = child_at(place, j);
+        const SegPick r = pick_segment(seg, (double)__shfl(u_lane, c));
+        if (r.s < 0) {   // nothing left to draw from, here and for the children that follow
+            if (threadIdx.x == 0) tree_tokens[(size_t)b * T + c] = 0;
+            continue;
+        }
+        if ((r.s & (NW - 1)) == wave) {
+            float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < NQ; ++u)
+                if (u == r.s / NW)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = w[u][e];
+            const int idx = pick_in_segment(x, r);
+#pragma unroll
+            for (int u = 0; u < NQ; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)   // drawn without replacement
+                    if (idx - (int)threadIdx.x * 4 == u * NT * 4 + e) w[u][e] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (r.s * SEG + 4 * l + e == idx) x[e] = 0.f;
+            const double left = wave_sum(seg_lane_sum(x));
+            if (l == 0) {
+                tree_tokens[(size_t)b * T + c] = idx;
+                sh.news[j & 1] = left;
+            }
+        }
+        __syncthreads();
+        if (l == r.s / 2) { if (r.s & 1) seg.b = sh.news[j & 1]; else seg.a = sh.news[j & 1]; }
+    }
+}
+
+// The walk holds the draft's row in registers and the target's in LDS, where a thread only ever touches its own 16-byte
+// pieces (no barriers, no bank conflicts): both in registers with 512 threads spilled.
+template <int NQ>
+__global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, int D, int V, float inv_tau,
+                                                        const int32_t *tree_tokens, const float *target_logits,
+                                                        const float *draft_logits, const float *u_accept,
+                                                        const float *u_resample, int32_t *accept_len, int32_t *accept_path,
+                                                        int32_t *next_token) {
+    extern __shared__ __attribute__((aligned(16))) f32q walk_q[];   // [NQ][NT]
+    __shared__ RegShared sh;
+    const int b = blockIdx.x, tid = threadIdx.x, l = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int32_t *path = accept_path + (size_t)b * (D + 1);
+    f32q *ql = walk_q + tid;
+    // one node a lane, in every wave
+    const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
+    int tok = l < T ? tree_tokens[(size_t)b * T + l] : 0;
+    tok = tok < 0 ? 0 : tok >= V ? V - 1 : tok;
+    const float ua = l < T ? u_accept[(size_t)b * T + l] : 0.f, ur = l < T ? u_resample[(size_t)b * T + l] : 0.f;
+    int cur = 0, a = 0;
+    if (tid == 0) path[0] = 0;
+    for (;;) {
+        const unsigned long long kids = children_of(par, cur);
+        const int nk = a < D ? __popcll(kids) : 0, place = child_order(kids, rank);
+        float d[NQ][4], mq, md = 0.f;
+        int Vi = V;
+        asm volatile("" : "+s"(Vi));   // the row's bounds are worked out anew for each node
+        double sq, sd = 1.0;
+        {
+            float q[NQ][4];
+            row_load<NQ>(target_logits + ((size_t)b * T + cur) * V, Vi, q);
+            if (nk > 0) row_load<NQ>(draft_logits + ((size_t)b * T + cur) * V, Vi, d);
+            mq = row_max<NQ>(q);
+            if (nk > 0) md = row_max<NQ>(d);
+            block_max2(mq, md, sh);
+            sq = row_exp<NQ>(q, mq, inv_tau);
+            if (nk > 0) sd = row_exp<NQ>(d, md, inv_tau);
+            block_sum2(sq, sd, sh);
+            row_scale<NQ>(q, 1.0 / sq);
+            if (nk > 0) row_scale<NQ>(d, 1.0 / sd);
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) ql[u * NT] = (f32q){q[u][0], q[u][1], q[u][2], q[u][3]};
+        }
+        bool moved = false;
+        for (int j = 0; j < nk; ++j) {
+            const int c = child_at(place, j), x = __shfl(tok, c), xo = x - tid * 4;
+            if (xo >= 0 && xo % (NT * 4) < 4) {   // this thread has the probabilities of the child's token
+                float dx = 0.f;
+#pragma unroll
+                for (int u = 0; u < NQ; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dx = xo == u * NT * 4 + e ? d[u][e] : dx;
+                sh.dx[j & 1] = dx;
+                sh.qx[j & 1] = ((const float *)(ql + xo / (NT * 4) * NT))[xo % 4];
+            }
+            __syncthreads();
+            const double qx = (double)sh.qx[j & 1], dx = (double)sh.dx[j & 1];
+            const double ratio = dx > 0.0 ? fmin(1.0, qx / dx) : 0.0;
+            if (dx > 0.0 && (double)__shfl(ua, c) < ratio) {
+                cur = c;
+                ++a;
+                if (tid == 0) path[a] = c;
+                moved = true;
+                break;
+            }
+            // rejected: q <- norm(max(0, q - d)) (kept if that is all zero); d loses x and is renormalised
+            double rs = 0.0, ds = 0.0;
+            int xd = xo;
+            asm volatile("" : "+v"(xd));   // compared anew: no 32 masks kept from above
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) {
+                const f32q q = ql[u * NT];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    rs += (double)fmaxf(0.f, q[e] - d[u][e]);
+                    d[u][e] = xd == u * NT * 4 + e ? 0.f : d[u][e];
+                    ds += (double)d[u][e];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            block_sum2(rs, ds, sh);
+            const bool keep = !(rs > 0.0);
+            const double fr = keep ? 1.0 : 1.0 / rs, fd = ds > 0.0 ? 1.0 / ds : 1.0;
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) {
+                f32q q = ql[u * NT];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    asm volatile("" : "+v"(d[u][e]));   // as in row_scale
+                    const float t = fmaxf(0.f, q[e] - d[u][e]);
+                    q[e] = (float)((double)(keep ? q[e] : t) * fr);
+                    d[u][e] = (float)((double)d[u][e] * fd);
+                }
+                ql[u * NT] = q;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (xo >= 0 && xo % (NT * 4) < 4) {   // d has lost x by now: q there once more, from the values tried above
+                const float qo = sh.qx[j & 1], t = fmaxf(0.f, qo - sh.dx[j & 1]);
+                ((float *)(ql + xo / (NT * 4) * NT))[xo % 4] = (float)((double)(keep ? qo : t) * fr);
+            }
+        }
+        if (moved) continue;
+        float q[NQ][4];
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+            const f32q x = ql[u * NT];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[u][e] = x[e];
+        }
+        const SegPair seg = segment_pairs<NQ>(q, sh);
+        const SegPick r = pick_segment(seg, (double)__shfl(ur, cur));
+        if (r.s < 0 ? wave == 0 : (r.s & (NW - 1)) == wave) {
+            float y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < NQ; ++u)
+                if (r.s >= 0 && u == r.s / NW)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = q[u][e];
+            const int idx = r.s < 0 ? 0 : pick_in_segment(y, r);
+            if (l == 0) next_token[b] = idx;
+        }
+        if (tid == 0) {
+            accept_len[b] = a;
+            for (int j = a + 1; j <= D; ++j) path[j] = -1;
+        }
+        return;
+    }
+}
+
 }  // namespace
 
 namespace ks {
 
 int max_vocab() { return MAX_SEG * SEG; }
 
-void repeat_rows(hipStream_t st, const float *src, int src_row0, float *dst, int V, int n_level, int batch) {
-    k_repeat_rows<<<batch * n_level, 256, 0, st>>>(src, src_row0, dst, V, n_level);
-}
-
-void sample_children(hipStream_t st, float *logits, const int32_t *level_nodes, int n_level, const TreeTables &tt,
-                     int T, int V, float temperature, const float *u_draw, int32_t *tree_tokens,
+void sample_children(hipStream_t st, const float *src, float *scratch, const NodeList &nodes, bool by_depth,
+                     const TreeTables &tt, int T, int V, float temperature, const float *u_draw, int32_t *tree_tokens,
                      float *draft_logits, int batch) {
-    k_sample_children<<<batch * n_level, NT, 0, st>>>(logits, level_nodes, n_level, tt, T, V, 1.0f / temperature,
-                                                      u_draw, tree_tokens, draft_logits);
+    const float it = 1.0f / temperature;
+    const int grid = batch * nodes.n;
+#define KOALA_DRAW(NQ) k_sample_children_r<NQ><<<grid, NT, 0, st>>>(src, nodes, by_depth, batch, tt, T, V, it, u_draw, tree_tokens, draft_logits)
+    if (V <= REG_V / 8) KOALA_DRAW(1);
+    else if (V <= REG_V / 2) KOALA_DRAW(4);
+    else if (V <= REG_V) KOALA_DRAW(8);
+    else k_sample_children<<<grid, NT, 0, st>>>(src, scratch, nodes, by_depth, batch, tt, T, V, it, u_draw, tree_tokens, draft_logits);
+#undef KOALA_DRAW
 }
 
 void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, float temperature,
                    const int32_t *tree_tokens, const float *target_logits, const float *draft_logits,
                    const float *u_accept, const float *u_resample, float *qv, float *dv, int32_t *accept_len,
                    int32_t *accept_path, int32_t *next_token, int batch) {
-    k_accept_sample<<<batch, NT, 0, st>>>(tt, T, D, V, 1.0f / temperature, tree_tokens, target_logits, draft_logits,
-                                          u_accept, u_resample, qv, dv, accept_len, accept_path, next_token);
+    const float it = 1.0f / temperature;
+#define KOALA_WALK(NQ)                                                                                                  \
+    {                                                                                                                  \
+        static const hipError_t attr = hipFuncSetAttribute((const void *)k_accept_sample_r<NQ>,                        \
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, NQ * NT * 16);  \
+        (void)attr;   /* a failure shows at the launch */                                                              \
+        k_accept_sample_r<NQ><<<batch, NT, NQ * NT * 16, st>>>(tt, T, D, V, it, tree_tokens, target_logits, draft_logits, u_accept, u_resample, accept_len, accept_path, next_token); \
+    }
+    if (V <= REG_V / 8) KOALA_WALK(1)
+    else if (V <= REG_V / 2) KOALA_WALK(4)
+    else if (V <= REG_V) KOALA_WALK(8)
+    else k_accept_sample<<<batch, NT, 0, st>>>(tt, T, D, V, it, tree_tokens, target_logits, draft_logits, u_accept, u_resample,
+                                               qv, dv, accept_len, accept_path, next_token);
+#undef KOALA_WALK
 }
 
 }  // namespace ks

@@ -309,15 +309,52 @@ void decoder_layer_bf16(koala_ctx *c, hipStream_t st, int batch, int rows_per_se
     c->pend_mode = 1;
 }
 
-// top-k of the LM-head logits of `rows` fp32 rows at a (row stride lda)
-void bf_lm_head_topk(koala_ctx *c, hipStream_t st, const float *a, int lda, int rows, int k, int32_t *idx,
-                     float *val) {
-    const koala_shape &s = c->shape;
-    const int MT = kb::mt_of(rows), Vp = kb::pad64(s.vocab);
-    rows_to_frags(c, st, a, lda, rows, s.hidden, MT);
-    const int S = bf_gemm(c, st, c->w.lm_head, s.vocab, s.hidden, MT);
-    kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), nullptr, 0, rows, s.vocab, k, c->cand_val, c->cand_idx,
-                    idx, val);
+// The residual blocks of a Medusa-style draft's D heads (bf16): leaves the heads' outputs in c->x (row j * batch + b: head j,
+// sequence b) and as fragments in c->xf.  Up to 64 rows in all, every launch serves several heads: each head's matrix
+// meets the rows of all heads (the weights are what it streams; rows of other heads cost nothing there) and its own rows
+// are picked out of the sums.  Four heads and eight sequences at 4096 x 4096: 86 us in sixteen launches head by head, 33 us in three.
+// More rows: head by head.
+void medusa_blocks(koala_ctx *c, hipStream_t st, int batch, const float *feat_in, int m) {
+    const int H = c->shape.hidden, D = c->D, K = c->draft.K, rows = D * batch, MT = kb::mt_of(rows), Mp = MT * 16;
+    const int Npad = kb::pad64(H);
+    kb::medusa_in(st, feat_in, c->x, c->xf, batch, m, rows, H, MT);
+    if (MT <= 4) {
+        const int S = kb::rows_splits(Npad, H, std::min(D, (int)kb::GEMM_HEADS));
+        const size_t head_bytes = (size_t)S * Mp * H * sizeof(float);
+        const int group = (int)std::min({(size_t)D, (size_t)kb::GEMM_HEADS, std::max<size_t>(1, c->part_bytes / head_bytes)});
+        for (int k = 0; k < K; ++k)
+            for (int j = 0; j < D; j += group) {
+                const int n = std::min(group, D - j);
+                const void *w[kb::GEMM_HEADS];
+                for (int h = 0; h < n; ++h) w[h] = c->w.draft_w[(j + h) * K + k];
+                const LaunchEvents ev = timed_launch(c, (double)n * Npad * H * 2.0);
+                kb::gemm_rows_heads(st, w, n, c->xf, c->part, Npad, H, MT, S, ev.start, ev.stop);
+                kb::resblock_p(st, c->x, c->xf, c->part, S, Mp, batch, j * batch, 0, n * batch, H, MT);
+            }
+        return;
+    }
+    const int MTb = kb::mt_of(batch);
+    for (int j = 0; j < D; ++j)
+        for (int k = 0; k < K; ++k) {
+            const void *w = c->w.draft_w[j * K + k];
+            rows_to_frags(c, st, c->x + (size_t)j * batch * H, H, batch, H, MTb);
+            const int S = MTb <= 4 ? bf_gemm_rows(c, st, w, c->xf, H, H, MTb) : bf_gemm(c, st, w, H, H, MTb);
+            kb::resblock_p(st, c->x, nullptr, c->part, S, MTb * 16, batch, j * batch, j * batch, batch, H, MTb);
+        }
+    rows_to_frags(c, st, c->x, H, rows, H, MT);
+}
+
+// the nodes of depth d that have children
+void append_nodes(ks::NodeList &l, const koala_ctx *c, int d) {
+    for (int32_t u : c->level_exp[d]) {
+        l.node[l.n] = (uint8_t)u;
+        l.depth[l.n++] = (uint8_t)d;
+    }
+}
+ks::NodeList list_nodes(const koala_ctx *c, int d) {
+    ks::NodeList l{};
+    append_nodes(l, c, d);
+    return l;
 }
 
 size_t elt(const koala_ctx *c) { return c->shape.dtype == KOALA_BF16 ? 2 : 4; }
@@ -575,45 +612,39 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
 
     if (c->draft.kind == KOALA_DRAFT_MEDUSA) {
         // head j works on row block j of c->x: rows j*batch .. j*batch + batch - 1
-        for (int j = 0; j < D; ++j)
-            kg::gather_last_rows(st, feat_in, c->x + (size_t)j * batch * H, (size_t)H, batch, m, H);
-        for (int j = 0; j < D; ++j) {
-            float *xj = c->x + (size_t)j * batch * H;
-            for (int k = 0; k < K; ++k) {
-                if (bf) {
-                    const int MT = kb::mt_of(batch);
-                    rows_to_frags(c, st, xj, H, batch, H, MT);
-                    const int S = MT <= 4 ? bf_gemm_rows(c, st, c->w.draft_w[j * K + k], c->xf, H, H, MT)
-                                          : bf_gemm(c, st, c->w.draft_w[j * K + k], H, H, MT);
-                    kb::resblock_p(st, xj, H, c->part, S, MT * 16, H, batch, H);
-                } else {
+        if (bf && D > 0) {
+            medusa_blocks(c, st, batch, feat_in, m);
+        } else {
+            for (int j = 0; j < D; ++j)
+                kg::gather_last_rows(st, feat_in, c->x + (size_t)j * batch * H, (size_t)H, batch, m, H);
+            for (int j = 0; j < D; ++j) {
+                float *xj = c->x + (size_t)j * batch * H;
+                for (int k = 0; k < K; ++k) {
                     kg::gemm(st, bf, xj, H, c->w.draft_w[j * K + k], c->gu, H, batch, H, H, false);
                     kg::resblock_update(st, xj, c->gu, batch * H);
                 }
             }
         }
         if (D > 0 && sampling) {
-            // logits of the D heads (row j * batch + b), then per depth one private copy per parent node, from
-            // which that node's children are drawn
+            // logits of the D heads (row j * batch + b), from which every parent of that depth draws its children
             if (bf) {
                 const int MT = kb::mt_of(D * batch), Vp = kb::pad64(V);
-                rows_to_frags(c, st, c->x, H, D * batch, H, MT);
                 const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
-                kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), c->med_logits, V, D * batch, V, 1,
-                                c->cand_val, c->cand_idx, c->topk_idx, c->topk_val);
+                kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), c->med_logits, V, D * batch, V, 0, nullptr,
+                                nullptr, nullptr, nullptr);
             } else {
                 kg::gemm(st, bf, c->x, H, c->w.lm_head, c->med_logits, V, D * batch, V, H, false);
             }
-            for (int d = 0; d < D; ++d) {
-                const int nl = (int)c->level_exp[d].size();
-                if (nl == 0) continue;
-                ks::repeat_rows(st, c->med_logits, d * batch, c->logits, V, nl, batch);
-                ks::sample_children(st, c->logits, c->tt.level_nodes + (size_t)d * 64, nl, c->tt, T, V, temperature,
-                                    u_draw, tree_tokens, draft_logits, batch);
-            }
+            ks::NodeList nodes = list_nodes(c, 0);
+            for (int d = 1; d < D; ++d) append_nodes(nodes, c, d);
+            ks::sample_children(st, c->med_logits, c->logits, nodes, true, c->tt, T, V, temperature, u_draw, tree_tokens,
+                                draft_logits, batch);
         } else if (D > 0) {
             if (bf) {
-                bf_lm_head_topk(c, st, c->x, H, D * batch, kmax, c->topk_idx, c->topk_val);
+                const int MT = kb::mt_of(D * batch);
+                const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
+                kb::logits_topk(st, c->part, S, MT * 16, kb::pad64(V), no_scale(), nullptr, 0, D * batch, V, kmax,
+                                c->cand_val, c->cand_idx, c->topk_idx, c->topk_val);
             } else {
                 kg::gemm(st, bf, c->x, H, c->w.lm_head, c->logits, V, D * batch, V, H, false);
                 kg::topk_rows(st, c->logits, V, D * batch, V, kmax, c->topk_idx, c->topk_val);
@@ -655,14 +686,14 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
             rows_to_frags(c, st, a, lda, rows, H, MT);
             const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
             kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), sampling ? c->logits : nullptr, V, rows, V,
-                            sampling ? 1 : k, c->cand_val, c->cand_idx, c->topk_idx, c->topk_val);
+                            sampling ? 0 : k, c->cand_val, c->cand_idx, c->topk_idx, c->topk_val);
         } else {
             kg::gemm(st, bf, a, lda, c->w.lm_head, c->logits, V, rows, V, H, false);
             if (!sampling) kg::topk_rows(st, c->logits, V, rows, V, k, c->topk_idx, c->topk_val);
         }
         if (sampling)
-            ks::sample_children(st, c->logits, lv, nl, c->tt, T, V, temperature, u_draw, tree_tokens, draft_logits,
-                                batch);
+            ks::sample_children(st, c->logits, c->logits, list_nodes(c, d), false, c->tt, T, V, temperature, u_draw,
+                                tree_tokens, draft_logits, batch);
         else
             kg::fill_children(st, c->topk_idx, c->topk_val, k, lv, nl, c->tt, d, tree_tokens, tree_scores, batch, T);
     };

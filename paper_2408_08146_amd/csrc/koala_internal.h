@@ -157,13 +157,17 @@ namespace ks {
 
 int max_vocab();   // largest vocabulary the sampling kernels handle
 
-// logits: [batch * n_level][V] draft logits of the level's nodes (overwritten); children of those nodes get
-// draws without replacement from softmax(logits / temperature); the logits are copied to draft_logits[b][node]
-void sample_children(hipStream_t st, float *logits, const int32_t *level_nodes, int n_level, const TreeTables &tt,
-                     int T, int V, float temperature, const float *u_draw, int32_t *tree_tokens,
+// the nodes whose children are drawn in one launch, handed over by value
+struct NodeList {
+    int n;
+    uint8_t node[KOALA_MAX_NODES], depth[KOALA_MAX_NODES];
+};
+// Children of the listed nodes get draws without replacement from softmax(logits / temperature); the logits are copied to
+// draft_logits[b][node].  src: the logits, row depth * batch + b (by_depth) or b * n + index in the list.  scratch:
+// [batch * n][V], may be src unless by_depth (used for vocabularies above 32768 only).
+void sample_children(hipStream_t st, const float *src, float *scratch, const NodeList &nodes, bool by_depth,
+                     const TreeTables &tt, int T, int V, float temperature, const float *u_draw, int32_t *tree_tokens,
                      float *draft_logits, int batch);
-// dst[b * n_level + li][:] = src[src_row0 + b][:] for all li < n_level
-void repeat_rows(hipStream_t st, const float *src, int src_row0, float *dst, int V, int n_level, int batch);
 void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, float temperature,
                    const int32_t *tree_tokens, const float *target_logits, const float *draft_logits,
                    const float *u_accept, const float *u_resample, float *qv, float *dv, int32_t *accept_len,
@@ -176,6 +180,7 @@ void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, fl
 // ---------------------------------------------------------------------------------------------
 namespace kb {
 
+enum { GEMM_HEADS = 8 };   // matrices of one gemm_rows_heads launch, at most
 // number of 16-row activation tiles used for `rows` rows: 1, 2 or a multiple of 4
 inline int mt_of(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4 * ((rows + 63) / 64); }
 inline int pad64(int n) { return (n + 63) / 64 * 64; }
@@ -192,7 +197,7 @@ struct NormScale {
 };
 
 int gemm_splits(int Npad, int K, int MTT = 0);
-int rows_splits(int Npad, int K);              // split count of gemm_rows_partial   // MTT: activation tiles of the call (0: at most four)
+int rows_splits(int Npad, int K, int n_heads = 1);   // split count of gemm_rows_partial / _heads   // MTT: activation tiles of the call (0: at most four)
 // P[S][MTT*16][Npad] = partial sums of X * W^T, X given as fp16 fragments [K/32][MTT][64] x 16 B
 // ev_start/ev_stop (either may be null) are attached to the dispatch: they take the kernel's own begin and end times
 void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
@@ -204,6 +209,9 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 // scale, SiLU(gate) * up as fragments Xo of the down projection's input
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// n matrices W[h] of one shape on the same input: P[n][S][MTT*16][Npad]
+void gemm_rows_heads(hipStream_t st, const void *const *W, int n, const void *Xf, float *P, int Npad, int K, int MTT, int S,
+                     hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 void gemm_rows_qkv(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const NormScale &ns, int rows,
                    int rows_per_seq, const RowMeta &meta, void *qf, void *kc, void *vc, int H, int n_heads, int head_dim,
                    int cap, int n_cu, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
@@ -235,7 +243,12 @@ void attention_tree(hipStream_t st, const void *qf, const RowMeta &meta, const v
                     int rows_per_seq, int n_heads, int head_dim, int cap, int nsplit);
 void silu_frag(hipStream_t st, const float *P, int S, int Mp, int ldp, const NormScale &ns, void *Xf, int MT, int M,
                int F);
-void resblock_p(hipStream_t st, float *x, int ldx, const float *P, int S, int Mp, int ldp, int M, int H);
+// rows of x and their fragments: the newest feature of sequence row % batch
+void medusa_in(hipStream_t st, const float *feat, float *x, void *Xf, int batch, int m, int rows, int H, int MT);
+// x[r] += SiLU(partials of row r - p0) and (Xf not null) the fragments of the new x, r = r0 .. r0 + rows - 1;
+// P[head][S][Mp][H], batch rows a head
+void resblock_p(hipStream_t st, float *x, void *Xf, const float *P, int S, int Mp, int batch, int r0, int p0, int rows, int H,
+                int MT);
 void reduce_out(hipStream_t st, const float *P, int S, int Mp, int ldp, float *out, int ldo, int M, int N);
 void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const NormScale &ns, float *logits, int ldl,
                  int rows, int V, int k, float *cand_val, int *cand_idx, int32_t *idx, float *val);
