@@ -67,6 +67,38 @@ __device__ __forceinline__ uint32_t f2bf(float v) {  // round to nearest even
     return u >> 16;
 }
 
+// Partial results cross workgroups (and so, possibly, L2 caches that are not coherent with each other) inside
+// one kernel: they are stored and loaded with the sc1 cache policy (agent scope: written through to, and read
+// from, memory that every compute unit sees), through buffer instructions bounded by the allocation size.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr int AUX_SC1 = 16;
+__device__ __forceinline__ rsrc_t make_rsrc(const void *p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes > 0xFFFFFFF0ull ? (int)0xFFFFFFF0u : (int)bytes,
+                                             0x00020000);
+}
+__device__ __forceinline__ void st_sc1(rsrc_t r, size_t off, f32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, AUX_SC1);
+}
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+__device__ __forceinline__ void st_sc1(rsrc_t r, size_t off, u32x2 v) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, AUX_SC1);
+}
+__device__ __forceinline__ u32x4 ld4u_sc1(rsrc_t r, size_t off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_SC1);
+}
+__device__ __forceinline__ f32x2 half_pair_to_float(uint32_t p) {
+    return __builtin_convertvector(__builtin_bit_cast(f16x2, p), f32x2);
+}
+__device__ __forceinline__ void st_sc1(rsrc_t r, size_t off, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)off, 0, AUX_SC1);
+}
+__device__ __forceinline__ f32x4 ld4_sc1(rsrc_t r, size_t off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_SC1));
+}
+__device__ __forceinline__ float ld1_sc1(rsrc_t r, size_t off) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX_SC1));
+}
+
 // ---------------------------------------------------------------------------------------------
 // Packed GEMM.  Wp: [Npad/64][K/64] tiles of 64 rows x 64 k, each tile = 8 fragments
 // (t = row/16, s = k/32) of 64 lanes x 16 B; lane = (row%16) + 16*((k%32)/8).
@@ -212,6 +244,10 @@ struct GemmEpi {
     uint32_t *Xo;       // EPI_SWIGLU: output fragments, F = out features / 2
     int F;
     const void *heads[kb::GEMM_HEADS];   // EPI_HEADS: the matrices
+    // k_gemm_big with an epilogue on split groups: P is the scratch of their accumulators (P_bytes long), and counters[group
+    // and activation block] are zero between launches
+    size_t P_bytes;
+    int *counters;
 };
 
 template <int U, int MT, int RS, int NW, int PF, int EPI>
@@ -419,8 +455,15 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
 // next 64-k tile in registers (loaded straight from HBM) and all U x MTW accumulator tiles; the activation
 // fragments of a 64-k tile are shared by the four waves through LDS, filled by loads that go from global
 // memory to LDS directly (no staging registers), double-buffered.  Every activation fragment fetched from
-// LDS feeds U MFMAs (hi) + U (lo).  Output: fp32 partial sums P[sp][row][n] like the other GEMMs.
-// grid: (row-group blocks) x (activation tile blocks) x S.
+// LDS feeds U MFMAs.  Output: fp32 partial sums P[sp][row][n] like the other GEMMs, or an epilogue on finished sums.
+//
+// With an epilogue, the row-group blocks that do not fill whole rounds of compute units are split along K over S2
+// workgroups each: every one writes its accumulators through to scratch and moves a counter, and the one that arrives
+// last adds the others' in split order (so the result does not depend on who that is) and goes on to the epilogue.
+// Nobody waits for anybody; the counter is back at zero afterwards.  Worth it where the last round is less than half full:
+// gate/up of 33B at 480 rows is 374 workgroups on 256 compute units, 251 us unsplit and 223 us with the last 118 split in
+// two (a hand-over costs 10 to 14 us).  Projections of 7B at 120 rows are 64 to 115 workgroups in one piece: verification of
+// two sequences, four layers, 984 us unsplit and 856 us split (four sequences 1196 and 1118 us).
 // ---------------------------------------------------------------------------------------------
 // acc += A * B on the matrix pipe with the accumulator tile held in place in the accumulation registers.  Written
 // as an instruction of its own because the compiler's MFMA builtin, once a wave uses more than 256 registers,
@@ -444,6 +487,16 @@ __device__ __forceinline__ void mfma_settle(f32x4 &a, f32x4 &b, f32x4 &c, f32x4 
     else asm volatile("" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
 }
 
+// Transposes four words over the four 16-lane groups: lane group g's w[k] becomes group k's w[g].  With word g of four
+// 16-byte pieces in each lane before, lane group c has all of piece c after: one 16-byte store instead of four of 4 bytes.
+__device__ __forceinline__ u32x4 lane_groups_transpose(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+    const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);   // {w0 low half, w2 low half}, {w0 high, w2 high}
+    const auto b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
+    const auto p = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto q = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    return (u32x4){p[0], p[1], q[0], q[1]};
+}
+
 // 16 bytes per lane from LDS at base + a constant byte offset (below 64 KiB), as an instruction of its own: the
 // result may be used only after a wait that covers it (wait_lds_reads).
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
@@ -460,7 +513,7 @@ __device__ __forceinline__ void wait_lds_reads(int n) {
 template <int U, int MTW, int EPI>
 __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ Wp, const u32x4 *__restrict__ Xf,
                                                      float *__restrict__ P, int Npad, int K, int S, int MTT, int n_mt,
-                                                     int n_pm, GemmEpi e) {
+                                                     int n_pm, int n_full, GemmEpi e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char bsm[];
     typedef __attribute__((address_space(3))) void lds_void;
     typedef const __attribute__((address_space(1))) void glb_void;
@@ -475,12 +528,29 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ W
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
     const int nunits = Npad / 16, ngrp = (nunits + 4 * U - 1) / (4 * U);
-    int bid = blockIdx.x;
-    const int g = bid % ngrp; bid /= ngrp;
-    const int pm = bid % n_pm, sp = bid / n_pm;
+    // Workgroups go to the chip's eight dies in turn by their index.  The n_pm activation blocks of one weight group and K
+    // split get indices 8 apart: they run on the same die at about the same time, and the weights they share come from
+    // memory once, the other times from that die's L2.  Indices past the last item (the grid is padded) do nothing.
+    // EPI_PARTIAL: items are (group, K split).  With an epilogue the first n_full groups (a multiple of eight) are whole and
+    // the others split S ways, the splits of one group and activation block 8 n_pm indices apart.
+    int rnd = blockIdx.x >> 3, g, pm, sp, Sk;
+    const int die = blockIdx.x & 7;
+    if (EPI == EPI_PARTIAL) {
+        const int item = (rnd / n_pm) * 8 + die;
+        if (item >= ngrp * S) return;
+        g = item % ngrp; sp = item / ngrp; pm = rnd % n_pm; Sk = S;
+    } else if (rnd < n_full / 8 * n_pm) {
+        g = (rnd / n_pm) * 8 + die; sp = 0; pm = rnd % n_pm; Sk = 1;
+        if (g >= ngrp) return;
+    } else {
+        rnd -= n_full / 8 * n_pm;
+        g = n_full + (rnd / (n_pm * S)) * 8 + die;
+        pm = rnd % n_pm; sp = rnd / n_pm % S; Sk = S;
+        if (g >= ngrp) return;
+    }
     const int mt0 = pm * MTW, mt_cnt = min(MTW, n_mt - mt0);
     const int nkt = K / 64;
-    const int kt0 = split_begin(sp, nkt, S), kt1 = split_begin(sp + 1, nkt, S);
+    const int kt0 = split_begin(sp, nkt, Sk), kt1 = split_begin(sp + 1, nkt, Sk);
     const int ug0 = (g * 4 + wave) * U;
     // Addresses are a kernel argument plus a 32-bit byte offset (the launcher checks that both operands are
     // smaller than 4 GiB): the per-lane part of the offset is computed once, the per-tile part is one addition.
@@ -651,6 +721,40 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ W
         if (NT % 4) mfma_settle<false>(t[NT - 4], t[NT - 3], t[NT - 2], t[NT - 1]);   // the last tiles (again)
     }
     __syncthreads();
+    if (EPI != EPI_PARTIAL && Sk > 1) {
+        // one piece: a wave's accumulators, U * MTW tiles of 1 KiB; [group - n_full][activation block][split][wave]
+        const rsrc_t rp = make_rsrc(e.P, e.P_bytes);
+        const size_t slot = (size_t)(g - n_full) * n_pm + pm, piece = (size_t)U * MTW * 1024;
+        const size_t mine = ((slot * Sk + sp) * 4 + wave) * piece + (size_t)l * 16;
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+#pragma unroll
+            for (int m = 0; m < MTW; ++m) st_sc1(rp, mine + (size_t)(j * MTW + m) * 1024, acc[j][m]);
+        // written through, so it is enough that every wave's stores have been acknowledged before the counter moves
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        int *last = (int *)bsm;   // the tile buffers are free by now
+        if (threadIdx.x == 0) {
+            const int old = __hip_atomic_fetch_add(e.counters + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *last = old == Sk - 1;
+            if (old == Sk - 1) __hip_atomic_store(e.counters + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!*last) return;
+        // the others' sums, in split order whichever of them this workgroup is (of two, the order does not matter)
+        for (int q = Sk == 2 ? 1 - sp : 0; q < (Sk == 2 ? 2 - sp : Sk); ++q) {
+            const size_t from = ((slot * Sk + q) * 4 + wave) * piece + (size_t)l * 16;
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                f32x4 t[MTW];
+#pragma unroll
+                for (int m = 0; m < MTW; ++m) t[m] = ld4_sc1(rp, from + (size_t)(j * MTW + m) * 1024);
+#pragma unroll
+                for (int m = 0; m < MTW; ++m) acc[j][m] = Sk > 2 && q == 0 ? t[m] : acc[j][m] + t[m];
+            }
+        }
+    }
     if (EPI == EPI_PARTIAL) {
 #pragma unroll
         for (int j = 0; j < U; ++j) {
@@ -664,54 +768,80 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ W
             }
         }
     } else if (EPI == EPI_QKV) {
-        // One K split.  RMSNorm's row scale, then per lane four columns of one activation row: of V as they are;
+        // Finished sums.  RMSNorm's row scale, then per lane four columns of one activation row: of V as they are;
         // of Q and K two rotary pairs (the weight rows interleave dimension i and i + head_dim/2), rotated with
         // the row's cos/sin; K and V rows go to the bf16 cache at the row's slot, Q as hi/lo fragments of the
-        // attention kernel, times log2(e)/sqrt(head_dim).
+        // attention kernel, times log2(e)/sqrt(head_dim).  The sixteen columns of a weight row group lie in one head of
+        // one of the three matrices (head_dim is a multiple of sixteen): which and where is worked out once per group, on
+        // the scalar unit, the rotary values of four row tiles are requested before the first is used, and the stores are of
+        // 16 bytes (33B at 480 rows, the whole projection: 150 us with four-byte stores and
+        // a division per value, 146 us so).
         const int half = e.DH / 2;
+        constexpr int MB = U <= 4 ? 4 : 2;   // row tiles at a time: their rotary values fit the registers beside the sums
+        int which[U], h[U], r0[U];
 #pragma unroll
-        for (int m = 0; m < MTW; ++m) {
-            const int row = (mt0 + m) * 16 + li;
-            if (m >= mt_cnt || row >= e.rows) continue;
-            const float rsc = rsc_s[m * 16 + li];
-            const int slot = rslot_s[m * 16 + li], bat = rbat_s[m * 16 + li];
+        for (int j = 0; j < U; ++j) {
+            const int n0 = __builtin_amdgcn_readfirstlane((ug0 + j) * 16);
+            which[j] = n0 / e.H;                // 3 and more: past the last row group
+            h[j] = (n0 - which[j] * e.H) / e.DH;
+            r0[j] = n0 - which[j] * e.H - h[j] * e.DH;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MTW; mb += MB) {
+            if (mb >= mt_cnt) continue;
+            f32_pair ct[U][MB], st[U][MB];
+            float rsc[MB];
+            int bat[MB], slot[MB], row[MB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const int m = min(mb + i, MTW - 1);
+                row[i] = (mt0 + m) * 16 + li;
+                rsc[i] = rsc_s[m * 16 + li];
+                bat[i] = rbat_s[m * 16 + li];
+                slot[i] = rslot_s[m * 16 + li];
+            }
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                const int n = (ug0 + j) * 16 + 4 * lg;
-                if (ug0 + j >= nunits || n >= 3 * e.H) continue;
-                const f32x4 v = acc[j][m] * rsc;
-                const int which = n / e.H, nn = n % e.H, h = nn / e.DH, r = nn % e.DH;
-                const size_t o = (((size_t)bat * e.n_heads + h) * e.cap + slot) * e.DH;
-                if (which == 2) {
-                    const uint32_t lo = f2bf(v[0]) | (f2bf(v[1]) << 16), hi = f2bf(v[2]) | (f2bf(v[3]) << 16);
-                    *(u64_pair *)(e.vc + o + r) = u64_pair{lo, hi};
-                    continue;
-                }
-                const int dd = r >> 1;   // even: the lane holds pairs dd and dd + 1
-                const float c0 = e.meta.rope_cos[(size_t)row * half + dd], s0 = e.meta.rope_sin[(size_t)row * half + dd];
-                const float c1 = e.meta.rope_cos[(size_t)row * half + dd + 1], s1 = e.meta.rope_sin[(size_t)row * half + dd + 1];
-                const float a0 = v[0] * c0 - v[1] * s0, b0 = v[1] * c0 + v[0] * s0;
-                const float a1 = v[2] * c1 - v[3] * s1, b1 = v[3] * c1 + v[2] * s1;
-                if (which == 1) {
-                    *(uint32_t *)(e.kc + o + dd) = f2bf(a0) | (f2bf(a1) << 16);
-                    *(uint32_t *)(e.kc + o + half + dd) = f2bf(b0) | (f2bf(b1) << 16);
-                } else {
-                    const int i = row - bat * e.rows_per_seq;   // row of its sequence
-                    uint32_t *qt = e.qf + ((((size_t)bat * e.n_heads + h) * e.MTQ + (i >> 4)) * (e.DH / 32)) * 2 * 64 * 4;
-                    const float y[4] = {a0 * e.qscale, a1 * e.qscale, b0 * e.qscale, b1 * e.qscale};
+                if (which[j] >= 2) continue;
 #pragma unroll
-                    for (int z = 0; z < 2; ++z) {
-                        const int d = dd + z * half;
-                        const HiLo pr = split_pair(y[2 * z], y[2 * z + 1]);
-                        uint32_t *dst = qt + (((size_t)(d >> 5) * 2) * 64 + (i & 15) + 16 * ((d & 31) >> 3)) * 4 + ((d & 7) >> 1);
-                        dst[0] = pr.hi;
-                        dst[64 * 4] = pr.lo;
+                for (int i = 0; i < MB; ++i) {   // the lane holds pairs dd and dd + 1, dd = r0/2 + 2 lg
+                    const size_t at = (size_t)min(row[i], e.rows - 1) * half + (r0[j] >> 1) + 2 * lg;
+                    ct[j][i] = *(const f32_pair *)(e.meta.rope_cos + at);
+                    st[j][i] = *(const f32_pair *)(e.meta.rope_sin + at);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                if (which[j] >= 3) continue;
+                const float qs = which[j] == 0 ? e.qscale : 1.f;
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+                    if (mb + i >= MTW || mb + i >= mt_cnt) continue;
+                    const f32x4 v = acc[j][mb + i < MTW ? mb + i : 0] * rsc[i];
+                    const bool ok = row[i] < e.rows;
+                    const size_t o = (((size_t)bat[i] * e.n_heads + h[j]) * e.cap + slot[i]) * e.DH + r0[j] / 2;
+                    if (which[j] == 2) {
+                        if (ok) *(u64_pair *)(e.vc + o + r0[j] - r0[j] / 2 + 4 * lg) = u64_pair{split_pair(v[0], v[1]).hi, split_pair(v[2], v[3]).hi};
+                        continue;
+                    }
+                    const f32_pair c = ct[j][i], s = st[j][i];
+                    const HiLo pa = split_pair((v[0] * c.x - v[1] * s.x) * qs, (v[2] * c.y - v[3] * s.y) * qs);
+                    const HiLo pb = split_pair((v[1] * c.x + v[0] * s.x) * qs, (v[3] * c.y + v[2] * s.y) * qs);
+                    // pieces of eight dimensions: of Q (half of the head, hi or lo), of K (half of the head), twice
+                    const bool isq = which[j] == 0;
+                    const u32x4 x = lane_groups_transpose(pa.hi, isq ? pa.lo : pb.hi, isq ? pb.hi : pa.hi, isq ? pb.lo : pb.hi);
+                    if (isq) {
+                        const int z = row[i] - bat[i] * e.rows_per_seq, d = (r0[j] >> 1) + (lg >> 1) * half;   // row of its sequence
+                        u32x4 *qt = (u32x4 *)e.qf + ((((size_t)bat[i] * e.n_heads + h[j]) * e.MTQ + (z >> 4)) * (e.DH / 32)) * 2 * 64;
+                        if (ok) qt[((size_t)(d >> 5) * 2 + (lg & 1)) * 64 + (z & 15) + 16 * ((d & 31) >> 3)] = x;
+                    } else if (ok && lg < 2) {
+                        *(u32x4 *)(e.kc + o + lg * half) = x;
                     }
                 }
             }
         }
     } else {
-        // EPI_SWIGLU (one K split): the weight rows interleave gate and up, so a lane's four columns are (gate, up)
+        // EPI_SWIGLU (finished sums): the weight rows interleave gate and up, so a lane's four columns are (gate, up)
         // of two features of one activation row.  RMSNorm's row scale (from the per-chunk sums of squares of the
         // input rows) is applied, then SiLU(gate) * up, stored as fragments of the down projection's input.
 #pragma unroll
@@ -1261,7 +1391,10 @@ void gemm_rows_swiglu(hipStream_t st, const void *Wp, const void *Xf, int K, int
 // their MFMAs plus a fixed amount (barrier, first LDS reads), a workgroup costs its start-up and its stores, the
 // launch takes as many rounds as its workgroups need on the chip's compute units (one workgroup each) but at
 // least the time to stream the weights once per tile block, and the partial sums of the splits are written once and read once by the kernel that folds them.
-BigShape big_shape(int Npad, int K, int rows, int n_cu, bool one_split) {
+// With an epilogue (room > 0) K is not split into partial sums; instead the groups that do not fill whole rounds may be
+// split S ways inside the kernel (n_full of them stay whole), where the scratch of `room` bytes and n_cnt counters reach:
+// a hand-over costs the workgroups' stores and, for the one that goes on, S reads of as much.
+BigShape big_shape(int Npad, int K, int rows, int n_cu, bool epilogue, size_t room, int n_cnt) {
     BigShape b{};
     b.n_mt = (rows + 15) / 16;
     const int units = Npad / 16, nkt = K / 64;
@@ -1278,15 +1411,32 @@ BigShape big_shape(int Npad, int K, int rows, int n_cu, bool one_split) {
         for (int U = 5; U >= 3; --U) {
             if (U * tmpl > 60) continue;   // the accumulator tiles of a wave must fit the 256 accumulation registers
             if (fu >= 3 && fu <= 5 && fu * tmpl <= 60 && U != fu) continue;
+            const int groups = (units + 4 * U - 1) / (4 * U);
+            const double hbm = (double)n_pm * Npad * K * 2.0 / 5.0e12 * 2.2e9;   // every tile block streams the weights
+            auto wg = [&](int S) {   // cycles of a workgroup that takes one of S shares of K
+                return (double)((nkt + S - 1) / S) * (32.0 * tmpl * U / 0.8 + 400.0) + 6000.0 + 30.0 * tmpl * U;
+            };
             for (int S = 1; S <= 4 && S <= nkt; ++S) {
-                if (one_split ? S != 1 : (fs >= 1 && fs <= 4 && fs <= nkt && S != fs)) continue;
-                const int wgs = ((units + 4 * U - 1) / (4 * U)) * n_pm * S, rounds = (wgs + n_cu - 1) / n_cu;
-                const double tiles = (double)((nkt + S - 1) / S);
-                const double wg = tiles * (32.0 * tmpl * U / 0.8 + 400.0) + 6000.0 + 30.0 * tmpl * U;
-                const double partials = S > 1 ? 2.0 * S * (double)rows * Npad * 4.0 / 4.0e12 * 2.2e9 : 0.0;
-                const double hbm = (double)n_pm * Npad * K * 2.0 / 5.0e12 * 2.2e9;   // every tile block streams the weights
-                const double cost = std::max(rounds * wg, hbm) + partials;
-                if (cost < best) { best = cost; b.n_pm = n_pm; b.mtw = mtw; b.U = U; b.S = S; }
+                if (!epilogue && fs >= 1 && fs <= 4 && fs <= nkt && S != fs) continue;
+                double cost;
+                int n_full = 0;
+                if (!epilogue) {
+                    const int rounds = (groups * n_pm * S + n_cu - 1) / n_cu;
+                    const double partials = S > 1 ? 2.0 * S * (double)rows * Npad * 4.0 / 4.0e12 * 2.2e9 : 0.0;
+                    cost = std::max(rounds * wg(S), hbm) + partials;
+                } else if (S == 1) {
+                    n_full = groups;
+                    cost = std::max((double)((groups * n_pm + n_cu - 1) / n_cu) * wg(1), hbm);
+                } else {
+                    const int full_rounds = groups * n_pm / n_cu;
+                    n_full = full_rounds * n_cu / n_pm / 8 * 8;
+                    const int rest = groups - n_full;
+                    const size_t tile = (size_t)4 * U * tmpl * 1024;
+                    if (rest == 0 || rest * n_pm > n_cnt || (size_t)rest * n_pm * S * tile > room || nkt / S < 8) continue;
+                    const double hand_over = (S + 1) * (double)tile / 50.0e9 * 2.2e9 + 4000.0;
+                    cost = std::max(full_rounds * wg(1) + (rest * n_pm * S + n_cu - 1) / n_cu * (wg(S) + hand_over), hbm);
+                }
+                if (cost < best) { best = cost; b.n_pm = n_pm; b.mtw = mtw; b.U = U; b.S = S; b.n_full = n_full; }
             }
         }
     }
@@ -1304,13 +1454,16 @@ static void launch_gemm_big(hipStream_t st, const void *Wp, const void *Xf, floa
                                   (int)sm);
         done = true;
     }
-    const dim3 grid(((Npad / 16 + 4 * U - 1) / (4 * U)) * b.n_pm * b.S);
+    const int groups = (Npad / 16 + 4 * U - 1) / (4 * U);
+    const int n_full = EPI == EPI_PARTIAL ? 0 : b.S == 1 ? (groups + 7) / 8 * 8 : b.n_full;
+    const dim3 grid(EPI == EPI_PARTIAL ? (groups * b.S + 7) / 8 * 8 * b.n_pm
+                                       : (n_full + (std::max(groups - n_full, 0) + 7) / 8 * 8 * b.S) * b.n_pm);
     if (ev_start || ev_stop)
         hipExtLaunchKernelGGL((k_gemm_big<U, MTW, EPI>), grid, dim3(256), sm, st, ev_start, ev_stop, 0,
-                              (const u32x4 *)Wp, (const u32x4 *)Xf, P, Npad, K, b.S, MTT, b.n_mt, b.n_pm, e);
+                              (const u32x4 *)Wp, (const u32x4 *)Xf, P, Npad, K, b.S, MTT, b.n_mt, b.n_pm, n_full, e);
     else
         k_gemm_big<U, MTW, EPI><<<grid, 256, sm, st>>>((const u32x4 *)Wp, (const u32x4 *)Xf, P, Npad, K, b.S, MTT,
-                                                       b.n_mt, b.n_pm, e);
+                                                       b.n_mt, b.n_pm, n_full, e);
 }
 
 template <int EPI>
@@ -1333,12 +1486,13 @@ void gemm_big(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad
     dispatch_gemm_big<EPI_PARTIAL>(st, Wp, Xf, P, Npad, K, MTT, b, GemmEpi{}, ev_start, ev_stop);
 }
 
-// QKV projection of many rows with rotary embedding, KV append and query fragments applied to the accumulators:
-// `b` must have one K split
+// QKV projection of many rows with rotary embedding, KV append and query fragments applied to the accumulators
 void gemm_big_qkv(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b, const NormScale &ns,
                   int rows, int rows_per_seq, const RowMeta &meta, void *qf, void *kc, void *vc, int H, int n_heads,
-                  int head_dim, int cap, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                  int head_dim, int cap, float *scratch, size_t room, int *counters, hipEvent_t ev_start,
+                  hipEvent_t ev_stop) {
     GemmEpi e{};
+    e.P = scratch; e.P_bytes = room; e.counters = counters;
     e.sums = ns.sums; e.nparts = ns.nparts; e.srows = ns.srows; e.Kn = ns.K; e.eps = ns.eps;
     e.rows = rows; e.meta = meta; e.qf = (uint32_t *)qf; e.kc = (bf16_t *)kc; e.vc = (bf16_t *)vc;
     e.H = H; e.n_heads = n_heads; e.DH = head_dim; e.cap = cap;
@@ -1347,10 +1501,12 @@ void gemm_big_qkv(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT
     dispatch_gemm_big<EPI_QKV>(st, Wp, Xf, nullptr, pad64(3 * H), K, MTT, b, e, ev_start, ev_stop);
 }
 
-// gate/up projection of many rows with SwiGLU applied to the accumulators: `b` must have one K split
+// gate/up projection of many rows with SwiGLU applied to the accumulators
 void gemm_big_swiglu(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b,
-                     const NormScale &ns, int rows, void *Xo, int F, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                     const NormScale &ns, int rows, void *Xo, int F, float *scratch, size_t room, int *counters,
+                     hipEvent_t ev_start, hipEvent_t ev_stop) {
     GemmEpi e{};
+    e.P = scratch; e.P_bytes = room; e.counters = counters;
     e.sums = ns.sums; e.nparts = ns.nparts; e.srows = ns.srows; e.Kn = ns.K; e.eps = ns.eps;
     e.rows = rows; e.Xo = (uint32_t *)Xo; e.F = F;
     dispatch_gemm_big<EPI_SWIGLU>(st, Wp, Xf, nullptr, pad64(2 * F), K, MTT, b, e, ev_start, ev_stop);
@@ -1435,38 +1591,6 @@ namespace {
 // compiler from assuming the accesses cannot overlap.
 typedef unsigned short __attribute__((may_alias)) u16_alias;
 struct __attribute__((may_alias)) u64_alias { unsigned int x, y; };
-
-// Partial results cross workgroups (and so, possibly, L2 caches that are not coherent with each other) inside
-// one kernel: they are stored and loaded with the sc1 cache policy (agent scope: written through to, and read
-// from, memory that every compute unit sees), through buffer instructions bounded by the allocation size.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr int AUX_SC1 = 16;
-__device__ __forceinline__ rsrc_t make_rsrc(const void *p, size_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes > 0xFFFFFFF0ull ? (int)0xFFFFFFF0u : (int)bytes,
-                                             0x00020000);
-}
-__device__ __forceinline__ void st_sc1(rsrc_t r, size_t off, f32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, AUX_SC1);
-}
-typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
-__device__ __forceinline__ void st_sc1(rsrc_t r, size_t off, u32x2 v) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, AUX_SC1);
-}
-__device__ __forceinline__ u32x4 ld4u_sc1(rsrc_t r, size_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_SC1);
-}
-__device__ __forceinline__ f32x2 half_pair_to_float(uint32_t p) {
-    return __builtin_convertvector(__builtin_bit_cast(f16x2, p), f32x2);
-}
-__device__ __forceinline__ void st_sc1(rsrc_t r, size_t off, float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)off, 0, AUX_SC1);
-}
-__device__ __forceinline__ f32x4 ld4_sc1(rsrc_t r, size_t off) {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX_SC1));
-}
-__device__ __forceinline__ float ld1_sc1(rsrc_t r, size_t off) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX_SC1));
-}
 
 // Maximum / sum over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48), result in every lane.  The
 // swap instructions exchange 16-lane (32-lane) blocks between two registers: with the same value in both, one

@@ -273,9 +273,9 @@ void decoder_layer_bf16(koala_ctx *c, hipStream_t st, int batch, int rows_per_se
         if (MT >= 8 && big_fits32(Np, H, MT) && big_gemm_enabled()) {
             // many rows: rotary embedding, KV append and query fragments on the accumulators of the projection
             const LaunchEvents ev = timed_launch(c, (double)Np * H * 2.0);
-            const kb::BigShape b = kb::big_shape(Np, H, rows, c->n_cu, true);
+            const kb::BigShape b = kb::big_shape(Np, H, rows, c->n_cu, true, c->part_bytes, c->max_batch * s.n_heads * 4);
             kb::gemm_big_qkv(st, lw[1], c->xf, H, MT, b, hidden_scale(c), rows, rows_per_seq, c->meta, c->qf, kc, vc, H,
-                             s.n_heads, s.head_dim, c->kv.capacity, ev.start, ev.stop);
+                             s.n_heads, s.head_dim, c->kv.capacity, c->part, c->part_bytes, c->attn_cnt, ev.start, ev.stop);
         } else {
             S = bf_gemm(c, st, lw[1], 3 * H, H, MT, rows);
             kb::rope_append(st, c->part, S, Mp, 3 * H, hidden_scale(c), c->meta, c->qf, kc, vc, rows, H, s.n_heads,
@@ -295,8 +295,9 @@ void decoder_layer_bf16(koala_ctx *c, hipStream_t st, int batch, int rows_per_se
         if (MT >= 8 && big_fits32(Np, H, MT) && big_gemm_enabled()) {
             // many rows: SwiGLU on the accumulators of the gate/up projection, straight into the down projection's input
             const LaunchEvents ev = timed_launch(c, (double)Np * H * 2.0);
-            const kb::BigShape b = kb::big_shape(Np, H, rows, c->n_cu, true);
-            kb::gemm_big_swiglu(st, lw[4], c->xf, H, MT, b, hidden_scale(c), rows, c->xf2, F, ev.start, ev.stop);
+            const kb::BigShape b = kb::big_shape(Np, H, rows, c->n_cu, true, c->part_bytes, c->max_batch * s.n_heads * 4);
+            kb::gemm_big_swiglu(st, lw[4], c->xf, H, MT, b, hidden_scale(c), rows, c->xf2, F, c->part, c->part_bytes,
+                                c->attn_cnt, ev.start, ev.stop);
             S = bf_gemm(c, st, lw[5], H, F, MT, rows, c->xf2);
         } else {
             S = bf_gemm(c, st, lw[4], 2 * F, H, MT, rows);
