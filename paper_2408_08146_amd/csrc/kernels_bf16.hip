@@ -12,7 +12,7 @@
 //     result), since the GEMM is linear in the row scale;
 //   * K is split over workgroups; partial sums go to a scratch buffer that the consumer
 //     kernel adds up in a fixed order (deterministic, no float atomics).
-#include "koala_internal.h"
+#include "koala_pass.h"
 
 namespace {
 
@@ -223,7 +223,6 @@ __global__ __launch_bounds__(256 * RS, RS > 1 ? 1 : MT == 4 ? 2 : 3) void k_gemm
 // Every compute unit can take in only so many bytes per second (about 53 GB/s measured, weights and
 // activations together), and with S = 1 every workgroup reads all activation fragments; U is therefore
 // chosen so that one launch is one workgroup per compute unit with equal shares of the weights.
-// RS > 1: RS waves share a tile position and split the MT * RS activation tiles between them.
 // ---------------------------------------------------------------------------------------------
 enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_HEADS = 3 };
 
@@ -865,20 +864,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ W
 
 // Sums of split-K partials.  Loads are issued in batches (16 vector loads / 24 scalar loads in
 // flight) so that a sum costs one or two memory round trips; the order of the additions is fixed.
-__device__ __forceinline__ float psum(const float *P, int S, int Mp, int ld, int row, int col) {
-    const float *p = P + (size_t)row * ld + col;
-    const size_t stride = (size_t)Mp * ld;
-    float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f;
-    int s = 0;
-    for (; s + 4 <= S; s += 4) {
-        v0 += p[(size_t)s * stride];
-        v1 += p[(size_t)(s + 1) * stride];
-        v2 += p[(size_t)(s + 2) * stride];
-        v3 += p[(size_t)(s + 3) * stride];
-    }
-    for (; s < S; ++s) v0 += p[(size_t)s * stride];
-    return (v0 + v1) + (v2 + v3);
-}
 
 // N sums at once: element (row, col[i]) for i < N
 template <int N>
@@ -943,6 +928,21 @@ __device__ __forceinline__ void store_frag8(u32x4 *Xf, int MT, int m, int k0, co
     Xf[(size_t)(ks * MT + mt) * 64 + lane] = half8(y);
 }
 
+// Sum of squares of a 512-column chunk of row m (64 threads x 8 values), to sums[chunk][m]
+__device__ __forceinline__ void chunk_sum(const float *v, float *sums, int c, int srows, int m) {
+    float ss = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    if (threadIdx.x == 0) sums[(size_t)c * srows + m] = ss;
+}
+__device__ __forceinline__ void load_bf8(const bf16_t *p, float *v) {
+    const u32x4 g = *(const u32x4 *)p;
+    const uint32_t w[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = bf2f((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
+}
+
 // RMSNorm row scale from the per-chunk sums of squares a fold left: 1/sqrt(mean(x^2) + eps).
 // sums == nullptr: no normalisation pending, scale 1.
 struct RowScale {
@@ -998,10 +998,9 @@ __global__ __launch_bounds__(64) void k_fold(float *x, const float *P, const bf1
         if (Xf) {
             float y[8];
             if (gain) {
-                const u32x4 g = *(const u32x4 *)(gain + j);
-                const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
+                load_bf8(gain + j, y);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) y[e] = v[e] * bf2f((e & 1) ? (gw[e >> 1] >> 16) : (gw[e >> 1] & 0xFFFFu));
+                for (int e = 0; e < 8; ++e) y[e] *= v[e];
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) y[e] = v[e];
@@ -1009,12 +1008,7 @@ __global__ __launch_bounds__(64) void k_fold(float *x, const float *P, const bf1
             store_frag8(Xf, MT, m, j, y);
         }
     }
-    if (!sums) return;
-    float ss = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    if (threadIdx.x == 0) sums[(size_t)c * srows + m] = ss;
+    if (sums) chunk_sum(v, sums, c, srows, m);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1071,10 +1065,68 @@ __global__ __launch_bounds__(64) void k_silu_frag(const float *P, int S, int Mp,
     store_frag8(Xf, MT, r, g * 8, y);
 }
 
-// Input of a Medusa-style draft's heads: row r of x, and its fragments, is the newest feature of sequence r % batch.
-// grid (ceil(H/512), rows), 64 threads x 8 columns
-__global__ __launch_bounds__(64) void k_medusa_in(const float *feat, float *x, u32x4 *Xf, int batch, int m, int H, int MT) {
+// First kernel of a pass: metadata and rotary table of a row (by its first workgroup) and, 64 threads x 8 columns, mode 0:
+// x = embedding, fragments of gain * x, chunk sums of squares; modes 1, 2: fragments of [embedding ; feature].  Each of the
+// separate kernels this stands for (metadata, embedding or fc input, fold) took 5 to 10 us of stream time.
+// grid (ceil(width/512), rows)
+__global__ __launch_bounds__(64) void k_pass_in_bf(PassArgs a, const bf16_t *E, const bf16_t *gain, float *x, u32x4 *Xf, float *sums,
+                                                   int srows, int H, int MT) {
+    const int c = blockIdx.x, r = blockIdx.y, j = (c * 64 + threadIdx.x) * 8, W = a.mode == 0 ? H : 2 * H;
+    const float *f;
+    const size_t t = (size_t)pass_token(a, r, H, f);
+    float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (j < H) {
+        load_bf8(E + t * H + j, v);
+    } else if (j < W) {
+        const f32x4 p = *(const f32x4 *)(f + j - H), q = *(const f32x4 *)(f + j - H + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[e] = p[e]; v[4 + e] = q[e]; }
+    }
+    if (a.mode == 0) {
+        if (j < W) {
+            float g[8];
+            load_bf8(gain + j, g);
+            *(f32x4 *)(x + (size_t)r * H + j) = (f32x4){v[0], v[1], v[2], v[3]};
+            *(f32x4 *)(x + (size_t)r * H + j + 4) = (f32x4){v[4], v[5], v[6], v[7]};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) g[e] *= v[e];
+            store_frag8(Xf, MT, r, j, g);
+        }
+        chunk_sum(v, sums, c, srows, r);
+    } else if (j < W) {
+        store_frag8(Xf, MT, r, j, v);
+    }
+    if (c == 0) pass_meta(a, r);
+}
+
+// Last kernel of a draft pass: the predicted feature x + partials of each row that is wanted, to fhat and as fragments of the
+// LM head's input.  grid (ceil(H/512), rows out)
+__global__ __launch_bounds__(64) void k_head_out(const float *x, const float *P, int S, int Mp, float *fhat, const int32_t *level_nodes,
+                                                 int n_level, int m, int T, u32x4 *Xf, int MT, int H) {
+    const int o = blockIdx.y, j = (blockIdx.x * 64 + threadIdx.x) * 8;
+    if (j >= H) return;
+    const int b = level_nodes ? o / n_level : o, u = level_nodes ? level_nodes[o % n_level] : 0;
+    const int src = level_nodes ? o : b * m + m - 1;
+    float v[8];
+    psum8(P, S, Mp, H, src, j, v);
+    const f32x4 p = *(const f32x4 *)(x + (size_t)src * H + j), q = *(const f32x4 *)(x + (size_t)src * H + j + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] += p[e]; v[4 + e] += q[e]; }
+    float *dst = fhat + ((size_t)b * T + u) * H + j;
+    *(f32x4 *)dst = (f32x4){v[0], v[1], v[2], v[3]};
+    *(f32x4 *)(dst + 4) = (f32x4){v[4], v[5], v[6], v[7]};
+    store_frag8(Xf, MT, o, j, v);
+}
+
+// Input of a Medusa-style draft's heads: row r of x, and its fragments, is the newest feature of sequence r % batch; the
+// first rows' workgroups also set the roots.  grid (ceil(H/512), rows), 64 threads x 8 columns
+__global__ __launch_bounds__(64) void k_medusa_in(const float *feat, const int32_t *tok_in, float *x, u32x4 *Xf, int batch, int m,
+                                                  int H, int MT, int T, int32_t *root_tok, float *root_score) {
     const int r = blockIdx.y, j = (blockIdx.x * 64 + threadIdx.x) * 8;
+    if (j == 0 && r < batch) {
+        root_tok[r * T] = tok_in[r * m + m - 1];
+        if (root_score) root_score[r * T] = 0.f;
+    }
     if (j >= H) return;
     const float *src = feat + ((size_t)(r % batch) * m + m - 1) * H + j;
     const f32x4 a = *(const f32x4 *)src, b = *(const f32x4 *)(src + 4);
@@ -1101,14 +1153,6 @@ __global__ __launch_bounds__(64) void k_resblock_p(float *x, u32x4 *Xf, const fl
     *(f32x4 *)xr = (f32x4){y[0], y[1], y[2], y[3]};
     *(f32x4 *)(xr + 4) = (f32x4){y[4], y[5], y[6], y[7]};
     if (Xf) store_frag8(Xf, MT, r, j, y);
-}
-
-// logits[r][v] = sum of partials for v < V
-__global__ void k_reduce_out(const float *P, int S, int Mp, int ldp, float *out, int ldo, int M, int N) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)M * N) return;
-    const int r = (int)(i / N), j = (int)(i % N);
-    out[(size_t)r * ldo + j] = psum(P, S, Mp, ldp, r, j);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1139,10 +1183,16 @@ __device__ __forceinline__ void block_best(float &v, int &i, float *sv, int *si)
 
 __global__ __launch_bounds__(256) void k_topk_stage1(const float *P, int S, int Mp, int ldp, RowScale rs,
                                                      float *logits, int ldl, int V, int k, float *cand_val,
-                                                     int *cand_idx) {
+                                                     int *cand_idx, kb::FeatOut fo) {
     __shared__ float sv[4];
     __shared__ int si[4];
     const int r = blockIdx.y, c = blockIdx.x, tid = threadIdx.x, j0 = c * 1024 + tid * 4;
+    if (fo.feat) {   // the row after the final norm, cut over the row's workgroups
+        const int per = (fo.H + gridDim.x - 1) / gridDim.x, end = min(fo.H, (c + 1) * per);
+        const float inv = row_scale(rs, r);
+        for (int j = c * per + tid; j < end; j += 256)
+            fo.feat[(size_t)r * fo.H + j] = fo.x[(size_t)r * fo.H + j] * inv * bf2f(((const bf16_t *)fo.gain)[j]);
+    }
     float val[4] = {0.f, 0.f, 0.f, 0.f};
     if (j0 < V) {   // ldp is a multiple of 64 and j0 of 4: the four columns exist in P even past V
         for (int s = 0; s < S; ++s) {
@@ -1174,9 +1224,9 @@ __global__ __launch_bounds__(256) void k_topk_stage1(const float *P, int S, int 
 }
 
 __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, const int *cand_idx, int n_cand, int k,
-                                                     int32_t *idx, float *val) {
-    __shared__ float sv[4];
-    __shared__ int si[4];
+                                                     int32_t *idx, float *val, ChildFill fill) {
+    __shared__ float sv[4], best_val[KOALA_TOPK_MAX];
+    __shared__ int si[4], best[KOALA_TOPK_MAX];
     const int r = blockIdx.x, tid = threadIdx.x;
     // each thread owns candidates tid, tid+256, ... (at most 4: n_cand <= 1024)
     float cv[4];
@@ -1198,14 +1248,19 @@ __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, cons
         for (int q = 0; q < 4; ++q)
             if (ci[q] == bi) ci[q] = 0x7fffffff;   // token ids are unique among the candidates
         if (tid == 0) {
-            idx[(size_t)r * k + it] = bi;
+            if (idx) idx[(size_t)r * k + it] = bi;
             if (val) val[(size_t)r * k + it] = bv;
+            best[it] = bi;
+            best_val[it] = bv;
         }
+    }
+    if (fill.tree_tokens) {
+        __syncthreads();
+        fill_children(fill, r, best, best_val);
     }
 }
 
-inline int cdiv(size_t a, size_t b) { return (int)((a + b - 1) / b); }
-
+// 32-k steps in flight per wave: what the accumulators (U * MT tiles) leave of the 256 registers
 template <int U, int MT, int RS, int NW, int PF, int EPI>
 void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, int K, int S, const GemmEpi &e,
                       hipEvent_t ev_start, hipEvent_t ev_stop, int n_heads = 1) {
@@ -1347,6 +1402,15 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
         mt0 += g;
     }
 #undef KOALA_GEMM
+}
+
+bool rows_wide(int Npad, int n_cu) { return Npad / 16 > 7 * n_cu && (Npad / 16 + 7) / 8 <= n_cu; }
+
+void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, hipEvent_t ev_start,
+                    hipEvent_t ev_stop) {
+    GemmEpi e{};
+    e.P = P;
+    launch_gemm_rows<8, 1, 1, 8, 2, EPI_PARTIAL>(st, Wp, Xf, Npad, K, 1, e, ev_start, ev_stop);
 }
 
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
@@ -1538,8 +1602,20 @@ void silu_frag(hipStream_t st, const float *P, int S, int Mp, int ldp, const Nor
     k_silu_frag<<<dim3((F / 8 + 63) / 64, M), 64, 0, st>>>(P, S, Mp, ldp, mk_scale(ns), (u32x4 *)Xf, MT, F);
 }
 
-void medusa_in(hipStream_t st, const float *feat, float *x, void *Xf, int batch, int m, int rows, int H, int MT) {
-    k_medusa_in<<<dim3((H + 511) / 512, rows), 64, 0, st>>>(feat, x, (u32x4 *)Xf, batch, m, H, MT);
+void pass_in(hipStream_t st, const PassArgs &a, const void *E, const void *gain, float *x, void *Xf, float *sums, int srows,
+             int rows, int H, int MT) {
+    k_pass_in_bf<<<dim3(((a.mode == 0 ? H : 2 * H) + 511) / 512, rows), 64, 0, st>>>(a, (const bf16_t *)E, (const bf16_t *)gain, x,
+                                                                                 (u32x4 *)Xf, sums, srows, H, MT);
+}
+
+void head_out(hipStream_t st, const float *x, const float *P, int S, int Mp, float *fhat, const int32_t *level_nodes, int n_level,
+              int m, int T, void *Xf, int MT, int rows_out, int H) {
+    k_head_out<<<dim3((H + 511) / 512, rows_out), 64, 0, st>>>(x, P, S, Mp, fhat, level_nodes, n_level, m, T, (u32x4 *)Xf, MT, H);
+}
+
+void medusa_in(hipStream_t st, const float *feat, const int32_t *tok_in, float *x, void *Xf, int batch, int m, int rows, int H,
+               int MT, int T, int32_t *root_tok, float *root_score) {
+    k_medusa_in<<<dim3((H + 511) / 512, rows), 64, 0, st>>>(feat, tok_in, x, (u32x4 *)Xf, batch, m, H, MT, T, root_tok, root_score);
 }
 
 void resblock_p(hipStream_t st, float *x, void *Xf, const float *P, int S, int Mp, int batch, int r0, int p0, int rows, int H,
@@ -1549,15 +1625,12 @@ void resblock_p(hipStream_t st, float *x, void *Xf, const float *P, int S, int M
 
 // cand buffers: rows * ceil(V/1024) * k entries each
 void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const NormScale &ns, float *logits, int ldl,
-                 int rows, int V, int k, float *cand_val, int *cand_idx, int32_t *idx, float *val) {
+                 int rows, int V, int k, float *cand_val, int *cand_idx, int32_t *idx, float *val, const ChildFill &fill,
+                 const FeatOut &fo) {
     const int nchunk = (V + 1023) / 1024;
     k_topk_stage1<<<dim3(nchunk, rows), 256, 0, st>>>(P, S, Mp, ldp, mk_scale(ns), logits, ldl, V, k, cand_val,
-                                                      cand_idx);
-    if (k > 0) k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val);
-}
-
-void reduce_out(hipStream_t st, const float *P, int S, int Mp, int ldp, float *out, int ldo, int M, int N) {
-    k_reduce_out<<<cdiv((size_t)M * N, 256), 256, 0, st>>>(P, S, Mp, ldp, out, ldo, M, N);
+                                                      cand_idx, fo);
+    if (k > 0) k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val, fill);
 }
 
 }  // namespace kb

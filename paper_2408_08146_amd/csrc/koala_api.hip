@@ -8,7 +8,7 @@
 
 #include <mutex>
 
-#include "koala_internal.h"
+#include "koala_pass.h"
 
 // Scratch of koala_accept_sample_static: the two distributions of the stochastic acceptance walk,
 // [2][KOALA_STATIC_SCRATCH_FLOATS / 2] floats.  Every device the library runs on holds its own copy of
@@ -159,23 +159,18 @@ hipError_t upload(T *dst, const std::vector<T> &src) {
     return hipMemcpy(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
 }
 
-// One Llama decoder layer over `rows` rows (rows_per_seq per sequence) whose metadata is in c->meta.
+// One fp32 Llama decoder layer over `rows` rows (rows_per_seq per sequence) whose metadata is in c->meta.
 // lw: in_norm, wqkv, wo, post_norm, wgu, wdown.  x (c->x) is updated in place.
 void decoder_layer(koala_ctx *c, hipStream_t st, int batch, int rows_per_seq, const void *const *lw,
                    void *kc, void *vc) {
     const koala_shape &s = c->shape;
-    const bool bf = s.dtype == KOALA_BF16;
     const int rows = batch * rows_per_seq, H = s.hidden, F = s.ffn;
-    kg::rmsnorm(st, bf, c->x, lw[0], c->act, rows, H, s.rms_eps);
-    kg::gemm(st, bf, c->act, H, lw[1], c->qkv, 3 * H, rows, 3 * H, H, false);
-    kg::rope_append(st, bf, c->qkv, c->meta, c->qrot, kc, vc, rows, H, s.n_heads, s.head_dim, c->kv.capacity, 0);
-    kg::attention(st, bf, c->qrot, c->meta, kc, vc, c->o_part, c->ml, c->attn_out, batch, rows_per_seq, s.n_heads,
-                  s.head_dim, c->kv.capacity, c->attn_ns);
-    kg::gemm(st, bf, c->attn_out, H, lw[2], c->x, H, rows, H, H, true);
-    kg::rmsnorm(st, bf, c->x, lw[3], c->act, rows, H, s.rms_eps);
-    kg::gemm(st, bf, c->act, H, lw[4], c->gu, 2 * F, rows, 2 * F, H, false);
-    kg::silu_mul(st, c->gu, c->act, rows, F);
-    kg::gemm(st, bf, c->act, F, lw[5], c->x, H, rows, H, F, true);
+    kf::norm_qkv(st, c->x, lw[0], s.rms_eps, lw[1], c->meta, c->qrot, kc, vc, rows, H, s.n_heads, s.head_dim, c->kv.capacity);
+    kf::attention(st, c->qrot, c->meta, kc, vc, c->o_part, c->ml, c->attn_out, batch, rows_per_seq, s.n_heads, s.head_dim,
+                  c->kv.capacity, c->attn_ns);
+    kf::gemm(st, c->attn_out, H, lw[2], c->x, H, rows, H, H, true);
+    kf::norm_swiglu(st, c->x, lw[3], s.rms_eps, lw[4], c->act, rows, F, H);
+    kf::gemm(st, c->act, F, lw[5], c->x, H, rows, H, F, true);
 }
 
 // Event pair for the next weight-streaming launch while profiling is on (else nulls); counts its weight bytes.
@@ -209,6 +204,10 @@ int bf_gemm(koala_ctx *c, hipStream_t st, const void *Wp, int N, int K, int MT, 
         const kb::BigShape b = kb::big_shape(Npad, K, rows > 0 ? rows : MT * 16, c->n_cu);
         kb::gemm_big(st, Wp, Xf, c->part, Npad, K, MT, b, ev.start, ev.stop);
         return b.S;
+    }
+    if (MT == 1 && kb::rows_wide(Npad, c->n_cu)) {
+        kb::gemm_rows_wide(st, Wp, Xf, c->part, Npad, K, ev.start, ev.stop);
+        return 1;
     }
     const int S = kb::gemm_splits(Npad, K, MT);
     kb::gemm_packed(st, Wp, Xf, c->part, Npad, K, MT, S, ev.start, ev.stop);
@@ -246,8 +245,8 @@ void rows_to_frags(koala_ctx *c, hipStream_t st, const float *a, int lda, int ro
     kb::fold(st, const_cast<float *>(a), lda, nullptr, 0, 0, 0, 0, rows, K, nullptr, c->xf, MT, nullptr, 0);
 }
 
-// bf16 decoder layer.  On entry c->pend_* may describe partial sums still to be folded into x; on exit
-// the down projection's are pending.  Up to 64 rows: seven launches (fold, QKV projection with rotary embedding
+// bf16 decoder layer.  On entry c->pend_* may describe partial sums still to be folded into x, or c->frags_ready says that
+// the input's fragments are in place; on exit the down projection's sums are pending.  Up to 64 rows: seven launches (fold, QKV projection with rotary embedding
 // and cache append, attention, merge of its key splits, O projection, fold, gate/up projection with SwiGLU,
 // down projection).  More rows: the projections run in passes with their element-wise steps as kernels of
 // their own.
@@ -262,7 +261,8 @@ void decoder_layer_bf16(koala_ctx *c, hipStream_t st, int batch, int rows_per_se
     const int ns_room = std::max(1, std::min(c->attn_ns, c->n_cu / (s.n_heads * batch * (rows_per_seq > 32 ? 2 : 1))));
     const int ns = std::min(ns_room, std::max(1, ((c->kv.capacity + 31) / 32 + 7) / 8));
     const bool fused = MT <= 4;
-    fold_pending(c, st, rows, MT, lw[0]);
+    if (c->frags_ready) c->frags_ready = false;
+    else fold_pending(c, st, rows, MT, lw[0]);
     int S;
     if (fused) {
         const LaunchEvents ev = timed_launch(c, 3.0 * H * H * 2.0);
@@ -315,10 +315,11 @@ void decoder_layer_bf16(koala_ctx *c, hipStream_t st, int batch, int rows_per_se
 // meets the rows of all heads (the weights are what it streams; rows of other heads cost nothing there) and its own rows
 // are picked out of the sums.  Four heads and eight sequences at 4096 x 4096: 86 us in sixteen launches head by head, 33 us in three.
 // More rows: head by head.
-void medusa_blocks(koala_ctx *c, hipStream_t st, int batch, const float *feat_in, int m) {
+void medusa_blocks(koala_ctx *c, hipStream_t st, int batch, const float *feat_in, const int32_t *tok_in, int m,
+                   int32_t *tree_tokens, float *tree_scores) {
     const int H = c->shape.hidden, D = c->D, K = c->draft.K, rows = D * batch, MT = kb::mt_of(rows), Mp = MT * 16;
     const int Npad = kb::pad64(H);
-    kb::medusa_in(st, feat_in, c->x, c->xf, batch, m, rows, H, MT);
+    kb::medusa_in(st, feat_in, tok_in, c->x, c->xf, batch, m, rows, H, MT, c->T, tree_tokens, tree_scores);
     if (MT <= 4) {
         const int S = kb::rows_splits(Npad, H, std::min(D, (int)kb::GEMM_HEADS));
         const size_t head_bytes = (size_t)S * Mp * H * sizeof(float);
@@ -408,6 +409,7 @@ koala_status koala_create(const koala_shape *shape, const koala_draft_shape *dra
     c->prof_used = 0;
     c->prof_bytes = 0.0;
     c->pend_S = 0;
+    c->frags_ready = false;
     c->attn_ns = attn_nsplit(s);
     c->n_cu = 256;
     c->parent.assign(tree->parent, tree->parent + T);
@@ -553,32 +555,34 @@ koala_status koala_tree_verify(koala_ctx *c, void *hip_stream, int batch, const 
     const koala_shape &s = c->shape;
     const bool bf = s.dtype == KOALA_BF16;
     const int T = c->T, rows = batch * T, H = s.hidden, V = s.vocab;
-    kg::setup_verify(st, c, batch);
-    kg::embed_rows(st, bf, tree_tokens, c->w.embed, c->x, rows, H);
     const size_t ls = layer_stride_bytes(c);
+    PassArgs pa = kg::pass_args(c, 0, T, 0, 0);
+    pa.tok = tree_tokens;
     float *logits = logits_out ? logits_out : c->logits;
     if (bf) {
         const int MT = kb::mt_of(rows), Mp = MT * 16;
+        kb::pass_in(st, pa, c->w.embed, c->w.layer_w[0], c->x, c->xf, c->row_sums, c->max_rows, rows, H, MT);
         c->pend_S = 0;
+        c->frags_ready = true;
         for (int l = 0; l < s.n_layers; ++l)
             decoder_layer_bf16(c, st, batch, T, c->w.layer_w + 6 * l, (char *)c->kv.target_k + ls * l,
                                (char *)c->kv.target_v + ls * l);
-        // last down projection folded in; the LM head runs on gain * x and its logits take the row scale;
-        // the features (an output) are normalised separately
+        // last down projection folded in; the LM head runs on gain * x and its logits take the row scale; the features
+        // (an output) are written beside the logits
         fold_pending(c, st, rows, MT, c->w.final_norm);
-        kg::rmsnorm(st, true, c->x, c->w.final_norm, feat_out, rows, H, s.rms_eps);
         const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
         kb::logits_topk(st, c->part, S, Mp, kb::pad64(V), hidden_scale(c), logits_out, V, rows, V, 1, c->cand_val,
-                        c->cand_idx, greedy_out, nullptr);
+                        c->cand_idx, greedy_out, nullptr, ChildFill{}, kb::FeatOut{c->x, c->w.final_norm, feat_out, H});
         KOALA_CHECK_LAUNCH(c);
         return KOALA_OK;
     }
+    kg::pass_in(st, pa, c->w.embed, c->x, rows, H);
     for (int l = 0; l < s.n_layers; ++l)
         decoder_layer(c, st, batch, T, c->w.layer_w + 6 * l, (char *)c->kv.target_k + ls * l,
                       (char *)c->kv.target_v + ls * l);
-    kg::rmsnorm(st, bf, c->x, c->w.final_norm, feat_out, rows, H, s.rms_eps);
-    kg::gemm(st, bf, feat_out, H, c->w.lm_head, logits, V, rows, V, H, false);
-    kg::topk_rows(st, logits, V, rows, V, 1, greedy_out, nullptr);
+    kg::rmsnorm(st, c->x, c->w.final_norm, feat_out, rows, H, s.rms_eps);
+    kf::gemm(st, feat_out, H, c->w.lm_head, logits, V, rows, V, H, false);
+    kg::topk_rows(st, logits, V, rows, V, 1, greedy_out, nullptr, ChildFill{});
     KOALA_CHECK_LAUNCH(c);
     return KOALA_OK;
 }
@@ -609,19 +613,24 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
     const int T = c->T, D = c->D, H = s.hidden, V = s.vocab, K = c->draft.K;
     int kmax = 1;
     for (int d = 0; d < D; ++d) kmax = std::max(kmax, c->topk[d]);
-    kg::set_root(st, tok_in, m, tree_tokens, tree_scores, batch, T);
+    // where the winners of a greedy level go (n_level 0: the heads of a Medusa-style draft)
+    auto fill = [&](int d, int n_level) {
+        ChildFill f{c->tt, n_level, d, batch, T, sampling ? nullptr : tree_tokens, tree_scores};
+        return f;
+    };
 
     if (c->draft.kind == KOALA_DRAFT_MEDUSA) {
+        if (!bf || D == 0) kg::set_root(st, tok_in, m, tree_tokens, tree_scores, batch, T);
         // head j works on row block j of c->x: rows j*batch .. j*batch + batch - 1
         if (bf && D > 0) {
-            medusa_blocks(c, st, batch, feat_in, m);
+            medusa_blocks(c, st, batch, feat_in, tok_in, m, tree_tokens, tree_scores);
         } else {
             for (int j = 0; j < D; ++j)
                 kg::gather_last_rows(st, feat_in, c->x + (size_t)j * batch * H, (size_t)H, batch, m, H);
             for (int j = 0; j < D; ++j) {
                 float *xj = c->x + (size_t)j * batch * H;
                 for (int k = 0; k < K; ++k) {
-                    kg::gemm(st, bf, xj, H, c->w.draft_w[j * K + k], c->gu, H, batch, H, H, false);
+                    kf::gemm(st, xj, H, c->w.draft_w[j * K + k], c->gu, H, batch, H, H, false);
                     kg::resblock_update(st, xj, c->gu, batch * H);
                 }
             }
@@ -632,9 +641,9 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
                 const int MT = kb::mt_of(D * batch), Vp = kb::pad64(V);
                 const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
                 kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), c->med_logits, V, D * batch, V, 0, nullptr,
-                                nullptr, nullptr, nullptr);
+                                nullptr, nullptr, nullptr, ChildFill{}, kb::FeatOut{});
             } else {
-                kg::gemm(st, bf, c->x, H, c->w.lm_head, c->med_logits, V, D * batch, V, H, false);
+                kf::gemm(st, c->x, H, c->w.lm_head, c->med_logits, V, D * batch, V, H, false);
             }
             ks::NodeList nodes = list_nodes(c, 0);
             for (int d = 1; d < D; ++d) append_nodes(nodes, c, d);
@@ -645,12 +654,11 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
                 const int MT = kb::mt_of(D * batch);
                 const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
                 kb::logits_topk(st, c->part, S, MT * 16, kb::pad64(V), no_scale(), nullptr, 0, D * batch, V, kmax,
-                                c->cand_val, c->cand_idx, c->topk_idx, c->topk_val);
+                                c->cand_val, c->cand_idx, nullptr, nullptr, fill(0, 0), kb::FeatOut{});
             } else {
-                kg::gemm(st, bf, c->x, H, c->w.lm_head, c->logits, V, D * batch, V, H, false);
-                kg::topk_rows(st, c->logits, V, D * batch, V, kmax, c->topk_idx, c->topk_val);
+                kf::gemm(st, c->x, H, c->w.lm_head, c->logits, V, D * batch, V, H, false);
+                kg::topk_rows(st, c->logits, V, D * batch, V, kmax, nullptr, nullptr, fill(0, 0));
             }
-            kg::fill_medusa(st, c->topk_idx, c->topk_val, kmax, c->tt, tree_tokens, tree_scores, batch, T, D);
         }
         KOALA_CHECK_LAUNCH(c);
         return KOALA_OK;
@@ -658,63 +666,74 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
 
     // EAGLE-style: catch-up rows first, then one pass per tree depth that has expanded nodes
     const size_t ls = layer_stride_bytes(c);
-    // fc over [embedding ; feature] then the K draft layers; leaves the predicted features in c->x
-    auto run_head = [&](int rows_per_seq) {
+    // fc over [embedding ; feature] then the K draft layers; level_nodes: the pass of a tree level, else the catch-up pass.  The
+    // predicted features go to fhat (the root's, or the level nodes') and, for the LM head, are left in c->xf (bf16) or
+    // returned as rows with their stride (fp32).
+    struct Rows { const float *a; int lda; };
+    auto run_head = [&](const PassArgs &pa, int rows_per_seq, const int32_t *level_nodes) {
         const int rows = batch * rows_per_seq;
         if (bf) {
             const int MT = kb::mt_of(rows), Mp = MT * 16;
-            rows_to_frags(c, st, c->act, 2 * H, rows, 2 * H, MT);
+            kb::pass_in(st, pa, c->w.embed, nullptr, nullptr, c->xf, nullptr, 0, rows, H, MT);
             c->pend_S = MT <= 4 ? bf_gemm_rows(c, st, c->w.fc, c->xf, H, 2 * H, MT) : bf_gemm(c, st, c->w.fc, H, 2 * H, MT);
             c->pend_ld = H;
             c->pend_mode = 2;
+            c->frags_ready = false;
             for (int k = 0; k < K; ++k)
                 decoder_layer_bf16(c, st, batch, rows_per_seq, c->w.draft_w + 6 * k, (char *)c->kv.draft_k + ls * k,
                                    (char *)c->kv.draft_v + ls * k);
-            fold_pending(c, st, rows, MT, nullptr);
-        } else {
-            kg::gemm(st, bf, c->act, 2 * H, c->w.fc, c->x, H, rows, H, 2 * H, false);
-            for (int k = 0; k < K; ++k)
-                decoder_layer(c, st, batch, rows_per_seq, c->w.draft_w + 6 * k, (char *)c->kv.draft_k + ls * k,
-                              (char *)c->kv.draft_v + ls * k);
+            const int rows_out = level_nodes ? rows : batch;
+            if (D > 0)
+                kb::head_out(st, c->x, c->part, c->pend_S, Mp, c->fhat, level_nodes, rows_per_seq, m, T, c->xf,
+                             kb::mt_of(rows_out), rows_out, H);
+            c->pend_S = 0;
+            return Rows{nullptr, 0};
         }
+        kg::pass_in(st, pa, c->w.embed, c->act, rows, H);
+        kf::gemm(st, c->act, 2 * H, c->w.fc, c->x, H, rows, H, 2 * H, false);
+        for (int k = 0; k < K; ++k)
+            decoder_layer(c, st, batch, rows_per_seq, c->w.draft_w + 6 * k, (char *)c->kv.draft_k + ls * k,
+                          (char *)c->kv.draft_v + ls * k);
+        if (D == 0) return Rows{nullptr, 0};
+        if (level_nodes) {
+            kg::store_fhat(st, c->x, c->fhat, level_nodes, batch, rows_per_seq, T, H);
+            return Rows{c->x, H};
+        }
+        kg::gather_last_rows(st, c->x, c->fhat, (size_t)T * H, batch, m, H);
+        return Rows{c->fhat, T * H};
     };
-    // LM head on `rows` fp32 rows at a (row stride lda), then the children of the level's nodes: their
-    // parent's top-k tokens by rank, or draws from the parent's distribution
-    auto head_children = [&](float *a, int lda, int rows, int d, const int32_t *lv, int nl) {
-        const int k = c->topk[d];
+    // LM head on the rows run_head left, then the children of the level's nodes: their parent's top-k tokens by rank, or
+    // draws from the parent's distribution
+    auto head_children = [&](const Rows &in, int d, int nl) {
+        const int k = c->topk[d], rows = batch * nl;
         if (bf) {
             const int MT = kb::mt_of(rows), Vp = kb::pad64(V);
-            rows_to_frags(c, st, a, lda, rows, H, MT);
             const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
             kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), sampling ? c->logits : nullptr, V, rows, V,
-                            sampling ? 0 : k, c->cand_val, c->cand_idx, c->topk_idx, c->topk_val);
+                            sampling ? 0 : k, c->cand_val, c->cand_idx, nullptr, nullptr, fill(d, nl), kb::FeatOut{});
         } else {
-            kg::gemm(st, bf, a, lda, c->w.lm_head, c->logits, V, rows, V, H, false);
-            if (!sampling) kg::topk_rows(st, c->logits, V, rows, V, k, c->topk_idx, c->topk_val);
+            kf::gemm(st, in.a, in.lda, c->w.lm_head, c->logits, V, rows, V, H, false);
+            if (!sampling) kg::topk_rows(st, c->logits, V, rows, V, k, nullptr, nullptr, fill(d, nl));
         }
         if (sampling)
             ks::sample_children(st, c->logits, c->logits, list_nodes(c, d), false, c->tt, T, V, temperature, u_draw,
                                 tree_tokens, draft_logits, batch);
-        else
-            kg::fill_children(st, c->topk_idx, c->topk_val, k, lv, nl, c->tt, d, tree_tokens, tree_scores, batch, T);
     };
-    kg::setup_catchup(st, c, batch, m);
-    kg::fc_input(st, bf, tok_in, c->w.embed, feat_in, c->act, batch * m, H);
-    run_head(m);
-    if (D > 0) {
-        // root's predicted feature -> fhat[b][0]; its logits decide the depth-1 tokens
-        kg::gather_last_rows(st, c->x, c->fhat, (size_t)T * H, batch, m, H);
-        head_children(c->fhat, T * H, batch, 0, c->tt.level_nodes, 1);
-    }
+    PassArgs pa = kg::pass_args(c, 1, m, m, 0);
+    pa.tok = tok_in;
+    pa.feat = feat_in;
+    pa.root_tok = tree_tokens;
+    pa.root_score = tree_scores;
+    Rows in = run_head(pa, m, nullptr);
+    if (D > 0) head_children(in, 0, 1);   // the root's predicted feature decides the depth-1 tokens
     for (int d = 1; d < D; ++d) {
         const int nl = (int)c->level_exp[d].size();
         if (nl == 0) continue;
-        const int32_t *lv = c->tt.level_nodes + (size_t)d * 64;
-        kg::setup_level(st, c, batch, d, nl);
-        kg::level_inputs(st, bf, tree_tokens, c->w.embed, c->fhat, lv, c->tt.parent, c->act, batch, nl, T, H);
-        run_head(nl);
-        kg::store_fhat(st, c->x, c->fhat, lv, batch, nl, T, H);
-        head_children(c->x, H, batch * nl, d, lv, nl);
+        pa = kg::pass_args(c, 2, nl, 0, d);
+        pa.tok = tree_tokens;
+        pa.feat = c->fhat;
+        in = run_head(pa, nl, c->tt.level_nodes + (size_t)d * 64);
+        head_children(in, d, nl);
     }
     KOALA_CHECK_LAUNCH(c);
     return KOALA_OK;
@@ -799,11 +818,13 @@ koala_status koala_accept_prefix(koala_ctx *c, void *hip_stream, int batch, cons
         return fail(c, KOALA_E_NULL, "all accept_prefix pointers are required");
     hipStream_t st = (hipStream_t)hip_stream;
     const koala_shape &s = c->shape;
-    kg::accept_scan(st, c->tt, c->T, c->D, tree_tokens, greedy, accept_len, accept_path, next_token, batch);
     if (commit) {
-        kg::kv_commit(st, s.dtype == KOALA_BF16, c->kv.target_k, c->kv.target_v, c->kv.ctx_len, accept_len,
-                      accept_path, c->D, s.n_layers, c->max_batch, batch, s.n_heads, c->kv.capacity, s.head_dim);
+        kg::accept_commit(st, s.dtype == KOALA_BF16, c->tt, c->T, c->D, tree_tokens, greedy, c->kv.target_k, c->kv.target_v,
+                          c->kv.ctx_len, accept_len, accept_path, next_token, s.n_layers, c->max_batch, batch, s.n_heads,
+                          c->kv.capacity, s.head_dim);
         kg::advance_ctx(st, c->kv.ctx_len, accept_len, batch);
+    } else {
+        kg::accept_scan(st, c->tt, c->T, c->D, tree_tokens, greedy, accept_len, accept_path, next_token, batch);
     }
     KOALA_CHECK_LAUNCH(c);
     return KOALA_OK;

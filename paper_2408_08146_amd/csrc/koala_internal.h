@@ -76,6 +76,7 @@ struct koala_ctx {
     int *cand_idx;
     float *row_sums;   // [64 chunks][rows] sums of squares per 512-column chunk (RMSNorm row scale)
     int pend_S, pend_ld, pend_mode;  // partial sums waiting to be folded into x (0 = none)
+    bool frags_ready;                // the next layer's input fragments and row sums are in place already
 
     // optional event timing of the GEMM launches (koala_profile_begin / _end)
     std::vector<hipEvent_t> prof_ev;
@@ -93,50 +94,45 @@ struct koala_ctx {
         }                                                                    \
     } while (0)
 
+struct PassArgs;   // koala_pass.h: what the first kernel of a pass works from
+
+// Where the winners of a top-k go (tree_tokens null: nowhere): see fill_children in koala_pass.h
+struct ChildFill {
+    TreeTables tt;
+    int n_level, d, batch, T;
+    int32_t *tree_tokens;
+    float *scores;
+};
+
 // ---------------------------------------------------------------------------------------------
-// launchers implemented in kernels_generic.hip (is_bf16 selects the storage type of weights/KV)
+// launchers implemented in kernels_generic.hip: bookkeeping shared by both model dtypes
 // ---------------------------------------------------------------------------------------------
 namespace kg {
 
-void setup_verify(hipStream_t s, const koala_ctx *c, int batch);
-void setup_catchup(hipStream_t s, const koala_ctx *c, int batch, int m);
-void setup_level(hipStream_t s, const koala_ctx *c, int batch, int d, int n_level);
-
-void embed_rows(hipStream_t s, bool bf16, const int32_t *tok, const void *E, float *x, int rows, int H);
-void fc_input(hipStream_t s, bool bf16, const int32_t *tok, const void *E, const float *feat,
-              float *act, int rows, int H);
-void rmsnorm(hipStream_t s, bool bf16, const float *x, const void *g, float *out, int rows, int H, float eps);
-// Y[M,N] (ldy) = or += A[M,K] (lda) * W[N,K]^T
-void gemm(hipStream_t s, bool bf16, const float *A, int lda, const void *W, float *Y, int ldy,
-          int M, int N, int K, bool accumulate);
-void rope_append(hipStream_t s, bool bf16, const float *qkv, const RowMeta &meta, float *qrot,
-                 void *kcache, void *vcache, int rows, int H, int n_heads, int head_dim,
-                 int capacity, int max_batch_stride_rows);
-void attention(hipStream_t s, bool bf16, const float *qrot, const RowMeta &meta, const void *kcache,
-               const void *vcache, float *o_part, float *ml, float *attn_out, int batch,
-               int rows_per_seq, int n_heads, int head_dim, int capacity, int nsplit);  // attn_out NULL: no merge
-void silu_mul(hipStream_t s, const float *gu, float *act, int rows, int F);
+PassArgs pass_args(const koala_ctx *c, int mode, int rows_per_seq, int m, int d);
+// fp32 form of the first kernel of a pass: row metadata and rotary tables, and the embedded rows (mode 0: x [rows][H]) or the
+// fc input [embedding ; feature] (modes 1, 2: x [rows][2H])
+void pass_in(hipStream_t s, const PassArgs &a, const void *E, float *x, int rows, int H);
+// fp32 features after the final norm
+void rmsnorm(hipStream_t s, const float *x, const void *g, float *out, int rows, int H, float eps);
 void resblock_update(hipStream_t s, float *x, const float *y, int n);
-void topk_rows(hipStream_t s, const float *logits, int ld, int rows, int V, int k, int32_t *idx, float *val);
-void copy_f32(hipStream_t s, float *dst, const float *src, size_t n);
+// k largest of each row, to idx / val (may be null) and to the nodes `fill` names
+void topk_rows(hipStream_t s, const float *logits, int ld, int rows, int V, int k, int32_t *idx, float *val,
+               const ChildFill &fill);
 
 // draft bookkeeping
 void gather_last_rows(hipStream_t s, const float *x, float *dst, size_t dst_stride, int batch, int m, int H);
 void store_fhat(hipStream_t s, const float *x, float *fhat, const int32_t *level_nodes, int batch,
                 int n_level, int T, int H);
-void level_inputs(hipStream_t s, bool bf16, const int32_t *tree_tokens, const void *E, const float *fhat,
-                  const int32_t *level_nodes, const int32_t *parent, float *act, int batch,
-                  int n_level, int T, int H);
 void set_root(hipStream_t s, const int32_t *tok_in, int m, int32_t *tree_tokens, float *scores, int batch, int T);
-void fill_children(hipStream_t s, const int32_t *topk_idx, const float *topk_val, int kmax,
-                   const int32_t *level_nodes, int n_level, const TreeTables &tt, int d,
-                   int32_t *tree_tokens, float *scores, int batch, int T);
-void fill_medusa(hipStream_t s, const int32_t *topk_idx, const float *topk_val, int kmax,
-                 const TreeTables &tt, int32_t *tree_tokens, float *scores, int batch, int T, int heads);
 
 void accept_scan(hipStream_t s, const TreeTables &tt, int T, int D, const int32_t *tree_tokens,
                  const int32_t *greedy, int32_t *accept_len, int32_t *accept_path, int32_t *next_token,
                  int batch);
+// accept_scan and kv_commit in one launch
+void accept_commit(hipStream_t s, bool bf16, const TreeTables &tt, int T, int D, const int32_t *tree_tokens, const int32_t *greedy,
+                   void *kcache, void *vcache, const int32_t *ctx_len, int32_t *accept_len, int32_t *accept_path,
+                   int32_t *next_token, int n_layers, int max_batch, int batch, int n_heads, int capacity, int head_dim);
 void kv_commit(hipStream_t s, bool bf16, void *kcache, void *vcache, const int32_t *ctx_len,
                const int32_t *accept_len, const int32_t *accept_path, int D, int n_layers,
                int max_batch, int batch, int n_heads, int capacity, int head_dim);
@@ -149,6 +145,23 @@ void gen_next(hipStream_t s, const float *feat_out, const int32_t *tree_tokens, 
               int32_t *tok_next, int32_t *out_tokens, int n_done, int max_new);
 
 }  // namespace kg
+
+// ---------------------------------------------------------------------------------------------
+// launchers implemented in kernels_fp32.hip (fp32 model: row-major weights and caches)
+// ---------------------------------------------------------------------------------------------
+namespace kf {
+
+// Y[M,N] (ldy) = or += X[M,K] (ldx) * W[N,K]^T
+void gemm(hipStream_t st, const float *X, int ldx, const void *W, float *Y, int ldy, int M, int N, int K, bool add);
+// QKV projection of RMSNorm(X): rotated queries to qrot [rows][H], keys and values to their cache slots
+void norm_qkv(hipStream_t st, const float *X, const void *gain, float eps, const void *W, const RowMeta &meta, float *qrot,
+              void *kc, void *vc, int rows, int H, int n_heads, int head_dim, int cap);
+// act[rows][F] = SiLU(gate) * up of RMSNorm(X)
+void norm_swiglu(hipStream_t st, const float *X, const void *gain, float eps, const void *W, float *act, int rows, int F, int H);
+void attention(hipStream_t st, const float *qrot, const RowMeta &meta, const void *kc, const void *vc, float *o_part, float *ml,
+               float *out, int batch, int rows_per_seq, int n_heads, int head_dim, int cap, int max_split);
+
+}  // namespace kf
 
 // ---------------------------------------------------------------------------------------------
 // launchers implemented in kernels_sampling.hip (non-greedy drafting and acceptance, section 2.2)
@@ -209,6 +222,13 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 // scale, SiLU(gate) * up as fragments Xo of the down projection's input
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// Up to sixteen rows against a matrix whose row groups in eights fill one round of compute units, and no smaller groups do:
+// the LM head of a 32000-token vocabulary (250 workgroups, one split, so P holds finished sums: 42 us at 4096 columns where
+// gemm_packed with three splits takes 44; with more rows the registers do not hold two tiles of eight groups and it loses,
+// 51 against 49 us at 32 rows, 56 against 54 at 64).
+bool rows_wide(int Npad, int n_cu);
+void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, hipEvent_t ev_start = nullptr,
+                    hipEvent_t ev_stop = nullptr);
 // n matrices W[h] of one shape on the same input: P[n][S][MTT*16][Npad]
 void gemm_rows_heads(hipStream_t st, const void *const *W, int n, const void *Xf, float *P, int Npad, int K, int MTT, int S,
                      hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
@@ -244,14 +264,26 @@ void attention_tree(hipStream_t st, const void *qf, const RowMeta &meta, const v
                     int rows_per_seq, int n_heads, int head_dim, int cap, int nsplit);
 void silu_frag(hipStream_t st, const float *P, int S, int Mp, int ldp, const NormScale &ns, void *Xf, int MT, int M,
                int F);
-// rows of x and their fragments: the newest feature of sequence row % batch
-void medusa_in(hipStream_t st, const float *feat, float *x, void *Xf, int batch, int m, int rows, int H, int MT);
+// First kernel of a pass: row metadata and rotary tables, and mode 0: the embedded rows x, fragments of gain * x and chunk
+// sums of squares; modes 1, 2: fragments of the fc input [embedding ; feature]
+void pass_in(hipStream_t st, const PassArgs &a, const void *E, const void *gain, float *x, void *Xf, float *sums, int srows,
+             int rows, int H, int MT);
+// Last kernel of a draft pass: x + pending partials -> fhat, and their fragments.  Level pass: every row b * n_level + li to
+// fhat[b][node]; catch-up pass (level_nodes null): row b * m + m - 1 to fhat[b][0]
+void head_out(hipStream_t st, const float *x, const float *P, int S, int Mp, float *fhat, const int32_t *level_nodes, int n_level,
+              int m, int T, void *Xf, int MT, int rows_out, int H);
+// rows of x and their fragments: the newest feature of sequence row % batch; and each sequence's root
+void medusa_in(hipStream_t st, const float *feat, const int32_t *tok_in, float *x, void *Xf, int batch, int m, int rows, int H,
+               int MT, int T, int32_t *root_tok, float *root_score);
 // x[r] += SiLU(partials of row r - p0) and (Xf not null) the fragments of the new x, r = r0 .. r0 + rows - 1;
 // P[head][S][Mp][H], batch rows a head
 void resblock_p(hipStream_t st, float *x, void *Xf, const float *P, int S, int Mp, int batch, int r0, int p0, int rows, int H,
                 int MT);
-void reduce_out(hipStream_t st, const float *P, int S, int Mp, int ldp, float *out, int ldo, int M, int N);
+// the k largest logits of each row (k = 0: none, the logits are only written) to idx / val (may be null) and to the nodes
+// `fill` names; feat (may be null): the rows after the final norm
+struct FeatOut { const float *x; const void *gain; float *feat; int H; };
 void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const NormScale &ns, float *logits, int ldl,
-                 int rows, int V, int k, float *cand_val, int *cand_idx, int32_t *idx, float *val);
+                 int rows, int V, int k, float *cand_val, int *cand_idx, int32_t *idx, float *val, const ChildFill &fill,
+                 const FeatOut &fo);
 
 }  // namespace kb
