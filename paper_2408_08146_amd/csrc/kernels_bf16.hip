@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256 * RS, RS > 1 ? 1 : MT == 4 ? 2 : 3) void k_gemm
 // ---------------------------------------------------------------------------------------------
 // Row-group GEMM with a fused epilogue.  One workgroup owns U consecutive 16-row groups of the weights
 // (16 U output columns) over a K range; its waves take the 64-k tiles of that range in turn (wave w:
-// tiles w, w + KW, ...) and every wave loads both operands of its tiles straight into MFMA registers -
+// tiles w, w + NW, ...) and every wave loads both operands of its tiles straight into MFMA registers -
 // the U 2 KiB weight pieces and the matching activation fragments - so the streaming loop has no
 // barrier and no LDS traffic.  The waves' accumulators meet at the end, in LDS, and are added in a fixed order
 // (deterministic).  With S = 1 the workgroup then holds finished outputs and applies the consumer's
@@ -249,21 +249,24 @@ struct GemmEpi {
     int *counters;
 };
 
-template <int U, int MT, int RS, int NW, int PF, int EPI>
+template <int U, int MT, int NW, int PF, int EPI>
 __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__ Wp, const u32x4 *__restrict__ Xf,
                                                        int Npad, int K, int S, GemmEpi e) {
-    constexpr int MTT = MT * RS, KW = NW / RS;
     constexpr bool TREE = gemm_rows_tree(U, MT, NW);
     constexpr int NRED = TREE ? NW / 2 : NW;
     extern __shared__ __attribute__((aligned(16))) unsigned char gsm[];
+    constexpr bool ROWS = EPI == EPI_QKV || EPI == EPI_SWIGLU;       // the epilogue needs data of the activation rows
+    constexpr int R = MT * 16, NT = 64 * NW, NPL = NT / R;          // threads of a row in the prologue
     f32x4 *red = (f32x4 *)gsm;                                     // [NRED][U][MT][64]
-    float *cs = (float *)(gsm + (size_t)NRED * U * MT * 64 * 16);    // EPI_QKV: [MTT*16][U][8][cos, sin]
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
-    const int kw = wave / RS, mh = wave % RS;
+    float *sq_s = (float *)(gsm + (size_t)NRED * U * MT * 64 * 16);  // ROWS: [NPL][R] shares of the rows' sums of squares
+    int *slot_s = (int *)(sq_s + (ROWS ? NT : 0)), *bat_s = slot_s + R;   // EPI_QKV: [R] cache slot and sequence
+    float *cs = (float *)(bat_s + R);                                // EPI_QKV: [R][U][8][cos, sin]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
     const int nunits = Npad / 16, nwg = (nunits + U - 1) / U;
     const int g = blockIdx.x % nwg, sp = blockIdx.x / nwg, ug0 = g * U;
     const int nkt = K / 64;
-    const int kt0 = split_begin(sp, nkt, S), kt1 = split_begin(sp + 1, nkt, S);
+    // the split's 64-k tiles, dealt to the waves in turn: tile i of this wave is number kt0 + i * NW
+    const int kt0 = split_begin(sp, nkt, S) + wave, nst = max(0, (split_begin(sp + 1, nkt, S) - kt0 + NW - 1) / NW);
     if (EPI == EPI_HEADS) Wp = (const u32x4 *)e.heads[blockIdx.y];
     const u32x4 *w[U];   // unit j, tile kt, half s: w[j] + kt * 512 + s * 64 (a ragged last group re-reads its last unit)
 #pragma unroll
@@ -271,10 +274,41 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
         const int ug = min(ug0 + j, nunits - 1);
         w[j] = Wp + ((size_t)(ug >> 2) * nkt * 8 + (ug & 3) * 2) * 64 + l;
     }
-    const u32x4 *x = Xf + (size_t)mh * MT * 64 + l;
+    const u32x4 *x = Xf + l;
 
-    u32x4 wr[PF][U][2], xr[PF][2][MT];
-    auto load = [&](int kt, int slot) {
+    // What the epilogue needs of the activation rows is requested ahead of the first tiles, spread over the threads, and goes
+    // to LDS behind them: memory answers in order, so the wait for it is over before the first tile is there, and the
+    // tiles stay under way.  (Requested behind the tiles it held the loop back until all of them had arrived, with
+    // nothing new under way: the loop began 5 to 10 us into the kernel.  7B model, QKV 28.6 -> 23.7 us and gate/up
+    // 40.0 -> 35.5 us at 64 rows, 20.4 -> 18.7 and 32.0 -> 30.6 us at 26.)
+    constexpr int NCS = EPI == EPI_QKV ? (R * U * 8 + NT - 1) / NT : 1;
+    float sq[2] = {0.f, 0.f}, rc[NCS], rs_[NCS];
+    int slot = 0, bat = 0;
+    const int prow = threadIdx.x % R, ppart = threadIdx.x / R;
+    if (ROWS && e.sums) {
+        const float *src = e.sums + min(prow, e.rows - 1);
+        sq[0] = src[(size_t)min(ppart, e.nparts - 1) * e.srows];
+        sq[1] = src[(size_t)min(ppart + NPL, e.nparts - 1) * e.srows];
+    }
+    if (EPI == EPI_QKV) {
+        const int half = e.DH / 2, row = min(prow, e.rows - 1);
+        slot = e.meta.row_slot[row];
+        bat = e.meta.row_b[row];
+#pragma unroll
+        for (int i = 0; i < NCS; ++i) {
+            const int u = min((int)threadIdx.x + i * NT, R * U * 8 - 1);
+            const int dd = u & 7, j = (u >> 3) % U, r = min((u >> 3) / U, e.rows - 1);
+            const int n = min(ug0 + j, nunits - 1) * 16;   // of V as well: loaded, not used
+            const size_t at = (size_t)r * half + ((n % e.H) % e.DH) / 2 + dd;
+            rc[i] = e.meta.rope_cos[at];
+            rs_[i] = e.meta.rope_sin[at];
+        }
+    }
+    if (ROWS) __builtin_amdgcn_sched_barrier(0);
+
+    u32x4 wr[PF][U][2], xr[PF][2][MT];   // PF tiles are under way per wave
+    auto load = [&](int i, int slot) {
+        const int kt = kt0 + i * NW;
 #pragma unroll
         for (int j = 0; j < U; ++j)
 #pragma unroll
@@ -282,40 +316,29 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int m = 0; m < MT; ++m) xr[slot][s][m] = x[(size_t)(2 * kt + s) * (MTT * 64) + m * 64];
+            for (int m = 0; m < MT; ++m) xr[slot][s][m] = x[(size_t)(2 * kt + s) * (MT * 64) + m * 64];
     };
-    int kt = kt0 + kw;
 #pragma unroll
     for (int p = 0; p < PF; ++p)
-        if (kt + p * KW < kt1) load(kt + p * KW, p);
-
-    // per-lane row data of the epilogue, fetched while the first tiles are in flight
-    float rsc[MTT];
-    int rslot[MTT], rbat[MTT];
-    if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
-#pragma unroll
-        for (int m = 0; m < MTT; ++m) {
-            const int row = m * 16 + li;
-            const bool ok = row < e.rows;
-            float tot = 0.f;
-            if (e.sums && ok)
-                for (int c = 0; c < e.nparts; ++c) tot += e.sums[(size_t)c * e.srows + row];
-            rsc[m] = e.sums ? 1.0f / sqrtf(tot / (float)e.Kn + e.eps) : 1.f;
-            if (EPI == EPI_QKV) {
-                rslot[m] = ok ? e.meta.row_slot[row] : 0;
-                rbat[m] = ok ? e.meta.row_b[row] : 0;
-            }
+        if (p < nst) load(p, p);
+    __builtin_amdgcn_sched_barrier(0);
+    if (ROWS) {
+        float t = 0.f;
+        if (e.sums) {
+            t = (ppart < e.nparts ? sq[0] : 0.f) + (ppart + NPL < e.nparts ? sq[1] : 0.f);
+            for (int c = ppart + 2 * NPL; c < e.nparts; c += NPL) t += e.sums[(size_t)c * e.srows + min(prow, e.rows - 1)];
         }
+        sq_s[threadIdx.x] = t;
     }
     if (EPI == EPI_QKV) {
-        const int half = e.DH / 2;
-        for (int u = threadIdx.x; u < MTT * 16 * U * 8; u += 64 * NW) {
-            const int dd = u & 7, j = (u >> 3) % U, row = (u >> 3) / U;
-            const int n = min(ug0 + j, nunits - 1) * 16;
-            const bool ok = row < e.rows && n < 2 * e.H;
-            const int ddg = ((n % e.H) % e.DH) / 2 + dd;
-            cs[2 * u] = ok ? e.meta.rope_cos[(size_t)row * half + ddg] : 1.f;
-            cs[2 * u + 1] = ok ? e.meta.rope_sin[(size_t)row * half + ddg] : 0.f;
+        if (threadIdx.x < R) {
+            slot_s[threadIdx.x] = slot;
+            bat_s[threadIdx.x] = bat;
+        }
+#pragma unroll
+        for (int i = 0; i < NCS; ++i) {
+            const int u = threadIdx.x + i * NT;
+            if (u < R * U * 8) *(f32_pair *)(cs + 2 * u) = f32_pair{rc[i], rs_[i]};
         }
     }
 
@@ -324,10 +347,10 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
     for (int j = 0; j < U; ++j)
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[j][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (; kt < kt1; kt += PF * KW) {
+    for (int i = 0; i < nst; i += PF) {
 #pragma unroll
         for (int p = 0; p < PF; ++p) {
-            if (kt + p * KW < kt1) {
+            if (i + p < nst) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
 #pragma unroll
@@ -339,13 +362,13 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
                                 a, __builtin_bit_cast(f16x8, xr[p][s][m]), acc[j][m], 0, 0, 0);
                     }
                 }
-                if (kt + (p + PF) * KW < kt1) load(kt + (p + PF) * KW, p);
+                if (i + p + PF < nst) load(i + p + PF, p);
             }
         }
     }
     // The waves' sums meet in LDS.  Where it fits (TREE false) every wave stores its accumulators and the epilogue
-    // adds the KW copies of a piece in wave order; otherwise the number of live accumulators is halved per round
-    // (waves [n/2, n) hand theirs to waves [0, n/2)) and waves 0 .. RS-1 store the totals.  Either order is fixed,
+    // adds the NW copies of a piece in wave order; otherwise the number of live accumulators is halved per round
+    // (waves [n/2, n) hand theirs to waves [0, n/2)) and wave 0 stores the totals.  Either order is fixed,
     // so results are bit-for-bit repeatable.
     if (!TREE) {
 #pragma unroll
@@ -354,7 +377,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             for (int m = 0; m < MT; ++m) red[((size_t)(wave * U + j) * MT + m) * 64 + l] = acc[j][m];
     } else {
 #pragma unroll
-        for (int n = NW; n > RS; n >>= 1) {
+        for (int n = NW; n > 1; n >>= 1) {
             const int hn = n >> 1;
             if (n < NW) __syncthreads();
             if (wave >= hn && wave < n) {
@@ -372,7 +395,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             }
         }
         __syncthreads();
-        if (wave < RS) {
+        if (wave == 0) {
 #pragma unroll
             for (int j = 0; j < U; ++j)
 #pragma unroll
@@ -383,30 +406,32 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
 
     // output piece (j, mtt): weight rows of unit j x activation tile mtt; lane (li, lg) holds columns
     // n .. n + 3 of activation row mtt * 16 + li
-    for (int u = wave; u < U * MTT; u += NW) {
-        const int j = u / MTT, mtt = u % MTT, umh = mtt / MT, um = mtt % MT;
+    for (int u = wave; u < U * MT; u += NW) {
+        const int j = u / MT, mtt = u % MT;
         if (ug0 + j >= nunits) continue;
-        f32x4 v = red[((size_t)(umh * U + j) * MT + um) * 64 + l];
+        f32x4 v = red[((size_t)j * MT + mtt) * 64 + l];
         if (!TREE) {
 #pragma unroll
-            for (int q = 1; q < KW; ++q) v += red[((size_t)((q * RS + umh) * U + j) * MT + um) * 64 + l];
+            for (int q = 1; q < NW; ++q) v += red[((size_t)(q * U + j) * MT + mtt) * 64 + l];
         }
         const int row = mtt * 16 + li, n = (ug0 + j) * 16 + 4 * lg;
         if (EPI == EPI_PARTIAL || EPI == EPI_HEADS) {
             const int part = EPI == EPI_HEADS ? blockIdx.y * S + sp : sp;
-            *(f32x4 *)(e.P + ((size_t)part * (MTT * 16) + row) * Npad + n) = v;
+            *(f32x4 *)(e.P + ((size_t)part * (MT * 16) + row) * Npad + n) = v;
             continue;
         }
         if (row >= e.rows) continue;
         float sc = 1.f;
-        int slot = 0, bat = 0;
-#pragma unroll
-        for (int m = 0; m < MTT; ++m)   // static indexing keeps the per-row data in registers
-            if (m == mtt) { sc = rsc[m]; if (EPI == EPI_QKV) { slot = rslot[m]; bat = rbat[m]; } }
+        if (e.sums) {
+            float tot = 0.f;
+            for (int c = 0; c < min(NPL, e.nparts); ++c) tot += sq_s[c * R + row];
+            sc = 1.0f / sqrtf(tot / (float)e.Kn + e.eps);
+        }
         v *= sc;
         if (EPI == EPI_QKV) {
             const int which = n / e.H, nn = n % e.H, h = nn / e.DH, r = nn % e.DH, half = e.DH / 2;
-            const size_t o = (((size_t)bat * e.n_heads + h) * e.cap + slot) * e.DH;
+            const int bat = bat_s[row];
+            const size_t o = (((size_t)bat * e.n_heads + h) * e.cap + slot_s[row]) * e.DH;
             if (which == 2) {
                 const uint32_t lo = f2bf(v[0]) | (f2bf(v[1]) << 16), hi = f2bf(v[2]) | (f2bf(v[3]) << 16);
                 *(u64_pair *)(e.vc + o + r) = u64_pair{lo, hi};
@@ -441,7 +466,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             const float g0 = v[0], g1 = v[2];
             const float y0 = g0 / (1.0f + __expf(-g0)) * v[1], y1 = g1 / (1.0f + __expf(-g1)) * v[3];
             const int ks = f0 >> 5, lane = li + 16 * ((f0 & 31) >> 3);
-            e.Xo[(((size_t)ks * MTT + mtt) * 64 + lane) * 4 + ((f0 & 7) >> 1)] = half_pair(y0, y1);
+            e.Xo[(((size_t)ks * MT + mtt) * 64 + lane) * 4 + ((f0 & 7) >> 1)] = half_pair(y0, y1);
         }
     }
 }
@@ -1261,34 +1286,41 @@ __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, cons
 }
 
 // 32-k steps in flight per wave: what the accumulators (U * MT tiles) leave of the 256 registers
-template <int U, int MT, int RS, int NW, int PF, int EPI>
+// 64-k tiles under way per wave of k_gemm_rows: two, or one where two do not fit in the registers with the accumulators.
+// More does not pay: a stream of 256 workgroups is at the memory's rate with these (7B gate/up at 26 rows: 180 MB in 30.6 us,
+// where a plain read of as much takes 28.4 us), and 32-k steps with up to 8 under way, all loads unconditional, measured
+// 14.3 instead of 12.6 us on the short K ranges of the output and down projections (a 4096-k split is two tiles per wave).
+constexpr int rows_tiles(int U, int MT) { return MT == 4 && U > 4 ? 1 : 2; }
+
+template <int U, int MT, int EPI>
 void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, int K, int S, const GemmEpi &e,
                       hipEvent_t ev_start, hipEvent_t ev_stop, int n_heads = 1) {
-    const size_t sm = (size_t)(gemm_rows_tree(U, MT, NW) ? NW / 2 : NW) * U * MT * 64 * 16 + (EPI == EPI_QKV ? (size_t)MT * RS * 16 * U * 8 * 2 * 4 : 0);
+    constexpr int NW = 8, PF = rows_tiles(U, MT);
+    constexpr int R = MT * 16;   // accumulators, shares of the rows' sums, cache slots and sequences, cos/sin
+    const size_t sm = (size_t)(gemm_rows_tree(U, MT, NW) ? NW / 2 : NW) * U * MT * 64 * 16 +
+                      (EPI == EPI_QKV || EPI == EPI_SWIGLU ? (size_t)64 * NW * 4 + R * 8 : 0) +
+                      (EPI == EPI_QKV ? (size_t)R * U * 8 * 2 * 4 : 0);
     static bool done = false;
     if (!done) {
-        (void)hipFuncSetAttribute((const void *)k_gemm_rows<U, MT, RS, NW, PF, EPI>,
+        (void)hipFuncSetAttribute((const void *)k_gemm_rows<U, MT, NW, PF, EPI>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
         done = true;
     }
     const dim3 grid(((Npad / 16 + U - 1) / U) * S, n_heads);
     if (ev_start || ev_stop)
-        hipExtLaunchKernelGGL((k_gemm_rows<U, MT, RS, NW, PF, EPI>), grid, dim3(64 * NW), sm, st, ev_start, ev_stop, 0,
+        hipExtLaunchKernelGGL((k_gemm_rows<U, MT, NW, PF, EPI>), grid, dim3(64 * NW), sm, st, ev_start, ev_stop, 0,
                               (const u32x4 *)Wp, (const u32x4 *)Xf, Npad, K, S, e);
     else
-        k_gemm_rows<U, MT, RS, NW, PF, EPI><<<grid, 64 * NW, sm, st>>>((const u32x4 *)Wp, (const u32x4 *)Xf, Npad, K, S,
-                                                                      e);
+        k_gemm_rows<U, MT, NW, PF, EPI><<<grid, 64 * NW, sm, st>>>((const u32x4 *)Wp, (const u32x4 *)Xf, Npad, K, S, e);
 }
 
 // MTT = 1, 2 or 4 activation tiles
 template <int U, int EPI>
 void dispatch_gemm_rows_u(hipStream_t st, const void *Wp, const void *Xf, int Npad, int K, int MTT, int S,
                           const GemmEpi &e, hipEvent_t ev_start, hipEvent_t ev_stop, int n_heads = 1) {
-    // tiles in flight per wave: two, or one where the registers do not hold a second (four tiles with more than
-    // four groups)
-    if (MTT == 1) launch_gemm_rows<U, 1, 1, 8, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
-    else if (MTT == 2) launch_gemm_rows<U, 2, 1, 8, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
-    else launch_gemm_rows<U, 4, 1, 8, (U <= 4 ? 2 : 1), EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
+    if (MTT == 1) launch_gemm_rows<U, 1, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
+    else if (MTT == 2) launch_gemm_rows<U, 2, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
+    else launch_gemm_rows<U, 4, EPI>(st, Wp, Xf, Npad, K, S, e, ev_start, ev_stop, n_heads);
 }
 
 // 16-row groups per workgroup for an S = 1 launch over Npad rows: the smallest supported count that covers the
@@ -1410,7 +1442,7 @@ void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, in
                     hipEvent_t ev_stop) {
     GemmEpi e{};
     e.P = P;
-    launch_gemm_rows<8, 1, 1, 8, 2, EPI_PARTIAL>(st, Wp, Xf, Npad, K, 1, e, ev_start, ev_stop);
+    launch_gemm_rows<8, 1, EPI_PARTIAL>(st, Wp, Xf, Npad, K, 1, e, ev_start, ev_stop);
 }
 
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
