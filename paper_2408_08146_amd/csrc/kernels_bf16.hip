@@ -1285,17 +1285,24 @@ __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, cons
     }
 }
 
-// 32-k steps in flight per wave: what the accumulators (U * MT tiles) leave of the 256 registers
-// 64-k tiles under way per wave of k_gemm_rows: two, or one where two do not fit in the registers with the accumulators.
-// More does not pay: a stream of 256 workgroups is at the memory's rate with these (7B gate/up at 26 rows: 180 MB in 30.6 us,
-// where a plain read of as much takes 28.4 us), and 32-k steps with up to 8 under way, all loads unconditional, measured
-// 14.3 instead of 12.6 us on the short K ranges of the output and down projections (a 4096-k split is two tiles per wave).
-constexpr int rows_tiles(int U, int MT) { return MT == 4 && U > 4 ? 1 : 2; }
+// Waves of a k_gemm_rows workgroup, and 64-k tiles under way in each.  Eight waves (two per SIMD) with two tiles, or one where
+// two do not fit in 256 registers with the accumulators.  More in flight does not pay: a stream of 256 workgroups is at the
+// memory's rate with these (7B gate/up at 26 rows: 180 MB in 30.6 us, where a plain read of as much takes 28.4 us), and
+// 32-k steps with up to 8 under way, all loads unconditional, measured 14.3 instead of 12.6 us on the short K ranges
+// of the output and down projections.  Four waves with twice the registers and three tiles where eight row groups meet more
+// than one activation tile (LM head 32000 x 4096: 50 -> 44 us at 26 rows, 54 -> 48 at 64, 67 -> 56 for 5120 columns at 60, against
+// gemm_packed; eight waves with one tile were slower than that) and for partial sums of 64 rows, whose accumulators then meet
+// in half the LDS rounds (O and down projection together 33.3 -> 30.5 us at 4096, 7B).  With the epilogues four waves lose: their
+// rotary and SwiGLU step is spread over half the threads (QKV at 64 rows 23.6 -> 25.5 us).
+constexpr int rows_waves(int U, int MT, int EPI) {
+    return (EPI == EPI_PARTIAL || EPI == EPI_HEADS) && (U == 8 ? MT > 1 : MT == 4) ? 4 : 8;
+}
+constexpr int rows_tiles(int U, int MT, int NW) { return NW == 4 ? 3 : MT == 4 && U > 4 ? 1 : 2; }
 
 template <int U, int MT, int EPI>
 void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, int K, int S, const GemmEpi &e,
                       hipEvent_t ev_start, hipEvent_t ev_stop, int n_heads = 1) {
-    constexpr int NW = 8, PF = rows_tiles(U, MT);
+    constexpr int NW = rows_waves(U, MT, EPI), PF = rows_tiles(U, MT, NW);
     constexpr int R = MT * 16;   // accumulators, shares of the rows' sums, cache slots and sequences, cos/sin
     const size_t sm = (size_t)(gemm_rows_tree(U, MT, NW) ? NW / 2 : NW) * U * MT * 64 * 16 +
                       (EPI == EPI_QKV || EPI == EPI_SWIGLU ? (size_t)64 * NW * 4 + R * 8 : 0) +
@@ -1438,11 +1445,11 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 
 bool rows_wide(int Npad, int n_cu) { return Npad / 16 > 7 * n_cu && (Npad / 16 + 7) / 8 <= n_cu; }
 
-void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, hipEvent_t ev_start,
+void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, hipEvent_t ev_start,
                     hipEvent_t ev_stop) {
     GemmEpi e{};
     e.P = P;
-    launch_gemm_rows<8, 1, EPI_PARTIAL>(st, Wp, Xf, Npad, K, 1, e, ev_start, ev_stop);
+    dispatch_gemm_rows_u<8, EPI_PARTIAL>(st, Wp, Xf, Npad, K, MTT, 1, e, ev_start, ev_stop);
 }
 
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,

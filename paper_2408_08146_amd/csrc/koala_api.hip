@@ -205,8 +205,8 @@ int bf_gemm(koala_ctx *c, hipStream_t st, const void *Wp, int N, int K, int MT, 
         kb::gemm_big(st, Wp, Xf, c->part, Npad, K, MT, b, ev.start, ev.stop);
         return b.S;
     }
-    if (MT == 1 && kb::rows_wide(Npad, c->n_cu)) {
-        kb::gemm_rows_wide(st, Wp, Xf, c->part, Npad, K, ev.start, ev.stop);
+    if (MT <= 4 && kb::rows_wide(Npad, c->n_cu)) {
+        kb::gemm_rows_wide(st, Wp, Xf, c->part, Npad, K, MT, ev.start, ev.stop);
         return 1;
     }
     const int S = kb::gemm_splits(Npad, K, MT);

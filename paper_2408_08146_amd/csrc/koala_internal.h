@@ -222,12 +222,11 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 // scale, SiLU(gate) * up as fragments Xo of the down projection's input
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// Up to sixteen rows against a matrix whose row groups in eights fill one round of compute units, and no smaller groups do:
-// the LM head of a 32000-token vocabulary (250 workgroups, one split, so P holds finished sums: 42 us at 4096 columns where
-// gemm_packed with three splits takes 44; with more rows the registers do not hold two tiles of eight groups and it loses,
-// 51 against 49 us at 32 rows, 56 against 54 at 64).
+// Up to 64 rows against a matrix whose row groups in eights fill one round of compute units, and no smaller groups do:
+// the LM head of a 32000-token vocabulary (250 workgroups, one split, so P holds finished sums; 4096 columns: 40 us at one row,
+// 44 at 26, 48 at 64, where gemm_packed with three splits takes 44, 50 and 54).
 bool rows_wide(int Npad, int n_cu);
-void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, hipEvent_t ev_start = nullptr,
+void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, hipEvent_t ev_start = nullptr,
                     hipEvent_t ev_stop = nullptr);
 // n matrices W[h] of one shape on the same input: P[n][S][MTT*16][Npad]
 void gemm_rows_heads(hipStream_t st, const void *const *W, int n, const void *Xf, float *P, int Npad, int K, int MTT, int S,
