@@ -526,7 +526,7 @@ def main():
         "verify_hbm_frac": vb / (parts[1] * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "iteration_hbm_frac": (vb + db) / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "gpu_state": state,
-        "roofline": {"bound": "hbm", "kernel": "k_gemm_rows (weight-streaming GEMM; k_gemm_packed for the LM head)",
+        "roofline": {"bound": "hbm", "kernel": "k_gemm_rows (weight-streaming GEMM)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "launches_timed": gemm_launches, "avg_launch_us": gemm_ms * 1e3 / max(1, gemm_launches),
