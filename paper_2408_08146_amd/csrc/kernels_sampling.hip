@@ -376,15 +376,17 @@ __device__ __forceinline__ float row_max(const float (&w)[NQ][4]) {
     for (int u = 0; u < NQ; ++u) m = fmaxf(m, fmaxf(fmaxf(w[u][0], w[u][1]), fmaxf(w[u][2], w[u][3])));
     return m;
 }
-// w <- exp((w - m) / tau) (past the vocabulary, where w is -inf, zero); returns this thread's sum
+// w <- exp((w - m) / tau), past the vocabulary zero (by index: at an infinite temperature the exponent of the -inf there
+// is no number); returns this thread's sum
 template <int NQ>
-__device__ __forceinline__ double row_exp(float (&w)[NQ][4], float m, float inv_tau) {
+__device__ __forceinline__ double row_exp(float (&w)[NQ][4], int V, float m, float inv_tau) {
+    asm volatile("" : "+s"(V));   // compared anew: no masks kept from the loads
     double s = 0.0;
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            w[u][e] = expf((w[u][e] - m) * inv_tau);
+            w[u][e] = (int)threadIdx.x * 4 < V - u * NT * 4 - e ? expf((w[u][e] - m) * inv_tau) : 0.f;
             s += (double)w[u][e];
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(NT) void k_sample_children_r(const float *src, ks::
     }
     float m = row_max<NQ>(w), unused = 0.f;
     block_max2(m, unused, sh);
-    (void)row_exp<NQ>(w, m, inv_tau);
+    (void)row_exp<NQ>(w, V, m, inv_tau);
     SegPair seg = segment_pairs<NQ>(w, sh);
     for (int j = 0; j < nk; ++j) {
         const int c = child_at(place, j);
@@ -616,8 +618,8 @@ __global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, in
             mq = row_max<NQ>(q);
             if (nk > 0) md = row_max<NQ>(d);
             block_max2(mq, md, sh);
-            sq = row_exp<NQ>(q, mq, inv_tau);
-            if (nk > 0) sd = row_exp<NQ>(d, md, inv_tau);
+            sq = row_exp<NQ>(q, Vi, mq, inv_tau);
+            if (nk > 0) sd = row_exp<NQ>(d, Vi, md, inv_tau);
             block_sum2(sq, sd, sh);
             row_scale<NQ>(q, 1.0 / sq);
             if (nk > 0) row_scale<NQ>(d, 1.0 / sd);

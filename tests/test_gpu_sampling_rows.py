@@ -99,6 +99,35 @@ def test_draws_and_acceptance_at_every_row_form(V):
     assert seen >= 8, seen
 
 
+@pytest.mark.parametrize("V", [100, 4099, 16385, 32000, 32768, 32771])
+def test_infinite_temperature_is_uniform(V):
+    """1/temperature is zero: every token weighs the same, and columns past the vocabulary weigh nothing.  Sums of ones and
+    the product of an fp32 u with a count are exact in fp64, so each draw is known: id number floor(u * left) among those not
+    drawn yet.  Equal distributions accept every first child."""
+    import torch
+    tree, batch, inf = make_tree([5, 3, 2], [1, 5, 9, 7]), 2, float("inf")
+    c, g, _, _ = _context(V, tree, batch)
+    _, u, tok, logits = _sample(c, g, tree, V, batch, 128, inf)
+    ch = [sorted(k, key=lambda x: tree.rank[x]) for k in oracle.children_lists(tree.parent)]
+    u_np, tok_np = u.double().cpu().numpy(), tok.cpu().numpy()
+    for b in range(batch):
+        for n in range(tree.n_nodes):
+            left = list(range(V))
+            for x in ch[n]:
+                assert tok_np[b, x] == left.pop(int(u_np[b, x] * len(left))), (V, b, n, x)
+    ua, ur = torch.full((batch, tree.n_nodes), 0.5, device="cuda"), torch.full((batch, tree.n_nodes), 0.25, device="cuda")
+    acc, path, nxt = (torch.zeros(s, dtype=torch.int32, device="cuda") for s in ((batch,), (batch, tree.depth + 1), (batch,)))
+    c.accept_sample(batch, tok, logits, logits, ua, ur, inf, acc, path, nxt, False)
+    for b in range(batch):
+        want, cur = [0], 0
+        while ch[cur]:
+            cur = ch[cur][0]
+            want.append(cur)
+        assert path[b, :len(want)].tolist() == want and int(acc[b]) == len(want) - 1
+        # V equal probabilities of one rounding each: the id is within one of a quarter of the vocabulary
+        assert abs(int(nxt[b]) - V // 4) <= 1
+
+
 @pytest.mark.parametrize("depth,batch", [(1, 1), (4, 8), (9, 3), (8, 8), (9, 8), (3, 40)])
 def test_grouped_heads(depth, batch):
     """Logits of every head against float64: bf16-valued weights, inputs rounded to fp16 twice on the way (2^-11 of a value
