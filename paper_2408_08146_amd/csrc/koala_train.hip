@@ -14,6 +14,8 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 struct __attribute__((packed, aligned(4))) f32x4_any { float x, y, z, w; };   // 16 bytes at a 4-byte aligned address
 struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
@@ -21,12 +23,16 @@ struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 // ---------------------------------------------------------------------------------------------
 // fp32 products on the 16-bit matrix pipe: C[M,N] (+)= alpha * sum_k Q(m,k) P(n,k).
 //
-// A float is the exact sum of three bfloat16 values (its 24 significant bits in three runs of eight: truncate,
-// subtract, truncate, subtract; every step is exact), so a product of two floats is the sum of nine bfloat16 products,
-// each exact in the fp32 accumulator of the MFMA.  Six of them are kept; the other three are below 2^-22 of the
-// product each and 2^-24 on average, one rounding of the fp32 sum.  Six 16x16x32 MFMAs (16 cycles each) do the work of
-// eight 16x16x4 fp32 MFMAs (32 cycles each), so the pipe is 2.7 times as fast as in fp32, and each accumulator is
-// rounded once per 32 terms and plane pair instead of once per four terms: the sums come out closer to the exact ones.
+// A float is the exact sum of three bfloat16 values (round to nearest, subtract, twice: the rest has 16, then eight
+// significant bits, so every subtraction and the last piece are exact), so a product of two floats is the sum of nine
+// bfloat16 products, each exact in the fp32 accumulator of the MFMA.  Six of them are kept; the other three come to at most
+// 2^-24 of the product, with either sign, and to 2^-27 root mean square (pieces cut off instead of rounded cost as much but
+// leave up to 2^-21, always towards zero).  The products of two first pieces have an accumulator of their own, rounded once
+// per 32 terms; the others are 2^-8 of them and meet it once, at the end.  Error of a sum of K random terms, measured, as a
+// multiple of the same sum in fp32 MFMAs (which round with every term): 1.03 at one term, 0.85 at two, 0.5 at eight,
+// 0.35 at 64, 0.33 at 1024.
+// Six 16x16x32 MFMAs (16 cycles each) do the work of eight 16x16x4 fp32 MFMAs (32 cycles each), so the pipe is 2.7 times
+// as fast as in fp32.
 //
 // Workgroup of 256 threads on a tile of 64 n x BM m; K in chunks of 32.  Both operands of a chunk go from memory to
 // registers (two chunks ahead, so that about 50 KB a compute unit are under way), are cut into their three planes there
@@ -37,25 +43,35 @@ struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 //                                    eight values of a fragment lane
 // LDS plane of a 16-row tile: 64 slots of 16 B, lane (i, g = k/8) in slot (i ^ 4 g) + 16 g: the 8-byte stores of 32 lanes of
 // the k-contiguous form (four rows, all g) then fall into different banks.
-// Rows past the end re-read the last one (never stored); k past the end is zero in both operands.  A tile whose operands
-// hold an infinity or not-a-number is summed again in plain fp32, so that those come out as they do there.
+// Rows past the end re-read the last one (never stored); k past the end is zero in both operands.  Where pieces do not stand
+// for an operand of the tile (an infinity, or all of it below 2^-102: the MFMA takes pieces below 2^-126 as zero) the tile is
+// summed again on the fp32 pipe, so that it comes out as it does there.  Values below 2^-102 beside larger ones
+// are off by up to 2^-125.
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  With part set the
 // split's sums go to part[split][M][N] for k_sum_parts, else to C.  ACC: C += alpha * sum, C fetched before the loop.
 // Measured, with the 64 x 64 fp32-MFMA kernel this replaced: 40 x 1024 from K = 32000 4063 -> 55 us (31 splits), 128 x 4096
-// from K = 32000 4396 -> 311 us (8 splits), 20 x 32000 from K = 4096 590 -> 152 us, 128 x 32000 816 -> 291 us, update of
-// 32000 x 4096 by 20 rows 326 -> 346 us (1 GB moved: 3 TB/s).  Splitting and LDS traffic bound the large ones.
+// from K = 32000 4396 -> 305 us (8 splits), 20 x 32000 from K = 4096 590 -> 145 us, 128 x 32000 816 -> 296 us, update of
+// 32000 x 4096 by 20 rows 326 -> 354 us (1 GB moved: 3 TB/s).  Splitting and LDS traffic bound the large ones.
+// Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 143 us for the 20 rows above), two
+// beyond (three spill: 54 -> 95 us for the 40 rows).
 // ---------------------------------------------------------------------------------------------
 enum { X3_BN = 64, X3_BK = 32 };
 
-__device__ __forceinline__ void split3(float a, uint32_t &h, uint32_t &m, uint32_t &l, bool &odd) {
-    h = __float_as_uint(a);
-    const float r = a - __uint_as_float(h & 0xFFFF0000u);
-    m = __float_as_uint(r);
-    l = __float_as_uint(r - __uint_as_float(m & 0xFFFF0000u));
-    odd |= !__builtin_isfinite(a);
+// a and b as pairs of pieces; top: the largest magnitude so far
+__device__ __forceinline__ void split3(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l, float &top) {
+    auto round2 = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x, y}, bf16x2)); };
+    auto low = [](uint32_t p) { return __uint_as_float(p << 16); };
+    auto high = [](uint32_t p) { return __uint_as_float(p & 0xFFFF0000u); };
+    h = round2(a, b);
+    const float ra = a - low(h), rb = b - high(h);
+    m = round2(ra, rb);
+    l = round2(ra - low(m), rb - high(m));
+    top = fmaxf(fmaxf(fabsf(a), fabsf(b)), top);
 }
-// the upper halves of two words as one (first value in the lower half)
-__device__ __forceinline__ uint32_t upper_pair(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+// whether pieces stand for an operand of this largest magnitude: not where one is infinite or rounds to infinity in bfloat16,
+// nor where all are so small (but not zero) that their last pieces are below 2^-126, which the MFMA takes as zero.  Not-a-numbers
+// pass: their pieces are some as well.
+__device__ __forceinline__ bool pieces_hold(float top) { return top < 0x1.ffp127f && (top >= 0x1p-102f || top == 0.f); }
 
 // One operand's share of a chunk in a thread's registers, and its way into LDS.  T rows (32, 64 or 128).
 template <int T, bool KS, int DEPTH>
@@ -111,7 +127,7 @@ struct X3Loader {
         }
     }
     template <int SLOT>
-    __device__ __forceinline__ void store(u32x4 *lds, bool &odd) const {   // planes [3][T/16][64]
+    __device__ __forceinline__ void store(u32x4 *lds, float &top) const {   // planes [3][T/16][64]
         const int t = threadIdx.x;
         const float *d = v[SLOT];
         if (!KS) {
@@ -119,14 +135,14 @@ struct X3Loader {
 #pragma unroll
             for (int q = 0; q < T / 32; ++q) {
                 const int i = (t >> 3) + 32 * q;
-                uint32_t h[4], m[4], l[4];
+                uint32_t h[2], m[2], l[2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) split3(d[4 * q + e], h[e], m[e], l[e], odd);
+                for (int e = 0; e < 2; ++e) split3(d[4 * q + 2 * e], d[4 * q + 2 * e + 1], h[e], m[e], l[e], top);
                 unsigned char *dst = (unsigned char *)(lds + (i >> 4) * TILE + ((i & 15) ^ (4 * g)) + 16 * g) + 8 * (t & 1);
                 constexpr int PL = (T / 16) * TILE * 16;
-                *(u32x2 *)dst = (u32x2){upper_pair(h[0], h[1]), upper_pair(h[2], h[3])};
-                *(u32x2 *)(dst + PL) = (u32x2){upper_pair(m[0], m[1]), upper_pair(m[2], m[3])};
-                *(u32x2 *)(dst + 2 * PL) = (u32x2){upper_pair(l[0], l[1]), upper_pair(l[2], l[3])};
+                *(u32x2 *)dst = (u32x2){h[0], h[1]};
+                *(u32x2 *)(dst + PL) = (u32x2){m[0], m[1]};
+                *(u32x2 *)(dst + 2 * PL) = (u32x2){l[0], l[1]};
             }
         } else {
             constexpr int W = T / 64 > 0 ? T / 64 : 1;
@@ -134,20 +150,20 @@ struct X3Loader {
             if (T / W * 4 < 256 && g > 3) return;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-                uint32_t h[8], m[8], l[8];
+                uint32_t h[4], m[4], l[4];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) split3(d[w * 8 + e], h[e], m[e], l[e], odd);
+                for (int e = 0; e < 4; ++e) split3(d[w * 8 + 2 * e], d[w * 8 + 2 * e + 1], h[e], m[e], l[e], top);
                 u32x4 *dst = lds + ((i + w) >> 4) * TILE + (((i + w) & 15) ^ (4 * g)) + 16 * g;
-                dst[0] = (u32x4){upper_pair(h[0], h[1]), upper_pair(h[2], h[3]), upper_pair(h[4], h[5]), upper_pair(h[6], h[7])};
-                dst[(T / 16) * TILE] = (u32x4){upper_pair(m[0], m[1]), upper_pair(m[2], m[3]), upper_pair(m[4], m[5]), upper_pair(m[6], m[7])};
-                dst[2 * (T / 16) * TILE] = (u32x4){upper_pair(l[0], l[1]), upper_pair(l[2], l[3]), upper_pair(l[4], l[5]), upper_pair(l[6], l[7])};
+                dst[0] = (u32x4){h[0], h[1], h[2], h[3]};
+                dst[(T / 16) * TILE] = (u32x4){m[0], m[1], m[2], m[3]};
+                dst[2 * (T / 16) * TILE] = (u32x4){l[0], l[1], l[2], l[3]};
             }
         }
     }
 };
 
 template <int BM, bool PKS, bool QKS, bool ACC, int DEPTH>
-__global__ __launch_bounds__(256, 2) void k_gemm_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q,
+__global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q,
                                                     long ldq, float *C, long ldc, float *part, int M, int N, int K,
                                                     float alpha, int vec) {
     constexpr int WN = BM == 32 ? 4 : 2, WM = 4 / WN;        // waves along n and m
@@ -167,11 +183,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_x3(const float *__restrict__ P,
     X3Loader<BM, QKS, DEPTH> lq;
     lp.init(P, ldp, N, n0, K);
     lq.init(Q, ldq, M, m0, K);
-    f32x4 acc[TN][TM], old[ACC ? TN : 1][ACC ? TM : 1];
+    // the products of the first pieces, and all the others, which are 2^-8 of them: small as they are, the second sum's
+    // roundings are lost in the first one's, which is rounded once a chunk
+    f32x4 acc[TN][TM], low[TN][TM], old[ACC ? TN : 1][ACC ? TM : 1];
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < TM; ++j) acc[i][j] = low[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     auto fetch = [&](int c, auto sc) __attribute__((always_inline)) {
         constexpr int B = decltype(sc)::value;
         if (c < c1) { lp.template load<B>(c * X3_BK); lq.template load<B>(c * X3_BK); }
@@ -200,34 +218,37 @@ __global__ __launch_bounds__(256, 2) void k_gemm_x3(const float *__restrict__ P,
             }
     }
     const int slot = (li ^ (4 * lg)) + 16 * lg;
-    bool odd = false;   // an infinity or not-a-number was met
+    float ptop = 0.f, qtop = 0.f;   // largest magnitudes
     auto chunk = [&](int c, auto sc) __attribute__((always_inline)) {
         constexpr int B = decltype(sc)::value;
         u32x4 *lds = x3_lds + (B & 1) * (PU + QU);
-        lp.template store<B>(lds, odd);
-        lq.template store<B>(lds + PU, odd);
+        lp.template store<B>(lds, ptop);
+        lq.template store<B>(lds + PU, qtop);
         fetch(c + DEPTH, sc);
         // a bare barrier behind this wave's LDS writes: the fence of __syncthreads would wait for the loads too
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        bf16x8 a[3][TN], b[3][TM];
+        bf16x8 a[3][TN];
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) {
+        for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
             for (int i = 0; i < TN; ++i)
                 a[pl][i] = __builtin_bit_cast(bf16x8, lds[(pl * (X3_BN / 16) + wn * TN + i) * 64 + slot]);
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-                b[pl][j] = __builtin_bit_cast(bf16x8, lds[PU + (pl * (BM / 16) + wm * TM + j) * 64 + slot]);
-        }
         // small terms first
         constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
-        for (int z = 0; z < 6; ++z)
+        for (int j = 0; j < TM; ++j) {
+            bf16x8 b[3];
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
+            for (int pl = 0; pl < 3; ++pl)
+                b[pl] = __builtin_bit_cast(bf16x8, lds[PU + (pl * (BM / 16) + wm * TM + j) * 64 + slot]);
 #pragma unroll
-                for (int j = 0; j < TM; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[z]][i], b[PB[z]][j], acc[i][j], 0, 0, 0);
+            for (int z = 0; z < 6; ++z)
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    f32x4 &sum = z == 5 ? acc[i][j] : low[i][j];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[z]][i], b[PB[z]], sum, 0, 0, 0);
+                }
+        }
     };
     static_assert(DEPTH == 2 || DEPTH == 4, "a chunk's registers and its LDS buffer go by the chunk number");
     for (int c = c0; c < c1; c += DEPTH) {
@@ -238,25 +259,55 @@ __global__ __launch_bounds__(256, 2) void k_gemm_x3(const float *__restrict__ P,
             if (c + 3 < c1) chunk(c + 3, std::integral_constant<int, 3>{});
         }
     }
-    if (__syncthreads_or(odd)) {
-        // the pieces of an infinity times zero pieces would be no numbers: such a tile is summed in plain fp32 instead
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
+                acc[i][j][r] += fabsf(acc[i][j][r]) < INFINITY ? low[i][j][r] : 0.f;
+    // every thread has cut up its share of both operands: the tile's largest magnitudes
+    __shared__ float tops[2][4];
+    for (int o = 32; o > 0; o >>= 1) { ptop = fmaxf(ptop, __shfl_xor(ptop, o)); qtop = fmaxf(qtop, __shfl_xor(qtop, o)); }
+    if (l == 0) { tops[0][wave] = ptop; tops[1][wave] = qtop; }
+    __syncthreads();
+    ptop = fmaxf(fmaxf(tops[0][0], tops[0][1]), fmaxf(tops[0][2], tops[0][3]));
+    qtop = fmaxf(fmaxf(tops[1][0], tops[1][1]), fmaxf(tops[1][2], tops[1][3]));
+    if (!pieces_hold(ptop) || !pieces_hold(qtop)) {
+        // the tile once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds k = g of row i), sixteen k a step
+        const int kend = min(K, c1 * X3_BK);
 #pragma unroll
         for (int i = 0; i < TN; ++i)
 #pragma unroll
-            for (int j = 0; j < TM; ++j) {
-                const int m = min(m0 + (wm * TM + j) * 16 + li, M - 1), n = n0 + (wn * TN + i) * 16 + 4 * lg;
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < TM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-                for (int k = c0 * X3_BK; k < min(K, c1 * X3_BK); ++k) {
-                    const float q = Q[QKS ? (long)k * ldq + m : (long)m * ldq + k];
+        for (int k0 = c0 * X3_BK; k0 < kend; k0 += 16) {
+            float pv[4][TN], qv[4][TM];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const long nn = min(n + r, N - 1);
-                        v[r] = fmaf(q, P[PKS ? (long)k * ldp + nn : nn * ldp + k], v[r]);
-                    }
+            for (int e = 0; e < 4; ++e) {
+                const int k = k0 + 4 * e + lg;
+                const long kc = min(k, kend - 1);
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    const long n = min(n0 + (wn * TN + i) * 16 + li, N - 1);
+                    const float x = P[PKS ? kc * ldp + n : n * ldp + kc];
+                    pv[e][i] = k < kend ? x : 0.f;
                 }
-                acc[i][j] = v;
+#pragma unroll
+                for (int j = 0; j < TM; ++j) {
+                    const long m = min(m0 + (wm * TM + j) * 16 + li, M - 1);
+                    const float x = Q[QKS ? kc * ldq + m : m * ldq + kc];
+                    qv[e][j] = k < kend ? x : 0.f;
+                }
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < TN; ++i)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[e][i], qv[e][j], acc[i][j], 0, 0, 0);
+        }
     }
     float *out = part ? part + (long)blockIdx.y * M * N : C;
     const long ldo = part ? N : ldc;

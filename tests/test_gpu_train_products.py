@@ -1,9 +1,10 @@
 """The dense products of the training step at the edges of their tiles (rows 32 / 64 / 128 and one more, columns not
 a multiple of 64, contraction lengths around a chunk of 32, split and unsplit sums) against float64.
 
-Bound: the operands are represented exactly and each accumulator is rounded once per 32 terms and plane pair, so over
-K terms the relative error of a sum of random terms is about sqrt(6 K / 32) 2^-24 of the sum's typical size; four times
-that, at K = 1030, is 3.3e-6 in the 2-norm (the fp32 additions of the splits and of the residual block are fewer)."""
+Bound: a product may be off by 2^-24 (the products of low pieces that are left out) and each sum is rounded at most once per
+term, 2.53e-8 of it each, so over K terms the relative error of a sum of random terms is about 2.53e-8 sqrt((K + 1) / 2); five
+times that, at K = 1030, is 2.9e-6 in the 2-norm (the fp32 additions of the splits and of the residual block are fewer).  The
+sums by themselves are held to that bound itself further down."""
 import numpy as np
 import pytest
 
@@ -54,6 +55,39 @@ def test_head_products(n, H, V, K):
         upd = db[k].double().cpu().numpy() - blocks[k]
         floor = 2.0 ** -24 * np.linalg.norm(blocks[k])
         assert np.linalg.norm(upd + lr * grads[k]) < TOL * 4 * np.linalg.norm(lr * grads[k]) + floor
+
+
+@pytest.mark.parametrize("terms", [1, 2, 3, 4, 8, 16, 32, 33, 64, 65, 130, 1030])
+@pytest.mark.parametrize("form", ["forward", "input_gradient", "update"])
+@pytest.mark.parametrize("scale", [0, -118])
+def test_sums_are_as_exact_as_fp32_chains(form, terms, scale):
+    """Every form of product against float64, at the error of a chain of fp32 multiply-adds: each addition is rounded once, a
+    rounding is 2^-24 / sqrt(3) * sqrt((1 - 1/4) / (2 ln 2)) = 2.53e-8 of a value (2-norm, mantissas as in random data), and the
+    partial sums of K random terms are sqrt(1 .. K) of a term, so sqrt((K + 1) / 2) of that for the whole; 15 % on top for the
+    finite sample and because the products and additions of pieces may round a little more than once at a single term.
+    The head is set up so that nothing else rounds: zero blocks pass h on as it is, and powers of two or identities stand
+    in for the other factors.  scale: one operand in units of 2^-118, where low bits are below the smallest normal bfloat16,
+    the other in units of 2^60."""
+    import torch
+    import paper_2408_08146_amd as KO
+    rng = np.random.default_rng(terms)
+    small, large = np.float32(2.0 ** scale), np.float32(2.0 ** (60 if scale else 0))
+    f32 = lambda *s: rng.normal(size=s).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    exact = lambda a, b: a.astype(np.float64) @ b.astype(np.float64)
+    if form == "forward":            # d = h w_lm^T
+        h, w_lm = f32(40, terms) * small, f32(1000, terms) * large
+        got, want = torch.zeros(40, 1000, device="cuda"), exact(h, w_lm.T)
+        KO.MedusaHeadTrainer([dev(np.zeros((terms, terms)))], dev(w_lm)).forward(dev(h), got)
+    elif form == "input_gradient":   # W = -(g w_lm)^T / 2 * 2 with an identity for h
+        g, w_lm, w = f32(128, terms) * small, f32(terms, 128) * large, dev(np.zeros((128, 128)))
+        KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(np.eye(128)), dev(g), 2.0)
+        got, want = -w.T, exact(g, w_lm)
+    else:                            # W = -g^T h, with w_lm twice an identity
+        g, h, w = f32(terms, 200) * small, f32(terms, 200) * large, dev(np.zeros((200, 200)))
+        KO.MedusaHeadTrainer([w], dev(2 * np.eye(200))).step(dev(h), dev(g), 1.0)
+        got, want = -w, exact(g.T, h)
+    assert _rel(got, want) < 1.15 * 2.53e-8 * np.sqrt((terms + 1) / 2)
 
 
 def test_head_with_the_smallest_workspace():
@@ -124,6 +158,41 @@ def test_infinite_operand_stays_infinite():
     # the zero weights beside column 5 meet finite logits only; target rows: score 0, loss log 2
     D.step(z(n, H), z(n, V), d, 0.0, loss)
     assert abs(loss.item() - np.log(2.0)) < 1e-6
+
+
+@pytest.mark.parametrize("n", [1, 37, 70, 200])
+@pytest.mark.parametrize("form", ["forward", "input_gradient", "update"])
+def test_infinities_in_every_form(form, n):
+    """One infinite element where the other operand is positive: its row or column of the result is infinite and the rest, the
+    tile beside it too, is what it would be without (TOL: those sums are fp32 chains of up to 200 terms, 2.5e-7)."""
+    import torch
+    import paper_2408_08146_amd as KO
+    rng = np.random.default_rng(n)
+    V, H, v0, j0 = 70, 130, 41, 67
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    h, w_lm, g = (np.abs(rng.normal(size=s)).astype(np.float32) for s in ((n, H), (V, H), (n, V)))
+    w_lm *= np.where(rng.random(w_lm.shape) < 0.5, -1, 1)
+    w = dev(np.zeros((H, H)))
+    if form == "forward":            # d[:, v0] = +inf
+        want = h.astype(np.float64) @ w_lm.T
+        w_lm[v0, j0] = np.inf
+        got, where = torch.zeros(n, V, device="cuda"), (slice(None), v0)
+        KO.MedusaHeadTrainer([w], dev(w_lm)).forward(dev(h), got)
+    else:                            # the gradient at unit j0 is +inf, so its row of the update -inf
+        if form == "update":         # through an input gradient of one infinite and one zero-free factor
+            w_lm, g = np.abs(w_lm[:1]), g[:, :1]
+            w_lm[0, j0] = np.inf
+            gx = g.astype(np.float64) * np.where(np.isinf(w_lm), 0, w_lm)
+        else:
+            gx = g.astype(np.float64) @ w_lm
+            w_lm[v0, j0] = np.inf
+        want, where = -(gx / 2).T @ h.astype(np.float64), (j0, slice(None))
+        KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(h), dev(g), 1.0)
+        got = w
+    got = got.double().cpu().numpy()
+    assert np.isinf(got[where]).all() and (np.sign(got[where]) == (1 if form == "forward" else -1)).all()
+    got[where] = want[where] = 0.0
+    assert np.linalg.norm(got - want) < TOL * np.linalg.norm(want)
 
 
 @pytest.mark.parametrize("V", [1, 1023, 1025, 32768, 33001])
