@@ -51,7 +51,7 @@ struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 // split's sums go to part[split][M][N] for k_sum_parts, else to C.  ACC: C += alpha * sum, C fetched before the loop.
 // Measured, with the 64 x 64 fp32-MFMA kernel this replaced: 40 x 1024 from K = 32000 4063 -> 55 us (31 splits), 128 x 4096
 // from K = 32000 4396 -> 305 us (8 splits), 20 x 32000 from K = 4096 590 -> 145 us, 128 x 32000 816 -> 296 us, update of
-// 32000 x 4096 by 20 rows 326 -> 354 us (1 GB moved: 3 TB/s).  Splitting and LDS traffic bound the large ones.
+// 32000 x 4096 by 100 rows 662 us.  Splitting and LDS traffic bound the large ones.
 // Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 143 us for the 20 rows above), two
 // beyond (three spill: 54 -> 95 us for the 40 rows).
 // ---------------------------------------------------------------------------------------------
@@ -328,6 +328,85 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
         }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Weight update by few rows: W[M,N] += alpha * sum_r G[r,M] X[r,N], r < rows <= KP, plain fp32 multiply-adds in row order.
+// Bound by reading and writing W once (32000 x 4096 by 20 rows: 1.05 GB).  A wave streams rows of W in pieces of 64 NV
+// columns (1 KiB or 512 B, PF of them under way) and holds its columns of X in registers; a workgroup's four waves take the
+// rows of its panel in turn and share the panel of G, transposed, in LDS, where a row's KP factors are broadcast reads.
+// Measured, 32000 x 4096 by 20 rows: 219 us (4.8 TB/s), k_gemm_x3 329 to 354, the fp32-MFMA kernel before that 326; 1024 x 32000 by
+// 40 rows: 75 us, k_gemm_x3 88 to 94.
+// grid: x = column blocks, y = panels of mr rows.
+// ---------------------------------------------------------------------------------------------
+enum { UPD_MR = 128 };
+template <int KP, int NV>
+__global__ __launch_bounds__(256) void k_update_rows(const float *__restrict__ G, const float *__restrict__ X, float *W, int M,
+                                                     int N, int rows, int mr, float alpha) {
+    struct __attribute__((packed, aligned(4))) piece { float v[NV]; };
+    constexpr int PF = 8;
+    __shared__ f32x4 gs[UPD_MR][KP / 4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int m0 = blockIdx.y * mr, n = (blockIdx.x * 64 + l) * NV, cnt = N - n;   // columns of this lane: NV, or cnt of them
+    for (int i = threadIdx.x; i < mr * KP; i += 256) {
+        const int m = i % mr, r = i / mr;
+        ((float *)gs[m])[r] = r < rows && m0 + m < M ? G[(size_t)r * M + m0 + m] : 0.f;
+    }
+    auto load = [&](const float *p) {
+        piece w;
+        if (cnt >= NV) {
+            w = *(const piece *)p;
+        } else {
+#pragma unroll
+            for (int e = 0; e < NV; ++e) w.v[e] = e < cnt ? p[e] : 0.f;
+        }
+        return w;
+    };
+    piece x[KP], w[PF];
+#pragma unroll
+    for (int r = 0; r < KP; ++r) {
+        if (r < rows) x[r] = load(X + (size_t)r * N + n);
+        else
+#pragma unroll
+            for (int e = 0; e < NV; ++e) x[r].v[e] = 0.f;
+    }
+    // rows m0 + wave, + 4, ..
+    const int nrow = (min(mr, M - m0) - wave + 3) / 4;
+    float *row = W + (size_t)(m0 + wave) * N + n;
+    const size_t step = (size_t)4 * N;
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+        if (p < nrow) w[p] = load(row + p * step);
+    __syncthreads();
+    for (int i = 0; i < nrow; i += PF) {
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+            if (i + p >= nrow) continue;
+            const piece old = w[p];
+            float *o = row + (size_t)(i + p) * step;
+            if (i + p + PF < nrow) w[p] = load(o + PF * step);
+            piece t;
+#pragma unroll
+            for (int e = 0; e < NV; ++e) t.v[e] = 0.f;
+#pragma unroll
+            for (int q = 0; q < KP / 4; ++q) {
+                const f32x4 g = gs[wave + 4 * (i + p)][q];
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+#pragma unroll
+                    for (int e = 0; e < NV; ++e) t.v[e] = fmaf(g[z], x[4 * q + z].v[e], t.v[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < NV; ++e) t.v[e] = fmaf(alpha, t.v[e], old.v[e]);
+            if (cnt >= NV) {
+                *(piece *)o = t;
+            } else {
+#pragma unroll
+                for (int e = 0; e < NV; ++e)
+                    if (e < cnt) o[e] = t.v[e];
+            }
+        }
+    }
+}
+
 // How many K splits give about two workgroups a compute unit, at least four chunks each, and fit `room` floats of partial
 // sums (none: one split, straight into C)
 int x3_splits(int M, int N, int K, size_t room) {
@@ -366,8 +445,27 @@ void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *pa
 void gemm_nn(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
     gemm_x3<true, false, false>(st, W, N, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
 }
+template <int KP, int NV>
+void launch_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float alpha) {
+    const int nb = (N + 64 * NV - 1) / (64 * NV);
+    int mr = UPD_MR;   // panels as high as leave a workgroup a compute unit: each reads its columns of X for itself
+    while (mr > 16 && (long)nb * ((M + mr - 1) / mr) < 256) mr /= 2;
+    k_update_rows<KP, NV><<<dim3(nb, (M + mr - 1) / mr), 256, 0, st>>>(G, X, W, M, N, rows, mr, alpha);
+}
 // W[M,N] -= lr * G[rows,M]^T X[rows,N]
 void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr) {
+    // The multiply-adds of more than 32 rows take longer than a matrix that the caches hold (4000 x 1000: 14.7 us at 32
+    // rows, 24.9 at 40, where k_gemm_x3 takes 14.5 and 18.7), those of up to 48 about as long as a large one's way through
+    // memory (1024 x 32000 75 us at 40 rows and 85 at 48, k_gemm_x3 88 and 89; 32000 x 4096 306 and 346, k_gemm_x3 444
+    // and 452; at 64 rows 552 and 461).
+    switch (rows <= 32 || (size_t)M * N >= 24000000u ? (rows + 7) / 8 : 0) {
+        case 1: return launch_update<8, 4>(st, G, X, W, M, N, rows, -lr);
+        case 2: return launch_update<16, 4>(st, G, X, W, M, N, rows, -lr);
+        case 3: return launch_update<24, 4>(st, G, X, W, M, N, rows, -lr);
+        case 4: return launch_update<32, 4>(st, G, X, W, M, N, rows, -lr);
+        case 5: return launch_update<40, 2>(st, G, X, W, M, N, rows, -lr);
+        case 6: return launch_update<48, 2>(st, G, X, W, M, N, rows, -lr);
+    }
     gemm_x3<true, true, true>(st, X, N, G, M, W, N, nullptr, 1, M, N, rows, -lr);
 }
 

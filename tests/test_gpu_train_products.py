@@ -160,6 +160,23 @@ def test_infinite_operand_stays_infinite():
     assert abs(loss.item() - np.log(2.0)) < 1e-6
 
 
+@pytest.mark.parametrize("H,rows", [(1, 3), (63, 8), (130, 9), (257, 16), (515, 24), (1030, 25), (260, 32), (260, 33), (4900, 33),
+                                    (4901, 41), (4903, 48), (4900, 49)])
+def test_update_by_few_rows(H, rows):
+    """-g^T h at widths that leave columns of a wave and rows of a panel over, at each count of row groups, and on both sides of
+    the rule for more than 32 rows (24 million elements), at the error of an fp32 chain: on average as above, and every
+    element within rows * 2^-24 of the sum of its terms' magnitudes (a single element has no average)."""
+    import torch
+    import paper_2408_08146_amd as KO
+    gen = torch.Generator(device="cuda").manual_seed(H + rows)
+    h, g = (torch.randn(rows, H, generator=gen, device="cuda") for _ in range(2))
+    w = torch.zeros(H, H, device="cuda")
+    KO.MedusaHeadTrainer([w], 2 * torch.eye(H, device="cuda")).step(h, g, 1.0)
+    want = g.double().T @ h.double()
+    assert ((w.double() + want).abs() <= rows * 2.0 ** -24 * (g.double().abs().T @ h.double().abs())).all()
+    assert H == 1 or ((w.double() + want).norm() / want.norm()).item() < 1.2 * 2.53e-8 * np.sqrt((rows + 1) / 2)
+
+
 @pytest.mark.parametrize("n", [1, 37, 70, 200])
 @pytest.mark.parametrize("form", ["forward", "input_gradient", "update"])
 def test_infinities_in_every_form(form, n):
