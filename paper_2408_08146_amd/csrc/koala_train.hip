@@ -835,8 +835,8 @@ koala_status koala_train_gen_grad(const koala_disc_shape *shape, const koala_dis
 }
 
 // Medusa workspace, in slots of n_rows * hidden floats: x_1 .. x_K, y_0 .. y_{K-1}, gx, gx', gy and one spare, as many as
-// a call needs at least, then MED_PARTS slots of split sums.  A workspace without those is accepted as well: the
-// products then run unsplit, on fewer compute units.
+// a call needs at least, then MED_PARTS slots of split sums.  A workspace without (all of) those is accepted as well:
+// the products then run unsplit, on fewer compute units.
 enum { MED_PARTS = 8 };
 static size_t med_slot(int n_rows, int hidden) { return up256((size_t)n_rows * hidden * sizeof(float)); }
 static size_t med_need(int n_rows, int hidden, int K) { return med_slot(n_rows, hidden) * (size_t)(2 * K + 4); }
@@ -863,7 +863,10 @@ static MedWs med_carve(int n, int H, int K, const float *h, void *workspace, siz
     w.gx2 = w.gx + slot;
     w.gy = w.gx2 + slot;
     w.part = w.gy + slot;
-    w.room = (bytes - med_need(n, H, K)) / sizeof(float);
+    // all of the split area or none, however much larger the workspace is: the split count, and with it the last bits of a
+    // result, goes by the shapes alone
+    const size_t parts = MED_PARTS * med_slot(n, H);
+    w.room = bytes - med_need(n, H, K) >= parts ? parts / sizeof(float) : 0;
     return w;
 }
 

@@ -116,6 +116,26 @@ def test_head_with_the_smallest_workspace():
         head.forward(dev(h), d)
 
 
+def test_head_results_do_not_depend_on_earlier_calls():
+    """The binding keeps its largest workspace: the same rows give the same bits before and after a call of many rows."""
+    import torch
+    import paper_2408_08146_amd as KO
+    n, H, V = 20, 512, 4096
+    blocks, w_lm, h, g, dev = _head(n, H, V, 1, 11)
+    block = dev(blocks[0])
+    head = KO.MedusaHeadTrainer([block], dev(w_lm))
+    results = []
+    for many in (False, True):
+        if many:
+            head.forward(torch.zeros(300, H, device="cuda"), torch.zeros(300, V, device="cuda"))
+        block.copy_(dev(blocks[0]))
+        d = torch.zeros(n, V, device="cuda")
+        head.forward(dev(h), d)
+        head.step(dev(h), dev(g), 0.5)
+        results.append((d, block.clone()))
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
 @pytest.mark.parametrize("n,H,V,DH,n_fc", [(1, 64, 100, 0, 1), (16, 33, 1030, 40, 2), (17, 256, 2000, 64, 3), (65, 300, 700, 129, 3)])
 def test_discriminator_products(n, H, V, DH, n_fc):
     import torch
