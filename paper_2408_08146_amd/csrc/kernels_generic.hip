@@ -76,8 +76,12 @@ __global__ __launch_bounds__(256) void k_topk(const float *logits, int ld, int V
         }
         if ((tid & 63) == 0) { bv[it & 1][tid >> 6] = best; bi[it & 1][tid >> 6] = besti; }
         __syncthreads();
+        // from the waves' first lanes alone: a not-a-number leaves the lanes of a wave with different winners, and all threads
+        // have to agree on which token is taken
+        best = bv[it & 1][0];
+        besti = bi[it & 1][0];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 1; u < 4; ++u)
             if (topk_better(bv[it & 1][u], bi[it & 1][u], best, besti)) { best = bv[it & 1][u]; besti = bi[it & 1][u]; }
         if (besti % 256 == tid && besti < 256 * TR) taken |= 1u << (besti / 256);
         if (tid == 0) {

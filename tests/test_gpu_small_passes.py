@@ -76,6 +76,34 @@ def test_wide_output_head_matches_oracle(vocab, tree):
     compare_logits_and_greedy(c, lg, greedy, rlg, rgreedy)
 
 
+@pytest.mark.parametrize("V", [700, 5000])
+def test_fp32_top_k_never_repeats_a_token(V):
+    """A not-a-number among the logits compares false with everything, so what a lane of the workgroup has seen of the others
+    goes by the order it met them in; the tokens handed out must be different ones all the same."""
+    import torch
+    from koala_synth import make_tree
+    from test_gpu_sampling_rows import _context
+    tree = make_tree([6], [1, 6])
+    c, g, lm, blocks = _context(V, tree, 1)
+    for block in blocks:
+        block.zero_()                                     # a head's output is its input
+    feat = torch.zeros(1, 1, 128, device="cuda")
+    feat[0, 0, 0] = 1.0                                   # and the logits are the first column of the output head
+    for nan, largest, second in ((5, 37, 36), (5, 69, 64), (3, 133, 130), (0, 1, 2), (255, 511, 254)):
+        lm.zero_()
+        lm[:, 0] = torch.randn(V, generator=g, device="cuda")
+        lm[largest, 0], lm[second, 0] = 50.0, 40.0
+        for row in (False, True):
+            if row:
+                lm[nan, 0] = float("nan")
+            tok, scores = torch.zeros(1, 7, dtype=torch.int32, device="cuda"), torch.zeros(1, 7, device="cuda")
+            c.draft_expand(1, feat, torch.ones(1, 1, dtype=torch.int32, device="cuda"), 1, tok, scores)
+            kids = [int(tok[0, i]) for i in sorted(range(1, 7), key=lambda i: tree.rank[i])]
+            assert len(set(kids)) == 6 and 0 <= min(kids) and max(kids) < V, (nan, largest, second, kids)
+            if not row:
+                assert kids == torch.topk(lm[:, 0], 6).indices.tolist()
+
+
 def test_accept_takes_the_first_of_equal_children():
     """Siblings with the same token: the walk goes to the lowest-numbered one, in every sequence."""
     c = Case("cfg5_small", n_layers=1, K=1)
