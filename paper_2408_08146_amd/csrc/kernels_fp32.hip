@@ -183,7 +183,8 @@ void launch_gemm(hipStream_t st, const float *W, const float *X, int ldx, int gr
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tree-masked attention, fp32.  grid (key splits, n_heads, batch * row groups of 16), eight waves that take the 16-key
+// Tree-masked attention, fp32.  grid (batch * row groups of 16, n_heads, key splits; the first dimension alone holds
+// any batch), eight waves that take the 16-key
 // steps of the split's share in turn (step = split + splits * (wave + 8 k)), online softmax per wave, merged through LDS.
 //   S^T[key][row] = K Q^T    A = K rows straight from the cache, B = the queries, in registers
 //   O^T[d][row] += V^T P^T   B = the probabilities where the S^T tile left them (k step r: keys 4g + r), A = V, 16 consecutive
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *qrot, RowMeta
     constexpr int C = DH / 16;
     extern __shared__ __attribute__((aligned(16))) f32x4 mo[];   // [NW][C][64]
     __shared__ float mm[NW][16][2];
-    const int s = blockIdx.x, h = blockIdx.y, b = blockIdx.z / ngroups, r0 = blockIdx.z % ngroups * 16;
+    const int s = blockIdx.z, h = blockIdx.y, b = blockIdx.x / ngroups, r0 = blockIdx.x % ngroups * 16;
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
     const int kv_end = meta.kv_end[b];
     const bool ok = r0 + li < rows_per_seq;
@@ -348,7 +349,7 @@ void attention(hipStream_t st, const float *qrot, const RowMeta &meta, const voi
     // four steps of a full cache for each of a workgroup's waves
     const int nsplit = std::max(1, std::min(max_split, ((cap + 15) / 16 + 4 * NW - 1) / (4 * NW)));
     const int ngroups = (rows_per_seq + 15) / 16;
-    const dim3 grid(nsplit, n_heads, batch * ngroups);
+    const dim3 grid(batch * ngroups, n_heads, nsplit);
     const size_t sm = (size_t)NW * (head_dim / 16) * 64 * 16;
     if (head_dim == 128) {
         static const hipError_t attr = hipFuncSetAttribute((const void *)k_attn_f32<128>,

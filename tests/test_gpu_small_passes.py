@@ -104,6 +104,35 @@ def test_fp32_top_k_never_repeats_a_token(V):
                 assert kids == torch.topk(lm[:, 0], 6).indices.tolist()
 
 
+def test_fp32_batches_beyond_16383_sequences():
+    """Four groups of sixteen tree rows for each of 16400 sequences: more attention workgroups than the third dimension of a
+    launch holds.  Equal sequences give equal bits, those of a call of one sequence."""
+    import torch
+    import paper_2408_08146_amd as K
+    from koala_synth import make_tree
+    H, V, F, batch, cap = 64, 12, 8, 16400, 64
+    tree = make_tree([8, 6], [1, 8, 40])
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda") * 0.1
+    one = torch.ones(H, device="cuda")
+    w = dict(embed=rnd(V, H), lm_head=rnd(V, H), final_norm=one, fc=None, draft=[rnd(H, H)] * 2,
+             layers=[(one, rnd(3 * H, H), rnd(H, H), one, rnd(2 * F, H), rnd(H, F))])
+    shape = dict(hidden=H, n_heads=1, head_dim=64, ffn=F, vocab=V, n_layers=1, rms_eps=1e-6, rope_base=1e4, dtype=K.KOALA_FP32)
+    rows, tokens, results = rnd(2, 8, 64), torch.randint(0, V, (1, tree.n_nodes), generator=g, device="cuda").int(), []
+    for n in (1, batch):
+        c = K.KoalaContext(shape, dict(kind=K.KOALA_DRAFT_MEDUSA, K=1, medusa_heads=2, max_m=1), tree, n)
+        kv = K.alloc_kv(dict(n_layers=1, n_heads=1, head_dim=64, dtype="fp32"), n, cap, "cuda")
+        kv["target_k"][..., :8, :], kv["target_v"][..., :8, :] = rows[0], rows[1]
+        kv["ctx_len"].fill_(8)
+        c.bind(w, kv, torch.empty(c.workspace_bytes(), dtype=torch.uint8, device="cuda"))
+        feat, greedy = torch.zeros(n, tree.n_nodes, H, device="cuda"), torch.zeros(n, tree.n_nodes, dtype=torch.int32, device="cuda")
+        c.tree_verify(n, tokens.expand(n, -1).contiguous(), feat, None, greedy)
+        results.append((feat, greedy))
+    assert results[0][0].abs().max() > 0.1
+    for a, b in zip(*results):
+        assert (a == b).all()
+
+
 def test_accept_takes_the_first_of_equal_children():
     """Siblings with the same token: the walk goes to the lowest-numbered one, in every sequence."""
     c = Case("cfg5_small", n_layers=1, K=1)
