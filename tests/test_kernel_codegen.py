@@ -3,6 +3,7 @@ instructions the compiler does not know to be loads, and the register a read lan
 register until the hand-placed wait.  That holds as long as the compiler neither spills in that kernel nor copies
 registers inside its tile loop.  This test compiles the bf16 kernels to assembly with the library's flags and
 checks exactly that for every instantiation (no GPU needed)."""
+import glob
 import os
 import re
 import shutil
@@ -12,23 +13,41 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2408_08146_amd", "csrc")
-OUT = os.path.join(ROOT, "_build", "kernels_bf16.s")
 
 
-def _assembly():
+def _stale(out, src):
+    """Whether `out` is older than anything that decides what `src` compiles to: itself, any header, the library's flags."""
+    deps = [src, os.path.join(ROOT, "paper_2408_08146_amd", "build.py"), *glob.glob(os.path.join(CSRC, "*.h")),
+            *glob.glob(os.path.join(ROOT, "include", "*.h"))]
+    return not os.path.exists(out) or os.path.getmtime(out) < max(os.path.getmtime(d) for d in deps)
+
+
+def _assembly(name="kernels_bf16"):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     from paper_2408_08146_amd.build import FLAGS
-    src = os.path.join(CSRC, "kernels_bf16.hip")
-    deps = [src, os.path.join(CSRC, "koala_internal.h"), os.path.join(ROOT, "include", "koala.h")]
-    if not os.path.exists(OUT) or os.path.getmtime(OUT) < max(os.path.getmtime(d) for d in deps):
-        os.makedirs(os.path.dirname(OUT), exist_ok=True)
+    src, out = os.path.join(CSRC, name + ".hip"), os.path.join(ROOT, "_build", name + ".s")
+    if _stale(out, src):
+        os.makedirs(os.path.dirname(out), exist_ok=True)
         flags = [f for f in FLAGS if f not in ("-shared", "-fPIC")]
         res = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                              src, "-o", OUT], capture_output=True, text=True)
+                              src, "-o", out], capture_output=True, text=True)
         assert res.returncode == 0, res.stderr[-2000:]
-    return open(OUT).read().splitlines()
+    return open(out).read().splitlines()
+
+
+@pytest.mark.parametrize("dep", [os.path.join(CSRC, "koala_pass.h"), os.path.join(CSRC, "koala_internal.h"),
+                                 os.path.join(ROOT, "include", "koala.h"), os.path.join(ROOT, "paper_2408_08146_amd", "build.py"),
+                                 os.path.join(CSRC, "kernels_bf16.hip")])
+def test_cached_assembly_goes_by_everything_that_decides_it(dep, tmp_path, monkeypatch):
+    out, src = str(tmp_path / "old.s"), os.path.join(CSRC, "kernels_bf16.hip")
+    open(out, "w").close()
+    times = {out: 100.0, dep: 101.0}
+    monkeypatch.setattr(os.path, "getmtime", lambda p: times.get(p, 99.0))
+    assert _stale(out, src)
+    times[dep] = 99.0
+    assert not _stale(out, src)
 
 
 def test_many_row_gemm_has_no_spills_and_no_register_copies_in_its_tile_loop():
