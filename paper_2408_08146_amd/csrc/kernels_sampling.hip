@@ -430,8 +430,8 @@ __device__ __forceinline__ void block_sum2(double &a, double &b, RegShared &sh) 
 // The sums of segments 2l and 2l + 1 in lane l of every wave
 struct SegPair { double a, b; };
 template <int NQ>
-__device__ __forceinline__ SegPair segment_pairs(const float (&w)[NQ][4], RegShared &sh) {
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+__device__ __forceinline__ SegPair segment_pairs(const float (&w)[NQ][4], int wave, RegShared &sh) {
+    const int l = threadIdx.x & 63;
     double t[NQ];
 #pragma unroll
     for (int u = 0; u < NQ; ++u) t[u] = seg_lane_sum(w[u]);
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(NT) void k_sample_children_r(const float *src, ks::
     float m = row_max<NQ>(w), unused = 0.f;
     block_max2(m, unused, sh);
     (void)row_exp<NQ>(w, V, m, inv_tau);
-    SegPair seg = segment_pairs<NQ>(w, sh);
+    SegPair seg = segment_pairs<NQ>(w, wave, sh);
     for (int j = 0; j < nk; ++j) {
         const int c = child_at(place, j);
         const SegPick r = pick_segment(seg, (double)__shfl(u_lane, c));
@@ -593,15 +593,20 @@ __global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, in
                                                         int32_t *next_token) {
     extern __shared__ __attribute__((aligned(16))) f32q walk_q[];   // [NQ][NT]
     __shared__ RegShared sh;
+    __shared__ float ua[KOALA_MAX_NODES], ur[KOALA_MAX_NODES];       // what the walk asks of a node: in LDS, the rows fill the
+    __shared__ int tok[KOALA_MAX_NODES];                             // registers
     const int b = blockIdx.x, tid = threadIdx.x, l = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int32_t *path = accept_path + (size_t)b * (D + 1);
     f32q *ql = walk_q + tid;
     // one node a lane, in every wave
     const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
-    int tok = l < T ? tree_tokens[(size_t)b * T + l] : 0;
-    tok = tok < 0 ? 0 : tok >= V ? V - 1 : tok;
-    const float ua = l < T ? u_accept[(size_t)b * T + l] : 0.f, ur = l < T ? u_resample[(size_t)b * T + l] : 0.f;
+    if (tid < T) {   // read behind the barriers of the first reductions
+        const int x = tree_tokens[(size_t)b * T + tid];
+        tok[tid] = x < 0 ? 0 : x >= V ? V - 1 : x;
+        ua[tid] = u_accept[(size_t)b * T + tid];
+        ur[tid] = u_resample[(size_t)b * T + tid];
+    }
     int cur = 0, a = 0;
     if (tid == 0) path[0] = 0;
     for (;;) {
@@ -628,7 +633,7 @@ __global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, in
         }
         bool moved = false;
         for (int j = 0; j < nk; ++j) {
-            const int c = child_at(place, j), x = __shfl(tok, c), xo = x - tid * 4;
+            const int c = child_at(place, j), x = tok[c], xo = x - tid * 4;
             if (xo >= 0 && xo % (NT * 4) < 4) {   // this thread has the probabilities of the child's token
                 float dx = 0.f;
 #pragma unroll
@@ -641,7 +646,7 @@ __global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, in
             __syncthreads();
             const double qx = (double)sh.qx[j & 1], dx = (double)sh.dx[j & 1];
             const double ratio = dx > 0.0 ? fmin(1.0, qx / dx) : 0.0;
-            if (dx > 0.0 && (double)__shfl(ua, c) < ratio) {
+            if (dx > 0.0 && (double)ua[c] < ratio) {
                 cur = c;
                 ++a;
                 if (tid == 0) path[a] = c;
@@ -692,8 +697,8 @@ __global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, in
 #pragma unroll
             for (int e = 0; e < 4; ++e) q[u][e] = x[e];
         }
-        const SegPair seg = segment_pairs<NQ>(q, sh);
-        const SegPick r = pick_segment(seg, (double)__shfl(ur, cur));
+        const SegPair seg = segment_pairs<NQ>(q, wave, sh);
+        const SegPick r = pick_segment(seg, (double)ur[cur]);
         if (r.s < 0 ? wave == 0 : (r.s & (NW - 1)) == wave) {
             float y[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll

@@ -82,3 +82,16 @@ def test_many_row_gemm_has_no_spills_and_no_register_copies_in_its_tile_loop():
                       or re.match(r"^\s*v_accvgpr_write_b32\s+a\d+,\s*v\d+", l)]
             assert not copies, f"{name} copies registers inside a tile: {copies[:4]}"
         assert tiles >= 4, f"{name}: found {tiles} tile bodies"
+
+
+@pytest.mark.parametrize("name", ["kernels_bf16", "kernels_fp32", "kernels_generic", "kernels_sampling", "koala_train"])
+def test_no_kernel_keeps_anything_in_scratch_memory(name):
+    """Kernels that say their rows or tiles are in registers have them there."""
+    lines = _assembly(name)
+    kernel, seen = None, 0
+    for l in lines:
+        if l.startswith("\t.amdhsa_kernel "):
+            kernel, seen = l.split()[-1], seen + 1
+        elif ".amdhsa_private_segment_fixed_size" in l:
+            assert int(l.split()[-1]) == 0, f"{kernel} uses {l.split()[-1]} bytes of scratch per lane"
+    assert seen >= 5, "no kernels found"
