@@ -722,6 +722,7 @@ __global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, in
 namespace ks {
 
 int max_vocab() { return MAX_SEG * SEG; }
+int register_vocab() { return REG_V; }
 
 void sample_children(hipStream_t st, const float *src, float *scratch, const NodeList &nodes, bool by_depth,
                      const TreeTables &tt, int T, int V, float temperature, const float *u_draw, int32_t *tree_tokens,

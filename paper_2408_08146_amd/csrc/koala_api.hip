@@ -95,14 +95,14 @@ size_t carve(koala_ctx *c, char *base) {
     c->meta.kv_end = w.take<int32_t>(c->max_batch);
     c->meta.rope_cos = w.take<float>((size_t)R * half);
     c->meta.rope_sin = w.take<float>((size_t)R * half);
+    const bool bf = s.dtype == KOALA_BF16;
     c->x = w.take<float>((size_t)R * H);
-    c->act = w.take<float>((size_t)R * std::max(2 * H, F));
-    c->qkv = w.take<float>((size_t)R * 3 * H);
+    c->act = bf ? nullptr : w.take<float>((size_t)R * std::max(2 * H, F));
     // also holds the bf16 path's query fragments, whose rows are padded to 16 per sequence
     c->qrot = w.take<float>((size_t)c->max_batch * ((R / c->max_batch + 15) / 16 * 16) * H);
     c->qf = c->qrot;
-    c->attn_out = w.take<float>((size_t)R * H);
-    c->gu = w.take<float>((size_t)R * 2 * F);
+    c->attn_out = bf ? nullptr : w.take<float>((size_t)R * H);
+    c->block_y = bf || c->draft.kind != KOALA_DRAFT_MEDUSA ? nullptr : w.take<float>((size_t)c->max_batch * H);
     c->o_part = w.take<float>((size_t)R * H * ns);
     c->ml = w.take<float>((size_t)R * s.n_heads * ns * 2);
     c->opart_bytes = (size_t)R * H * ns * sizeof(float);
@@ -110,9 +110,6 @@ size_t carve(koala_ctx *c, char *base) {
     c->attn_cnt = w.take<int>((size_t)c->max_batch * s.n_heads * 4);
     c->logits = w.take<float>((size_t)R * V);
     c->fhat = w.take<float>((size_t)c->max_batch * T * H);
-    c->topk_val = w.take<float>((size_t)R * KOALA_TOPK_MAX);
-    c->topk_idx = w.take<int32_t>((size_t)R * KOALA_TOPK_MAX);
-    c->tok_tmp = w.take<int32_t>(R);
     {
         const int gm = std::max(D + 1, c->draft.max_m);
         c->gen_feat = w.take<float>((size_t)T * H);
@@ -127,12 +124,13 @@ size_t carve(koala_ctx *c, char *base) {
     c->gen_dlogits = w.take<float>((size_t)T * V);
     c->gen_tlogits = w.take<float>((size_t)T * V);
     c->med_logits = c->draft.kind == KOALA_DRAFT_MEDUSA ? w.take<float>((size_t)D * c->max_batch * V) : nullptr;
-    c->acc_q = w.take<float>((size_t)c->max_batch * V);
-    c->acc_d = w.take<float>((size_t)c->max_batch * V);
+    const size_t walk = V > ks::register_vocab() ? (size_t)c->max_batch * V : 0;
+    c->acc_q = w.take<float>(walk);
+    c->acc_d = w.take<float>(walk);
     c->xf = c->xf2 = nullptr;
     c->part = nullptr;
     c->xf_bytes = c->part_bytes = 0;
-    if (s.dtype == KOALA_BF16) {
+    if (bf) {
         const int MTmax = kb::mt_of(R);
         const int shapes[6][2] = {{3 * H, H}, {H, H}, {2 * F, H}, {H, F}, {kb::pad64(V), H}, {H, 2 * H}};
         size_t worst = 0;
@@ -630,8 +628,8 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
             for (int j = 0; j < D; ++j) {
                 float *xj = c->x + (size_t)j * batch * H;
                 for (int k = 0; k < K; ++k) {
-                    kf::gemm(st, xj, H, c->w.draft_w[j * K + k], c->gu, H, batch, H, H, false);
-                    kg::resblock_update(st, xj, c->gu, batch * H);
+                    kf::gemm(st, xj, H, c->w.draft_w[j * K + k], c->block_y, H, batch, H, H, false);
+                    kg::resblock_update(st, xj, c->block_y, batch * H);
                 }
             }
         }

@@ -55,8 +55,8 @@ struct koala_ctx {
     // workspace carve-up (device pointers)
     TreeTables tt;
     RowMeta meta;
-    float *x, *act, *qkv, *qrot, *attn_out, *gu, *o_part, *ml, *logits, *fhat, *topk_val;
-    int32_t *topk_idx, *tok_tmp;
+    float *x, *qrot, *o_part, *ml, *logits, *fhat;
+    float *act, *attn_out, *block_y;                     // fp32: fc input or SwiGLU output, attention output, a Medusa block's product
     // generation loop state of sequence 0 (koala_generate)
     float *gen_dlogits, *gen_tlogits;                    // [T][V] draft / target logits of the non-greedy loop
     float *gen_feat, *gen_feat_in;                       // [T][H] verify features; [max(D+1, max_m)][H] next draft inputs
@@ -64,7 +64,7 @@ struct koala_ctx {
     int n_cu;                      // compute units of the device the context is bound on
     int attn_ns;                   // key splits of the attention kernels (fixed at create)
     float *med_logits;                                   // [D * max_batch][V] per-depth logits of Medusa-style heads (sampled drafting)
-    float *acc_q, *acc_d;                                // [max_batch][V] distributions of the stochastic acceptance walk
+    float *acc_q, *acc_d;                                // [max_batch][V] distributions of the stochastic acceptance walk (rows in memory)
     // bf16 path: GEMM input as fp16 MFMA fragments, and the split-K partial sums
     void *xf, *xf2;   // xf2: input of the down projection (written by the gate/up projection's epilogue)
     float *part;
@@ -168,7 +168,8 @@ void attention(hipStream_t st, const float *qrot, const RowMeta &meta, const voi
 // ---------------------------------------------------------------------------------------------
 namespace ks {
 
-int max_vocab();   // largest vocabulary the sampling kernels handle
+int max_vocab();        // largest vocabulary the sampling kernels handle
+int register_vocab();   // and the largest whose rows they hold in registers: beyond, they need scratch
 
 // the nodes whose children are drawn in one launch, handed over by value
 struct NodeList {

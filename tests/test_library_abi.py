@@ -125,3 +125,33 @@ def test_every_compute_entry_point_refuses_an_unbound_or_missing_context():
     assert lib.koala_tree_verify(ctx._h, None, 1, dummy, dummy, None, dummy) == -6
     assert lib.koala_accept_prefix(ctx._h, None, 1, dummy, dummy, dummy, dummy, dummy, 0) == -6
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,kind,T,heads,vocab", [("bf16", "eagle", [1, 4, 16, 39], 0, 32000), ("bf16", "medusa", [1, 4, 16, 39], 3, 32000),
+                                                      ("fp32", "eagle", [1, 4, 6], 0, 1000), ("fp32", "medusa", [1, 4, 6], 2, 40000)])
+def test_the_workspace_is_what_the_passes_use(dtype, kind, T, heads, vocab):
+    """The floats a row of a pass needs, summed: nothing is carved that no kernel reads (256 bytes a buffer for alignment)."""
+    import paper_2408_08146_amd as K
+    from koala_synth import make_tree
+    tree, B, H, F, dh = make_tree([4] * (len(T) - 1), T), 8, 6656, 17920, 128
+    bf, n, D, nh = dtype == "bf16", tree.n_nodes, tree.depth, 6656 // 128
+    ctx = K.KoalaContext(dict(hidden=H, n_heads=nh, head_dim=dh, ffn=F, vocab=vocab, n_layers=2, rms_eps=1e-6, rope_base=1e4,
+                              dtype=K.KOALA_BF16 if bf else K.KOALA_FP32),
+                         dict(kind=K.KOALA_DRAFT_EAGLE if kind == "eagle" else K.KOALA_DRAFT_MEDUSA, K=1, medusa_heads=heads, max_m=1),
+                         tree, B)
+    splits = 256 // nh
+    per_row = dh + H + splits * (H + 2 * nh) + vocab + 16          # rotary table, stream, attention partials, logits, metadata
+    floats = B * n * per_row + B * (n + 15) // 16 * 16 * H         # queries, padded to 16 rows a sequence
+    floats += B * n * H + 2 * n * vocab + n * H + (D + 2) * H      # predicted features; the generation loop's rows
+    if kind == "medusa":
+        floats += D * B * vocab
+    if vocab > 32768:
+        floats += 2 * B * vocab                                    # the acceptance walk's rows in memory
+    if bf:
+        tiles = (B * n + 63) // 64 * 4
+        floats += 16 * tiles * (max(2 * H, F) + F) // 2            # the two fragment buffers, fp16
+        floats += 16 * tiles * 5 * (2 * F)                         # partial sums, at most five splits of the widest projection
+        floats += B * n * (64 + 2 * 16 * ((vocab + 1023) // 1024)) # row sums, top-k candidates
+    else:
+        floats += B * n * (max(2 * H, F) + H) + (B * H if kind == "medusa" else 0)
+    assert ctx.workspace_bytes() <= 4 * floats + 256 * 64
