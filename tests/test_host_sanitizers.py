@@ -3,6 +3,7 @@ AddressSanitizer and UndefinedBehaviorSanitizer: the sources are compiled with t
 side only (device code is untouched) together with tests/host_sanitize_driver.cpp, which creates, queries and
 destroys contexts for every benchmark tree and calls every entry point in ways that must be refused before
 anything is launched.  No GPU is needed; a sanitizer report makes the driver exit non-zero."""
+import glob
 import os
 import shutil
 import subprocess
@@ -24,7 +25,8 @@ def test_host_code_is_clean_under_asan_and_ubsan():
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     driver = os.path.join(ROOT, "tests", "host_sanitize_driver.cpp")
-    deps = _sources() + [driver, os.path.join(ROOT, "include", "koala.h"), os.path.join(CSRC, "koala_internal.h")]
+    deps = _sources() + [driver, os.path.join(ROOT, "paper_2408_08146_amd", "build.py"), *glob.glob(os.path.join(CSRC, "*.h")),
+                         *glob.glob(os.path.join(ROOT, "include", "*.h"))]
     if not os.path.exists(OUT) or os.path.getmtime(OUT) < max(os.path.getmtime(d) for d in deps):
         os.makedirs(os.path.dirname(OUT), exist_ok=True)
         cmd = [hipcc, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-Xarch_device", "-O3",
