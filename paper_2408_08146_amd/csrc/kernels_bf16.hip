@@ -1307,12 +1307,8 @@ void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, 
     const size_t sm = (size_t)(gemm_rows_tree(U, MT, NW) ? NW / 2 : NW) * U * MT * 64 * 16 +
                       (EPI == EPI_QKV || EPI == EPI_SWIGLU ? (size_t)64 * NW * 4 + R * 8 : 0) +
                       (EPI == EPI_QKV ? (size_t)R * U * 8 * 2 * 4 : 0);
-    static bool done = false;
-    if (!done) {
-        (void)hipFuncSetAttribute((const void *)k_gemm_rows<U, MT, NW, PF, EPI>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-        done = true;
-    }
+    static OncePerDevice once;
+    allow_lds(once, (const void *)k_gemm_rows<U, MT, NW, PF, EPI>, sm);
     const dim3 grid(((Npad / 16 + U - 1) / U) * S, n_heads);
     if (ev_start || ev_stop)
         hipExtLaunchKernelGGL((k_gemm_rows<U, MT, NW, PF, EPI>), grid, dim3(64 * NW), sm, st, ev_start, ev_stop, 0,
@@ -1404,22 +1400,17 @@ int rows_splits(int Npad, int K, int n_heads) {
     return S > nkt ? nkt : S;
 }
 
-static bool g_attr_done[4] = {false, false, false, false};
-
 static RowScale mk_scale(const NormScale &n) { return RowScale{n.sums, n.nparts, n.srows, n.K, n.eps}; }
 
 void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
                  hipEvent_t ev_start, hipEvent_t ev_stop) {
     const int nwb = (Npad / 64 + 3) / 4;
     const dim3 grid(nwb * S);
-#define KOALA_GEMM(MTV, RSV, IDX)                                                                                \
+#define KOALA_GEMM(MTV, RSV)                                                                                     \
     {                                                                                                            \
         const size_t sm = (size_t)2 * 4 * MTV * RSV * 64 * 16;                                                   \
-        if (!g_attr_done[IDX]) {                                                                                 \
-            (void)hipFuncSetAttribute((const void *)k_gemm_packed<MTV, RSV>,                                     \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);                      \
-            g_attr_done[IDX] = true;                                                                             \
-        }                                                                                                        \
+        static OncePerDevice once;                                                                               \
+        allow_lds(once, (const void *)k_gemm_packed<MTV, RSV>, sm);                                              \
         if (ev_start || ev_stop) /* events bound to the dispatch itself: they read the kernel's own begin and end */ \
             hipExtLaunchKernelGGL((k_gemm_packed<MTV, RSV>), grid, dim3(256 * RSV), sm, st,                      \
                                   mt0 == 0 ? ev_start : nullptr, mt0 + g >= MTT ? ev_stop : nullptr, 0,          \
@@ -1434,10 +1425,10 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
     for (int mt0 = 0; mt0 < MTT;) {
         const int left = MTT - mt0;
         const int g = left >= 8 && wide ? 8 : left >= 4 ? 4 : left;
-        if (g == 1) KOALA_GEMM(1, 1, 0)
-        else if (g == 2) KOALA_GEMM(2, 1, 1)
-        else if (g == 4) KOALA_GEMM(4, 1, 2)
-        else KOALA_GEMM(4, 2, 3)
+        if (g == 1) KOALA_GEMM(1, 1)
+        else if (g == 2) KOALA_GEMM(2, 1)
+        else if (g == 4) KOALA_GEMM(4, 1)
+        else KOALA_GEMM(4, 2)
         mt0 += g;
     }
 #undef KOALA_GEMM
@@ -1551,12 +1542,8 @@ static void launch_gemm_big(hipStream_t st, const void *Wp, const void *Xf, floa
                             const BigShape &b, const GemmEpi &e, hipEvent_t ev_start, hipEvent_t ev_stop) {
     // two tile buffers + the sink of the touches + the rows' scales, cache slots and sequences
     const size_t sm = (size_t)2 * 2 * MTW * 64 * 16 + 4 * 256 + 3 * MTW * 16 * 4;
-    static bool done = false;
-    if (!done) {
-        (void)hipFuncSetAttribute((const void *)k_gemm_big<U, MTW, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)sm);
-        done = true;
-    }
+    static OncePerDevice once;
+    allow_lds(once, (const void *)k_gemm_big<U, MTW, EPI>, sm);
     const int groups = (Npad / 16 + 4 * U - 1) / (4 * U);
     const int n_full = EPI == EPI_PARTIAL ? 0 : b.S == 1 ? (groups + 7) / 8 * 8 : b.n_full;
     const dim3 grid(EPI == EPI_PARTIAL ? (groups * b.S + 7) / 8 * 8 * b.n_pm
@@ -2089,12 +2076,8 @@ void launch_attn(hipStream_t st, const AttnArgs &a, int batch) {
     const size_t main_b = (size_t)MT * KS * 2 * 64 * 16 + (size_t)NWV * 32 * VS;
     const size_t merge_b = (size_t)NWV * MT * DT * 256 * 4 + (size_t)NWV * MT * 16 * 2 * 4;
     const size_t sm = main_b > merge_b ? main_b : merge_b;
-    static bool done = false;
-    if (!done) {
-        (void)hipFuncSetAttribute((const void *)k_attn_tree<DH, MT, NWV>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)sm);
-        done = true;
-    }
+    static OncePerDevice once;
+    allow_lds(once, (const void *)k_attn_tree<DH, MT, NWV>, sm);
     AttnArgs b = a;
     b.batch = batch;
     b.ngroups = (a.rows_per_seq + MT * 16 - 1) / (MT * 16);   // row-tile groups per (split, head, sequence)

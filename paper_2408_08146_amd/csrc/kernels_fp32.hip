@@ -352,9 +352,8 @@ void attention(hipStream_t st, const float *qrot, const RowMeta &meta, const voi
     const dim3 grid(batch * ngroups, n_heads, nsplit);
     const size_t sm = (size_t)NW * (head_dim / 16) * 64 * 16;
     if (head_dim == 128) {
-        static const hipError_t attr = hipFuncSetAttribute((const void *)k_attn_f32<128>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-        (void)attr;   // a failure shows at the launch
+        static OncePerDevice once;
+        allow_lds(once, (const void *)k_attn_f32<128>, sm);
         k_attn_f32<128><<<grid, 64 * NW, sm, st>>>(qrot, meta, (const float *)kc, (const float *)vc, o_part, ml, out,
                                                    rows_per_seq, n_heads, cap, nsplit, ngroups);
     } else {

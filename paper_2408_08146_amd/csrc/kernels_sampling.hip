@@ -744,9 +744,8 @@ void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, fl
     const float it = 1.0f / temperature;
 #define KOALA_WALK(NQ)                                                                                                  \
     {                                                                                                                  \
-        static const hipError_t attr = hipFuncSetAttribute((const void *)k_accept_sample_r<NQ>,                        \
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, NQ * NT * 16);  \
-        (void)attr;   /* a failure shows at the launch */                                                              \
+        static OncePerDevice once;                                                                                     \
+        allow_lds(once, (const void *)k_accept_sample_r<NQ>, NQ * NT * 16);                                            \
         k_accept_sample_r<NQ><<<batch, NT, NQ * NT * 16, st>>>(tt, T, D, V, it, tree_tokens, target_logits, draft_logits, u_accept, u_resample, accept_len, accept_path, next_token); \
     }
     if (V <= REG_V / 8) KOALA_WALK(1)

@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -84,6 +85,23 @@ struct koala_ctx {
     double prof_bytes;
     bool prof_on;
 };
+
+// Which of a process's devices something has been done on.  Devices past the 64th are always new.
+struct OncePerDevice {
+    std::atomic<uint64_t> done{0};
+    bool needed(int dev) const { return dev < 0 || dev >= 64 || !((done.load(std::memory_order_relaxed) >> dev) & 1u); }
+    void mark(int dev) {
+        if (dev >= 0 && dev < 64) done.fetch_or(1ull << dev, std::memory_order_relaxed);
+    }
+};
+// Allows a kernel its dynamic LDS on the current device: a function's attribute is set per device.  A failure shows at
+// the launch.
+inline void allow_lds(OncePerDevice &once, const void *kernel, size_t bytes) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || !once.needed(dev)) return;
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    once.mark(dev);
+}
 
 #define KOALA_CHECK_LAUNCH(ctx)                                              \
     do {                                                                     \

@@ -422,9 +422,8 @@ void launch_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ld
                int M, int N, int K, float alpha) {
     const size_t sm = (size_t)2 * 3 * (X3_BN + BM) / 16 * 64 * 16;
     constexpr int DEPTH = !ACC && BM <= 64 ? 4 : 2;
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_gemm_x3<BM, PKS, QKS, ACC, DEPTH>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    (void)attr;   // a failure shows at the launch
+    static OncePerDevice once;
+    allow_lds(once, (const void *)k_gemm_x3<BM, PKS, QKS, ACC, DEPTH>, sm);
     const long ldo = part ? N : ldc;
     const int vec = ldo % 4 == 0 && ((uintptr_t)(part ? part : C) & 15) == 0 && (!part || (size_t)M * N % 4 == 0);
     const dim3 grid(((N + X3_BN - 1) / X3_BN + 7) / 8 * 8 * ((M + BM - 1) / BM), S);

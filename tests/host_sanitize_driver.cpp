@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "koala.h"
+#include "koala_internal.h"
 
 static int failures = 0;
 #define EXPECT(cond)                                                         \
@@ -44,6 +45,17 @@ static Tree make_tree(const std::vector<int> &topk, const std::vector<int> &widt
 }
 
 int main() {
+    {   // what is set per device is set once on each
+        OncePerDevice once;
+        EXPECT(once.needed(0) && once.needed(5));
+        once.mark(0);
+        EXPECT(!once.needed(0) && once.needed(1) && once.needed(63));
+        once.mark(63);
+        EXPECT(!once.needed(63) && once.needed(62) && once.needed(64) && once.needed(-1));
+        once.mark(64);
+        once.mark(-1);
+        EXPECT(once.needed(64) && once.needed(-1) && once.needed(1));
+    }
     const koala_shape shape{256, 4, 64, 688, 1000, 4, 1e-6f, 1e4f, KOALA_FP32};
     const koala_shape shape_bf{512, 4, 128, 1408, 4000, 3, 1e-6f, 1e4f, KOALA_BF16};
     const koala_draft_shape eagle{KOALA_DRAFT_EAGLE, 2, 0, 8};
