@@ -1434,7 +1434,7 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 #undef KOALA_GEMM
 }
 
-bool rows_wide(int Npad, int n_cu) { return Npad / 16 > 7 * n_cu && (Npad / 16 + 7) / 8 <= n_cu; }
+bool rows_wide(int Npad, int n_cu) { return Npad / 16 > 5 * n_cu && (Npad / 16 + 7) / 8 <= n_cu; }
 
 void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, hipEvent_t ev_start,
                     hipEvent_t ev_stop) {

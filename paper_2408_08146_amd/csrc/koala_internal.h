@@ -241,9 +241,11 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 // scale, SiLU(gate) * up as fragments Xo of the down projection's input
 void gemm_rows_partial(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// Up to 64 rows against a matrix whose row groups in eights fill one round of compute units, and no smaller groups do:
-// the LM head of a 32000-token vocabulary (250 workgroups, one split, so P holds finished sums; 4096 columns: 40 us at one row,
-// 44 at 26, 48 at 64, where gemm_packed with three splits takes 44, 50 and 54).
+// Up to 64 rows against a matrix of which a workgroup takes eight row groups and finishes them (one split, so P holds finished
+// sums), where that is one round of compute units and at least five eighths of one: an LM head of 20481 to 32768 tokens.
+// Measured at 4096 columns, with the top-k behind it, us at 1 / 26 / 64 rows, against gemm_packed: 16000 tokens 32 / 36 / 47
+// against 30 / 35 / 42, 20000 34 / 38 / 47 against 35 / 40 / 48, 24000 36 / 39 / 49 against 40 / 45 / 54, 28600 41 / 44 / 53
+// against 49 / 54 / 64, 32768 46 / 49 / 57 against 52 / 57 / 68, 33000 (two rounds) 64 / 70 / 87 against 53 / 60 / 69.
 bool rows_wide(int Npad, int n_cu);
 void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, hipEvent_t ev_start = nullptr,
                     hipEvent_t ev_stop = nullptr);

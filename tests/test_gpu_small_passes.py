@@ -63,8 +63,8 @@ def test_row_groups_match_oracle(hidden, ffn, tree):
 
 
 # the output head of up to 64 rows: one workgroup per eight row groups where that is one round of the chip, at both ends of
-# the rule (28672 rows are the last before it, 32768 the last within it) and with a part-filled last group
-@pytest.mark.parametrize("vocab", [28672, 28680, 32000, 32768, 32770])
+# the rule (20480 rows are the last before it, 32768 the last within it) and with a part-filled last group
+@pytest.mark.parametrize("vocab", [20480, 20490, 24010, 28672, 28680, 32000, 32768, 32770])
 @pytest.mark.parametrize("tree", [dict(topk=[], widths=[1]), dict(topk=[3, 2, 1], widths=[1, 3, 6, 6]), T17, T64])
 def test_wide_output_head_matches_oracle(vocab, tree):
     c = Case("cfg2_small", n_layers=1, K=1, ctx=20, capacity=96, hidden=256, n_heads=2, head_dim=128, ffn=256, vocab=vocab, tree=tree)
