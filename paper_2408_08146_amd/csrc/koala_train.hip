@@ -727,12 +727,13 @@ bool params_ok(const koala_disc_shape *s, const koala_disc_params *p) {
 inline int fc_in(const koala_disc_shape &s, int k) { return k == 0 ? s.vocab : s.fc_hidden; }
 inline int fc_out(const koala_disc_shape &s, int k) { return k == s.n_fc - 1 ? 1 : s.fc_hidden; }
 
-// z = h W_lin^T joined to one or two sets of logits rows.  Two K splits, whose sums lie where u will: twice the
-// workgroups, so twice the bytes under way (20 rows, 32000 x 4096: 169 us with one split, 152 us with two).
+// z = h W_lin^T joined to one or two sets of logits rows.  Where its tiles do not fill the chip, two K splits, whose sums lie
+// where u will (4000 x 4096: 80 -> 43 us at 20 rows, 108 -> 58 at 64; 12345 x 4096: 81 -> 58 and 110 -> 85).  32000 x 4096 is
+// 500 tiles: 143 us with one split and 141 with two at 20 rows, 184 and 189 with the join at 64.
 void disc_join(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, const float *h,
                const float *la, const float *lb) {
     const long nV = (long)n * s.vocab;
-    const int S = n <= 64 && s.hidden >= 8 * X3_BK ? 2 : 1;
+    const int S = x3_splits(n, s.vocab, s.hidden, (size_t)2 * nV);
     gemm_nt(st, h, p.w_lin, w.z, w.u, S, n, s.vocab, s.hidden);
     k_join<<<blocks(nV), 256, 0, st>>>(S == 2 ? w.u : w.z, S == 2 ? w.u + nV : nullptr, la, lb, w.u, nV);
 }
@@ -896,7 +897,9 @@ koala_status koala_train_medusa_head_forward(void *hip_stream, int n_rows, int h
     hipStream_t st = (hipStream_t)hip_stream;
     const MedWs w = med_carve(n_rows, hidden, K, h, workspace, workspace_bytes);
     medusa_forward(st, n_rows, hidden, K, blocks_w, w);
-    gemm_nt(st, w.x[K], w_lm, d_logits, nullptr, 1, n_rows, vocab, hidden);
+    const int S = x3_splits(n_rows, vocab, hidden, w.room);
+    gemm_nt(st, w.x[K], w_lm, d_logits, w.part, S, n_rows, vocab, hidden);
+    if (S > 1) sum_parts<SUM_ONLY>(st, w.part, S, n_rows, vocab, nullptr, d_logits, nullptr);
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }
 
