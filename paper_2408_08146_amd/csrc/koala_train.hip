@@ -52,8 +52,8 @@ struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 // Measured, with the 64 x 64 fp32-MFMA kernel this replaced: 40 x 1024 from K = 32000 4063 -> 55 us (31 splits), 128 x 4096
 // from K = 32000 4396 -> 305 us (8 splits), 20 x 32000 from K = 4096 590 -> 145 us, 128 x 32000 816 -> 296 us, update of
 // 32000 x 4096 by 100 rows 662 us.  Splitting and LDS traffic bound the large ones.
-// Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 143 us for the 20 rows above), two
-// beyond (three spill: 54 -> 95 us for the 40 rows).
+// Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 132 us for the 20 rows above, by
+// themselves), two beyond (three spill: 54 -> 95 us for the 40 rows).
 // ---------------------------------------------------------------------------------------------
 enum { X3_BN = 64, X3_BK = 32 };
 
@@ -233,21 +233,26 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
 #pragma unroll
             for (int i = 0; i < TN; ++i)
                 a[pl][i] = __builtin_bit_cast(bf16x8, lds[(pl * (X3_BN / 16) + wn * TN + i) * 64 + slot]);
-        // small terms first
-        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+        // small terms first.  Up to 32 rows one row tile's fragments at a time, which leaves registers for four workgroups a
+        // compute unit; else all of them, whose reads are then over before the first MFMA
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0}, JT = BM == 32 ? 1 : TM;
 #pragma unroll
-        for (int j = 0; j < TM; ++j) {
-            bf16x8 b[3];
+        for (int j0 = 0; j0 < TM; j0 += JT) {
+            bf16x8 b[3][JT];
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl)
-                b[pl] = __builtin_bit_cast(bf16x8, lds[PU + (pl * (BM / 16) + wm * TM + j) * 64 + slot]);
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+                    b[pl][j] = __builtin_bit_cast(bf16x8, lds[PU + (pl * (BM / 16) + wm * TM + j0 + j) * 64 + slot]);
 #pragma unroll
             for (int z = 0; z < 6; ++z)
 #pragma unroll
-                for (int i = 0; i < TN; ++i) {
-                    f32x4 &sum = z == 5 ? acc[i][j] : low[i][j];
-                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[z]][i], b[PB[z]], sum, 0, 0, 0);
-                }
+                for (int i = 0; i < TN; ++i)
+#pragma unroll
+                    for (int j = 0; j < JT; ++j) {
+                        f32x4 &sum = z == 5 ? acc[i][j0 + j] : low[i][j0 + j];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA[z]][i], b[PB[z]][j], sum, 0, 0, 0);
+                    }
         }
     };
     static_assert(DEPTH == 2 || DEPTH == 4, "a chunk's registers and its LDS buffer go by the chunk number");
@@ -407,12 +412,13 @@ __global__ __launch_bounds__(256) void k_update_rows(const float *__restrict__ G
     }
 }
 
-// How many K splits give about two workgroups a compute unit, at least four chunks each, and fit `room` floats of partial
-// sums (none: one split, straight into C)
+// How many K splits give about as many workgroups as the compute units hold (two each, four up to 32 rows), at least four
+// chunks each, and fit `room` floats of partial sums (none: one split, straight into C)
 int x3_splits(int M, int N, int K, size_t room) {
     const long bm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
     const long tiles = (long)((N + X3_BN - 1) / X3_BN) * ((M + bm - 1) / bm), nch = (K + X3_BK - 1) / X3_BK;
-    long S = tiles >= 384 ? 1 : (512 + tiles / 2) / tiles;
+    const long want = bm == 32 ? 1024 : 512;
+    long S = tiles >= want * 3 / 4 ? 1 : (want + tiles / 2) / tiles;
     S = std::min({S, nch / 4, (long)(room / ((size_t)M * N)), 32L});
     return S < 2 ? 1 : (int)S;
 }
@@ -728,8 +734,8 @@ inline int fc_in(const koala_disc_shape &s, int k) { return k == 0 ? s.vocab : s
 inline int fc_out(const koala_disc_shape &s, int k) { return k == s.n_fc - 1 ? 1 : s.fc_hidden; }
 
 // z = h W_lin^T joined to one or two sets of logits rows.  Where its tiles do not fill the chip, two K splits, whose sums lie
-// where u will (4000 x 4096: 80 -> 43 us at 20 rows, 108 -> 58 at 64; 12345 x 4096: 81 -> 58 and 110 -> 85).  32000 x 4096 is
-// 500 tiles: 143 us with one split and 141 with two at 20 rows, 184 and 189 with the join at 64.
+// where u will (4000 x 4096: 80 -> 43 us at 20 rows, 108 -> 58 at 64; 12345 x 4096: 81 -> 58 and 110 -> 85; 32000 x 4096 at 20
+// rows 156 -> 147 us within a step).  At 64 rows 32000 x 4096 fills it: 184 us with one split and 189 with two, join included.
 void disc_join(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, const float *h,
                const float *la, const float *lb) {
     const long nV = (long)n * s.vocab;
