@@ -1479,12 +1479,15 @@ void gemm_rows_swiglu(hipStream_t st, const void *Wp, const void *Xf, int K, int
                                    ev_stop);
 }
 
-// Launch shape of gemm_big for `rows` activation rows: how many blocks the activation tiles are cut into (each
-// block streams the weights once, with up to 15 tiles per workgroup), weight row groups per wave (3, 4 or 5) and
+// Launch shape of gemm_big for `rows` activation rows: how many blocks the activation tiles are cut into (with up to 15
+// tiles per workgroup), weight row groups per wave (3, 4 or 5) and
 // K splits.  Every candidate is priced with a small model of the kernel, in cycles: a workgroup's 64-k tiles cost
 // their MFMAs plus a fixed amount (barrier, first LDS reads), a workgroup costs its start-up and its stores, the
 // launch takes as many rounds as its workgroups need on the chip's compute units (one workgroup each) but at
-// least the time to stream the weights once per tile block, and the partial sums of the splits are written once and read once by the kernel that folds them.
+// least the time to stream the weights once per tile block, and the partial sums of the splits are written once and read
+// once by the kernel that folds them.  Blocks of one group run on one die and share what they stream, so the price of the
+// stream is an upper one beyond one block; the shapes it chooses are the measured ones (priced once, about a third of
+// the launches of 200 rows and more would get another shape; not measured).
 // With an epilogue (room > 0) K is not split into partial sums; instead the groups that do not fill whole rounds may be
 // split S ways inside the kernel (n_full of them stay whole), where the scratch of `room` bytes and n_cnt counters reach:
 // a hand-over costs the workgroups' stores and, for the one that goes on, S reads of as much.
@@ -1506,7 +1509,7 @@ BigShape big_shape(int Npad, int K, int rows, int n_cu, bool epilogue, size_t ro
             if (U * tmpl > 60) continue;   // the accumulator tiles of a wave must fit the 256 accumulation registers
             if (fu >= 3 && fu <= 5 && fu * tmpl <= 60 && U != fu) continue;
             const int groups = (units + 4 * U - 1) / (4 * U);
-            const double hbm = (double)n_pm * Npad * K * 2.0 / 5.0e12 * 2.2e9;   // every tile block streams the weights
+            const double hbm = (double)n_pm * Npad * K * 2.0 / 5.0e12 * 2.2e9;   // of every tile block, see above
             auto wg = [&](int S) {   // cycles of a workgroup that takes one of S shares of K
                 return (double)((nkt + S - 1) / S) * (32.0 * tmpl * U / 0.8 + 400.0) + 6000.0 + 30.0 * tmpl * U;
             };

@@ -5,7 +5,7 @@
 //   QKV projection with RMSNorm in front and rotary embedding and cache append behind, attention, O projection added to
 //   the residual stream, gate/up projection with RMSNorm in front and SwiGLU behind, down projection added to the stream
 // (ten launches with norm, rotary embedding, split merge and SwiGLU as kernels of their own, which ran one output column
-// per wave on the vector unit and attention rows by the thread: iteration of the 4-layer model 519 us, so 225 us).
+// per wave on the vector unit and attention rows by the thread: iteration of the 4-layer model 515 us, so 224 us).
 //
 // Operand layout: the contraction order is free as long as both operands use the same, so lane (i = l%16, g = l/16) loads
 // four consecutive k, 16 bytes, and element e of every lane forms the MFMA's k step {4g + e}: sixteen k per load.

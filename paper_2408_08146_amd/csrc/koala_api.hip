@@ -10,8 +10,8 @@
 
 #include "koala_pass.h"
 
-// Scratch of koala_accept_sample_static: the two distributions of the stochastic acceptance walk,
-// [2][KOALA_STATIC_SCRATCH_FLOATS / 2] floats.  Every device the library runs on holds its own copy of
+// Scratch of koala_accept_sample_static: the two distributions of the stochastic acceptance walk where it keeps them in
+// memory (vocabularies above 32768), [2][KOALA_STATIC_SCRATCH_FLOATS / 2] floats.  Every device the library runs on holds its own copy of
 // the array until the process ends.  In host code the array's name is only a handle: the device
 // address is looked up once per device (static_scratch) and that pointer is what kernels receive.
 enum { KOALA_STATIC_SCRATCH_FLOATS = 2 * 262144 };

@@ -228,8 +228,8 @@ struct NormScale {
     float eps;
 };
 
-int gemm_splits(int Npad, int K, int MTT = 0);
-int rows_splits(int Npad, int K, int n_heads = 1);   // split count of gemm_rows_partial / _heads   // MTT: activation tiles of the call (0: at most four)
+int gemm_splits(int Npad, int K, int MTT = 0);       // split count of gemm_packed; MTT: activation tiles of the call (0: at most four)
+int rows_splits(int Npad, int K, int n_heads = 1);   // split count of gemm_rows_partial / _heads
 // P[S][MTT*16][Npad] = partial sums of X * W^T, X given as fp16 fragments [K/32][MTT][64] x 16 B
 // ev_start/ev_stop (either may be null) are attached to the dispatch: they take the kernel's own begin and end times
 void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, int S,
