@@ -385,10 +385,12 @@ __device__ __forceinline__ double row_exp(float (&w)[NQ][4], int V, float m, flo
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            w[u][e] = (int)threadIdx.x * 4 < V - u * NT * 4 - e ? expf((w[u][e] - m) * inv_tau) : 0.f;
-            s += (double)w[u][e];
-        }
+        for (int e = 0; e < 4; ++e) w[u][e] = expf((w[u][e] - m) * inv_tau);
+        if (V < (u + 1) * NT * 4)   // the same for all threads
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[u][e] = (int)threadIdx.x * 4 < V - u * NT * 4 - e ? w[u][e] : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += (double)w[u][e];
         __builtin_amdgcn_sched_barrier(0);
     }
     return s;
