@@ -13,9 +13,10 @@
 //
 // Two forms.  Up to 32768 tokens a workgroup holds its rows in registers (32 values of a row per thread): a row is read
 // once, every later pass over it is arithmetic, and the draws of a row exchange one number each through LDS.  Larger
-// vocabularies keep their rows in memory and read them again in every pass.  The register form of the acceptance walk took
-// 102 us where the memory form takes 278 us (eight sequences, 60 nodes, 32000 tokens), that of the draws (the children of
-// 208 nodes, a 64-node Medusa-style tree for eight sequences) 33 us where the memory form takes 427 us.
+// vocabularies keep their rows in memory and read them again in every pass.  Acceptance for eight sequences of 60 nodes and
+// 32000 tokens: 43 us with the nodes side by side in registers, 88 us with a workgroup a sequence that takes them in turn (100
+// with shuffles through LDS in its reductions), 278 us in the memory form.  Draws (the children of 208 nodes, a 64-node
+// Medusa-style tree for eight sequences): 33 us where the memory form takes 427 us.
 #include "koala_internal.h"
 
 namespace {
@@ -407,26 +408,81 @@ __device__ __forceinline__ void row_scale(float (&w)[NQ][4], double f) {
         __builtin_amdgcn_sched_barrier(0);
     }
 }
+// Reductions over the wave without LDS: a shuffle goes through LDS (two trips for a double, about 120 cycles each), the swap
+// and row instructions below stay in the vector unit.  A butterfly by 32, 16, 8, 4, 2, 1: the swap of a value with itself
+// leaves a lane's own and its partner's value in the two results; a rotation by o within sixteen lanes is the exchange with
+// lane ^ o once the lanes 2 o apart hold the same value (by 8 it is that exchange itself).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp32(uint32_t v) {   // lanes without a source, and rows not named, get zero
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
+}
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp64(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)dpp32<CTRL, ROWS>((uint32_t)(b >> 32)) << 32 | dpp32<CTRL, ROWS>((uint32_t)b));
+}
+enum { DPP_ROR = 0x120, DPP_SHR = 0x110, DPP_WAVE_SHR1 = 0x138, DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143 };
+__device__ __forceinline__ double swap_sum(double v, bool by32) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    const auto p = by32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto q = by32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __builtin_bit_cast(double, (uint64_t)q[0] << 32 | p[0]) + __builtin_bit_cast(double, (uint64_t)q[1] << 32 | p[1]);
+}
+__device__ __forceinline__ float swap_max(float v, bool by32) {
+    const uint32_t b = __float_as_uint(v);
+    const auto p = by32 ? __builtin_amdgcn_permlane32_swap(b, b, false, false) : __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ __forceinline__ double row16_sum(double v) {   // over sixteen lanes, in each of them
+    v += dpp64<DPP_ROR + 8>(v);
+    v += dpp64<DPP_ROR + 4>(v);
+    v += dpp64<DPP_ROR + 2>(v);
+    return v + dpp64<DPP_ROR + 1>(v);
+}
+__device__ __forceinline__ float row16_max(float v) {
+    v = fmaxf(v, __uint_as_float(dpp32<DPP_ROR + 8>(__float_as_uint(v))));
+    v = fmaxf(v, __uint_as_float(dpp32<DPP_ROR + 4>(__float_as_uint(v))));
+    v = fmaxf(v, __uint_as_float(dpp32<DPP_ROR + 2>(__float_as_uint(v))));
+    return fmaxf(v, __uint_as_float(dpp32<DPP_ROR + 1>(__float_as_uint(v))));
+}
+__device__ __forceinline__ double wave_total(double v) { return row16_sum(swap_sum(swap_sum(v, true), false)); }
+__device__ __forceinline__ double lane_value(double v, int lane) {   // of a lane that is the same for all
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+__device__ __forceinline__ double wave_scan(double v) {   // inclusive, in lane order
+    v += dpp64<DPP_SHR + 1>(v);
+    v += dpp64<DPP_SHR + 2>(v);
+    v += dpp64<DPP_SHR + 4>(v);
+    v += dpp64<DPP_SHR + 8>(v);
+    v += dpp64<DPP_BCAST15, 0xa>(v);   // the sums of rows 0 and 2 to rows 1 and 3
+    return v + dpp64<DPP_BCAST31, 0xc>(v);
+}
 // maxima / sums of two values over the workgroup; nobody may still be reading the arrays of an earlier call
 __device__ __forceinline__ void block_max2(float &a, float &b, RegShared &sh) {
-    for (int o = 32; o > 0; o >>= 1) { a = fmaxf(a, __shfl_xor(a, o)); b = fmaxf(b, __shfl_xor(b, o)); }
+    a = row16_max(swap_max(swap_max(a, true), false));
+    b = row16_max(swap_max(swap_max(b, true), false));
     if ((threadIdx.x & 63) == 0) { sh.mx[0][threadIdx.x >> 6] = a; sh.mx[1][threadIdx.x >> 6] = b; }
     __syncthreads();
     const int l = threadIdx.x & 63;   // sixteen lanes a value
-    float v = sh.mx[(l >> 4) & 1][l & 15];
-    for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    a = __shfl(v, 0);
-    b = __shfl(v, 16);
+    const float v = row16_max(sh.mx[(l >> 4) & 1][l & 15]);
+    a = lane_value(v, 0);
+    b = lane_value(v, 16);
 }
 __device__ __forceinline__ void block_sum2(double &a, double &b, RegShared &sh) {
-    for (int o = 32; o > 0; o >>= 1) { a += __shfl_xor(a, o); b += __shfl_xor(b, o); }
+    a = wave_total(a);
+    b = wave_total(b);
     if ((threadIdx.x & 63) == 0) { sh.red[0][threadIdx.x >> 6] = a; sh.red[1][threadIdx.x >> 6] = b; }
     __syncthreads();
     const int l = threadIdx.x & 63;
-    double v = sh.red[(l >> 4) & 1][l & 15];
-    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    a = __shfl(v, 0);
-    b = __shfl(v, 16);
+    const double v = row16_sum(sh.red[(l >> 4) & 1][l & 15]);
+    a = lane_value(v, 0);
+    b = lane_value(v, 16);
 }
 
 // The sums of segments 2l and 2l + 1 in lane l of every wave
@@ -436,10 +492,7 @@ __device__ __forceinline__ SegPair segment_pairs(const float (&w)[NQ][4], int wa
     const int l = threadIdx.x & 63;
     double t[NQ];
 #pragma unroll
-    for (int u = 0; u < NQ; ++u) t[u] = seg_lane_sum(w[u]);
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) t[u] += __shfl_xor(t[u], o);
+    for (int u = 0; u < NQ; ++u) t[u] = wave_total(seg_lane_sum(w[u]));
     if (l == 0) {
 #pragma unroll
         for (int u = 0; u < NQ; ++u) sh.seg[u * NW + wave] = t[u];
@@ -450,23 +503,14 @@ __device__ __forceinline__ SegPair segment_pairs(const float (&w)[NQ][4], int wa
     p.b = 2 * l + 1 < NQ * NW ? sh.seg[2 * l + 1] : 0.0;
     return p;
 }
-__device__ __forceinline__ double wave_scan(double v, int l) {   // inclusive, in lane order
-    for (int o = 1; o < 64; o <<= 1) {
-        const double t = __shfl_up(v, o);
-        if (l >= o) v += t;
-    }
-    return v;
-}
 struct SegPick { int s; bool rounding; double base, target; };   // s: the segment that holds the id, -1 if nothing is positive
 // The first segment with anything in it at which the running sum exceeds u * total; the last one with anything if
 // rounding leaves none.  The same in every wave.
 __device__ __forceinline__ SegPick pick_segment(const SegPair &p, double u) {
-    const int l = threadIdx.x & 63;
-    const double incl = wave_scan(p.a + p.b, l);
-    double excl = __shfl_up(incl, 1);
-    if (l == 0) excl = 0.0;
+    const double incl = wave_scan(p.a + p.b);
+    const double excl = dpp64<DPP_WAVE_SHR1>(incl);   // zero in lane 0
     SegPick r;
-    r.target = u * __shfl(incl, 63);
+    r.target = u * lane_value(incl, 63);
     const bool first = p.a > 0.0 && excl + p.a > r.target, second = p.b > 0.0 && incl > r.target;
     const unsigned long long hit = __ballot(first || second);
     const double base = first ? excl : excl + p.a;
@@ -474,20 +518,20 @@ __device__ __forceinline__ SegPick pick_segment(const SegPair &p, double u) {
     r.base = 0.0;
     if (hit) {
         const int at = __ffsll((long long)hit) - 1;
-        r.s = 2 * at + (__shfl((int)first, at) ? 0 : 1);
-        r.base = __shfl(base, at);
+        r.s = 2 * at + ((__ballot(first) >> at) & 1 ? 0 : 1);
+        r.base = lane_value(base, at);
     } else {
         const unsigned long long any = __ballot(p.a > 0.0 || p.b > 0.0);
         if (any == 0) { r.s = -1; return r; }
         const int at = 63 - __clzll((long long)any);
-        r.s = 2 * at + (__shfl((int)(p.b > 0.0), at) ? 1 : 0);
+        r.s = 2 * at + ((__ballot(p.b > 0.0) >> at) & 1 ? 1 : 0);
     }
     return r;
 }
 // The id inside the picked segment, by the wave that holds it in group x (every lane gets it)
 __device__ __forceinline__ int pick_in_segment(const float (&x)[4], const SegPick &r) {
     const int l = threadIdx.x & 63;
-    const double own = seg_lane_sum(x), incl = wave_scan(own, l);
+    const double own = seg_lane_sum(x), incl = wave_scan(own);
     const double lo = r.base + (incl - own), hi = r.base + incl;
     int pick = -1, last = -1;
     double run = lo;
@@ -500,7 +544,7 @@ __device__ __forceinline__ int pick_in_segment(const float (&x)[4], const SegPic
         }
     }
     const unsigned long long claims = __ballot(!r.rounding && lo <= r.target && hi > r.target && pick >= 0);
-    if (claims) return __shfl(pick, __ffsll((long long)claims) - 1);
+    if (claims) return __builtin_amdgcn_readlane(pick, __ffsll((long long)claims) - 1);
     for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
     return max(last, 0);
 }
@@ -553,7 +597,7 @@ __global__ __launch_bounds__(NT) void k_sample_children_r(const float *src, ks::
     SegPair seg = segment_pairs<NQ>(w, wave, sh);
     for (int j = 0; j < nk; ++j) {
         const int c = child_at(place, j);
-        const SegPick r = pick_segment(seg, (double)__shfl(u_lane, c));
+        const SegPick r = pick_segment(seg, (double)lane_value(u_lane, c));
         if (r.s < 0) {   // nothing left to draw from, here and for the children that follow
             if (threadIdx.x == 0) tree_tokens[(size_t)b * T + c] = 0;
             continue;
@@ -574,7 +618,7 @@ __global__ __launch_bounds__(NT) void k_sample_children_r(const float *src, ks::
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (r.s * SEG + 4 * l + e == idx) x[e] = 0.f;
-            const double left = wave_sum(seg_lane_sum(x));
+            const double left = wave_total(seg_lane_sum(x));
             if (l == 0) {
                 tree_tokens[(size_t)b * T + c] = idx;
                 sh.news[j & 1] = left;
@@ -585,138 +629,236 @@ __global__ __launch_bounds__(NT) void k_sample_children_r(const float *src, ks::
     }
 }
 
-// The walk holds the draft's row in registers and the target's in LDS, where a thread only ever touches its own 16-byte
-// pieces (no barriers, no bank conflicts): both in registers with 512 threads spilled.
-template <int NQ>
-__global__ __launch_bounds__(NT) void k_accept_sample_r(TreeTables tt, int T, int D, int V, float inv_tau,
-                                                        const int32_t *tree_tokens, const float *target_logits,
-                                                        const float *draft_logits, const float *u_accept,
-                                                        const float *u_resample, int32_t *accept_len, int32_t *accept_path,
-                                                        int32_t *next_token) {
-    extern __shared__ __attribute__((aligned(16))) f32q walk_q[];   // [NQ][NT]
-    __shared__ RegShared sh;
-    __shared__ float ua[KOALA_MAX_NODES], ur[KOALA_MAX_NODES];       // what the walk asks of a node: in LDS, the rows fill the
-    __shared__ int tok[KOALA_MAX_NODES];                             // registers
-    const int b = blockIdx.x, tid = threadIdx.x, l = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int32_t *path = accept_path + (size_t)b * (D + 1);
-    f32q *ql = walk_q + tid;
-    // one node a lane, in every wave
-    const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
-    if (tid < T) {   // read behind the barriers of the first reductions
-        const int x = tree_tokens[(size_t)b * T + tid];
-        tok[tid] = x < 0 ? 0 : x >= V ? V - 1 : x;
-        ua[tid] = u_accept[(size_t)b * T + tid];
-        ur[tid] = u_resample[(size_t)b * T + tid];
+// What acceptance asks of a sequence's nodes, and the tree held one node a lane in every wave
+struct WalkShared {
+    RegShared r;
+    float ua[KOALA_MAX_NODES], ur[KOALA_MAX_NODES];   // in LDS: the rows fill the registers
+    int tok[KOALA_MAX_NODES];
+};
+struct WalkArgs {
+    const int32_t *tree_tokens;
+    const float *target_logits, *draft_logits, *u_accept, *u_resample;
+    int32_t *accept_len, *accept_path, *next_token;
+};
+struct NodeEnd { int child, token; bool mine; };   // the accepted child or, 0, where the walk stops: then token, in the wave that says mine
+
+__device__ __forceinline__ void walk_inputs(const WalkArgs &g, int b, int T, int V, WalkShared &sh) {   // read behind the first barrier
+    const int tid = threadIdx.x;
+    if (tid < T) {
+        const int x = g.tree_tokens[(size_t)b * T + tid];
+        sh.tok[tid] = x < 0 ? 0 : x >= V ? V - 1 : x;
+        sh.ua[tid] = g.u_accept[(size_t)b * T + tid];
+        sh.ur[tid] = g.u_resample[(size_t)b * T + tid];
     }
-    int cur = 0, a = 0;
-    if (tid == 0) path[0] = 0;
-    for (;;) {
-        const unsigned long long kids = children_of(par, cur);
-        const int nk = a < D ? __popcll(kids) : 0, place = child_order(kids, rank);
-        float d[NQ][4], mq, md = 0.f;
-        int Vi = V;
-        asm volatile("" : "+s"(Vi));   // the row's bounds are worked out anew for each node
-        double sq, sd = 1.0;
-        {
-            float q[NQ][4];
-            row_load<NQ>(target_logits + ((size_t)b * T + cur) * V, Vi, q);
-            if (nk > 0) row_load<NQ>(draft_logits + ((size_t)b * T + cur) * V, Vi, d);
-            mq = row_max<NQ>(q);
-            if (nk > 0) md = row_max<NQ>(d);
-            block_max2(mq, md, sh);
-            sq = row_exp<NQ>(q, Vi, mq, inv_tau);
-            if (nk > 0) sd = row_exp<NQ>(d, Vi, md, inv_tau);
-            block_sum2(sq, sd, sh);
-            row_scale<NQ>(q, 1.0 / sq);
-            if (nk > 0) row_scale<NQ>(d, 1.0 / sd);
+}
+
+// What happens at node `cur` of sequence b, which depends on nothing that came before: its children are tried in draw order,
+// and where none is accepted a token is drawn.  The draft's row is in registers and the target's in LDS, where a thread only
+// ever touches its own 16-byte pieces (no barriers, no bank conflicts): both in registers with 512 threads spilled.  Both are
+// divided by their sums only once a child has been rejected or a token is drawn; the first child needs two quotients.
+template <int NQ>
+__device__ __forceinline__ NodeEnd walk_node(const WalkArgs &g, int b, int cur, int T, int V, float inv_tau, int par, int rank,
+                                             f32q *ql, WalkShared &sh) {
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned long long kids = children_of(par, cur);
+    const int nk = __popcll(kids), place = child_order(kids, rank);
+    float d[NQ][4], mq, md = 0.f;
+    int Vi = V;
+    asm volatile("" : "+s"(Vi));   // the row's bounds are worked out anew for each node
+    double sq, sd = 1.0;
+    {
+        float q[NQ][4];
+        row_load<NQ>(g.target_logits + ((size_t)b * T + cur) * V, Vi, q);
+        if (nk > 0) row_load<NQ>(g.draft_logits + ((size_t)b * T + cur) * V, Vi, d);
+        mq = row_max<NQ>(q);
+        if (nk > 0) md = row_max<NQ>(d);
+        block_max2(mq, md, sh.r);
+        sq = row_exp<NQ>(q, Vi, mq, inv_tau);
+        if (nk > 0) sd = row_exp<NQ>(d, Vi, md, inv_tau);
+        block_sum2(sq, sd, sh.r);
+        if (nk == 0) row_scale<NQ>(q, 1.0 / sq);
 #pragma unroll
-            for (int u = 0; u < NQ; ++u) ql[u * NT] = (f32q){q[u][0], q[u][1], q[u][2], q[u][3]};
+        for (int u = 0; u < NQ; ++u) ql[u * NT] = (f32q){q[u][0], q[u][1], q[u][2], q[u][3]};
+    }
+    for (int j = 0; j < nk; ++j) {
+        const int c = child_at(place, j), x = sh.tok[c], xo = x - tid * 4;
+        if (xo >= 0 && xo % (NT * 4) < 4) {   // this thread has the probabilities of the child's token
+            float dx = 0.f, qx = ((const float *)(ql + xo / (NT * 4) * NT))[xo % 4];
+#pragma unroll
+            for (int u = 0; u < NQ; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dx = xo == u * NT * 4 + e ? d[u][e] : dx;
+            if (j == 0) { qx = (float)((double)qx * (1.0 / sq)); dx = (float)((double)dx * (1.0 / sd)); }
+            sh.r.dx[j & 1] = dx;
+            sh.r.qx[j & 1] = qx;
         }
-        bool moved = false;
-        for (int j = 0; j < nk; ++j) {
-            const int c = child_at(place, j), x = tok[c], xo = x - tid * 4;
-            if (xo >= 0 && xo % (NT * 4) < 4) {   // this thread has the probabilities of the child's token
-                float dx = 0.f;
-#pragma unroll
-                for (int u = 0; u < NQ; ++u)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) dx = xo == u * NT * 4 + e ? d[u][e] : dx;
-                sh.dx[j & 1] = dx;
-                sh.qx[j & 1] = ((const float *)(ql + xo / (NT * 4) * NT))[xo % 4];
-            }
-            __syncthreads();
-            const double qx = (double)sh.qx[j & 1], dx = (double)sh.dx[j & 1];
-            const double ratio = dx > 0.0 ? fmin(1.0, qx / dx) : 0.0;
-            if (dx > 0.0 && (double)ua[c] < ratio) {
-                cur = c;
-                ++a;
-                if (tid == 0) path[a] = c;
-                moved = true;
-                break;
-            }
-            // rejected: q <- norm(max(0, q - d)) (kept if that is all zero); d loses x and is renormalised
-            double rs = 0.0, ds = 0.0;
-            int xd = xo;
-            asm volatile("" : "+v"(xd));   // compared anew: no 32 masks kept from above
-#pragma unroll
-            for (int u = 0; u < NQ; ++u) {
-                const f32q q = ql[u * NT];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    rs += (double)fmaxf(0.f, q[e] - d[u][e]);
-                    d[u][e] = xd == u * NT * 4 + e ? 0.f : d[u][e];
-                    ds += (double)d[u][e];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            block_sum2(rs, ds, sh);
-            const bool keep = !(rs > 0.0);
-            const double fr = keep ? 1.0 : 1.0 / rs, fd = ds > 0.0 ? 1.0 / ds : 1.0;
+        __syncthreads();
+        const double qx = (double)sh.r.qx[j & 1], dx = (double)sh.r.dx[j & 1];
+        const double ratio = dx > 0.0 ? fmin(1.0, qx / dx) : 0.0;
+        if (dx > 0.0 && (double)sh.ua[c] < ratio) return NodeEnd{c, 0, wave == 0};
+        // rejected: q <- norm(max(0, q - d)) (kept if that is all zero); d loses x and is renormalised
+        double rs = 0.0, ds = 0.0;
+        int xd = xo;
+        asm volatile("" : "+v"(xd));   // compared anew: no 32 masks kept from above
+        if (j == 0) {
+            const double fq = 1.0 / sq;
 #pragma unroll
             for (int u = 0; u < NQ; ++u) {
                 f32q q = ql[u * NT];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    asm volatile("" : "+v"(d[u][e]));   // as in row_scale
-                    const float t = fmaxf(0.f, q[e] - d[u][e]);
-                    q[e] = (float)((double)(keep ? q[e] : t) * fr);
-                    d[u][e] = (float)((double)d[u][e] * fd);
-                }
+                for (int e = 0; e < 4; ++e) q[e] = (float)((double)q[e] * fq);
                 ql[u * NT] = q;
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (xo >= 0 && xo % (NT * 4) < 4) {   // d has lost x by now: q there once more, from the values tried above
-                const float qo = sh.qx[j & 1], t = fmaxf(0.f, qo - sh.dx[j & 1]);
-                ((float *)(ql + xo / (NT * 4) * NT))[xo % 4] = (float)((double)(keep ? qo : t) * fr);
-            }
+            row_scale<NQ>(d, 1.0 / sd);
         }
-        if (moved) continue;
-        float q[NQ][4];
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
-            const f32q x = ql[u * NT];
+            const f32q q = ql[u * NT];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) q[u][e] = x[e];
+            for (int e = 0; e < 4; ++e) {
+                rs += (double)fmaxf(0.f, q[e] - d[u][e]);
+                d[u][e] = xd == u * NT * 4 + e ? 0.f : d[u][e];
+                ds += (double)d[u][e];
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const SegPair seg = segment_pairs<NQ>(q, wave, sh);
-        const SegPick r = pick_segment(seg, (double)ur[cur]);
-        if (r.s < 0 ? wave == 0 : (r.s & (NW - 1)) == wave) {
-            float y[4] = {0.f, 0.f, 0.f, 0.f};
+        block_sum2(rs, ds, sh.r);
+        const bool keep = !(rs > 0.0);
+        const double fr = keep ? 1.0 : 1.0 / rs, fd = ds > 0.0 ? 1.0 / ds : 1.0;
 #pragma unroll
-            for (int u = 0; u < NQ; ++u)
-                if (r.s >= 0 && u == r.s / NW)
+        for (int u = 0; u < NQ; ++u) {
+            f32q q = ql[u * NT];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) y[e] = q[u][e];
-            const int idx = r.s < 0 ? 0 : pick_in_segment(y, r);
-            if (l == 0) next_token[b] = idx;
+            for (int e = 0; e < 4; ++e) {
+                asm volatile("" : "+v"(d[u][e]));   // as in row_scale
+                const float t = fmaxf(0.f, q[e] - d[u][e]);
+                q[e] = (float)((double)(keep ? q[e] : t) * fr);
+                d[u][e] = (float)((double)d[u][e] * fd);
+            }
+            ql[u * NT] = q;
+            __builtin_amdgcn_sched_barrier(0);
         }
+        if (xo >= 0 && xo % (NT * 4) < 4) {   // d has lost x by now: q there once more, from the values tried above
+            const float qo = sh.r.qx[j & 1], t = fmaxf(0.f, qo - sh.r.dx[j & 1]);
+            ((float *)(ql + xo / (NT * 4) * NT))[xo % 4] = (float)((double)(keep ? qo : t) * fr);
+        }
+    }
+    float q[NQ][4];
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+        const f32q x = ql[u * NT];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[u][e] = x[e];
+    }
+    const SegPair seg = segment_pairs<NQ>(q, wave, sh.r);
+    const SegPick r = pick_segment(seg, (double)sh.ur[cur]);
+    const bool mine = r.s < 0 ? wave == 0 : (r.s & (NW - 1)) == wave;
+    int idx = 0;
+    if (mine && r.s >= 0) {
+        float y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < NQ; ++u)
+            if (u == r.s / NW)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = q[u][e];
+        idx = pick_in_segment(y, r);
+    }
+    return NodeEnd{0, idx, mine};
+}
+
+// One workgroup per sequence follows the path from the root.
+template <int NQ>
+__global__ __launch_bounds__(NT) void k_accept_walk(TreeTables tt, int T, int D, int V, float inv_tau, WalkArgs g) {
+    extern __shared__ __attribute__((aligned(16))) f32q walk_q[];   // [NQ][NT]
+    __shared__ WalkShared sh;
+    const int b = blockIdx.x, tid = threadIdx.x, l = tid & 63;
+    int32_t *path = g.accept_path + (size_t)b * (D + 1);
+    const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
+    walk_inputs(g, b, T, V, sh);
+    int cur = 0, a = 0;
+    if (tid == 0) path[0] = 0;
+    for (;;) {
+        const NodeEnd e = walk_node<NQ>(g, b, cur, T, V, inv_tau, par, rank, walk_q + tid, sh);
+        if (e.child > 0) {
+            cur = e.child;
+            ++a;
+            if (tid == 0) path[a] = cur;
+            continue;
+        }
+        if (e.mine && l == 0) g.next_token[b] = e.token;
         if (tid == 0) {
-            accept_len[b] = a;
+            g.accept_len[b] = a;
             for (int j = a + 1; j <= D; ++j) path[j] = -1;
         }
         return;
     }
+}
+
+// All nodes at once, one workgroup each: the path is a chain of nodes that each take a row's way through the compute unit
+// (about 13 us), but what happens at a node does not depend on the path to it.  Nodes are dealt out from the root down, the
+// sequences in turn.  A workgroup that does not start with the first ones looks whether an ancestor has already decided
+// against its branch, and is done if so.  state [sequence][STATE]: what became of each node (0: not known, the child
+// taken, or -1 - the token drawn) and a count of finished workgroups; the last of a sequence follows the path and leaves
+// zeros.  Nobody waits for anybody.
+enum { STATE = 80, DONE = 64 };
+static_assert((int)STATE == (int)ks::ACCEPT_STATE && (int)DONE >= KOALA_MAX_NODES, "room for every node");
+template <int NQ>
+__global__ __launch_bounds__(NT) void k_accept_nodes(TreeTables tt, int T, int D, int V, float inv_tau, WalkArgs g, int batch,
+                                                     int n_first, int *state) {
+    extern __shared__ __attribute__((aligned(16))) f32q walk_q[];   // [NQ][NT]
+    __shared__ WalkShared sh;
+    const int b = blockIdx.x % batch, cur = blockIdx.x / batch, tid = threadIdx.x, l = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int *mine = state + (size_t)b * STATE;
+    auto known = [&]() { return l < T ? __hip_atomic_load(mine + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0; };
+    const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
+    NodeEnd e{0, 0, wave == 0};
+    bool off = false;   // off the path: the waves may find different things out, the first one's decide
+    if ((int)blockIdx.x >= n_first) {
+        if (wave == 0) {
+            const int st = known();
+            for (int x = cur; x != 0 && !off;) {
+                const int p = __builtin_amdgcn_readlane(par, x), s = __builtin_amdgcn_readlane(st, p);
+                off = s != 0 && s != x;
+                x = p;
+            }
+            if (l == 0) sh.tok[0] = off;
+        }
+        __syncthreads();
+        off = sh.tok[0] != 0;
+        __syncthreads();
+    }
+    if (!off) {
+        walk_inputs(g, b, T, V, sh);
+        e = walk_node<NQ>(g, b, cur, T, V, inv_tau, par, rank, walk_q + tid, sh);
+    }
+    if (!e.mine) return;
+    // one wave is left: the result is written through before the count moves
+    int n = 0;
+    if (l == 0) {
+        if (!off) __hip_atomic_store(mine + cur, e.child > 0 ? e.child : -1 - e.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        n = __hip_atomic_fetch_add(mine + DONE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(n) != T - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int st = known();
+    int at = 0, a = 0, on = l == 0 ? 0 : -1;   // lane l: the path's node at depth l
+    for (int s = __builtin_amdgcn_readlane(st, 0); s > 0; s = __builtin_amdgcn_readlane(st, at)) {
+        at = s;
+        ++a;
+        if (l == a) on = at;
+    }
+    if (l <= D) g.accept_path[(size_t)b * (D + 1) + l] = on;
+    if (l == 0) {
+        g.next_token[b] = -1 - __builtin_amdgcn_readlane(st, at);
+        g.accept_len[b] = a;
+        __hip_atomic_store(mine + DONE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (l < T) __hip_atomic_store(mine + l, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
@@ -741,14 +883,24 @@ void sample_children(hipStream_t st, const float *src, float *scratch, const Nod
 
 void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, float temperature,
                    const int32_t *tree_tokens, const float *target_logits, const float *draft_logits,
-                   const float *u_accept, const float *u_resample, float *qv, float *dv, int32_t *accept_len,
+                   const float *u_accept, const float *u_resample, float *qv, float *dv, int *state, int n_cu, int32_t *accept_len,
                    int32_t *accept_path, int32_t *next_token, int batch) {
     const float it = 1.0f / temperature;
+    const WalkArgs g{tree_tokens, target_logits, draft_logits, u_accept, u_resample, accept_len, accept_path, next_token};
+    // Up to sixteen nodes a compute unit, as far as measured: 60 nodes of 32000 tokens, one workgroup a node against one a
+    // sequence, us at 1 / 8 / 16 / 32 / 64 sequences: 26 / 43 / 44 / 57 / 80 against 81 / 88 / 88 / 92 / 99; 4000 tokens
+    // 11 / 13 / 16 / 18 / 24 against 24 / 30 / 30 / 30 / 29.  Beyond, the nodes that the path leaves out would fill the chip.
+    const bool nodes = T > 1 && (long)batch * T <= 16L * n_cu;
 #define KOALA_WALK(NQ)                                                                                                  \
     {                                                                                                                  \
-        static OncePerDevice once;                                                                                     \
-        allow_lds(once, (const void *)k_accept_sample_r<NQ>, NQ * NT * 16);                                            \
-        k_accept_sample_r<NQ><<<batch, NT, NQ * NT * 16, st>>>(tt, T, D, V, it, tree_tokens, target_logits, draft_logits, u_accept, u_resample, accept_len, accept_path, next_token); \
+        static OncePerDevice once[2];                                                                                  \
+        if (nodes) {                                                                                                   \
+            allow_lds(once[0], (const void *)k_accept_nodes<NQ>, NQ * NT * 16);                                        \
+            k_accept_nodes<NQ><<<batch * T, NT, NQ * NT * 16, st>>>(tt, T, D, V, it, g, batch, n_cu, state);           \
+        } else {                                                                                                       \
+            allow_lds(once[1], (const void *)k_accept_walk<NQ>, NQ * NT * 16);                                         \
+            k_accept_walk<NQ><<<batch, NT, NQ * NT * 16, st>>>(tt, T, D, V, it, g);                                    \
+        }                                                                                                              \
     }
     if (V <= REG_V / 8) KOALA_WALK(1)
     else if (V <= REG_V / 2) KOALA_WALK(4)

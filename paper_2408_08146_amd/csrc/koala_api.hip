@@ -84,8 +84,6 @@ size_t carve(koala_ctx *c, char *base) {
     c->tt.exp_index = w.take<int32_t>(T);
     c->tt.draft_mask = w.take<uint64_t>(T);
     c->tt.level_nodes = w.take<int32_t>((size_t)(D + 1) * 64);
-    c->tt.child_first = nullptr;
-    c->tt.child_count = nullptr;
     c->meta.row_b = w.take<int32_t>(R);
     c->meta.row_pos = w.take<int32_t>(R);
     c->meta.row_slot = w.take<int32_t>(R);
@@ -125,6 +123,7 @@ size_t carve(koala_ctx *c, char *base) {
     c->gen_tlogits = w.take<float>((size_t)T * V);
     c->med_logits = c->draft.kind == KOALA_DRAFT_MEDUSA ? w.take<float>((size_t)D * c->max_batch * V) : nullptr;
     const size_t walk = V > ks::register_vocab() ? (size_t)c->max_batch * V : 0;
+    c->acc_state = w.take<int>((size_t)c->max_batch * ks::ACCEPT_STATE);
     c->acc_q = w.take<float>(walk);
     c->acc_d = w.take<float>(walk);
     c->xf = c->xf2 = nullptr;
@@ -505,7 +504,7 @@ koala_status koala_bind(koala_ctx *c, const koala_weights *w, const koala_kv *kv
     c->ws_bytes = bytes;
     carve(c, c->ws);
 
-    const int T = c->T, D = c->D, half = c->shape.head_dim / 2;
+    const int D = c->D, half = c->shape.head_dim / 2;
     std::vector<double> inv_freq(half);
     for (int i = 0; i < half; ++i)
         inv_freq[i] = pow((double)c->shape.rope_base, -2.0 * (double)i / (double)c->shape.head_dim);
@@ -525,6 +524,7 @@ koala_status koala_bind(koala_ctx *c, const koala_weights *w, const koala_kv *kv
         e = static_scratch(&unused);
     }
     if (e == hipSuccess) e = hipMemset(c->attn_cnt, 0, (size_t)c->max_batch * c->shape.n_heads * 4 * sizeof(int));
+    if (e == hipSuccess) e = hipMemset(c->acc_state, 0, (size_t)c->max_batch * ks::ACCEPT_STATE * sizeof(int));
     if (e == hipSuccess) {
         int dev = 0;
         hipDeviceProp_t prop;
@@ -537,7 +537,6 @@ koala_status koala_bind(koala_ctx *c, const koala_weights *w, const koala_kv *kv
         c->err = std::string("table upload failed: ") + hipGetErrorString(e);
         return KOALA_E_DEVICE;
     }
-    (void)T;
     c->bound = true;
     return KOALA_OK;
 }
@@ -780,7 +779,7 @@ static koala_status accept_sample_impl(koala_ctx *c, void *hip_stream, int batch
     }
     hipStream_t st = (hipStream_t)hip_stream;
     ks::accept_sample(st, c->tt, c->T, c->D, s.vocab, temperature, tree_tokens, target_logits, draft_logits,
-                      u_accept, u_resample, qv, dv, accept_len, accept_path, next_token, batch);
+                      u_accept, u_resample, qv, dv, c->acc_state, c->n_cu, accept_len, accept_path, next_token, batch);
     if (commit) {
         kg::kv_commit(st, s.dtype == KOALA_BF16, c->kv.target_k, c->kv.target_v, c->kv.ctx_len, accept_len,
                       accept_path, c->D, s.n_layers, c->max_batch, batch, s.n_heads, c->kv.capacity, s.head_dim);

@@ -33,7 +33,6 @@ struct TreeTables {
     int32_t *exp_index;               // [T] index among expanded non-root nodes, or -1
     uint64_t *draft_mask;             // [T] bit e: expanded non-root ancestor-or-self with index e
     int32_t *level_nodes;             // [D][64] expanded nodes of each depth (-1 padded)
-    int32_t *child_first, *child_count;  // unused by kernels that scan; kept for clarity
 };
 
 struct koala_ctx {
@@ -65,6 +64,7 @@ struct koala_ctx {
     int n_cu;                      // compute units of the device the context is bound on
     int attn_ns;                   // key splits of the attention kernels (fixed at create)
     float *med_logits;                                   // [D * max_batch][V] per-depth logits of Medusa-style heads (sampled drafting)
+    int *acc_state;                                      // [max_batch][ks::ACCEPT_STATE] zero between calls
     float *acc_q, *acc_d;                                // [max_batch][V] distributions of the stochastic acceptance walk (rows in memory)
     // bf16 path: GEMM input as fp16 MFMA fragments, and the split-K partial sums
     void *xf, *xf2;   // xf2: input of the down projection (written by the gate/up projection's epilogue)
@@ -187,6 +187,7 @@ void attention(hipStream_t st, const float *qrot, const RowMeta &meta, const voi
 // ---------------------------------------------------------------------------------------------
 namespace ks {
 
+enum { ACCEPT_STATE = 80 };   // whole numbers of state a sequence, see accept_sample
 int max_vocab();        // largest vocabulary the sampling kernels handle
 int register_vocab();   // and the largest whose rows they hold in registers: beyond, they need scratch
 
@@ -201,10 +202,11 @@ struct NodeList {
 void sample_children(hipStream_t st, const float *src, float *scratch, const NodeList &nodes, bool by_depth,
                      const TreeTables &tt, int T, int V, float temperature, const float *u_draw, int32_t *tree_tokens,
                      float *draft_logits, int batch);
+// state: [batch][ACCEPT_STATE], zero before the first call and zero again after each.  qv, dv: [batch][V], used for vocabularies above 32768.
 void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, float temperature,
                    const int32_t *tree_tokens, const float *target_logits, const float *draft_logits,
-                   const float *u_accept, const float *u_resample, float *qv, float *dv, int32_t *accept_len,
-                   int32_t *accept_path, int32_t *next_token, int batch);
+                   const float *u_accept, const float *u_resample, float *qv, float *dv, int *state, int n_cu,
+                   int32_t *accept_len, int32_t *accept_path, int32_t *next_token, int batch);
 
 }  // namespace ks
 

@@ -142,3 +142,59 @@ def test_grouped_heads(depth, batch):
         want = (x0 + y * torch.sigmoid(y)) @ lm.double().T
         err = (logits[:, j].double() - want).norm(dim=1) / want.norm(dim=1)
         assert err.max().item() < 2e-3, (j, err)
+
+
+@pytest.mark.parametrize("V, batch", [(100, 1), (100, 11), (300, 12), (4099, 40), (300, 186), (300, 187), (16385, 14)])
+def test_acceptance_of_a_batch_equals_that_of_its_sequences(V, batch):
+    """22 nodes a sequence, all at once in up to 4096 workgroups (186 sequences), the first 256 of which (11 sequences) look at
+    no other node's outcome, and in turn beyond.  Whichever way, the outcome of a sequence is its own, bit for bit, and a call
+    leaves nothing behind for the next."""
+    import torch
+    tree, temperature = make_tree([5, 3, 2], [1, 5, 9, 7]), 0.8
+    c, g, _, _ = _context(V, tree, batch)
+    T, D = tree.n_nodes, tree.depth
+    d = 3.0 * torch.randn(batch, T, V, generator=g, device="cuda")
+    q = d + 1.5 * torch.randn(batch, T, V, generator=g, device="cuda")
+    tok = torch.zeros(batch, T, dtype=torch.int32, device="cuda")
+    top = torch.topk(d, 5, dim=2).indices.to(torch.int32)
+    for i in range(1, T):
+        tok[:, i] = top[:, int(tree.parent[i]), int(tree.rank[i])]
+    ua, ur = (torch.rand(batch, 24, generator=g, device="cuda")[:, :T].contiguous() for _ in range(2))
+
+    def accept(q, d, tok, ua, ur):
+        n = tok.shape[0]
+        acc, path, nxt = (torch.full(s, -7, dtype=torch.int32, device="cuda") for s in ((n,), (n, D + 1), (n,)))
+        c.accept_sample(n, tok, q, d, ua, ur, temperature, acc, path, nxt, False)
+        return acc, path, nxt
+
+    whole = [accept(q, d, tok, ua, ur) for _ in range(3)]
+    for again in whole[1:]:
+        for x, y in zip(again, whole[0]):
+            assert torch.equal(x, y)
+    for b in range(min(batch, 40)):   # copies: rows of a batch of 22 nodes need not be 16-byte aligned
+        one = accept(*(x[b:b + 1].clone() for x in (q, d, tok, ua, ur)))
+        for x, y in zip(one, whole[0]):
+            assert torch.equal(x[0], y[b]), b
+    acc = whole[0][0]
+    if batch > 8:
+        assert int(acc.min()) == 0 and int(acc.max()) >= 2   # rejections at once, and paths
+
+
+def test_acceptance_along_a_chain_of_64_nodes():
+    """The deepest tree: equal logits accept every node (ratio 1 is above any uniform), a first uniform of 1 - 2^-24 beside a
+    draft that has its token too often rejects the first."""
+    import torch
+    V, tree = 300, chain_tree(63)
+    c, g, _, _ = _context(V, tree, 2)
+    T = tree.n_nodes
+    d = torch.randn(2, T, V, generator=g, device="cuda")
+    q = d.clone()
+    tok = torch.zeros(2, T, dtype=torch.int32, device="cuda")
+    tok[:, 1:] = d.argmax(2).to(torch.int32)[:, :-1]
+    q[1, 0, int(tok[1, 1])] -= 2.0
+    ua, ur = torch.full((2, T), 1 - 2.0 ** -24, device="cuda"), torch.full((2, T), 0.5, device="cuda")
+    ua[0] = 0.5
+    acc, path, nxt = (torch.zeros(s, dtype=torch.int32, device="cuda") for s in ((2,), (2, T), (2,)))
+    c.accept_sample(2, tok, q, d, ua, ur, 1.0, acc, path, nxt, False)
+    assert acc.tolist() == [63, 0]
+    assert path[0].tolist() == list(range(64)) and path[1].tolist() == [0] + [-1] * 63
