@@ -19,6 +19,8 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 struct __attribute__((packed, aligned(4))) f32x4_any { float x, y, z, w; };   // 16 bytes at a 4-byte aligned address
 struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
+typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;   // as vectors: loaded, kept and used as one
+typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 
 // ---------------------------------------------------------------------------------------------
 // fp32 products on the 16-bit matrix pipe: C[M,N] (+)= alpha * sum_k Q(m,k) P(n,k).
@@ -49,9 +51,8 @@ struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 // are off by up to 2^-125.
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  With part set the
 // split's sums go to part[split][M][N] for k_sum_parts, else to C.  ACC: C += alpha * sum, C fetched before the loop.
-// Measured, with the 64 x 64 fp32-MFMA kernel this replaced: 40 x 1024 from K = 32000 4063 -> 55 us (31 splits), 128 x 4096
-// from K = 32000 4396 -> 305 us (8 splits), 20 x 32000 from K = 4096 590 -> 145 us, 128 x 32000 816 -> 296 us, update of
-// 32000 x 4096 by 100 rows 662 us.  Splitting and LDS traffic bound the large ones.
+// The forward and backward products of all but the smallest matrices are k_stream_x3's (below); this form makes the updates
+// by many rows.  Measured: update of 32000 x 4096 by 100 rows 662 us.  Splitting and LDS traffic bound the large ones.
 // Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 132 us for the 20 rows above, by
 // themselves), two beyond (three spill: 54 -> 95 us for the 40 rows).
 // ---------------------------------------------------------------------------------------------
@@ -334,6 +335,298 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
 }
 
 // ---------------------------------------------------------------------------------------------
+// The same products for a weight matrix that streams past the activations, the forward and backward passes' form:
+// C[M,N] = sum_k Q(m,k) P(n,k), Q k-contiguous, P k-contiguous (KS false) or k-strided (KS true).
+//
+// Workgroup of eight waves on 128 n x up to 128 m (MT row tiles), K in stages of 64: waves 0..3 take the first 32 k of every
+// stage, waves 4..7 the others, each wave 32 n.  A weight goes from memory straight to the wave that multiplies with it: a
+// lane loads the eight k of a fragment lane (two 16-byte pieces of its row; KS: two neighbouring n of eight k) and cuts them
+// in registers, PF stages ahead.  The activations of a stage are loaded, cut and put into LDS by all threads, double-buffered
+// with one barrier a stage.  Waves 0..3 do their cutting at the start of a stage and waves 4..7 at its end, so that of the two
+// waves of a SIMD one has matrix work while the other cuts.  The two halves' sums meet in LDS.
+// k of fragment lane (i, g): element e < 4 is 4 g + e, the others 16 + 4 g + e - 4, so that the 16-byte pieces of the four
+// lanes of a row are 64 contiguous bytes.  The order of k within a fragment is free as long as both operands agree.
+// No load is conditional or bounded, so that the compiler can count those under way: a wave's n and the last stage's k are
+// moved back to where the matrix ends (columns that are another wave's are not stored, k that were another stage's are zero
+// in Q; where a weight there is infinite the tile is summed anew below), stages past the last re-read it.
+// grid: x = n tiles x m blocks, the m blocks of an n tile on one die, y = K splits.
+// N >= 32, K >= 64, ldp and ldq < 2^23 (32-bit offsets).
+// Measured against the form above (both operands through LDS): 20 x 32000 from K = 4096 147 -> 117 us (4.6 TB/s), 40 x 1024
+// from K = 32000 59 -> 40, 40 x 32000 from K = 1024 (KS) 61 -> 33, 128 x 32000 from K = 4096 300 -> 187 us (six products of pieces:
+// 1.08 PFLOP/s in bfloat16, about what a large product reaches here), 128 x 4096 from K = 32000 (KS) 306 -> 167.
+// The stream bounds up to 64 rows (without its MFMAs the kernel takes as long), the matrix pipe beyond.
+// ---------------------------------------------------------------------------------------------
+template <int MT, bool KS, bool KT>
+__global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q, long ldq,
+                                                      float *out, int M, int N, int K, int vec) {
+    constexpr int TN = 2, NQ = (MT + 1) / 2;                        // n tiles of a wave, rows of Q a thread
+    constexpr int PF = MT >= 6 ? 2 : MT == 2 ? 4 : 3, QF = MT >= 6 ? 1 : PF;   // stages of P and of Q under way
+    constexpr int PL = 2 * NQ * 64, ST = 2 * 3 * PL;                // 16-byte units of a plane of 32 k, of a stage
+    extern __shared__ __attribute__((aligned(16))) u32x4 x3s[];     // [2][ST]
+    __shared__ float tops[8];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15, lg = l >> 4;
+    const int kg = wave >> 2, wn = wave & 3;
+    const int nmb = (M + MT * 16 - 1) / (MT * 16), ntile = (N + 127) / 128;
+    const int die = blockIdx.x & 7, rnd = blockIdx.x >> 3;
+    const int nt = (rnd / nmb) * 8 + die, m0 = rnd % nmb * (MT * 16);
+    if (nt >= ntile) return;                                 // the grid is padded to whole rounds of eight
+    const int nown = nt * 128 + wn * 32, n0 = min(nown, N - 32);   // this wave's columns start at nown
+    const int nst = (K + 63) / 64, S = gridDim.y;
+    const int s0 = (int)((unsigned)(blockIdx.y * nst) / (unsigned)S), s1 = (int)((unsigned)((blockIdx.y + 1) * nst) / (unsigned)S);
+    // Stages are taken from a place that differs from workgroup to workgroup: all at the same k of rows a power of two apart
+    // would be after the same memory channels (20 x 32000 from K = 4096: 132 -> 121 us).
+    const int turn = (int)((unsigned)nt % (unsigned)(s1 - s0));
+    auto place = [&](int s) {
+        const int p = min(s, s1 - 1) + turn;
+        return p < s1 ? p : p - (s1 - s0);
+    };
+    auto first_k = [&](int p) { return KT ? min(p * 64, K - 64) : p * 64; };
+
+    // This lane's share of P: NT, rows 16 t + li, k 4 lg and 16 + 4 lg; KS, columns 2 li and 2 li + 1 of eight k.  Addresses
+    // are a scalar part, which says where in the matrix, and 32-bit byte offsets of the lane from there, worked out once.
+    auto at = [](const float *base, unsigned off) { return (const float *)((const char *)base + off); };
+    // an offset as the loads see it: were it known to be the same in every stage, it would be widened to 64 bits outside the
+    // loop, and kept and added that way
+    auto here = [](unsigned off) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(off));
+        return off;
+    };
+    const float *pn = P + (KS ? (long)n0 : (long)n0 * ldp);
+    unsigned poff[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+        poff[t] = 4u * (KS ? 4u * lg * (unsigned)ldp + 2u * li + t : (unsigned)(16 * t + li) * (unsigned)ldp + 4u * lg);
+    typedef std::conditional_t<KS, f32x2, f32x4> piece;   // KS: k number e of both columns; NT: four k of row tile t
+    constexpr int NP = KS ? 8 : 2 * TN;
+    piece pv[PF][NP];                                     // KS [e]; NT [t][half of the fragment]
+    auto load_p = [&](int s, auto slot) __attribute__((always_inline)) {
+        piece *d = pv[decltype(slot)::value];
+        const int k0 = first_k(place(s)) + kg * 32;
+        if constexpr (!KS) {
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                const unsigned off = here(poff[t]);
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) d[2 * t + hf] = *(const f32x4_a4 *)at(pn + k0 + 16 * hf, off);
+            }
+        } else {
+            const unsigned off = here(poff[0]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d[e] = *(const f32x2_a4 *)at(pn + (long)(k0 + (e < 4 ? e : 12 + e)) * ldp, off);
+        }
+    };
+    // this thread's share of Q: four k (quad kq of the stage) of rows qrow + 32 i
+    const int kq = tid & 15, qrow = tid >> 4;
+    const float *qm = Q + (long)m0 * ldq;
+    unsigned qoff[NQ];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) qoff[i] = 4u * ((unsigned)(min(m0 + qrow + 32 * i, M - 1) - m0) * (unsigned)ldq + 4u * kq);
+    f32x4 qv[QF][NQ];
+    auto load_q = [&](int s, auto slot) __attribute__((always_inline)) {
+        auto &d = qv[decltype(slot)::value];
+        const float *base = qm + first_k(place(s));
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) d[i] = *(const f32x4_a4 *)at(base, here(qoff[i]));
+    };
+    float ptop = 0.f, qtop = 0.f;   // largest magnitudes
+    // Lane (i, g) of a fragment lies in slot (i ^ swizzle) + 16 g of its 64: the 8-byte stores of 32 lanes (two rows, all g,
+    // both halves of the stage) fall into different banks, and so do the 16 lanes that a 16-byte read serves at a time
+    // (0..3, 12..15, 20..27 and so on).
+    auto swizzle = [](int g, int half) { return (4 * (-g & 3)) ^ (2 * half); };
+    unsigned char *const qdst = (unsigned char *)(x3s + (kq >> 3) * 3 * PL + (qrow >> 4) * 64 + ((qrow & 15) ^ swizzle(kq & 3, kq >> 3)) + 16 * (kq & 3)) + ((kq >> 2) & 1) * 8;
+    auto store_q = [&](int s, auto slot) __attribute__((always_inline)) {   // stage s into its buffer
+        auto &d = qv[decltype(slot)::value];
+        const int p = place(s), drop = p * 64 - first_k(p);   // k of the stage before, in the last stage
+        if (KT)
+#pragma unroll
+            for (int i = 0; i < NQ; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) d[i][e] = 4 * kq + e < drop ? 0.f : d[i][e];
+        unsigned char *base = qdst + ((s - s0) & 1) * (ST * 16);
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            uint32_t h[2], m[2], w[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) split3(d[i][2 * e], d[i][2 * e + 1], h[e], m[e], w[e], qtop);
+            unsigned char *dst = base + i * 2048;   // 32 rows on
+            *(u32x2 *)dst = (u32x2){h[0], h[1]};
+            *(u32x2 *)(dst + PL * 16) = (u32x2){m[0], m[1]};
+            *(u32x2 *)(dst + 2 * PL * 16) = (u32x2){w[0], w[1]};
+        }
+    };
+    u32x4 a[3][TN];
+    auto cut_p = [&](auto slot) __attribute__((always_inline)) {
+        const piece *d = pv[decltype(slot)::value];
+        auto value = [&](int t, int e) { if constexpr (KS) return d[e][t]; else return d[2 * t + (e >> 2)][e & 3]; };
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t h, m, w;
+                split3(value(t, 2 * e), value(t, 2 * e + 1), h, m, w, ptop);
+                a[0][t][e] = h; a[1][t][e] = m; a[2][t][e] = w;
+            }
+    };
+    // the products of the first pieces, and all the others
+    f32x4 acc[TN][MT], low[TN][MT];
+    const int frag = (li ^ swizzle(lg, kg)) + 16 * lg;
+    auto multiply = [&](int s) __attribute__((always_inline)) {
+        const u32x4 *base = x3s + ((s - s0) & 1) * ST + kg * 3 * PL + frag;
+        // fragments of Q in the order third, second, first piece of each row tile, three reads ahead of their products
+        auto read = [&](int f) { return base[(2 - f % 3) * PL + f / 3 * 64]; };
+        u32x4 b[4];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) b[f] = read(f);
+#pragma unroll
+        for (int f = 0; f < 3 * MT; ++f) {
+            const int pq = 2 - f % 3, j = f / 3;
+            if (f + 3 < 3 * MT) b[(f + 3) & 3] = read(f + 3);
+#pragma unroll
+            for (int pp = 2 - pq; pp >= 0; --pp)
+#pragma unroll
+                for (int t = 0; t < TN; ++t) {
+                    f32x4 &sum = pq + pp == 0 ? acc[t][j] : low[t][j];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[pp][t]), __builtin_bit_cast(bf16x8, b[f & 3]), sum, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto meet = [&]() __attribute__((always_inline)) {
+        // a bare barrier behind this wave's LDS accesses: the fence of __syncthreads would wait for the loads too
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    // Memory answers in order: a wait for Q is one for every older load of P, so Q is requested first and as far ahead.  The
+    // two halves of the workgroup have loops of their own: the compiler counts the loads under way along every path it sees,
+    // and waits for as many as the shortest one leaves.
+    using std::integral_constant;
+    auto stage = [&](int s, auto slot, auto half) __attribute__((always_inline)) {
+        constexpr int B = decltype(slot)::value, KG = decltype(half)::value;
+        constexpr integral_constant<int, (B + KG) % PF> pslot{};
+        constexpr integral_constant<int, (B + 1) % QF> qslot{};
+        if (KG == 1) multiply(s);
+        __builtin_amdgcn_sched_barrier(0);
+        cut_p(pslot);
+        store_q(s + 1, qslot);
+        __builtin_amdgcn_sched_barrier(0);   // what is loaded next takes the registers of what has been cut
+        load_q(s + 1 + QF, qslot);
+        __builtin_amdgcn_sched_barrier(0);
+        load_p(s + KG + PF, pslot);
+        __builtin_amdgcn_sched_barrier(0);
+        if (KG == 0) multiply(s);
+        meet();
+    };
+    auto sum_up = [&](auto half) __attribute__((always_inline)) {
+        load_q(s0, integral_constant<int, 0>{});
+        load_p(s0, integral_constant<int, 0>{});
+        if constexpr (QF > 1) load_q(s0 + 1, integral_constant<int, 1 % QF>{});
+        load_p(s0 + 1, integral_constant<int, 1>{});
+        if constexpr (QF > 2) load_q(s0 + 2, integral_constant<int, 2 % QF>{});
+        if constexpr (PF > 2) load_p(s0 + 2, integral_constant<int, 2 % PF>{});
+        if constexpr (QF > 3) load_q(s0 + 3, integral_constant<int, 3 % QF>{});
+        if constexpr (PF > 3) load_p(s0 + 3, integral_constant<int, 3 % PF>{});
+        store_q(s0, integral_constant<int, 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+        load_q(s0 + QF, integral_constant<int, 0>{});
+        if (decltype(half)::value == 1) {
+            cut_p(integral_constant<int, 0>{});
+            __builtin_amdgcn_sched_barrier(0);
+            load_p(s0 + PF, integral_constant<int, 0>{});
+        }
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) acc[t][j] = low[t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        meet();
+        int s = s0;
+        for (; s + PF <= s1; s += PF) {
+            stage(s, integral_constant<int, 0>{}, half);
+            stage(s + 1, integral_constant<int, 1>{}, half);
+            if constexpr (PF > 2) stage(s + 2, integral_constant<int, 2>{}, half);
+            if constexpr (PF > 3) stage(s + 3, integral_constant<int, 3>{}, half);
+        }
+        if (s < s1) stage(s, integral_constant<int, 0>{}, half);
+        if constexpr (PF > 2)
+            if (s + 1 < s1) stage(s + 1, integral_constant<int, 1>{}, half);
+        if constexpr (PF > 3)
+            if (s + 2 < s1) stage(s + 2, integral_constant<int, 2>{}, half);
+    };
+    if (kg == 0) sum_up(integral_constant<int, 0>{});
+    else sum_up(integral_constant<int, 1>{});
+    // the lane's place once more: nothing of it is kept in registers over the loop
+    int tid2 = threadIdx.x;
+    asm volatile("" : "+v"(tid2));
+    const int li2 = tid2 & 15, lg2 = (tid2 & 63) >> 4;
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
+                acc[t][j][r] += fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f;
+    // the largest magnitudes of Q's rows and of this wave's share of P
+    for (int o = 32; o > 0; o >>= 1) { ptop = fmaxf(ptop, __shfl_xor(ptop, o)); qtop = fmaxf(qtop, __shfl_xor(qtop, o)); }
+    if ((tid2 & 63) == 0) tops[wave] = qtop;
+    __syncthreads();
+    qtop = tops[0];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) qtop = fmaxf(qtop, tops[w]);
+    if (!pieces_hold(ptop) || !pieces_hold(qtop)) {
+        // this wave's k once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds k = g of row i), four k a step
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) acc[t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int q = s0 * 8; q < s1 * 8; ++q) {
+            const int k = first_k(q >> 3) + kg * 32 + (q & 7) * 4 + lg2;
+            float pe[TN];
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                const long n = n0 + (KS ? 2 * li2 + t : 16 * t + li2);
+                const float x = P[KS ? k * ldp + n : n * ldp + k];
+                pe[t] = KT && k < (q >> 3) * 64 ? 0.f : x;   // a k of the stage before
+            }
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                const float x = Q[(long)min(m0 + j * 16 + li2, M - 1) * ldq + k], qe = KT && k < (q >> 3) * 64 ? 0.f : x;
+#pragma unroll
+                for (int t = 0; t < TN; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(pe[t], qe, acc[t][j], 0, 0, 0);
+            }
+        }
+    }
+    // waves 4..7 hand their sums to waves 0..3
+    f32x4 *red = (f32x4 *)x3s + (size_t)wn * TN * MT * 64 + (tid2 & 63);
+    if (kg == 1)
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) red[(t * MT + j) * 64] = acc[t][j];
+    __syncthreads();
+    if (kg == 1) return;
+    out += (long)blockIdx.y * M * N;
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+        const int m = m0 + j * 16 + li2;
+        if (m >= M) continue;
+        f32x4 v[TN];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) v[t] = acc[t][j] + red[(t * MT + j) * 64];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+            // NT: tile t, four n from 4 lg2; KS: the two tiles take turns, four n from 8 lg2 + 4 t
+            const int n = n0 + (KS ? 8 * lg2 + 4 * t : 16 * t + 4 * lg2);
+            const f32x4 x = KS ? (f32x4){v[0][2 * t], v[1][2 * t], v[0][2 * t + 1], v[1][2 * t + 1]} : v[t];
+            float *o = out + (long)m * N + n;
+            if (vec && n >= nown) *(f32x4 *)o = x;
+            else
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (n + r >= nown) o[r] = x[r];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Weight update by few rows: W[M,N] += alpha * sum_r G[r,M] X[r,N], r < rows <= KP, plain fp32 multiply-adds in row order.
 // Bound by reading and writing W once (32000 x 4096 by 20 rows: 1.05 GB).  A wave streams rows of W in pieces of 64 NV
 // columns (1 KiB or 512 B, PF of them under way) and holds its columns of X in registers; a workgroup's four waves take the
@@ -412,15 +705,23 @@ __global__ __launch_bounds__(256) void k_update_rows(const float *__restrict__ G
     }
 }
 
-// How many K splits give about as many workgroups as the compute units hold (two each, four up to 32 rows), at least four
-// chunks each, and fit `room` floats of partial sums (none: one split, straight into C)
+// row tiles of a workgroup of k_stream_x3: those of all rows, or of equal blocks of up to eight
+int x3_tiles(int M) {
+    const int tiles = (M + 15) / 16, nmb = (tiles + 7) / 8, mt = (tiles + nmb - 1) / nmb;
+    return mt <= 2 ? 2 : mt <= 4 ? mt : mt <= 6 ? 6 : 8;
+}
+// K splits that take the least time, with partial sums that fit `room` floats (none: one split, straight into C).  In units
+// of a stage: rounds of workgroups on the chip's compute units, a start and an end of a workgroup (about four stages), the
+// partial sums written and read (1 MB each way is about a third of a stage).
 int x3_splits(int M, int N, int K, size_t room) {
-    const long bm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
-    const long tiles = (long)((N + X3_BN - 1) / X3_BN) * ((M + bm - 1) / bm), nch = (K + X3_BK - 1) / X3_BK;
-    const long want = bm == 32 ? 1024 : 512;
-    long S = tiles >= want * 3 / 4 ? 1 : (want + tiles / 2) / tiles;
-    S = std::min({S, nch / 4, (long)(room / ((size_t)M * N)), 32L});
-    return S < 2 ? 1 : (int)S;
+    const long mt = x3_tiles(M), tiles = (long)((N + 127) / 128) * ((M + 16 * mt - 1) / (16 * mt)), nst = (K + 63) / 64;
+    double best = 1e300;
+    int S = 1;
+    for (int s = 1; s <= 32 && (s == 1 || (s * 2 <= nst && (size_t)s * M * N <= room)); ++s) {
+        const double t = (double)((tiles * s + 255) / 256) * ((nst + s - 1) / s + 4) + (s > 1 ? 0.66 * s * M * N * 4.0 / 1e6 : 0.0);
+        if (t < best) { best = t; S = s; }
+    }
+    return S;
 }
 
 template <int BM, bool PKS, bool QKS, bool ACC>
@@ -442,13 +743,40 @@ void gemm_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq,
     else if (M <= 64) launch_x3<64, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
     else launch_x3<128, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
 }
-// C[M,N] = X[M,K] W[N,K]^T, split sums to part (S > 1) or straight to C
-void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
-    gemm_x3<false, false, false>(st, W, K, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
+template <int MT, bool KS, bool KT>
+void launch_stream(hipStream_t st, const float *P, long ldp, const float *X, float *out, int S, int M, int N, int K) {
+    constexpr size_t sm = (size_t)2 * 2 * 3 * ((MT + 1) / 2 * 2) * 1024;
+    static OncePerDevice once;
+    allow_lds(once, (const void *)k_stream_x3<MT, KS, KT>, sm);
+    const int vec = N % 4 == 0 && ((uintptr_t)out & 15) == 0;
+    const dim3 grid(((N + 127) / 128 + 7) / 8 * 8 * ((M + MT * 16 - 1) / (MT * 16)), S);
+    k_stream_x3<MT, KS, KT><<<grid, 512, sm, st>>>(P, ldp, X, K, out, M, N, K, vec);
 }
-// C[M,N] = X[M,K] W[K,N]
+// C[M,N] = X[M,K] P, P(k, n) = W[n,K] or (KS) W[K,n]; split sums to part (S > 1) or straight to C
+template <bool KS>
+void gemm_weights(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
+    const long ldp = KS ? N : K;
+    // What k_stream_x3 does not take, and workgroups of up to four stages, which are over before its loads ahead are worth
+    // their start (a head step of 10 rows at 512 x 4000: 125 us all streamed, 115 so; discriminator step of 4 rows 81 and 75;
+    // of 290 rows at 512 x 32000 805 and 785; up to eight stages: 90 rows at 512 x 32000 377 and 412 us).
+    if (N < 32 || K < 64 || N >= 1 << 23 || K >= 1 << 23 || (K + 63) / 64 <= 4 * S)
+        return gemm_x3<KS, false, false>(st, W, ldp, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
+    float *out = S > 1 ? part : C;
+#define KOALA_STREAM(MT) return K % 64 ? launch_stream<MT, KS, true>(st, W, ldp, X, out, S, M, N, K) : launch_stream<MT, KS, false>(st, W, ldp, X, out, S, M, N, K)
+    switch (x3_tiles(M)) {
+        case 2: KOALA_STREAM(2);
+        case 3: KOALA_STREAM(3);
+        case 4: KOALA_STREAM(4);
+        case 6: KOALA_STREAM(6);
+        default: KOALA_STREAM(8);
+    }
+#undef KOALA_STREAM
+}
+void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
+    gemm_weights<false>(st, X, W, C, part, S, M, N, K);
+}
 void gemm_nn(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
-    gemm_x3<true, false, false>(st, W, N, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
+    gemm_weights<true>(st, X, W, C, part, S, M, N, K);
 }
 template <int KP, int NV>
 void launch_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float alpha) {
@@ -734,8 +1062,7 @@ inline int fc_in(const koala_disc_shape &s, int k) { return k == 0 ? s.vocab : s
 inline int fc_out(const koala_disc_shape &s, int k) { return k == s.n_fc - 1 ? 1 : s.fc_hidden; }
 
 // z = h W_lin^T joined to one or two sets of logits rows.  Where its tiles do not fill the chip, two K splits, whose sums lie
-// where u will (4000 x 4096: 80 -> 43 us at 20 rows, 108 -> 58 at 64; 12345 x 4096: 81 -> 58 and 110 -> 85; 32000 x 4096 at 20
-// rows 156 -> 147 us within a step).  At 64 rows 32000 x 4096 fills it: 184 us with one split and 189 with two, join included.
+// where u will.
 void disc_join(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, const float *h,
                const float *la, const float *lb) {
     const long nV = (long)n * s.vocab;

@@ -90,6 +90,27 @@ def test_sums_are_as_exact_as_fp32_chains(form, terms, scale):
     assert _rel(got, want) < 1.15 * 2.53e-8 * np.sqrt((terms + 1) / 2)
 
 
+@pytest.mark.parametrize("n,V,H", [(1, 32, 64), (32, 31, 64), (33, 33, 63), (48, 127, 65), (49, 128, 127), (64, 129, 128), (65, 160, 192),
+                                   (96, 161, 193), (97, 64, 320), (128, 65, 1000), (129, 1000, 96), (200, 515, 449), (20, 4099, 640)])
+def test_products_at_the_edges_of_a_streamed_tile(n, V, H):
+    """d = h w_lm^T and g w_lm, set up and bounded as above, where V and H are both the length of the sums and the number of
+    columns: a wave's 32 columns and a stage's 64 terms that the matrix does not fill, one row tile up to eight, several
+    blocks of them, fewer columns or terms than a wave or a stage."""
+    import torch
+    import paper_2408_08146_amd as KO
+    rng = np.random.default_rng(n + V + H)
+    f32 = lambda *s: rng.normal(size=s).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    h, g, w_lm = f32(n, H), f32(n, V), f32(V, H)
+    bound = lambda terms: 1.15 * 2.53e-8 * np.sqrt((terms + 1) / 2)
+    got, w = torch.zeros(n, V, device="cuda"), dev(np.zeros((H, H)))
+    KO.MedusaHeadTrainer([w], dev(w_lm)).forward(dev(h), got)
+    assert _rel(got, h.astype(np.float64) @ w_lm.T.astype(np.float64)) < bound(H)
+    m = min(n, H)
+    KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(np.eye(n, H)), dev(g), 2.0)   # W = -(g w_lm)^T / 2 * 2 [identity]
+    assert _rel(-w.T[:m], g[:m].astype(np.float64) @ w_lm.astype(np.float64)) < bound(V)
+
+
 def test_head_with_the_smallest_workspace():
     """A workspace without room for split sums is accepted (one byte less is not) and gives the same results to rounding."""
     import torch
