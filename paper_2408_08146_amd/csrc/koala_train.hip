@@ -23,7 +23,7 @@ typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;   // as 
 typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 
 // ---------------------------------------------------------------------------------------------
-// fp32 products on the 16-bit matrix pipe: C[M,N] (+)= alpha * sum_k Q(m,k) P(n,k).
+// fp32 products on the 16-bit matrix pipe: C[M,N] = sum_k Q(m,k) P(n,k).
 //
 // A float is the exact sum of three bfloat16 values (round to nearest, subtract, twice: the rest has 16, then eight
 // significant bits, so every subtraction and the last piece are exact), so a product of two floats is the sum of nine
@@ -40,9 +40,9 @@ typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 // registers (two chunks ahead, so that about 50 KB a compute unit are under way), are cut into their three planes there
 // and put into LDS as MFMA fragments, double-buffered with one barrier a chunk.  P is the MFMA's row operand: a lane then
 // holds four consecutive n of one m, a 16-byte piece of a row of C.
-//   operand k-contiguous (KS false): element (i, k) at i * ld + k;  8 threads x 16 B cover 128 B of a row
-//   operand k-strided    (KS true):  element (i, k) at k * ld + i;  a thread takes 8 consecutive k of one or two i, the
-//                                    eight values of a fragment lane
+//   k-contiguous (KS false; Q is): element (i, k) at i * ld + k;  8 threads x 16 B cover 128 B of a row
+//   k-strided    (KS true):        element (i, k) at k * ld + i;  a thread takes 8 consecutive k of one or two i, the
+//                                  eight values of a fragment lane
 // LDS plane of a 16-row tile: 64 slots of 16 B, lane (i, g = k/8) in slot (i ^ 4 g) + 16 g: the 8-byte stores of 32 lanes of
 // the k-contiguous form (four rows, all g) then fall into different banks.
 // Rows past the end re-read the last one (never stored); k past the end is zero in both operands.  Where pieces do not stand
@@ -50,9 +50,8 @@ typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 // summed again on the fp32 pipe, so that it comes out as it does there.  Values below 2^-102 beside larger ones
 // are off by up to 2^-125.
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  With part set the
-// split's sums go to part[split][M][N] for k_sum_parts, else to C.  ACC: C += alpha * sum, C fetched before the loop.
-// The forward and backward products of all but the smallest matrices are k_stream_x3's (below); this form makes the updates
-// by many rows.  Measured: update of 32000 x 4096 by 100 rows 662 us.  Splitting and LDS traffic bound the large ones.
+// split's sums go to part[split][M][N] for k_sum_parts, else to C.
+// The products of all but the smallest matrices are k_stream_x3's, the updates k_update_x3's (both below).
 // Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 132 us for the 20 rows above, by
 // themselves), two beyond (three spill: 54 -> 95 us for the 40 rows).
 // ---------------------------------------------------------------------------------------------
@@ -163,10 +162,10 @@ struct X3Loader {
     }
 };
 
-template <int BM, bool PKS, bool QKS, bool ACC, int DEPTH>
+template <int BM, bool PKS, int DEPTH>
 __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q,
                                                     long ldq, float *C, long ldc, float *part, int M, int N, int K,
-                                                    float alpha, int vec) {
+                                                    int vec) {
     constexpr int WN = BM == 32 ? 4 : 2, WM = 4 / WN;        // waves along n and m
     constexpr int TN = X3_BN / 16 / WN, TM = BM / 16 / WM;   // accumulator tiles of a wave
     constexpr int PU = 3 * (X3_BN / 16) * 64, QU = 3 * (BM / 16) * 64;   // 16-byte units of a chunk's planes
@@ -181,12 +180,12 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
     const int nch = (K + X3_BK - 1) / X3_BK, S = gridDim.y;
     const int c0 = (int)((unsigned)(blockIdx.y * nch) / (unsigned)S), c1 = (int)((unsigned)((blockIdx.y + 1) * nch) / (unsigned)S);
     X3Loader<X3_BN, PKS, DEPTH> lp;
-    X3Loader<BM, QKS, DEPTH> lq;
+    X3Loader<BM, false, DEPTH> lq;
     lp.init(P, ldp, N, n0, K);
     lq.init(Q, ldq, M, m0, K);
     // the products of the first pieces, and all the others, which are 2^-8 of them: small as they are, the second sum's
     // roundings are lost in the first one's, which is rounded once a chunk
-    f32x4 acc[TN][TM], low[TN][TM], old[ACC ? TN : 1][ACC ? TM : 1];
+    f32x4 acc[TN][TM], low[TN][TM];
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
@@ -200,23 +199,6 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
     if constexpr (DEPTH == 4) {
         fetch(c0 + 2, std::integral_constant<int, 2>{});
         fetch(c0 + 3, std::integral_constant<int, 3>{});
-    }
-    if (ACC) {
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-            for (int j = 0; j < TM; ++j) {
-                const int m = m0 + (wm * TM + j) * 16 + li, n = n0 + (wn * TN + i) * 16 + 4 * lg;
-                const float *c = C + (long)m * ldc + n;
-                old[ACC ? i : 0][ACC ? j : 0] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                if (m < M) {
-                    if (vec && n + 4 <= N) old[ACC ? i : 0][ACC ? j : 0] = *(const f32x4 *)c;
-                    else
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (n + r < N) old[ACC ? i : 0][ACC ? j : 0][r] = c[r];
-                }
-            }
     }
     const int slot = (li ^ (4 * lg)) + 16 * lg;
     float ptop = 0.f, qtop = 0.f;   // largest magnitudes
@@ -302,7 +284,7 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
 #pragma unroll
                 for (int j = 0; j < TM; ++j) {
                     const long m = min(m0 + (wm * TM + j) * 16 + li, M - 1);
-                    const float x = Q[QKS ? kc * ldq + m : m * ldq + kc];
+                    const float x = Q[m * ldq + kc];
                     qv[e][j] = k < kend ? x : 0.f;
                 }
             }
@@ -323,8 +305,7 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
         for (int j = 0; j < TM; ++j) {
             const int m = m0 + (wm * TM + j) * 16 + li, n = n0 + (wn * TN + i) * 16 + 4 * lg;
             if (m >= M) continue;
-            f32x4 v = acc[i][j] * alpha;
-            if (ACC) v += old[ACC ? i : 0][ACC ? j : 0];
+            const f32x4 v = acc[i][j];
             float *o = out + (long)m * ldo + n;
             if (vec && n + 4 <= N) *(f32x4 *)o = v;
             else
@@ -627,81 +608,234 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Weight update by few rows: W[M,N] += alpha * sum_r G[r,M] X[r,N], r < rows <= KP, plain fp32 multiply-adds in row order.
-// Bound by reading and writing W once (32000 x 4096 by 20 rows: 1.05 GB).  A wave streams rows of W in pieces of 64 NV
-// columns (1 KiB or 512 B, PF of them under way) and holds its columns of X in registers; a workgroup's four waves take the
-// rows of its panel in turn and share the panel of G, transposed, in LDS, where a row's KP factors are broadcast reads.
-// Measured, 32000 x 4096 by 20 rows: 219 us (4.8 TB/s), k_gemm_x3 329 to 354, the fp32-MFMA kernel before that 326; 1024 x 32000 by
-// 40 rows: 75 us, k_gemm_x3 88 to 94.
-// grid: x = column blocks, y = panels of mr rows.
+// Weight update: W[M,N] += alpha * sum_r G[r,M] X[r,N], both operands k-strided, with k_gemm_x3's pieces and accumulators.
+// Bound by reading and writing W once up to about 150 rows, by the matrix pipe and the cutting beyond.  Workgroup of four
+// waves on 64 m x 128 n (rows of 512 B), 64 m x 32 n a wave.  G is cut for the whole tile, 128 r at a time, and shared through
+// LDS; a wave's columns of X are its own and go from memory straight into matrix operands, cut in registers, a chunk of 32 r
+// ahead.  The sums go through LDS, so that W is read and written in whole rows of the tile; it is requested before the last
+// chunk's products (FEW, up to 32 rows: with the operands).  Registers and LDS for three workgroups a compute unit: one's
+// products and cutting run beside the others' memory.  Tiles go by rows of W, and each die has an eighth of them that is
+// contiguous in memory.
+// Measured, 32000 x 4096 by 20 rows: 188 us (5.6 TB/s), a kernel of plain multiply-adds with the rows of W dealt to all dies
+// 227; by 60 rows 222, both operands through LDS and W in pieces of 256 B 478; by 300 rows 615 and 1446; 4096 x 4096 by 128
+// rows 41 and 90; 1024 x 32000 by 40 rows 65 and 84; 4000 x 1000 by 4 rows 9.6 and 9.3.  Two workgroups a compute unit
+// with X two chunks ahead: 277 us at 32000 x 4096 by 60 rows, 49 at 4096 x 4096 by 128.
 // ---------------------------------------------------------------------------------------------
-enum { UPD_MR = 128 };
-template <int KP, int NV>
-__global__ __launch_bounds__(256) void k_update_rows(const float *__restrict__ G, const float *__restrict__ X, float *W, int M,
-                                                     int N, int rows, int mr, float alpha) {
-    struct __attribute__((packed, aligned(4))) piece { float v[NV]; };
-    constexpr int PF = 8;
-    __shared__ f32x4 gs[UPD_MR][KP / 4];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int m0 = blockIdx.y * mr, n = (blockIdx.x * 64 + l) * NV, cnt = N - n;   // columns of this lane: NV, or cnt of them
-    for (int i = threadIdx.x; i < mr * KP; i += 256) {
-        const int m = i % mr, r = i / mr;
-        ((float *)gs[m])[r] = r < rows && m0 + m < M ? G[(size_t)r * M + m0 + m] : 0.f;
-    }
-    auto load = [&](const float *p) {
-        piece w;
-        if (cnt >= NV) {
-            w = *(const piece *)p;
-        } else {
+template <bool FEW>
+__global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ G, const float *__restrict__ X, float *W, int M,
+                                                      int N, int rows, float alpha) {
+    constexpr int BM = 64, BN = 128, TM = BM / 16, TN = 2, PL = TM * 64, LDO = BN + 4, NC = FEW ? 1 : 4;
+    __shared__ u32x4 gs[FEW ? BM * LDO / 4 : NC * 3 * PL];   // [chunk][plane][m tile][64 lanes]; then the sums [BM][LDO]
+    __shared__ float tops[4];
+    static_assert(BM * LDO * 4 <= (int)sizeof(gs), "the sums fit where the pieces were");
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15, lg = l >> 4;
+    const int ntn = (N + BN - 1) / BN, ntm = (M + BM - 1) / BM;
+    const int tile = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (tile >= ntn * ntm) return;
+    const int m0 = tile / ntn * BM, n0 = tile % ntn * BN;
+    // G: this thread's column, r = 8 wave + 0..7 of each 32; X: the columns nx and nx + 1, r = 8 lg + 0..7 of each 32.  Columns
+    // past the end are the last ones again (their sums are not stored): where nx is the last column of all, the pair's second.
+    const unsigned goff = 4u * (unsigned)min(l, M - 1 - m0);
+    const int nx = n0 + wave * 32 + 2 * li, nl = max(min(nx, N - 2), 0);
+    const bool edge = n0 + BN > N, whole = !edge && m0 + BM <= M, second = nx > nl;
+    f32x2 xv[8];
+    float gtop = 0.f, xtop = 0.f;   // largest magnitudes
+    auto load_x = [&](int r0) __attribute__((always_inline)) {
+        if (r0 + 32 <= rows && N > 1 && N < 1 << 25) {
+            unsigned off = 4u * (8u * lg * (unsigned)N + nl);
+            asm volatile("" : "+v"(off));   // else widened to 64 bits ahead of the loop, once for every load
 #pragma unroll
-            for (int e = 0; e < NV; ++e) w.v[e] = e < cnt ? p[e] : 0.f;
+            for (int e = 0; e < 8; ++e) xv[e] = *(const f32x2_a4 *)((const char *)(X + (size_t)(r0 + e) * N) + off);
+        } else {                    // rows past the last: the last, times zeros of G
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                int r = 8 * lg + e;
+                asm volatile("" : "+v"(r));
+                const float *p = X + nl + (size_t)min(r0 + r, rows - 1) * N;
+                xv[e] = (f32x2){p[0], p[N > 1]};
+            }
         }
-        return w;
     };
-    piece x[KP], w[PF];
+    u32x4 a[3][TN];
+    auto cut_x = [&]() __attribute__((always_inline)) {
+        if (edge)
 #pragma unroll
-    for (int r = 0; r < KP; ++r) {
-        if (r < rows) x[r] = load(X + (size_t)r * N + n);
+            for (int e = 0; e < 8; ++e) xv[e].x = second ? xv[e].y : xv[e].x;
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t h, m, w;
+                split3(xv[2 * e][t], xv[2 * e + 1][t], h, m, w, xtop);
+                a[0][t][e] = h; a[1][t][e] = m; a[2][t][e] = w;
+            }
+    };
+    // the products of the first pieces, and all the others
+    f32x4 acc[TN][TM], low[TN][TM];
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[t][j] = low[t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int c) __attribute__((always_inline)) {
+        const u32x4 *base = gs + c * 3 * PL + l;
+        auto read = [&](int f) { return base[(2 - f % 3) * PL + f / 3 * 64]; };
+        u32x4 b[4];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) b[f] = read(f);
+#pragma unroll
+        for (int f = 0; f < 3 * TM; ++f) {
+            const int pq = 2 - f % 3, j = f / 3;
+            if (f + 3 < 3 * TM) b[(f + 3) & 3] = read(f + 3);
+#pragma unroll
+            for (int pp = 2 - pq; pp >= 0; --pp)
+#pragma unroll
+                for (int t = 0; t < TN; ++t) {
+                    f32x4 &sum = pq + pp == 0 ? acc[t][j] : low[t][j];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[pp][t]), __builtin_bit_cast(bf16x8, b[f & 3]), sum, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // what this thread stores: four columns of rows (thread / 32) + 8 i; worked out where it is used, not kept over the loop
+    struct Mine { float *p; int row, col, cnt; };
+    auto mine = [&]() __attribute__((always_inline)) {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        const int row = t >> 5, col = (t & 31) * 4;
+        return Mine{W + (size_t)(m0 + row) * N + n0 + col, row, col, N - n0 - col};
+    };
+    f32x4 old[8];
+    auto load_old = [&]() __attribute__((always_inline)) {
+        const Mine w = mine();
+        if (whole) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) old[i] = *(const f32x4_a4 *)(w.p + (size_t)(8 * i) * N);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            old[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (m0 + w.row + 8 * i >= M) continue;
+            const float *p = w.p + (size_t)(8 * i) * N;
+            if (w.cnt >= 4) old[i] = *(const f32x4_a4 *)p;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < w.cnt) old[i][e] = p[e];
+        }
+    };
+    load_x(0);
+    int rb = 0, nck;
+    while (true) {
+        nck = FEW ? 1 : min((rows - rb + 31) / 32, 4);
+        float gv[NC][8];
+#pragma unroll
+        for (int i = 0; i < NC; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                gv[i][e] = *(const float *)((const char *)(G + m0 + (size_t)min(rb + 32 * i + 8 * wave + e, rows - 1) * M) + goff);
+        if (FEW) load_old();
+        if (!FEW && rb) __syncthreads();   // the pieces of the rows before have been read
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NC; ++i)
+            if (i < nck) {
+                u32x4 h, m, w;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (rb + 32 * i + 8 * wave + e >= rows) gv[i][e] = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t p, q, r;
+                    split3(gv[i][2 * e], gv[i][2 * e + 1], p, q, r, gtop);
+                    h[e] = p; m[e] = q; w[e] = r;
+                }
+                u32x4 *dst = gs + i * 3 * PL + (l >> 4) * 64 + 16 * wave + li;
+                dst[0] = h; dst[PL] = m; dst[2 * PL] = w;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        // a bare barrier behind this wave's LDS writes: the fence of __syncthreads would wait for the loads too
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (FEW) break;
+#pragma unroll 1
+        for (int c = 0; c + 1 < nck; ++c) {
+            cut_x();
+            __builtin_amdgcn_sched_barrier(0);
+            load_x(rb + 32 * (c + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(c);
+        }
+        if (rb + 128 >= rows) break;
+        cut_x();
+        rb += 128;
+        load_x(rb);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(3);
+    }
+    cut_x();
+    __builtin_amdgcn_sched_barrier(0);
+    if (!FEW) load_old();
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(nck - 1);
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
+                acc[t][j][r] += fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f;
+    // the largest magnitudes of G's columns and of this wave's columns of X
+    for (int o = 32; o > 0; o >>= 1) { gtop = fmaxf(gtop, __shfl_xor(gtop, o)); xtop = fmaxf(xtop, __shfl_xor(xtop, o)); }
+    if (l == 0) tops[wave] = gtop;
+    __syncthreads();
+    gtop = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
+    if (!pieces_hold(gtop) || !pieces_hold(xtop)) {
+        // once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds r = g of column i), four r a step
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[t][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int r0 = 0; r0 < rows; r0 += 4) {
+            const int r = r0 + lg;
+            const size_t rc = min(r, rows - 1);
+            f32x2 xe = {X[rc * N + nl], X[rc * N + nl + (N > 1)]};
+            if (second) xe.x = xe.y;
+            if (r >= rows) xe = (f32x2){0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < TM; ++j) {
+                const float x = G[rc * M + min(m0 + 16 * j + li, M - 1)], ge = r < rows ? x : 0.f;
+#pragma unroll
+                for (int t = 0; t < TN; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xe[t], ge, acc[t][j], 0, 0, 0);
+            }
+        }
+    }
+    // a lane's two tiles are eight consecutive columns of row 16 j + li
+    float *os = (float *)gs;
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+        float *o = os + (16 * j + li) * LDO + 32 * wave + 8 * lg;
+        *(f32x4 *)o = (f32x4){acc[0][j][0], acc[1][j][0], acc[0][j][1], acc[1][j][1]};
+        *(f32x4 *)(o + 4) = (f32x4){acc[0][j][2], acc[1][j][2], acc[0][j][3], acc[1][j][3]};
+    }
+    __syncthreads();
+    const Mine w = mine();
+    if (whole) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            *(f32x4_a4 *)(w.p + (size_t)(8 * i) * N) = old[i] + alpha * *(const f32x4 *)(os + (w.row + 8 * i) * LDO + w.col);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (m0 + w.row + 8 * i >= M) continue;
+        const f32x4 sum = *(const f32x4 *)(os + (w.row + 8 * i) * LDO + w.col), v = old[i] + alpha * sum;
+        float *p = w.p + (size_t)(8 * i) * N;
+        if (w.cnt >= 4) *(f32x4_a4 *)p = v;
         else
 #pragma unroll
-            for (int e = 0; e < NV; ++e) x[r].v[e] = 0.f;
-    }
-    // rows m0 + wave, + 4, ..
-    const int nrow = (min(mr, M - m0) - wave + 3) / 4;
-    float *row = W + (size_t)(m0 + wave) * N + n;
-    const size_t step = (size_t)4 * N;
-#pragma unroll
-    for (int p = 0; p < PF; ++p)
-        if (p < nrow) w[p] = load(row + p * step);
-    __syncthreads();
-    for (int i = 0; i < nrow; i += PF) {
-#pragma unroll
-        for (int p = 0; p < PF; ++p) {
-            if (i + p >= nrow) continue;
-            const piece old = w[p];
-            float *o = row + (size_t)(i + p) * step;
-            if (i + p + PF < nrow) w[p] = load(o + PF * step);
-            piece t;
-#pragma unroll
-            for (int e = 0; e < NV; ++e) t.v[e] = 0.f;
-#pragma unroll
-            for (int q = 0; q < KP / 4; ++q) {
-                const f32x4 g = gs[wave + 4 * (i + p)][q];
-#pragma unroll
-                for (int z = 0; z < 4; ++z)
-#pragma unroll
-                    for (int e = 0; e < NV; ++e) t.v[e] = fmaf(g[z], x[4 * q + z].v[e], t.v[e]);
-            }
-#pragma unroll
-            for (int e = 0; e < NV; ++e) t.v[e] = fmaf(alpha, t.v[e], old.v[e]);
-            if (cnt >= NV) {
-                *(piece *)o = t;
-            } else {
-#pragma unroll
-                for (int e = 0; e < NV; ++e)
-                    if (e < cnt) o[e] = t.v[e];
-            }
-        }
+            for (int e = 0; e < 4; ++e)
+                if (e < w.cnt) p[e] = v[e];
     }
 }
 
@@ -724,24 +858,24 @@ int x3_splits(int M, int N, int K, size_t room) {
     return S;
 }
 
-template <int BM, bool PKS, bool QKS, bool ACC>
+template <int BM, bool PKS>
 void launch_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *C, long ldc, float *part, int S,
-               int M, int N, int K, float alpha) {
+               int M, int N, int K) {
     const size_t sm = (size_t)2 * 3 * (X3_BN + BM) / 16 * 64 * 16;
-    constexpr int DEPTH = !ACC && BM <= 64 ? 4 : 2;
+    constexpr int DEPTH = BM <= 64 ? 4 : 2;
     static OncePerDevice once;
-    allow_lds(once, (const void *)k_gemm_x3<BM, PKS, QKS, ACC, DEPTH>, sm);
+    allow_lds(once, (const void *)k_gemm_x3<BM, PKS, DEPTH>, sm);
     const long ldo = part ? N : ldc;
     const int vec = ldo % 4 == 0 && ((uintptr_t)(part ? part : C) & 15) == 0 && (!part || (size_t)M * N % 4 == 0);
     const dim3 grid(((N + X3_BN - 1) / X3_BN + 7) / 8 * 8 * ((M + BM - 1) / BM), S);
-    k_gemm_x3<BM, PKS, QKS, ACC, DEPTH><<<grid, 256, sm, st>>>(P, ldp, Q, ldq, C, ldc, part, M, N, K, alpha, vec);
+    k_gemm_x3<BM, PKS, DEPTH><<<grid, 256, sm, st>>>(P, ldp, Q, ldq, C, ldc, part, M, N, K, vec);
 }
-template <bool PKS, bool QKS, bool ACC>
+template <bool PKS>
 void gemm_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *C, long ldc, float *part, int S,
-             int M, int N, int K, float alpha) {
-    if (M <= 32) launch_x3<32, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
-    else if (M <= 64) launch_x3<64, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
-    else launch_x3<128, PKS, QKS, ACC>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K, alpha);
+             int M, int N, int K) {
+    if (M <= 32) launch_x3<32, PKS>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K);
+    else if (M <= 64) launch_x3<64, PKS>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K);
+    else launch_x3<128, PKS>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K);
 }
 template <int MT, bool KS, bool KT>
 void launch_stream(hipStream_t st, const float *P, long ldp, const float *X, float *out, int S, int M, int N, int K) {
@@ -760,7 +894,7 @@ void gemm_weights(hipStream_t st, const float *X, const float *W, float *C, floa
     // their start (a head step of 10 rows at 512 x 4000: 125 us all streamed, 115 so; discriminator step of 4 rows 81 and 75;
     // of 290 rows at 512 x 32000 805 and 785; up to eight stages: 90 rows at 512 x 32000 377 and 412 us).
     if (N < 32 || K < 64 || N >= 1 << 23 || K >= 1 << 23 || (K + 63) / 64 <= 4 * S)
-        return gemm_x3<KS, false, false>(st, W, ldp, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K, 1.f);
+        return gemm_x3<KS>(st, W, ldp, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K);
     float *out = S > 1 ? part : C;
 #define KOALA_STREAM(MT) return K % 64 ? launch_stream<MT, KS, true>(st, W, ldp, X, out, S, M, N, K) : launch_stream<MT, KS, false>(st, W, ldp, X, out, S, M, N, K)
     switch (x3_tiles(M)) {
@@ -778,28 +912,12 @@ void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *pa
 void gemm_nn(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
     gemm_weights<true>(st, X, W, C, part, S, M, N, K);
 }
-template <int KP, int NV>
-void launch_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float alpha) {
-    const int nb = (N + 64 * NV - 1) / (64 * NV);
-    int mr = UPD_MR;   // panels as high as leave a workgroup a compute unit: each reads its columns of X for itself
-    while (mr > 16 && (long)nb * ((M + mr - 1) / mr) < 256) mr /= 2;
-    k_update_rows<KP, NV><<<dim3(nb, (M + mr - 1) / mr), 256, 0, st>>>(G, X, W, M, N, rows, mr, alpha);
-}
 // W[M,N] -= lr * G[rows,M]^T X[rows,N]
 void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr) {
-    // The multiply-adds of more than 32 rows take longer than a matrix that the caches hold (4000 x 1000: 14.7 us at 32
-    // rows, 24.9 at 40, where k_gemm_x3 takes 14.5 and 18.7), those of up to 48 about as long as a large one's way through
-    // memory (1024 x 32000 75 us at 40 rows and 85 at 48, k_gemm_x3 88 and 89; 32000 x 4096 306 and 346, k_gemm_x3 444
-    // and 452; at 64 rows 552 and 461).
-    switch (rows <= 32 || (size_t)M * N >= 24000000u ? (rows + 7) / 8 : 0) {
-        case 1: return launch_update<8, 4>(st, G, X, W, M, N, rows, -lr);
-        case 2: return launch_update<16, 4>(st, G, X, W, M, N, rows, -lr);
-        case 3: return launch_update<24, 4>(st, G, X, W, M, N, rows, -lr);
-        case 4: return launch_update<32, 4>(st, G, X, W, M, N, rows, -lr);
-        case 5: return launch_update<40, 2>(st, G, X, W, M, N, rows, -lr);
-        case 6: return launch_update<48, 2>(st, G, X, W, M, N, rows, -lr);
-    }
-    gemm_x3<true, true, true>(st, X, N, G, M, W, N, nullptr, 1, M, N, rows, -lr);
+    const long tiles = (long)((M + 63) / 64) * ((N + 127) / 128);
+    const int grid = (int)((tiles + 7) / 8 * 8);
+    if (rows <= 32) k_update_x3<true><<<grid, 256, 0, st>>>(G, X, W, M, N, rows, -lr);
+    else k_update_x3<false><<<grid, 256, 0, st>>>(G, X, W, M, N, rows, -lr);
 }
 
 // The S split sums of element i added in split order, and the element-wise step that follows the product:

@@ -111,6 +111,27 @@ def test_products_at_the_edges_of_a_streamed_tile(n, V, H):
     assert _rel(-w.T[:m], g[:m].astype(np.float64) @ w_lm.astype(np.float64)) < bound(V)
 
 
+@pytest.mark.parametrize("rows,H", [(1, 1), (33, 1), (32, 2), (31, 63), (32, 65), (33, 64), (64, 127), (97, 128), (127, 129), (128, 193), (129, 130),
+                                    (160, 191), (256, 66), (257, 515), (20, 1030)])
+@pytest.mark.parametrize("scale", [0, -118])
+def test_updates_at_the_edges_of_a_tile(rows, H, scale):
+    """W = -g^T h, set up and bounded as above: a matrix that a tile of 64 x 128, a wave's 32 columns or a pair of columns does
+    not fill, chunks of 32 rows and blocks of 128 that the rows do not fill; scale: where the pieces do not hold.  That bound is
+    one for a sample of many sums; each by itself is within (rows + 2) roundings of 2^-24 of its terms' magnitudes."""
+    import torch
+    import paper_2408_08146_amd as KO
+    rng = np.random.default_rng(rows + H)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    g, h = (rng.normal(size=(rows, H)).astype(np.float32) * np.float32(2.0 ** e) for e in (scale, -scale // 2))
+    w = dev(np.zeros((H, H)))
+    KO.MedusaHeadTrainer([w], dev(2 * np.eye(H))).step(dev(h), dev(g), 1.0)
+    g, h = g.astype(np.float64), h.astype(np.float64)
+    off = np.abs(-w.double().cpu().numpy() - g.T @ h)
+    assert (off <= (rows + 2) * 2.0 ** -24 * (np.abs(g).T @ np.abs(h))).all()
+    if H >= 31:
+        assert _rel(-w, g.T @ h) < 1.15 * 2.53e-8 * np.sqrt((rows + 1) / 2)
+
+
 def test_head_with_the_smallest_workspace():
     """A workspace without room for split sums is accepted (one byte less is not) and gives the same results to rounding."""
     import torch
