@@ -218,13 +218,16 @@ __global__ __launch_bounds__(256 * RS, RS > 1 ? 1 : MT == 4 ? 2 : 3) void k_gemm
 //                (koala.h), so the two halves of a rotary pair are neighbours in one lane;
 //   EPI_SWIGLU   row scale, SiLU(gate) * up (rows interleaved gate, up), written as fragments of the
 //                down projection's input;
+//   EPI_LOGITS   row scale, finished logits to their rows, and the largest of the workgroup's columns per row for
+//                k_topk_stage2 (its own launch for this, k_topk_stage1 behind partial sums, took 5 us at one row, 7 at 26,
+//                11 at 64 and 71 at 480);
 //   EPI_HEADS    EPI_PARTIAL of several matrices of one shape on the same input, matrix blockIdx.y into its own
 //                P[blockIdx.y][sp][row][n]: the residual blocks of a Medusa-style draft's heads in one launch.
 // Every compute unit can take in only so many bytes per second (about 53 GB/s measured, weights and
 // activations together), and with S = 1 every workgroup reads all activation fragments; U is therefore
 // chosen so that one launch is one workgroup per compute unit with equal shares of the weights.
 // ---------------------------------------------------------------------------------------------
-enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_HEADS = 3 };
+enum { EPI_PARTIAL = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_HEADS = 3, EPI_LOGITS = 4 };
 
 // whether the wave accumulators of k_gemm_rows are combined in halving rounds (they do not all fit in LDS at once)
 constexpr bool gemm_rows_tree(int U, int MT, int NW) { return NW * U * MT > 96; }
@@ -243,11 +246,47 @@ struct GemmEpi {
     uint32_t *Xo;       // EPI_SWIGLU: output fragments, F = out features / 2
     int F;
     const void *heads[kb::GEMM_HEADS];   // EPI_HEADS: the matrices
+    float *logits;      // EPI_LOGITS: [rows][V], may be null
+    float *cand_val;    // EPI_LOGITS: [rows][n_cand] largest logit of a workgroup's columns and its column (null: not wanted)
+    int *cand_idx;
+    int V, n_cand;
     // k_gemm_big with an epilogue on split groups: P is the scratch of their accumulators (P_bytes long), and counters[group
     // and activation block] are zero between launches
     size_t P_bytes;
     int *counters;
 };
+
+__device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
+    return v > bv || (v == bv && i < bi);
+}
+struct __attribute__((may_alias, aligned(8))) Best { float v; int i; };
+constexpr int NO_COLUMN = 0x7fffffff;
+// the better of the four 16-lane groups' candidates, in every lane
+__device__ __forceinline__ Best lane_groups_best(Best b) {
+    auto pick = [](auto v, auto i) {
+        const float v0 = __uint_as_float(v[0]), v1 = __uint_as_float(v[1]);
+        return better(v1, (int)i[1], v0, (int)i[0]) ? Best{v1, (int)i[1]} : Best{v0, (int)i[0]};
+    };
+    b = pick(__builtin_amdgcn_permlane16_swap(__float_as_uint(b.v), __float_as_uint(b.v), false, false),
+             __builtin_amdgcn_permlane16_swap(b.i, b.i, false, false));
+    return pick(__builtin_amdgcn_permlane32_swap(__float_as_uint(b.v), __float_as_uint(b.v), false, false),
+                __builtin_amdgcn_permlane32_swap(b.i, b.i, false, false));
+}
+// Four logits of columns n .. n + 3 to their row (if wanted and it is one), and the best of them and b
+typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;   // rows of V floats need not be 16-byte aligned
+__device__ __forceinline__ void put_logits(float *logits, int row, int V, int n, f32x4 v, bool ok, Best &b) {
+    if (logits && ok) {
+        float *o = logits + (size_t)row * V + n;
+        if (n + 4 <= V) *(f32x4_a4 *)o = v;
+        else
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (n + q < V) o[q] = v[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (n + q < V && better(v[q], n + q, b.v, b.i)) b = Best{v[q], n + q};
+}
 
 template <int U, int MT, int NW, int PF, int EPI>
 __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__ Wp, const u32x4 *__restrict__ Xf,
@@ -255,12 +294,13 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
     constexpr bool TREE = gemm_rows_tree(U, MT, NW);
     constexpr int NRED = TREE ? NW / 2 : NW;
     extern __shared__ __attribute__((aligned(16))) unsigned char gsm[];
-    constexpr bool ROWS = EPI == EPI_QKV || EPI == EPI_SWIGLU;       // the epilogue needs data of the activation rows
+    constexpr bool ROWS = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LOGITS;   // the epilogue needs data of the activation rows
     constexpr int R = MT * 16, NT = 64 * NW, NPL = NT / R;          // threads of a row in the prologue
     f32x4 *red = (f32x4 *)gsm;                                     // [NRED][U][MT][64]
     float *sq_s = (float *)(gsm + (size_t)NRED * U * MT * 64 * 16);  // ROWS: [NPL][R] shares of the rows' sums of squares
     int *slot_s = (int *)(sq_s + (ROWS ? NT : 0)), *bat_s = slot_s + R;   // EPI_QKV: [R] cache slot and sequence
     float *cs = (float *)(bat_s + R);                                // EPI_QKV: [R][U][8][cos, sin]
+    Best *best = (Best *)(bat_s + R);                                // EPI_LOGITS: [U][R]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
     const int nunits = Npad / 16, nwg = (nunits + U - 1) / U;
     const int g = blockIdx.x % nwg, sp = blockIdx.x / nwg, ug0 = g * U;
@@ -282,13 +322,16 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
     // nothing new under way: the loop began 5 to 10 us into the kernel.  7B model, QKV 28.6 -> 23.7 us and gate/up
     // 40.0 -> 35.5 us at 64 rows, 20.4 -> 18.7 and 32.0 -> 30.6 us at 26.)
     constexpr int NCS = EPI == EPI_QKV ? (R * U * 8 + NT - 1) / NT : 1;
-    float sq[2] = {0.f, 0.f}, rc[NCS], rs_[NCS];
+    constexpr int NSQ = NPL == 4 ? 4 : 2;   // sums a thread requests ahead: of 16 chunks (8192 columns) at least
+    float sq[NSQ], rc[NCS], rs_[NCS];
+#pragma unroll
+    for (int i = 0; i < NSQ; ++i) sq[i] = 0.f;
     int slot = 0, bat = 0;
     const int prow = threadIdx.x % R, ppart = threadIdx.x / R;
     if (ROWS && e.sums) {
         const float *src = e.sums + min(prow, e.rows - 1);
-        sq[0] = src[(size_t)min(ppart, e.nparts - 1) * e.srows];
-        sq[1] = src[(size_t)min(ppart + NPL, e.nparts - 1) * e.srows];
+#pragma unroll
+        for (int i = 0; i < NSQ; ++i) sq[i] = src[(size_t)min(ppart + i * NPL, e.nparts - 1) * e.srows];
     }
     if (EPI == EPI_QKV) {
         const int half = e.DH / 2, row = min(prow, e.rows - 1);
@@ -326,7 +369,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
         float t = 0.f;
         if (e.sums) {
             t = (ppart < e.nparts ? sq[0] : 0.f) + (ppart + NPL < e.nparts ? sq[1] : 0.f);
-            for (int c = ppart + 2 * NPL; c < e.nparts; c += NPL) t += e.sums[(size_t)c * e.srows + min(prow, e.rows - 1)];
+#pragma unroll
+            for (int i = 2; i < NSQ; ++i) t += ppart + i * NPL < e.nparts ? sq[i] : 0.f;
+            for (int c = ppart + NSQ * NPL; c < e.nparts; c += NPL) t += e.sums[(size_t)c * e.srows + min(prow, e.rows - 1)];
         }
         sq_s[threadIdx.x] = t;
     }
@@ -408,7 +453,10 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
     // n .. n + 3 of activation row mtt * 16 + li
     for (int u = wave; u < U * MT; u += NW) {
         const int j = u / MT, mtt = u % MT;
-        if (ug0 + j >= nunits) continue;
+        if (ug0 + j >= nunits) {
+            if (EPI == EPI_LOGITS && lg == 0) best[j * R + mtt * 16 + li] = Best{-INFINITY, NO_COLUMN};
+            continue;
+        }
         f32x4 v = red[((size_t)j * MT + mtt) * 64 + l];
         if (!TREE) {
 #pragma unroll
@@ -420,7 +468,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             *(f32x4 *)(e.P + ((size_t)part * (MT * 16) + row) * Npad + n) = v;
             continue;
         }
-        if (row >= e.rows) continue;
+        if (EPI != EPI_LOGITS && row >= e.rows) continue;   // of four lane groups that hold a row together, all or none
         float sc = 1.f;
         if (e.sums) {
             float tot = 0.f;
@@ -428,6 +476,13 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             sc = 1.0f / sqrtf(tot / (float)e.Kn + e.eps);
         }
         v *= sc;
+        if (EPI == EPI_LOGITS) {
+            Best b{-INFINITY, NO_COLUMN};
+            put_logits(e.logits, row, e.V, n, v, row < e.rows, b);
+            b = lane_groups_best(b);
+            if (lg == 0) best[j * R + row] = b;
+            continue;
+        }
         if (EPI == EPI_QKV) {
             const int which = n / e.H, nn = n % e.H, h = nn / e.DH, r = nn % e.DH, half = e.DH / 2;
             const int bat = bat_s[row];
@@ -468,6 +523,19 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const u32x4 *__restrict__
             const int ks = f0 >> 5, lane = li + 16 * ((f0 & 31) >> 3);
             e.Xo[(((size_t)ks * MT + mtt) * 64 + lane) * 4 + ((f0 & 7) >> 1)] = half_pair(y0, y1);
         }
+    }
+    if (EPI == EPI_LOGITS && e.cand_val) {
+        __syncthreads();
+        const int row = threadIdx.x;
+        if (row >= R || row >= e.rows) return;
+        Best b = best[row];
+#pragma unroll
+        for (int j = 1; j < U; ++j) {
+            const Best o = best[j * R + row];
+            if (better(o.v, o.i, b.v, b.i)) b = o;
+        }
+        e.cand_val[(size_t)row * e.n_cand + g] = b.v;
+        e.cand_idx[(size_t)row * e.n_cand + g] = b.i;
     }
 }
 
@@ -610,7 +678,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ W
     const int pf_lines = min(MTW, MTT - mt0) * 8;
     const unsigned pf_off = (unsigned)mt0 * 1024u + (unsigned)min((int)threadIdx.x, pf_lines - 1) * 128u;
     unsigned char *pf_sink = bsm + (size_t)2 * XT * 16 + wave * 256;
-    // EPI_SWIGLU: RMSNorm's scale of each of the workgroup's rows (from the per-chunk sums of squares of the input
+    // EPI_SWIGLU, EPI_LOGITS: RMSNorm's scale of each of the workgroup's rows (from the per-chunk sums of squares of the input
     // rows), one row per thread, fetched now and parked in LDS behind the sinks until the epilogue
     float *rsc_s = (float *)(bsm + (size_t)2 * XT * 16 + 4 * 256);   // [MTW * 16]
     int *rslot_s = (int *)(rsc_s + MTW * 16), *rbat_s = rslot_s + MTW * 16;   // EPI_QKV: cache slot and sequence of a row
@@ -864,6 +932,34 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(const u32x4 *__restrict__ W
                 }
             }
         }
+    } else if (EPI == EPI_LOGITS) {
+        // Finished sums: the row scale, logits to their rows, and per row the largest of the workgroup's columns, first over
+        // the wave's, then over the four waves' through LDS.
+        Best *best = (Best *)(bsm + 1024);   // [wave][MTW * 16], beside the first bytes, which other waves may still read
+#pragma unroll
+        for (int m = 0; m < MTW; ++m) {
+            if (m >= mt_cnt) continue;
+            const int row = (mt0 + m) * 16 + li;
+            const float rsc = rsc_s[m * 16 + li];
+            Best b{-INFINITY, NO_COLUMN};
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                if (ug0 + j < nunits) put_logits(e.logits, row, e.V, (ug0 + j) * 16 + 4 * lg, acc[j][m] * rsc, row < e.rows, b);
+            b = lane_groups_best(b);
+            if (lg == 0) best[wave * (MTW * 16) + m * 16 + li] = b;
+        }
+        if (!e.cand_val) return;
+        __syncthreads();
+        const int r = threadIdx.x, row = mt0 * 16 + r;
+        if (r >= mt_cnt * 16 || row >= e.rows) return;
+        Best b = best[r];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+            const Best o = best[w * (MTW * 16) + r];
+            if (better(o.v, o.i, b.v, b.i)) b = o;
+        }
+        e.cand_val[(size_t)row * e.n_cand + g] = b.v;
+        e.cand_idx[(size_t)row * e.n_cand + g] = b.i;
     } else {
         // EPI_SWIGLU (finished sums): the weight rows interleave gate and up, so a lane's four columns are (gate, up)
         // of two features of one activation row.  RMSNorm's row scale (from the per-chunk sums of squares of the
@@ -978,7 +1074,13 @@ struct RowScale {
 __device__ __forceinline__ float row_scale(const RowScale &rs, int row) {
     if (!rs.sums) return 1.f;
     float tot = 0.f;
-    for (int c = 0; c < rs.nparts; ++c) tot += rs.sums[(size_t)c * rs.srows + row];
+    for (int c0 = 0; c0 < rs.nparts; c0 += 8) {   // eight loads under way
+        float part[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) part[c] = rs.sums[(size_t)min(c0 + c, rs.nparts - 1) * rs.srows + row];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) tot += c0 + c < rs.nparts ? part[c] : 0.f;
+    }
     return 1.0f / sqrtf(tot / (float)rs.K + rs.eps);
 }
 
@@ -1186,10 +1288,6 @@ __global__ __launch_bounds__(64) void k_resblock_p(float *x, u32x4 *Xf, const fl
 // Stage 1, grid (ceil(V/1024), rows): each block reduces 1024 columns, optionally stores the
 // logits, and emits its own k best.  Stage 2, grid (rows): merges the blocks' candidates.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
-    return v > bv || (v == bv && i < bi);
-}
-
 // block-wide arg-best over (v, i); every thread gets the winner.  4 waves.
 __device__ __forceinline__ void block_best(float &v, int &i, float *sv, int *si) {
     for (int o = 32; o > 0; o >>= 1) {
@@ -1248,8 +1346,9 @@ __global__ __launch_bounds__(256) void k_topk_stage1(const float *P, int S, int 
     }
 }
 
+// The features (the row after the final norm) come from here where stage 1 has no launch of its own.
 __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, const int *cand_idx, int n_cand, int k,
-                                                     int32_t *idx, float *val, ChildFill fill) {
+                                                     int32_t *idx, float *val, ChildFill fill, RowScale rs, kb::FeatOut fo) {
     __shared__ float sv[4], best_val[KOALA_TOPK_MAX];
     __shared__ int si[4], best[KOALA_TOPK_MAX];
     const int r = blockIdx.x, tid = threadIdx.x;
@@ -1261,6 +1360,18 @@ __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, cons
         const int a = tid + 256 * q;
         cv[q] = a < n_cand ? cand_val[(size_t)r * n_cand + a] : -INFINITY;
         ci[q] = a < n_cand ? cand_idx[(size_t)r * n_cand + a] : 0x7fffffff;
+    }
+    if (fo.feat) {
+        const float inv = row_scale(rs, r);
+        for (int j = tid * 8; j < fo.H; j += 2048) {   // the hidden size is a multiple of eight
+            const float *xr = fo.x + (size_t)r * fo.H + j;
+            const f32x4 a = *(const f32x4 *)xr, b = *(const f32x4 *)(xr + 4);
+            float g[8];
+            load_bf8((const bf16_t *)fo.gain + j, g);
+            float *o = fo.feat + (size_t)r * fo.H + j;
+            *(f32x4 *)o = (f32x4){a[0] * inv * g[0], a[1] * inv * g[1], a[2] * inv * g[2], a[3] * inv * g[3]};
+            *(f32x4 *)(o + 4) = (f32x4){b[0] * inv * g[4], b[1] * inv * g[5], b[2] * inv * g[6], b[3] * inv * g[7]};
+        }
     }
     for (int it = 0; it < k; ++it) {
         float bv = -INFINITY;
@@ -1295,7 +1406,7 @@ __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, cons
 // in half the LDS rounds (O and down projection together 33.3 -> 30.5 us at 4096, 7B).  With the epilogues four waves lose: their
 // rotary and SwiGLU step is spread over half the threads (QKV at 64 rows 23.6 -> 25.5 us).
 constexpr int rows_waves(int U, int MT, int EPI) {
-    return (EPI == EPI_PARTIAL || EPI == EPI_HEADS) && (U == 8 ? MT > 1 : MT == 4) ? 4 : 8;
+    return (EPI == EPI_PARTIAL || EPI == EPI_HEADS || EPI == EPI_LOGITS) && (U == 8 ? MT > 1 : MT == 4) ? 4 : 8;
 }
 constexpr int rows_tiles(int U, int MT, int NW) { return NW == 4 ? 3 : MT == 4 && U > 4 ? 1 : 2; }
 
@@ -1305,8 +1416,8 @@ void launch_gemm_rows(hipStream_t st, const void *Wp, const void *Xf, int Npad, 
     constexpr int NW = rows_waves(U, MT, EPI), PF = rows_tiles(U, MT, NW);
     constexpr int R = MT * 16;   // accumulators, shares of the rows' sums, cache slots and sequences, cos/sin
     const size_t sm = (size_t)(gemm_rows_tree(U, MT, NW) ? NW / 2 : NW) * U * MT * 64 * 16 +
-                      (EPI == EPI_QKV || EPI == EPI_SWIGLU ? (size_t)64 * NW * 4 + R * 8 : 0) +
-                      (EPI == EPI_QKV ? (size_t)R * U * 8 * 2 * 4 : 0);
+                      (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LOGITS ? (size_t)64 * NW * 4 + R * 8 : 0) +
+                      (EPI == EPI_QKV ? (size_t)R * U * 8 * 2 * 4 : 0) + (EPI == EPI_LOGITS ? (size_t)R * U * 8 : 0);
     static OncePerDevice once;
     allow_lds(once, (const void *)k_gemm_rows<U, MT, NW, PF, EPI>, sm);
     const dim3 grid(((Npad / 16 + U - 1) / U) * S, n_heads);
@@ -1434,6 +1545,8 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 #undef KOALA_GEMM
 }
 
+int rows_wide_groups(int Npad) { return (Npad / 16 + 7) / 8; }
+int big_groups(int Npad, const BigShape &b) { return (Npad / 16 + 4 * b.U - 1) / (4 * b.U); }
 bool rows_wide(int Npad, int n_cu) { return Npad / 16 > 5 * n_cu && (Npad / 16 + 7) / 8 <= n_cu; }
 
 void gemm_rows_wide(hipStream_t st, const void *Wp, const void *Xf, float *P, int Npad, int K, int MTT, hipEvent_t ev_start,
@@ -1659,7 +1772,36 @@ void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const N
     const int nchunk = (V + 1023) / 1024;
     k_topk_stage1<<<dim3(nchunk, rows), 256, 0, st>>>(P, S, Mp, ldp, mk_scale(ns), logits, ldl, V, k, cand_val,
                                                       cand_idx, fo);
-    if (k > 0) k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val, fill);
+    if (k > 0)
+        k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val, fill, RowScale{}, FeatOut{});
+}
+
+static GemmEpi logits_epi(const NormScale &ns, int rows, float *logits, int V, float *cand_val, int *cand_idx, int n_cand) {
+    GemmEpi e{};
+    e.sums = ns.sums; e.nparts = ns.nparts; e.srows = ns.srows; e.Kn = ns.K; e.eps = ns.eps;
+    e.rows = rows; e.logits = logits; e.V = V; e.cand_val = cand_val; e.cand_idx = cand_idx; e.n_cand = n_cand;
+    return e;
+}
+
+void gemm_rows_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const NormScale &ns, int rows,
+                      float *logits, int V, float *cand_val, int *cand_idx, hipEvent_t ev_start, hipEvent_t ev_stop) {
+    const int Npad = pad64(V);
+    dispatch_gemm_rows_u<8, EPI_LOGITS>(st, Wp, Xf, Npad, K, MTT, 1,
+                                        logits_epi(ns, rows, logits, V, cand_val, cand_idx, rows_wide_groups(Npad)), ev_start, ev_stop);
+}
+
+void gemm_big_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b, const NormScale &ns,
+                     int rows, float *logits, int V, float *cand_val, int *cand_idx, float *scratch, size_t room, int *counters,
+                     hipEvent_t ev_start, hipEvent_t ev_stop) {
+    const int Npad = pad64(V);
+    GemmEpi e = logits_epi(ns, rows, logits, V, cand_val, cand_idx, big_groups(Npad, b));
+    e.P = scratch; e.P_bytes = room; e.counters = counters;
+    dispatch_gemm_big<EPI_LOGITS>(st, Wp, Xf, nullptr, Npad, K, MTT, b, e, ev_start, ev_stop);
+}
+
+void best_logit(hipStream_t st, const float *cand_val, const int *cand_idx, int n_cand, int rows, int32_t *idx,
+                const NormScale &ns, const FeatOut &fo) {
+    k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, n_cand, 1, idx, nullptr, ChildFill{}, mk_scale(ns), fo);
 }
 
 }  // namespace kb

@@ -242,6 +242,30 @@ void rows_to_frags(koala_ctx *c, hipStream_t st, const float *a, int lda, int ro
     kb::fold(st, const_cast<float *>(a), lda, nullptr, 0, 0, 0, 0, rows, K, nullptr, c->xf, MT, nullptr, 0);
 }
 
+// LM head whose logits are finished in the GEMM, on the fragments in c->xf: to `logits` (may be null) and, if wanted, the
+// candidates for kb::best_logit.  Returns the candidates of a row, 0 where the vocabulary or the number of rows is one that
+// takes partial sums instead (bf_gemm, then kb::logits_topk).
+int bf_head_logits(koala_ctx *c, hipStream_t st, int rows, int MT, const kb::NormScale &ns, float *logits, bool best) {
+    const int V = c->shape.vocab, H = c->shape.hidden, Npad = kb::pad64(V);
+    float *val = best ? c->cand_val : nullptr;
+    int *idx = best ? c->cand_idx : nullptr;
+    if (MT >= 8 && big_fits32(Npad, H, MT) && big_gemm_enabled()) {
+        const kb::BigShape b = kb::big_shape(Npad, H, rows, c->n_cu, true, c->part_bytes, c->max_batch * c->shape.n_heads * 4);
+        const int n = kb::big_groups(Npad, b);
+        if (n > 1024) return 0;   // more than k_topk_stage2 takes
+        const LaunchEvents ev = timed_launch(c, (double)Npad * H * 2.0);
+        kb::gemm_big_logits(st, c->w.lm_head, c->xf, H, MT, b, ns, rows, logits, V, val, idx, c->part, c->part_bytes, c->attn_cnt,
+                            ev.start, ev.stop);
+        return n;
+    }
+    if (MT <= 4 && kb::rows_wide(Npad, c->n_cu)) {
+        const LaunchEvents ev = timed_launch(c, (double)Npad * H * 2.0);
+        kb::gemm_rows_logits(st, c->w.lm_head, c->xf, H, MT, ns, rows, logits, V, val, idx, ev.start, ev.stop);
+        return kb::rows_wide_groups(Npad);
+    }
+    return 0;
+}
+
 // bf16 decoder layer.  On entry c->pend_* may describe partial sums still to be folded into x, or c->frags_ready says that
 // the input's fragments are in place; on exit the down projection's sums are pending.  Up to 64 rows: seven launches (fold, QKV projection with rotary embedding
 // and cache append, attention, merge of its key splits, O projection, fold, gate/up projection with SwiGLU,
@@ -567,9 +591,14 @@ koala_status koala_tree_verify(koala_ctx *c, void *hip_stream, int batch, const 
         // last down projection folded in; the LM head runs on gain * x and its logits take the row scale; the features
         // (an output) are written beside the logits
         fold_pending(c, st, rows, MT, c->w.final_norm);
-        const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
-        kb::logits_topk(st, c->part, S, Mp, kb::pad64(V), hidden_scale(c), logits_out, V, rows, V, 1, c->cand_val,
-                        c->cand_idx, greedy_out, nullptr, ChildFill{}, kb::FeatOut{c->x, c->w.final_norm, feat_out, H});
+        const kb::FeatOut fo{c->x, c->w.final_norm, feat_out, H};
+        if (const int n = bf_head_logits(c, st, rows, MT, hidden_scale(c), logits_out, true)) {
+            kb::best_logit(st, c->cand_val, c->cand_idx, n, rows, greedy_out, hidden_scale(c), fo);
+        } else {
+            const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT, rows);
+            kb::logits_topk(st, c->part, S, Mp, kb::pad64(V), hidden_scale(c), logits_out, V, rows, V, 1, c->cand_val,
+                            c->cand_idx, greedy_out, nullptr, ChildFill{}, fo);
+        }
         KOALA_CHECK_LAUNCH(c);
         return KOALA_OK;
     }
@@ -636,9 +665,11 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
             // logits of the D heads (row j * batch + b), from which every parent of that depth draws its children
             if (bf) {
                 const int MT = kb::mt_of(D * batch), Vp = kb::pad64(V);
-                const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
-                kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), c->med_logits, V, D * batch, V, 0, nullptr,
-                                nullptr, nullptr, nullptr, ChildFill{}, kb::FeatOut{});
+                if (!bf_head_logits(c, st, D * batch, MT, no_scale(), c->med_logits, false)) {
+                    const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT, D * batch);
+                    kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), c->med_logits, V, D * batch, V, 0, nullptr,
+                                    nullptr, nullptr, nullptr, ChildFill{}, kb::FeatOut{});
+                }
             } else {
                 kf::gemm(st, c->x, H, c->w.lm_head, c->med_logits, V, D * batch, V, H, false);
             }
@@ -649,7 +680,7 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
         } else if (D > 0) {
             if (bf) {
                 const int MT = kb::mt_of(D * batch);
-                const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
+                const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT, D * batch);
                 kb::logits_topk(st, c->part, S, MT * 16, kb::pad64(V), no_scale(), nullptr, 0, D * batch, V, kmax,
                                 c->cand_val, c->cand_idx, nullptr, nullptr, fill(0, 0), kb::FeatOut{});
             } else {
@@ -705,9 +736,11 @@ static koala_status draft_expand_impl(koala_ctx *c, void *hip_stream, int batch,
         const int k = c->topk[d], rows = batch * nl;
         if (bf) {
             const int MT = kb::mt_of(rows), Vp = kb::pad64(V);
-            const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT);
-            kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), sampling ? c->logits : nullptr, V, rows, V,
-                            sampling ? 0 : k, c->cand_val, c->cand_idx, nullptr, nullptr, fill(d, nl), kb::FeatOut{});
+            if (!sampling || !bf_head_logits(c, st, rows, MT, no_scale(), c->logits, false)) {
+                const int S = bf_gemm(c, st, c->w.lm_head, V, H, MT, rows);
+                kb::logits_topk(st, c->part, S, MT * 16, Vp, no_scale(), sampling ? c->logits : nullptr, V, rows, V,
+                                sampling ? 0 : k, c->cand_val, c->cand_idx, nullptr, nullptr, fill(d, nl), kb::FeatOut{});
+            }
         } else {
             kf::gemm(st, in.a, in.lda, c->w.lm_head, c->logits, V, rows, V, H, false);
             if (!sampling) kg::topk_rows(st, c->logits, V, rows, V, k, nullptr, nullptr, fill(d, nl));

@@ -272,6 +272,16 @@ void gemm_big_qkv(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT
 void gemm_big_swiglu(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b,
                      const NormScale &ns, int rows, void *Xo, int F, float *scratch, size_t room, int *counters,
                      hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// The LM head of V tokens with its logits finished in the GEMM (gemm_rows_logits where rows_wide, gemm_big_logits for MTT >= 8):
+// logits (may be null) [rows][V], and per row and workgroup (rows_wide_groups or big_groups of them) the largest logit and its
+// token to cand_val / cand_idx (may be null), which best_logit merges
+int rows_wide_groups(int Npad);
+int big_groups(int Npad, const BigShape &b);
+void gemm_rows_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const NormScale &ns, int rows,
+                      float *logits, int V, float *cand_val, int *cand_idx, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+void gemm_big_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b, const NormScale &ns,
+                     int rows, float *logits, int V, float *cand_val, int *cand_idx, float *scratch, size_t room, int *counters,
+                     hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // v = (mode 1: x +) sum of partials (mode 0: x as is); x <- v for modes 1, 2; Xf (may be NULL) receives the
 // fragments of gain * v (gain NULL: v); sums (may be NULL) the sums of squares of v per 512-column chunk
 void fold(hipStream_t st, float *x, int ldx, const float *P, int S, int Mp, int ldp, int mode, int M, int N,
@@ -308,5 +318,8 @@ struct FeatOut { const float *x; const void *gain; float *feat; int H; };
 void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const NormScale &ns, float *logits, int ldl,
                  int rows, int V, int k, float *cand_val, int *cand_idx, int32_t *idx, float *val, const ChildFill &fill,
                  const FeatOut &fo);
+// the best of a row's n_cand <= 1024 candidates to idx, and the rows after the final norm
+void best_logit(hipStream_t st, const float *cand_val, const int *cand_idx, int n_cand, int rows, int32_t *idx,
+                const NormScale &ns, const FeatOut &fo);
 
 }  // namespace kb

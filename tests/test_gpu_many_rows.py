@@ -25,3 +25,22 @@ def test_split_groups_match_oracle(batch, widths, head_dim):
     for _ in range(3):
         feat2, lg2, _ = c.gpu_verify(tt)
         assert np.array_equal(lg, lg2) and np.array_equal(feat, feat2)
+
+
+# vocabularies that leave a row group, a workgroup's groups or four columns of a lane partly empty; 65 and 240 rows
+@pytest.mark.parametrize("vocab", [5, 63, 257, 1001, 4099, 12345, 20481])
+@pytest.mark.parametrize("batch,widths", [(5, [1, 4, 8]), (4, [1, 4, 8, 16, 16, 15])])
+def test_output_head_of_many_rows(vocab, batch, widths):
+    """Logits finished in the GEMM: as the oracle's, and the greedy token is the first largest of the logits returned, also
+    where no logits are returned."""
+    c = Case("cfg5_small", n_layers=1, batch=batch, ctx=(20, 40), capacity=128, hidden=256, n_heads=2, head_dim=128, ffn=256,
+             vocab=vocab, tree=dict(topk=[4, 2, 2, 1, 1][:len(widths) - 1], widths=widths))
+    c.fill_kv_normal()
+    c.upload_kv()
+    tt = c.random_tree_tokens()
+    feat, lg, greedy = c.gpu_verify(tt)
+    rfeat, rlg, rgreedy = c.oracle_verify(tt)
+    compare_logits_and_greedy(c, lg, greedy, rlg, rgreedy)
+    assert rel_err_rows(feat, rfeat).max() < c.tol
+    assert np.array_equal(greedy, lg.argmax(-1))
+    assert np.array_equal(greedy, c.gpu_verify(tt, want_logits=False)[2])
