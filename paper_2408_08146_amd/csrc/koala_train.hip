@@ -49,13 +49,32 @@ typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 // for an operand of the tile (an infinity, or all of it below 2^-102: the MFMA takes pieces below 2^-126 as zero) the tile is
 // summed again on the fp32 pipe, so that it comes out as it does there.  Values below 2^-102 beside larger ones
 // are off by up to 2^-125.
-// grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  With part set the
-// split's sums go to part[split][M][N] for k_sum_parts, else to C.
+// grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  A
+// split's sums go to out[split][M][N], for k_sum_parts where there are several.
 // The products of all but the smallest matrices are k_stream_x3's, the updates k_update_x3's (both below).
 // Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 132 us for the 20 rows above, by
 // themselves), two beyond (three spill: 54 -> 95 us for the 40 rows).
 // ---------------------------------------------------------------------------------------------
 enum { X3_BN = 64, X3_BK = 32 };
+
+// The mapped hidden state z[p][v] joined to a logits row: u[p] = z + la[p] and, with lb, u[n + p] = z + lb[p], nV elements on.
+struct Join { const float *la, *lb; long nV; };
+// elements lo .. hi - 1 of the four at `at` of an output; vec: they are 16-byte aligned in every matrix
+__device__ __forceinline__ void put4(float *out, const Join &j, long at, f32x4 v, int lo, int hi, bool vec) {
+    if (vec && lo <= 0 && hi >= 4) {
+        if (!j.la) { *(f32x4 *)(out + at) = v; return; }
+        *(f32x4 *)(out + at) = v + *(const f32x4 *)(j.la + at);
+        if (j.lb) *(f32x4 *)(out + j.nV + at) = v + *(const f32x4 *)(j.lb + at);
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (r >= lo && r < hi) {
+            out[at + r] = j.la ? v[r] + j.la[at + r] : v[r];
+            if (j.lb) out[j.nV + at + r] = v[r] + j.lb[at + r];
+        }
+}
+bool join_aligned(const Join &j) { return (((uintptr_t)j.la | (uintptr_t)j.lb) & 15) == 0 && j.nV % 4 == 0; }
 
 // a and b as pairs of pieces; top: the largest magnitude so far
 __device__ __forceinline__ void split3(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l, float &top) {
@@ -164,8 +183,7 @@ struct X3Loader {
 
 template <int BM, bool PKS, int DEPTH>
 __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q,
-                                                    long ldq, float *C, long ldc, float *part, int M, int N, int K,
-                                                    int vec) {
+                                                    long ldq, float *out, int M, int N, int K, int vec, Join join) {
     constexpr int WN = BM == 32 ? 4 : 2, WM = 4 / WN;        // waves along n and m
     constexpr int TN = X3_BN / 16 / WN, TM = BM / 16 / WM;   // accumulator tiles of a wave
     constexpr int PU = 3 * (X3_BN / 16) * 64, QU = 3 * (BM / 16) * 64;   // 16-byte units of a chunk's planes
@@ -297,21 +315,13 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[e][i], qv[e][j], acc[i][j], 0, 0, 0);
         }
     }
-    float *out = part ? part + (long)blockIdx.y * M * N : C;
-    const long ldo = part ? N : ldc;
+    out += (long)blockIdx.y * M * N;
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
             const int m = m0 + (wm * TM + j) * 16 + li, n = n0 + (wn * TN + i) * 16 + 4 * lg;
-            if (m >= M) continue;
-            const f32x4 v = acc[i][j];
-            float *o = out + (long)m * ldo + n;
-            if (vec && n + 4 <= N) *(f32x4 *)o = v;
-            else
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (n + r < N) o[r] = v[r];
+            if (m < M) put4(out, join, (long)m * N + n, acc[i][j], 0, N - n, vec);
         }
 }
 
@@ -339,7 +349,7 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
 // ---------------------------------------------------------------------------------------------
 template <int MT, bool KS, bool KT>
 __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ P, long ldp, const float *__restrict__ Q, long ldq,
-                                                      float *out, int M, int N, int K, int vec) {
+                                                      float *out, int M, int N, int K, int vec, Join join) {
     constexpr int TN = 2, NQ = (MT + 1) / 2;                        // n tiles of a wave, rows of Q a thread
     constexpr int PF = MT >= 6 ? 2 : MT == 2 ? 4 : 3, QF = MT >= 6 ? 1 : PF;   // stages of P and of Q under way
     constexpr int PL = 2 * NQ * 64, ST = 2 * 3 * PL;                // 16-byte units of a plane of 32 k, of a stage
@@ -597,18 +607,14 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
             // NT: tile t, four n from 4 lg2; KS: the two tiles take turns, four n from 8 lg2 + 4 t
             const int n = n0 + (KS ? 8 * lg2 + 4 * t : 16 * t + 4 * lg2);
             const f32x4 x = KS ? (f32x4){v[0][2 * t], v[1][2 * t], v[0][2 * t + 1], v[1][2 * t + 1]} : v[t];
-            float *o = out + (long)m * N + n;
-            if (vec && n >= nown) *(f32x4 *)o = x;
-            else
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (n + r >= nown) o[r] = x[r];
+            put4(out, join, (long)m * N + n, x, nown - n, 4, vec);
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Weight update: W[M,N] += alpha * sum_r G[r,M] X[r,N], both operands k-strided, with k_gemm_x3's pieces and accumulators.
+// Weight update: W[M,N] += alpha * sum_r G[r,M] X[r,N], both operands k-strided, with k_gemm_x3's pieces and accumulators, and
+// with bias bias[M] += alpha * sum_r G[r,M], by the workgroups of the first columns.  FEW: G2, if given, is added to G.
 // Bound by reading and writing W once up to about 150 rows, by the matrix pipe and the cutting beyond.  Workgroup of four
 // waves on 64 m x 128 n (rows of 512 B), 64 m x 32 n a wave.  G is cut for the whole tile, 128 r at a time, and shared through
 // LDS; a wave's columns of X are its own and go from memory straight into matrix operands, cut in registers, a chunk of 32 r
@@ -621,12 +627,13 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
 // rows 41 and 90; 1024 x 32000 by 40 rows 65 and 84; 4000 x 1000 by 4 rows 9.6 and 9.3.  Two workgroups a compute unit
 // with X two chunks ahead: 277 us at 32000 x 4096 by 60 rows, 49 at 4096 x 4096 by 128.
 // ---------------------------------------------------------------------------------------------
+enum { UPD_FEW = 32 };
 template <bool FEW>
-__global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ G, const float *__restrict__ X, float *W, int M,
-                                                      int N, int rows, float alpha) {
+__global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ G, const float *__restrict__ G2, const float *__restrict__ X,
+                                                      float *W, float *bias, int M, int N, int rows, float alpha) {
     constexpr int BM = 64, BN = 128, TM = BM / 16, TN = 2, PL = TM * 64, LDO = BN + 4, NC = FEW ? 1 : 4;
     __shared__ u32x4 gs[FEW ? BM * LDO / 4 : NC * 3 * PL];   // [chunk][plane][m tile][64 lanes]; then the sums [BM][LDO]
-    __shared__ float tops[4];
+    __shared__ float tops[4], bsum[4][BM];
     static_assert(BM * LDO * 4 <= (int)sizeof(gs), "the sums fit where the pieces were");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15, lg = l >> 4;
     const int ntn = (N + BN - 1) / BN, ntm = (M + BM - 1) / BM;
@@ -639,7 +646,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     const int nx = n0 + wave * 32 + 2 * li, nl = max(min(nx, N - 2), 0);
     const bool edge = n0 + BN > N, whole = !edge && m0 + BM <= M, second = nx > nl;
     f32x2 xv[8];
-    float gtop = 0.f, xtop = 0.f;   // largest magnitudes
+    float gtop = 0.f, xtop = 0.f, gsum = 0.f;   // largest magnitudes, this thread's share of its column's sum
     auto load_x = [&](int r0) __attribute__((always_inline)) {
         if (r0 + 32 <= rows && N > 1 && N < 1 << 25) {
             unsigned off = 4u * (8u * lg * (unsigned)N + nl);
@@ -734,7 +741,17 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 gv[i][e] = *(const float *)((const char *)(G + m0 + (size_t)min(rb + 32 * i + 8 * wave + e, rows - 1) * M) + goff);
-        if (FEW) load_old();
+        float g2[FEW ? 8 : 1];
+        if (FEW) {
+            if (G2)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    g2[FEW ? e : 0] = *(const float *)((const char *)(G2 + m0 + (size_t)min(8 * wave + e, rows - 1) * M) + goff);
+            load_old();
+            if (G2)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) gv[0][e] += g2[FEW ? e : 0];
+        }
         if (!FEW && rb) __syncthreads();   // the pieces of the rows before have been read
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -744,6 +761,9 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     if (rb + 32 * i + 8 * wave + e >= rows) gv[i][e] = 0.f;
+                if (bias)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) gsum += gv[i][e];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     uint32_t p, q, r;
@@ -787,7 +807,9 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     // the largest magnitudes of G's columns and of this wave's columns of X
     for (int o = 32; o > 0; o >>= 1) { gtop = fmaxf(gtop, __shfl_xor(gtop, o)); xtop = fmaxf(xtop, __shfl_xor(xtop, o)); }
     if (l == 0) tops[wave] = gtop;
+    bsum[wave][l] = gsum;
     __syncthreads();
+    if (bias && n0 == 0 && wave == 0 && m0 + l < M) bias[m0 + l] += alpha * ((bsum[0][l] + bsum[1][l]) + (bsum[2][l] + bsum[3][l]));
     gtop = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
     if (!pieces_hold(gtop) || !pieces_hold(xtop)) {
         // once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds r = g of column i), four r a step
@@ -804,7 +826,8 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
             if (r >= rows) xe = (f32x2){0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < TM; ++j) {
-                const float x = G[rc * M + min(m0 + 16 * j + li, M - 1)], ge = r < rows ? x : 0.f;
+                const size_t at = rc * M + min(m0 + 16 * j + li, M - 1);
+                const float x = FEW && G2 ? G[at] + G2[at] : G[at], ge = r < rows ? x : 0.f;
 #pragma unroll
                 for (int t = 0; t < TN; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xe[t], ge, acc[t][j], 0, 0, 0);
             }
@@ -859,44 +882,43 @@ int x3_splits(int M, int N, int K, size_t room) {
 }
 
 template <int BM, bool PKS>
-void launch_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *C, long ldc, float *part, int S,
-               int M, int N, int K) {
+void launch_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *out, int S, int M, int N, int K,
+               const Join &join) {
     const size_t sm = (size_t)2 * 3 * (X3_BN + BM) / 16 * 64 * 16;
     constexpr int DEPTH = BM <= 64 ? 4 : 2;
     static OncePerDevice once;
     allow_lds(once, (const void *)k_gemm_x3<BM, PKS, DEPTH>, sm);
-    const long ldo = part ? N : ldc;
-    const int vec = ldo % 4 == 0 && ((uintptr_t)(part ? part : C) & 15) == 0 && (!part || (size_t)M * N % 4 == 0);
+    const int vec = N % 4 == 0 && ((uintptr_t)out & 15) == 0 && join_aligned(join);
     const dim3 grid(((N + X3_BN - 1) / X3_BN + 7) / 8 * 8 * ((M + BM - 1) / BM), S);
-    k_gemm_x3<BM, PKS, DEPTH><<<grid, 256, sm, st>>>(P, ldp, Q, ldq, C, ldc, part, M, N, K, vec);
+    k_gemm_x3<BM, PKS, DEPTH><<<grid, 256, sm, st>>>(P, ldp, Q, ldq, out, M, N, K, vec, join);
 }
 template <bool PKS>
-void gemm_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *C, long ldc, float *part, int S,
-             int M, int N, int K) {
-    if (M <= 32) launch_x3<32, PKS>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K);
-    else if (M <= 64) launch_x3<64, PKS>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K);
-    else launch_x3<128, PKS>(st, P, ldp, Q, ldq, C, ldc, part, S, M, N, K);
+void gemm_x3(hipStream_t st, const float *P, long ldp, const float *Q, long ldq, float *out, int S, int M, int N, int K,
+             const Join &join) {
+    if (M <= 32) launch_x3<32, PKS>(st, P, ldp, Q, ldq, out, S, M, N, K, join);
+    else if (M <= 64) launch_x3<64, PKS>(st, P, ldp, Q, ldq, out, S, M, N, K, join);
+    else launch_x3<128, PKS>(st, P, ldp, Q, ldq, out, S, M, N, K, join);
 }
 template <int MT, bool KS, bool KT>
-void launch_stream(hipStream_t st, const float *P, long ldp, const float *X, float *out, int S, int M, int N, int K) {
+void launch_stream(hipStream_t st, const float *P, long ldp, const float *X, float *out, int S, int M, int N, int K, const Join &join) {
     constexpr size_t sm = (size_t)2 * 2 * 3 * ((MT + 1) / 2 * 2) * 1024;
     static OncePerDevice once;
     allow_lds(once, (const void *)k_stream_x3<MT, KS, KT>, sm);
-    const int vec = N % 4 == 0 && ((uintptr_t)out & 15) == 0;
+    const int vec = N % 4 == 0 && ((uintptr_t)out & 15) == 0 && join_aligned(join);
     const dim3 grid(((N + 127) / 128 + 7) / 8 * 8 * ((M + MT * 16 - 1) / (MT * 16)), S);
-    k_stream_x3<MT, KS, KT><<<grid, 512, sm, st>>>(P, ldp, X, K, out, M, N, K, vec);
+    k_stream_x3<MT, KS, KT><<<grid, 512, sm, st>>>(P, ldp, X, K, out, M, N, K, vec, join);
 }
-// C[M,N] = X[M,K] P, P(k, n) = W[n,K] or (KS) W[K,n]; split sums to part (S > 1) or straight to C
+// C[M,N] = X[M,K] P, P(k, n) = W[n,K] or (KS) W[K,n]; split sums to part (S > 1) or straight to C, joined to logits if any
 template <bool KS>
-void gemm_weights(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
+void gemm_weights(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K, const Join &join) {
+    float *out = S > 1 ? part : C;
     const long ldp = KS ? N : K;
     // What k_stream_x3 does not take, and workgroups of up to four stages, which are over before its loads ahead are worth
     // their start (a head step of 10 rows at 512 x 4000: 125 us all streamed, 115 so; discriminator step of 4 rows 81 and 75;
     // of 290 rows at 512 x 32000 805 and 785; up to eight stages: 90 rows at 512 x 32000 377 and 412 us).
     if (N < 32 || K < 64 || N >= 1 << 23 || K >= 1 << 23 || (K + 63) / 64 <= 4 * S)
-        return gemm_x3<KS>(st, W, ldp, X, K, C, N, S > 1 ? part : nullptr, S, M, N, K);
-    float *out = S > 1 ? part : C;
-#define KOALA_STREAM(MT) return K % 64 ? launch_stream<MT, KS, true>(st, W, ldp, X, out, S, M, N, K) : launch_stream<MT, KS, false>(st, W, ldp, X, out, S, M, N, K)
+        return gemm_x3<KS>(st, W, ldp, X, K, out, S, M, N, K, join);
+#define KOALA_STREAM(MT) return K % 64 ? launch_stream<MT, KS, true>(st, W, ldp, X, out, S, M, N, K, join) : launch_stream<MT, KS, false>(st, W, ldp, X, out, S, M, N, K, join)
     switch (x3_tiles(M)) {
         case 2: KOALA_STREAM(2);
         case 3: KOALA_STREAM(3);
@@ -906,31 +928,30 @@ void gemm_weights(hipStream_t st, const float *X, const float *W, float *C, floa
     }
 #undef KOALA_STREAM
 }
-void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
-    gemm_weights<false>(st, X, W, C, part, S, M, N, K);
+void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K, const Join &join = {}) {
+    gemm_weights<false>(st, X, W, C, part, S, M, N, K, join);
 }
 void gemm_nn(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
-    gemm_weights<true>(st, X, W, C, part, S, M, N, K);
+    gemm_weights<true>(st, X, W, C, part, S, M, N, K, Join{});
 }
-// W[M,N] -= lr * G[rows,M]^T X[rows,N]
-void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr) {
+// W[M,N] -= lr * G[rows,M]^T X[rows,N] and (bias not null) bias[M] -= lr * column sums of G; G2 (up to UPD_FEW rows, may be
+// null) is added to G
+void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr, float *bias = nullptr,
+                 const float *G2 = nullptr) {
     const long tiles = (long)((M + 63) / 64) * ((N + 127) / 128);
     const int grid = (int)((tiles + 7) / 8 * 8);
-    if (rows <= 32) k_update_x3<true><<<grid, 256, 0, st>>>(G, X, W, M, N, rows, -lr);
-    else k_update_x3<false><<<grid, 256, 0, st>>>(G, X, W, M, N, rows, -lr);
+    if (rows <= UPD_FEW) k_update_x3<true><<<grid, 256, 0, st>>>(G, G2, X, W, bias, M, N, rows, -lr);
+    else k_update_x3<false><<<grid, 256, 0, st>>>(G, nullptr, X, W, bias, M, N, rows, -lr);
 }
 
 // The S split sums of element i added in split order, and the element-wise step that follows the product:
-//   SUM_ONLY  out = sum;  SUM_BASE  out = base + sum;
+//   SUM_ONLY  out = sum;  SUM_MASK  out = sum where base > 0, else 0;
 //   SUM_RELU  out = sum + bias[column] (the pre-activation), out2 = max(out, 0);
-//   SUM_SILU  out = sum, out2 = base + SiLU(sum).
+//   SUM_SILU  out = sum, out2 = base + SiLU(sum);
+//   SUM_BACK  out = sum (+ add), out2 = out * SiLU'(base).
 // part may be out itself (S = 1).
-enum { SUM_ONLY = 0, SUM_BASE = 1, SUM_RELU = 2, SUM_SILU = 3 };
-template <int MODE>
-__global__ __launch_bounds__(256) void k_sum_parts(const float *part, int S, long count, int N, const float *base,
-                                                   float *out, float *out2) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
+enum { SUM_ONLY, SUM_MASK, SUM_RELU, SUM_SILU, SUM_BACK };
+__device__ __forceinline__ float split_sum(const float *part, int S, long count, long i) {
     float v = 0.f;
     int s = 0;
     for (; s + 8 <= S; s += 8) {
@@ -941,15 +962,29 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float *part, int S, lon
         for (int u = 0; u < 8; ++u) v += t[u];
     }
     for (; s < S; ++s) v += part[(long)s * count + i];
-    if (MODE == SUM_BASE) v += base[i];
+    return v;
+}
+template <int MODE>
+__global__ __launch_bounds__(256) void k_sum_parts(const float *part, int S, long count, int N, const float *base,
+                                                   float *out, float *out2, const float *add) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= count) return;
+    float v = split_sum(part, S, count, i);
+    if (MODE == SUM_MASK && !(base[i] > 0.f)) v = 0.f;
+    if (MODE == SUM_BACK) {
+        if (add) v += add[i];
+        const float y = base[i], g = 1.0f / (1.0f + expf(-y));
+        out2[i] = v * g * (1.0f + y * (1.0f - g));
+    }
     if (MODE == SUM_RELU) { v += base[i % N]; out2[i] = fmaxf(v, 0.f); }
     if (MODE == SUM_SILU) out2[i] = base[i] + v / (1.0f + expf(-v));
     out[i] = v;
 }
 template <int MODE>
-void sum_parts(hipStream_t st, const float *part, int S, int M, int N, const float *base, float *out, float *out2) {
+void sum_parts(hipStream_t st, const float *part, int S, int M, int N, const float *base, float *out, float *out2,
+               const float *add = nullptr) {
     const long count = (long)M * N;
-    k_sum_parts<MODE><<<(int)((count + 255) / 256), 256, 0, st>>>(part, S, count, N, base, out, out2);
+    k_sum_parts<MODE><<<(int)((count + 255) / 256), 256, 0, st>>>(part, S, count, N, base, out, out2, add);
 }
 
 __device__ __forceinline__ float softplus(float x) { return fmaxf(x, 0.f) + log1pf(expf(-fabsf(x))); }
@@ -983,22 +1018,15 @@ __device__ __forceinline__ float block_max(float v, float *sh) {
     return t;
 }
 
-// The mapped hidden state z[p][v], in two halves z0 + z1 (z1 may be null), joined to a logits row: u[p] = z + la[p] and,
-// with lb, u[n + p] = z + lb[p].  The halves may lie where u does (row p and row n + p).
+// The mapped hidden state z0 + z1, the sums of two K splits, joined to the logits as by a product's Join.  The halves may lie
+// where u does (row p and row n + p).
 __global__ __launch_bounds__(256) void k_join(const float *z0, const float *z1, const float *la, const float *lb, float *u,
                                               long nV) {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= nV) return;
-    float z = z0[i];
-    if (z1) z += z1[i];
+    const float z = z0[i] + z1[i];
     u[i] = z + la[i];
     if (lb) u[nV + i] = z + lb[i];
-}
-
-// g[r][j] *= (pre[r][j] > 0)
-__global__ void k_relu_back(float *g, const float *pre, long n) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && !(pre[i] > 0.f)) g[i] = 0.f;
 }
 
 // s[r] = a[r] . w: the width-1 layer.  One workgroup per row.
@@ -1011,44 +1039,53 @@ __global__ __launch_bounds__(256) void k_row_dot(const float *a, const float *w,
     if (threadIdx.x == 0) s[blockIdx.x] = v;
 }
 
-// bias[j] -= lr * sum_r g[r][j]
-__global__ void k_bias_update(float *bias, const float *g, int rows, int W, float lr) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= W) return;
-    float t = 0.f;
-    for (int r = 0; r < rows; ++r) t += g[(long)r * W + j];
-    bias[j] -= lr * t;
+// SUM_RELU of row r and the width-1 layer behind it, s[r] = out2[r] . w.  One workgroup per row.
+__global__ __launch_bounds__(1024) void k_sum_relu_dot(const float *part, int S, long count, int N, const float *bias, float *pre,
+                                                       float *act, const float *w, float *s) {
+    __shared__ float sh[16];
+    const long at = (long)blockIdx.x * N;
+    float dot = 0.f;
+    for (int j = threadIdx.x; j < N; j += 1024) {
+        const float v = split_sum(part, S, count, at + j) + bias[j], a = fmaxf(v, 0.f);
+        pre[at + j] = v;
+        act[at + j] = a;
+        dot += a * w[j];
+    }
+    dot = block_sum<16>(dot, sh);
+    if (threadIdx.x == 0) s[blockIdx.x] = dot;
 }
 
-// Scores s (pre-sigmoid, the last layer's bias already added) -> dL/ds per row and the loss.  One workgroup.
+// Scores s (pre-sigmoid; the last layer's bias is added here) -> dL/ds per row and the loss, and the width-1 layer's input
+// gradient g[r][j] = ds[r] w[j], zero where the unit was off (pre, if given).
 //   mode 0 (Eq. 6): rows [0, n) are the draft's, [n, 2n) the target's:
 //          L_D = mean softplus(s_d) + mean softplus(-s_q);  ds_d = sigmoid(s)/n, ds_q = -(1 - sigmoid(s))/n
 //   mode 1 (Eq. 5, adversarial term): n draft rows: L = lambda mean softplus(-s); ds = -lambda (1 - sigmoid(s))/n
-__global__ __launch_bounds__(256) void k_score_loss(const float *s, const float *bias_p, float *ds, float *loss, int n,
-                                                    int mode, float lambda) {
-    __shared__ float sh[4];
+// grid: nb workgroups a row for g, each with the row's ds worked out for itself, and one for ds and the loss.
+struct ScoreLoss { int n, mode; float lambda; float *loss; };
+__global__ __launch_bounds__(256) void k_score_outer(const float *s, const float *bias_p, float *ds, ScoreLoss t, const float *w,
+                                                     const float *pre, float *g, int rows, int W, int nb) {
     const float bias = bias_p[0];
-    float part = 0.f;
-    const int rows = mode == 0 ? 2 * n : n;
-    for (int r = threadIdx.x; r < rows; r += 256) {
-        const float v = s[r] + bias;
-        if (mode == 0) {
-            part += r < n ? softplus(v) : softplus(-v);
-            ds[r] = r < n ? sigmoidf(v) / n : -(1.0f - sigmoidf(v)) / n;
-        } else {
-            part += lambda * softplus(-v);
-            ds[r] = -lambda * (1.0f - sigmoidf(v)) / n;
+    auto slope = [&](int r, float v) {
+        if (t.mode == 0) return r < t.n ? sigmoidf(v) / t.n : -(1.0f - sigmoidf(v)) / t.n;
+        return -t.lambda * (1.0f - sigmoidf(v)) / t.n;
+    };
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ float sh[4];
+        float part = 0.f;
+        for (int r = threadIdx.x; r < rows; r += 256) {
+            const float v = s[r] + bias;
+            if (t.mode == 0) part += r < t.n ? softplus(v) : softplus(-v);
+            else part += t.lambda * softplus(-v);
+            ds[r] = slope(r, v);
         }
+        const float tot = block_sum(part, sh);
+        if (threadIdx.x == 0) t.loss[0] = tot / t.n;
+        return;
     }
-    const float tot = block_sum(part, sh);
-    if (threadIdx.x == 0) loss[0] = tot / n;
-}
-
-// g[r][j] = ds[r] * w[j] (backward of the width-1 layer towards its input), zero where the unit was off (pre, if given)
-__global__ void k_outer(const float *ds, const float *w, const float *pre, float *g, int rows, int W) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long)rows * W) return;
-    g[i] = pre && !(pre[i] > 0.f) ? 0.f : ds[i / W] * w[i % W];
+    const int r = (int)(blockIdx.x / (unsigned)nb), j = (int)(blockIdx.x % (unsigned)nb) * 256 + threadIdx.x;
+    if (j >= W) return;
+    const size_t i = (size_t)r * W + j;
+    g[i] = pre && !(pre[i] > 0.f) ? 0.f : slope(r, s[r] + bias) * w[j];
 }
 
 // gz[p][v] = gu[p][v] + gu[n + p][v]
@@ -1124,14 +1161,6 @@ __global__ __launch_bounds__(256) void k_mean(const float *ce, float *loss, int 
     if (threadIdx.x == 0) loss[0] = t / n;
 }
 
-// gy = gx * SiLU'(y)
-__global__ void k_silu_back(const float *gx, const float *y, float *gy, long n) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float s = 1.0f / (1.0f + expf(-y[i]));
-    gy[i] = gx[i] * s * (1.0f + y[i] * (1.0f - s));
-}
-
 inline int blocks(long n) { return (int)((n + 255) / 256); }
 inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
@@ -1179,53 +1208,52 @@ bool params_ok(const koala_disc_shape *s, const koala_disc_params *p) {
 inline int fc_in(const koala_disc_shape &s, int k) { return k == 0 ? s.vocab : s.fc_hidden; }
 inline int fc_out(const koala_disc_shape &s, int k) { return k == s.n_fc - 1 ? 1 : s.fc_hidden; }
 
-// z = h W_lin^T joined to one or two sets of logits rows.  Where its tiles do not fill the chip, two K splits, whose sums lie
-// where u will.
+// z = h W_lin^T joined to one or two sets of logits rows, where the product stores it or (its tiles do not fill the chip) by
+// k_join on the sums of two K splits, which lie where u will.
 void disc_join(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, const float *h,
                const float *la, const float *lb) {
     const long nV = (long)n * s.vocab;
     const int S = x3_splits(n, s.vocab, s.hidden, (size_t)2 * nV);
-    gemm_nt(st, h, p.w_lin, w.z, w.u, S, n, s.vocab, s.hidden);
-    k_join<<<blocks(nV), 256, 0, st>>>(S == 2 ? w.u : w.z, S == 2 ? w.u + nV : nullptr, la, lb, w.u, nV);
+    if (S == 1) return gemm_nt(st, h, p.w_lin, w.u, nullptr, 1, n, s.vocab, s.hidden, Join{la, lb, nV});
+    gemm_nt(st, h, p.w_lin, nullptr, w.u, 2, n, s.vocab, s.hidden);
+    k_join<<<blocks(nV), 256, 0, st>>>(w.u, w.u + nV, la, lb, w.u, nV);
 }
 
 // scores of `rows` joined rows u: leaves every layer's input and pre-activation in the workspace, s = w_last . a.
 // g[0], which only the backward pass fills, holds the split sums of the inner layers.
 void disc_forward(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, int rows) {
-    for (int k = 0; k < s.n_fc; ++k) {
-        const int in = fc_in(s, k), out = fc_out(s, k);
-        if (k == s.n_fc - 1) {   // width 1 (bias added where the score is used)
-            k_row_dot<<<rows, 256, 0, st>>>(w.a[k], p.w_fc[k], w.s, in);
-        } else {
-            const int S = x3_splits(rows, out, in, (size_t)2 * n * s.vocab);
-            gemm_nt(st, w.a[k], p.w_fc[k], w.pre[k], w.g[0], S, rows, out, in);
-            sum_parts<SUM_RELU>(st, S > 1 ? w.g[0] : w.pre[k], S, rows, out, p.b_fc[k], w.pre[k], w.a[k + 1]);
-        }
+    const int last = s.n_fc - 1;   // width 1 (bias added where the score is used)
+    if (last == 0) k_row_dot<<<rows, 256, 0, st>>>(w.a[0], p.w_fc[0], w.s, s.vocab);
+    for (int k = 0; k < last; ++k) {
+        const int in = fc_in(s, k), out = fc_out(s, k), S = x3_splits(rows, out, in, (size_t)2 * n * s.vocab);
+        gemm_nt(st, w.a[k], p.w_fc[k], w.pre[k], w.g[0], S, rows, out, in);
+        const float *part = S > 1 ? w.g[0] : w.pre[k];
+        if (k + 1 < last) sum_parts<SUM_RELU>(st, part, S, rows, out, p.b_fc[k], w.pre[k], w.a[k + 1]);
+        else k_sum_relu_dot<<<rows, 1024, 0, st>>>(part, S, (long)rows * out, out, p.b_fc[k], w.pre[k], w.a[k + 1], p.w_fc[last], w.s);
     }
 }
 
-// from ds (dL/ds per row) back to g[0] = dL/du; lr > 0: the parameters are updated on the way (each layer's
-// input gradient is taken with the layer's old weights first).  z (the mapped hidden state, no longer needed) holds the
-// split sums of the inner layers' input gradients.
+// from the scores to the loss, ds (dL/ds per row) and back to g[0] = dL/du; lr > 0: the parameters are updated on the way (each
+// layer's input gradient is taken with the layer's old weights first).  z (used only here) holds the split sums of the inner
+// layers' input gradients.
 void disc_backward(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, int rows,
-                   float lr) {
+                   float lr, const ScoreLoss &t) {
     for (int k = s.n_fc - 1; k >= 0; --k) {
         const int in = fc_in(s, k), out = fc_out(s, k);
         const float *gout = k == s.n_fc - 1 ? w.ds : w.g[k + 1];   // dL/d(pre of layer k): [rows, out]
         const float *pre = k > 0 ? w.pre[k - 1] : nullptr;
         if (k == s.n_fc - 1) {
-            k_outer<<<blocks((long)rows * in), 256, 0, st>>>(w.ds, p.w_fc[k], pre, w.g[k], rows, in);
+            const int nb = (in + 255) / 256;
+            k_score_outer<<<rows * nb + 1, 256, 0, st>>>(w.s, p.b_fc[k], w.ds, t, p.w_fc[k], pre, w.g[k], rows, in, nb);
         } else {
             const int S = x3_splits(rows, in, out, (size_t)n * s.vocab);
             gemm_nn(st, gout, p.w_fc[k], w.g[k], w.z, S, rows, in, out);
-            if (S > 1) sum_parts<SUM_ONLY>(st, w.z, S, rows, in, nullptr, w.g[k], nullptr);
-            if (pre) k_relu_back<<<blocks((long)rows * in), 256, 0, st>>>(w.g[k], pre, (long)rows * in);
+            const float *part = S > 1 ? w.z : w.g[k];
+            if (pre) sum_parts<SUM_MASK>(st, part, S, rows, in, pre, w.g[k], nullptr);
+            else if (S > 1) sum_parts<SUM_ONLY>(st, part, S, rows, in, nullptr, w.g[k], nullptr);
         }
-        if (lr > 0.f) {
-            // W_k[out, in] -= lr * gout^T a_k ;  b_k -= lr * column sums of gout
-            gemm_update(st, gout, w.a[k], p.w_fc[k], out, in, rows, lr);
-            k_bias_update<<<blocks(out), 256, 0, st>>>(p.b_fc[k], gout, rows, out, lr);
-        }
+        // W_k[out, in] -= lr * gout^T a_k ;  b_k -= lr * column sums of gout
+        if (lr > 0.f) gemm_update(st, gout, w.a[k], p.w_fc[k], out, in, rows, lr, p.b_fc[k]);
     }
 }
 
@@ -1254,12 +1282,15 @@ koala_status koala_train_disc_step(const koala_disc_shape *shape, const koala_di
     // z = h W_lin^T, u = [z + d ; z + q]
     disc_join(st, s, *params, w, n, h, d_logits, q_logits);
     disc_forward(st, s, *params, w, n, rows);
-    k_score_loss<<<1, 256, 0, st>>>(w.s, params->b_fc[s.n_fc - 1], w.ds, loss_out, n, 0, 0.f);
-    disc_backward(st, s, *params, w, n, rows, lr);
+    disc_backward(st, s, *params, w, n, rows, lr, ScoreLoss{n, 0, 0.f, loss_out});
     if (lr > 0.f) {
         // u = W_lin h + logits for both halves: dL/dW_lin = (g_u[draft rows] + g_u[target rows])^T h
-        k_fold_rows<<<blocks((long)n * V), 256, 0, st>>>(w.g[0], w.z, n, V);
-        gemm_update(st, w.z, h, params->w_lin, V, H, n, lr);
+        if (n <= UPD_FEW) {
+            gemm_update(st, w.g[0], h, params->w_lin, V, H, n, lr, nullptr, w.g[0] + (size_t)n * V);
+        } else {
+            k_fold_rows<<<blocks((long)n * V), 256, 0, st>>>(w.g[0], w.z, n, V);
+            gemm_update(st, w.z, h, params->w_lin, V, H, n, lr);
+        }
     }
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }
@@ -1278,8 +1309,7 @@ koala_status koala_train_gen_grad(const koala_disc_shape *shape, const koala_dis
     const int n = n_rows, V = s.vocab, H = s.hidden;
     disc_join(st, s, *params, w, n, h, d_logits, nullptr);
     disc_forward(st, s, *params, w, n, n);
-    k_score_loss<<<1, 256, 0, st>>>(w.s, params->b_fc[s.n_fc - 1], w.ds, loss_out, n, 1, lambda);
-    disc_backward(st, s, *params, w, n, n, 0.f);
+    disc_backward(st, s, *params, w, n, n, 0.f, ScoreLoss{n, 1, lambda, loss_out});
     // dL_G/dd = dL_adv/du (u = z + d) + the distillation term's gradient
     k_distill<<<n, 1024, 0, st>>>(q_logits, d_logits, w.g[0], grad_d, w.ce, V, n);
     k_mean<<<1, 256, 0, st>>>(w.ce, loss_out + 1, n);
@@ -1365,16 +1395,16 @@ koala_status koala_train_medusa_head_step(void *hip_stream, int n_rows, int hidd
     MedWs w = med_carve(n, H, K, h, workspace, workspace_bytes);
     medusa_forward(st, n, H, K, blocks_w, w);
     const int Sv = x3_splits(n, H, V, w.room), Sh = x3_splits(n, H, H, w.room);
-    gemm_nn(st, grad_d, w_lm, w.gx, w.part, Sv, n, H, V);                 // gx = grad_d W_lm
-    if (Sv > 1) sum_parts<SUM_ONLY>(st, w.part, Sv, n, H, nullptr, w.gx, nullptr);
+    gemm_nn(st, grad_d, w_lm, w.gx, w.part, Sv, n, H, V);                 // gx = grad_d W_lm, gy = gx * SiLU'(y)
+    sum_parts<SUM_BACK>(st, Sv > 1 ? w.part : w.gx, Sv, n, H, w.y[K - 1], w.gx, w.gy);
     for (int k = K - 1; k >= 0; --k) {
-        k_silu_back<<<blocks((long)n * H), 256, 0, st>>>(w.gx, w.y[k], w.gy, (long)n * H);
-        if (k > 0) {   // gx <- gx + gy W_k with the block's old weights, for the block below
-            gemm_nn(st, w.gy, blocks_w[k], w.gx2, w.part, Sh, n, H, H);
-            sum_parts<SUM_BASE>(st, Sh > 1 ? w.part : w.gx2, Sh, n, H, w.gx, w.gx2, nullptr);
+        // gx <- gx + gy W_k with the block's old weights, and gy for the block below
+        if (k > 0) gemm_nn(st, w.gy, blocks_w[k], w.gx2, w.part, Sh, n, H, H);
+        gemm_update(st, w.gy, w.x[k], blocks_w[k], H, H, n, lr);             // W_k -= lr * gy^T x_k
+        if (k > 0) {
+            sum_parts<SUM_BACK>(st, Sh > 1 ? w.part : w.gx2, Sh, n, H, w.y[k - 1], w.gx2, w.gy, w.gx);
             std::swap(w.gx, w.gx2);
         }
-        gemm_update(st, w.gy, w.x[k], blocks_w[k], H, H, n, lr);             // W_k -= lr * gy^T x_k
     }
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
 }
