@@ -1978,6 +1978,18 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_tree(const u32x4 *qf_in, cons
         for (int dt = 0; dt < DT; ++dt) acc_o[mt][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     __syncthreads();
+    // Heads of 128: one workgroup fits a compute unit anyway, so a wave has the registers to keep the query fragments (eight
+    // sequences of the 33B shape: 1799 -> 1790 us for two layers); heads of 64 would lose their second workgroup.
+    constexpr bool QREG = DH == 128;
+    auto query = [&](int mt, int ks, int z) { return __builtin_bit_cast(bf16x8, qf[((mt * KS + ks) * 2 + z) * 64 + l]); };
+    bf16x8 qr[QREG ? MT : 1][QREG ? KS : 1][2];
+    if (QREG)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int z = 0; z < 2; ++z) qr[QREG ? mt : 0][QREG ? ks : 0][z] = query(mt, ks, z);
 
     for (int st = s + nsplit * wave; st < nsteps; st += tstride) {
         const int k0 = st * 32;
@@ -1991,8 +2003,8 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_tree(const u32x4 *qf_in, cons
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                const bf16x8 qh = __builtin_bit_cast(bf16x8, qf[((mt * KS + ks) * 2 + 0) * 64 + l]);
-                const bf16x8 ql = __builtin_bit_cast(bf16x8, qf[((mt * KS + ks) * 2 + 1) * 64 + l]);
+                const bf16x8 qh = QREG ? qr[QREG ? mt : 0][QREG ? ks : 0][0] : query(mt, ks, 0);
+                const bf16x8 ql = QREG ? qr[QREG ? mt : 0][QREG ? ks : 0][1] : query(mt, ks, 1);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const bf16x8 ka = __builtin_bit_cast(bf16x8, kf[j][ks]);
@@ -2144,8 +2156,14 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_tree(const u32x4 *qf_in, cons
         const int row = (mt0 + mt) * 16 + li;
         if (row < rows_per_seq) {
             const size_t r = (size_t)b * rows_per_seq + row;
-            const size_t o = (((r * n_heads + h) * nsplit + s) * DH) * 2;
             const f32x4 v = O * (L > 0.f ? 1.0f / L : 0.f);
+            if (nsplit == 1) {   // nothing to merge with: the average is the result, in its place in the input fragments
+                const int k0 = h * DH + dt * 16 + 4 * lg, m = (int)r;
+                u32x2 *dst = (u32x2 *)(a.Xf + ((size_t)(k0 >> 5) * a.MT_out + (m >> 4)) * 64 + (m & 15) + 16 * ((k0 & 31) >> 3));
+                dst[lg & 1] = (u32x2){half_pair(v[0], v[1]), half_pair(v[2], v[3])};
+                continue;
+            }
+            const size_t o = (((r * n_heads + h) * nsplit + s) * DH) * 2;
             st_sc1(ro, o + (dt * 16 + 4 * lg) * 2, (u32x2){half_pair(v[0], v[1]), half_pair(v[2], v[3])});
             if (dt == 0 && lg == 0) {
                 const size_t pm = (((r * n_heads + h) * nsplit + s) * 2) * 4;
@@ -2154,6 +2172,7 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_tree(const u32x4 *qf_in, cons
             }
         }
     }
+    if (nsplit == 1) return;
     // the partial results were written through (sc1), so nothing of a wave's is left in a cache to be written back:
     // it is enough that every wave's stores have been acknowledged before the counter moves
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
