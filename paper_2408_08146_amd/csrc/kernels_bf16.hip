@@ -1545,7 +1545,17 @@ void gemm_packed(hipStream_t st, const void *Wp, const void *Xf, float *P, int N
 #undef KOALA_GEMM
 }
 
-int rows_wide_groups(int Npad) { return (Npad / 16 + 7) / 8; }
+// row groups of a workgroup, at least four (the candidates of a row are then at most 16 per 1024 tokens, which is their room), and
+// the workgroups; 0: more than one a compute unit
+static int rows_logits_units(int Npad, int n_cu) {
+    for (int u : {4, 6, 8})
+        if ((Npad / 16 + u - 1) / u <= n_cu) return u;
+    return 0;
+}
+int rows_logits_groups(int Npad, int n_cu) {
+    const int u = rows_logits_units(Npad, n_cu);
+    return u ? (Npad / 16 + u - 1) / u : 0;
+}
 int big_groups(int Npad, const BigShape &b) { return (Npad / 16 + 4 * b.U - 1) / (4 * b.U); }
 bool rows_wide(int Npad, int n_cu) { return Npad / 16 > 5 * n_cu && (Npad / 16 + 7) / 8 <= n_cu; }
 
@@ -1784,10 +1794,14 @@ static GemmEpi logits_epi(const NormScale &ns, int rows, float *logits, int V, f
 }
 
 void gemm_rows_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const NormScale &ns, int rows,
-                      float *logits, int V, float *cand_val, int *cand_idx, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                      float *logits, int V, float *cand_val, int *cand_idx, int n_cu, hipEvent_t ev_start, hipEvent_t ev_stop) {
     const int Npad = pad64(V);
-    dispatch_gemm_rows_u<8, EPI_LOGITS>(st, Wp, Xf, Npad, K, MTT, 1,
-                                        logits_epi(ns, rows, logits, V, cand_val, cand_idx, rows_wide_groups(Npad)), ev_start, ev_stop);
+    const GemmEpi e = logits_epi(ns, rows, logits, V, cand_val, cand_idx, rows_logits_groups(Npad, n_cu));
+    switch (rows_logits_units(Npad, n_cu)) {
+    case 4: return dispatch_gemm_rows_u<4, EPI_LOGITS>(st, Wp, Xf, Npad, K, MTT, 1, e, ev_start, ev_stop);
+    case 6: return dispatch_gemm_rows_u<6, EPI_LOGITS>(st, Wp, Xf, Npad, K, MTT, 1, e, ev_start, ev_stop);
+    default: return dispatch_gemm_rows_u<8, EPI_LOGITS>(st, Wp, Xf, Npad, K, MTT, 1, e, ev_start, ev_stop);
+    }
 }
 
 void gemm_big_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b, const NormScale &ns,

@@ -258,10 +258,14 @@ int bf_head_logits(koala_ctx *c, hipStream_t st, int rows, int MT, const kb::Nor
                             ev.start, ev.stop);
         return n;
     }
-    if (MT <= 4 && kb::rows_wide(Npad, c->n_cu)) {
+    // Every workgroup takes in all of the rows: with 33 rows and more of many columns that is the longer way where the vocabulary
+    // makes few workgroups (64 rows, one layer at 4096 columns: 4000 tokens, 63 workgroups, 106 us against 102 with K split over
+    // the chip; 8000 tokens 107 and 110, 512 columns and 4000 tokens 46 and 50; 26 rows at 4096 columns and 4000 tokens 83 and 86).
+    const int n = MT <= 4 ? kb::rows_logits_groups(Npad, c->n_cu) : 0;
+    if (n && !(MT == 4 && H >= 2048 && 8 * n < 3 * c->n_cu)) {
         const LaunchEvents ev = timed_launch(c, (double)Npad * H * 2.0);
-        kb::gemm_rows_logits(st, c->w.lm_head, c->xf, H, MT, ns, rows, logits, V, val, idx, ev.start, ev.stop);
-        return kb::rows_wide_groups(Npad);
+        kb::gemm_rows_logits(st, c->w.lm_head, c->xf, H, MT, ns, rows, logits, V, val, idx, c->n_cu, ev.start, ev.stop);
+        return n;
     }
     return 0;
 }

@@ -272,13 +272,14 @@ void gemm_big_qkv(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT
 void gemm_big_swiglu(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b,
                      const NormScale &ns, int rows, void *Xo, int F, float *scratch, size_t room, int *counters,
                      hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// The LM head of V tokens with its logits finished in the GEMM (gemm_rows_logits where rows_wide, gemm_big_logits for MTT >= 8):
-// logits (may be null) [rows][V], and per row and workgroup (rows_wide_groups or big_groups of them) the largest logit and its
-// token to cand_val / cand_idx (may be null), which best_logit merges
-int rows_wide_groups(int Npad);
+// The LM head of V tokens with its logits finished in the GEMM (gemm_rows_logits up to 64 rows, gemm_big_logits for MTT >= 8):
+// logits (may be null) [rows][V], and per row and workgroup (rows_logits_groups or big_groups of them) the largest logit and its
+// token to cand_val / cand_idx (may be null), which best_logit merges.  rows_logits_groups is 0 where the vocabulary is more
+// than one round of compute units with eight row groups each (32768 tokens on 256).
+int rows_logits_groups(int Npad, int n_cu);
 int big_groups(int Npad, const BigShape &b);
 void gemm_rows_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const NormScale &ns, int rows,
-                      float *logits, int V, float *cand_val, int *cand_idx, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+                      float *logits, int V, float *cand_val, int *cand_idx, int n_cu, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 void gemm_big_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int MTT, const BigShape &b, const NormScale &ns,
                      int rows, float *logits, int V, float *cand_val, int *cand_idx, float *scratch, size_t room, int *counters,
                      hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);

@@ -76,6 +76,21 @@ def test_wide_output_head_matches_oracle(vocab, tree):
     compare_logits_and_greedy(c, lg, greedy, rlg, rgreedy)
 
 
+# smaller vocabularies: four, six or eight row groups a workgroup, all of them part-filled somewhere; logits' rows not 16-byte aligned
+@pytest.mark.parametrize("vocab", [5, 64, 1001, 4001, 16384, 16390, 19999])
+@pytest.mark.parametrize("tree", [dict(topk=[], widths=[1]), T17, T64])
+def test_output_head_of_small_vocabularies(vocab, tree):
+    c = Case("cfg2_small", n_layers=1, K=1, ctx=20, capacity=96, hidden=256, n_heads=2, head_dim=128, ffn=256, vocab=vocab, tree=tree)
+    c.fill_kv_normal()
+    c.upload_kv()
+    tt = c.random_tree_tokens()
+    feat, lg, greedy = c.gpu_verify(tt)
+    rfeat, rlg, rgreedy = c.oracle_verify(tt)
+    compare_logits_and_greedy(c, lg, greedy, rlg, rgreedy)
+    assert rel_err_rows(feat, rfeat).max() < c.tol
+    assert np.array_equal(greedy, lg.argmax(-1))
+
+
 @pytest.mark.parametrize("V", [700, 5000])
 def test_fp32_top_k_never_repeats_a_token(V):
     """A not-a-number among the logits compares false with everything, so what a lane of the workgroup has seen of the others
