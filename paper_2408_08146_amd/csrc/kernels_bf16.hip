@@ -1346,7 +1346,8 @@ __global__ __launch_bounds__(256) void k_topk_stage1(const float *P, int S, int 
     }
 }
 
-// The features (the row after the final norm) come from here where stage 1 has no launch of its own.
+// FEAT: the features (the row after the final norm) come from here, where stage 1 has no launch of its own.
+template <bool FEAT>
 __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, const int *cand_idx, int n_cand, int k,
                                                      int32_t *idx, float *val, ChildFill fill, RowScale rs, kb::FeatOut fo) {
     __shared__ float sv[4], best_val[KOALA_TOPK_MAX];
@@ -1361,7 +1362,7 @@ __global__ __launch_bounds__(256) void k_topk_stage2(const float *cand_val, cons
         cv[q] = a < n_cand ? cand_val[(size_t)r * n_cand + a] : -INFINITY;
         ci[q] = a < n_cand ? cand_idx[(size_t)r * n_cand + a] : 0x7fffffff;
     }
-    if (fo.feat) {
+    if (FEAT) {
         const float inv = row_scale(rs, r);
         for (int j = tid * 8; j < fo.H; j += 2048) {   // the hidden size is a multiple of eight
             const float *xr = fo.x + (size_t)r * fo.H + j;
@@ -1783,7 +1784,7 @@ void logits_topk(hipStream_t st, const float *P, int S, int Mp, int ldp, const N
     k_topk_stage1<<<dim3(nchunk, rows), 256, 0, st>>>(P, S, Mp, ldp, mk_scale(ns), logits, ldl, V, k, cand_val,
                                                       cand_idx, fo);
     if (k > 0)
-        k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val, fill, RowScale{}, FeatOut{});
+        k_topk_stage2<false><<<rows, 256, 0, st>>>(cand_val, cand_idx, nchunk * k, k, idx, val, fill, RowScale{}, FeatOut{});
 }
 
 static GemmEpi logits_epi(const NormScale &ns, int rows, float *logits, int V, float *cand_val, int *cand_idx, int n_cand) {
@@ -1815,7 +1816,7 @@ void gemm_big_logits(hipStream_t st, const void *Wp, const void *Xf, int K, int 
 
 void best_logit(hipStream_t st, const float *cand_val, const int *cand_idx, int n_cand, int rows, int32_t *idx,
                 const NormScale &ns, const FeatOut &fo) {
-    k_topk_stage2<<<rows, 256, 0, st>>>(cand_val, cand_idx, n_cand, 1, idx, nullptr, ChildFill{}, mk_scale(ns), fo);
+    k_topk_stage2<true><<<rows, 256, 0, st>>>(cand_val, cand_idx, n_cand, 1, idx, nullptr, ChildFill{}, mk_scale(ns), fo);
 }
 
 }  // namespace kb
@@ -1992,9 +1993,11 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_tree(const u32x4 *qf_in, cons
         for (int dt = 0; dt < DT; ++dt) acc_o[mt][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     __syncthreads();
-    // Heads of 128: one workgroup fits a compute unit anyway, so a wave has the registers to keep the query fragments (eight
-    // sequences of the 33B shape: 1799 -> 1790 us for two layers); heads of 64 would lose their second workgroup.
-    constexpr bool QREG = DH == 128;
+    // Two row tiles of heads of 128: one workgroup fits a compute unit anyway, so a wave has the registers to keep the query
+    // fragments (eight sequences of the 33B shape: 1799 -> 1790 us for two layers).  Heads of 64 would lose their second
+    // workgroup; a single row tile has few reads to save, and passes of a few rows few steps (EAGLE-style drafting at 7B
+    // with it: 0.5 % slower).
+    constexpr bool QREG = DH == 128 && MT == 2;
     auto query = [&](int mt, int ks, int z) { return __builtin_bit_cast(bf16x8, qf[((mt * KS + ks) * 2 + z) * 64 + l]); };
     bf16x8 qr[QREG ? MT : 1][QREG ? KS : 1][2];
     if (QREG)
