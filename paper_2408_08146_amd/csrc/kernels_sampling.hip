@@ -3,7 +3,7 @@
 //   * the acceptance walk keeps child x with probability min(1, q(x)/d(x)); after a rejection the target
 //     distribution becomes norm(max(0, q - d)), the rejected token leaves the draft distribution, and the
 //     next child (in draw order) is tried; where the walk stops, one token is drawn from what q has become.
-// Every uniform random number is an input.  One workgroup of 1024 threads per row / sequence.
+// Every uniform random number is an input.  One workgroup of 1024 threads per row, sequence or node.
 //
 // A draw is an inverse CDF over ascending token id: the first id at which the running sum of the weights
 // exceeds u * total.  The vocabulary is cut into segments of 256 consecutive ids; a wave sums a segment
@@ -14,7 +14,7 @@
 // Two forms.  Up to 32768 tokens a workgroup holds its rows in registers (32 values of a row per thread): a row is read
 // once, every later pass over it is arithmetic, and the draws of a row exchange one number each through LDS.  Larger
 // vocabularies keep their rows in memory and read them again in every pass.  Acceptance for eight sequences of 60 nodes and
-// 32000 tokens: 43 us with the nodes side by side in registers, 88 us with a workgroup a sequence that takes them in turn (100
+// 32000 tokens: 35 us with the nodes side by side in registers, 81 us with a workgroup a sequence that takes them in turn (94
 // with shuffles through LDS in its reductions), 278 us in the memory form.  Draws (the children of 208 nodes, a 64-node
 // Medusa-style tree for eight sequences): 33 us where the memory form takes 427 us.
 #include "koala_internal.h"
@@ -634,13 +634,25 @@ struct WalkShared {
     RegShared r;
     float ua[KOALA_MAX_NODES], ur[KOALA_MAX_NODES];   // in LDS: the rows fill the registers
     int tok[KOALA_MAX_NODES];
+    int off;                                          // found, on the way, not to be on the path
 };
 struct WalkArgs {
     const int32_t *tree_tokens;
     const float *target_logits, *draft_logits, *u_accept, *u_resample;
     int32_t *accept_len, *accept_path, *next_token;
 };
-struct NodeEnd { int child, token; bool mine; };   // the accepted child or, 0, where the walk stops: then token, in the wave that says mine
+// the accepted child or, 0, where the walk stops: then token, in the wave that says mine; -1: not on the path
+struct NodeEnd { int child, token; bool mine; };
+// Nodes side by side: those that their parent has turned down, one bit each, and the bits of a node and its ancestors
+struct Branch {
+    unsigned long long *dead, line;
+    __device__ __forceinline__ void turn_down(unsigned long long kids) const {
+        if (threadIdx.x == 0) __hip_atomic_fetch_or(dead, kids, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ unsigned long long told() const {
+        return __hip_atomic_load(dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
 
 __device__ __forceinline__ void walk_inputs(const WalkArgs &g, int b, int T, int V, WalkShared &sh) {   // read behind the first barrier
     const int tid = threadIdx.x;
@@ -652,13 +664,20 @@ __device__ __forceinline__ void walk_inputs(const WalkArgs &g, int b, int T, int
     }
 }
 
+__device__ __forceinline__ void written_through() {   // this lane's atomics have been performed (see k_accept_nodes)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
 // What happens at node `cur` of sequence b, which depends on nothing that came before: its children are tried in draw order,
 // and where none is accepted a token is drawn.  The draft's row is in registers and the target's in LDS, where a thread only
 // ever touches its own 16-byte pieces (no barriers, no bank conflicts): both in registers with 512 threads spilled.  Both are
 // divided by their sums only once a child has been rejected or a token is drawn; the first child needs two quotients.
-template <int NQ>
+// SIDE: other nodes are under way; they are told of every child turned down, and what they tell ends this one.
+template <int NQ, bool SIDE>
 __device__ __forceinline__ NodeEnd walk_node(const WalkArgs &g, int b, int cur, int T, int V, float inv_tau, int par, int rank,
-                                             f32q *ql, WalkShared &sh) {
+                                             f32q *ql, WalkShared &sh, const Branch &br) {
+    constexpr bool LOOK = SIDE && NQ >= 4;   // passes over rows of up to 4096 tokens are too short to cover the look (13 -> 15 us)
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned long long kids = children_of(par, cur);
@@ -696,7 +715,12 @@ __device__ __forceinline__ NodeEnd walk_node(const WalkArgs &g, int b, int cur, 
         __syncthreads();
         const double qx = (double)sh.r.qx[j & 1], dx = (double)sh.r.dx[j & 1];
         const double ratio = dx > 0.0 ? fmin(1.0, qx / dx) : 0.0;
-        if (dx > 0.0 && (double)sh.ua[c] < ratio) return NodeEnd{c, 0, wave == 0};
+        if (dx > 0.0 && (double)sh.ua[c] < ratio) {
+            if (SIDE) br.turn_down(kids & ~(1ull << c));
+            return NodeEnd{c, 0, wave == 0};
+        }
+        if (SIDE) br.turn_down(1ull << c);
+        const unsigned long long told = LOOK && tid == 0 ? br.told() : 0;   // on its way while the distributions are passed over
         // rejected: q <- norm(max(0, q - d)) (kept if that is all zero); d loses x and is renormalised
         double rs = 0.0, ds = 0.0;
         int xd = xo;
@@ -724,7 +748,9 @@ __device__ __forceinline__ NodeEnd walk_node(const WalkArgs &g, int b, int cur, 
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (LOOK && tid == 0) sh.off = (told & br.line) != 0;
         block_sum2(rs, ds, sh.r);
+        if (LOOK && sh.off) return NodeEnd{-1, 0, wave == 0};
         const bool keep = !(rs > 0.0);
         const double fr = keep ? 1.0 : 1.0 / rs, fd = ds > 0.0 ? 1.0 / ds : 1.0;
 #pragma unroll
@@ -752,6 +778,7 @@ __device__ __forceinline__ NodeEnd walk_node(const WalkArgs &g, int b, int cur, 
 #pragma unroll
         for (int e = 0; e < 4; ++e) q[u][e] = x[e];
     }
+    if (SIDE && wave == 0) written_through();   // what it has told the others, before the barrier behind which any wave may count
     const SegPair seg = segment_pairs<NQ>(q, wave, sh.r);
     const SegPick r = pick_segment(seg, (double)sh.ur[cur]);
     const bool mine = r.s < 0 ? wave == 0 : (r.s & (NW - 1)) == wave;
@@ -780,7 +807,7 @@ __global__ __launch_bounds__(NT) void k_accept_walk(TreeTables tt, int T, int D,
     int cur = 0, a = 0;
     if (tid == 0) path[0] = 0;
     for (;;) {
-        const NodeEnd e = walk_node<NQ>(g, b, cur, T, V, inv_tau, par, rank, walk_q + tid, sh);
+        const NodeEnd e = walk_node<NQ, false>(g, b, cur, T, V, inv_tau, par, rank, walk_q + tid, sh, Branch{});
         if (e.child > 0) {
             cur = e.child;
             ++a;
@@ -798,12 +825,19 @@ __global__ __launch_bounds__(NT) void k_accept_walk(TreeTables tt, int T, int D,
 
 // All nodes at once, one workgroup each: the path is a chain of nodes that each take a row's way through the compute unit
 // (about 13 us), but what happens at a node does not depend on the path to it.  Nodes are dealt out from the root down, the
-// sequences in turn.  A workgroup that does not start with the first ones looks whether an ancestor has already decided
-// against its branch, and is done if so.  state [sequence][STATE]: what became of each node (0: not known, the child
-// taken, or -1 - the token drawn) and a count of finished workgroups; the last of a sequence follows the path and leaves
-// zeros.  Nobody waits for anybody.
-enum { STATE = 80, DONE = 64 };
-static_assert((int)STATE == (int)ks::ACCEPT_STATE && (int)DONE >= KOALA_MAX_NODES, "room for every node");
+// sequences in turn.  A node tells the others of every child it turns down (the rejected, one by one, and the siblings of an
+// accepted one); a workgroup that does not start with the first ones looks whether its branch has been, and is done if so, and
+// longer rows look again with every rejection of their own.
+// state [sequence][STATE], whole numbers: what became of each node (0: not known, the child taken, or -1 - the token drawn), a
+// count of finished workgroups, and a bit for every node turned down.  The last workgroup of a sequence follows the path and
+// leaves zeros.  Nobody waits for anybody.
+// State is read and written by agent-scope atomics only.  Those go past the caches that are not coherent between dies (the sc1
+// bit of their instructions: loads miss them, stores and read-modify-writes are performed behind them), and the count of memory
+// operations that s_waitcnt waits for covers them until then; so a wave that has waited has its results where every other
+// workgroup's atomics look, and no cache has to be written back or dropped, which a fence of agent scope would do.
+enum { STATE = 80, DONE = 64, DEAD = 66 };
+static_assert((int)STATE == (int)ks::ACCEPT_STATE && (int)DONE >= KOALA_MAX_NODES && STATE % 2 == 0 && DEAD % 2 == 0 && DEAD + 2 <= STATE,
+              "room for every node, the bits at a multiple of eight bytes");
 template <int NQ>
 __global__ __launch_bounds__(NT) void k_accept_nodes(TreeTables tt, int T, int D, int V, float inv_tau, WalkArgs g, int batch,
                                                      int n_first, int *state) {
@@ -815,32 +849,27 @@ __global__ __launch_bounds__(NT) void k_accept_nodes(TreeTables tt, int T, int D
     auto known = [&]() { return l < T ? __hip_atomic_load(mine + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0; };
     const int par = l < T ? tt.parent[l] : -2, rank = l < T ? tt.rank[l] : 0;
     NodeEnd e{0, 0, wave == 0};
-    bool off = false;   // off the path: the waves may find different things out, the first one's decide
-    if ((int)blockIdx.x >= n_first) {
-        if (wave == 0) {
-            const int st = known();
-            for (int x = cur; x != 0 && !off;) {
-                const int p = __builtin_amdgcn_readlane(par, x), s = __builtin_amdgcn_readlane(st, p);
-                off = s != 0 && s != x;
-                x = p;
-            }
-            if (l == 0) sh.tok[0] = off;
-        }
+    Branch br{(unsigned long long *)(mine + DEAD), 0};
+    if (wave == 0)
+        for (int x = cur; x != 0; x = __builtin_amdgcn_readlane(par, x)) br.line |= 1ull << x;
+    bool off = false;
+    if ((int)blockIdx.x >= n_first) {   // the waves may find different things out: the first one's decide
+        if (tid == 0) sh.off = (br.told() & br.line) != 0;
         __syncthreads();
-        off = sh.tok[0] != 0;
+        off = sh.off != 0;
         __syncthreads();
     }
     if (!off) {
         walk_inputs(g, b, T, V, sh);
-        e = walk_node<NQ>(g, b, cur, T, V, inv_tau, par, rank, walk_q + tid, sh);
+        e = walk_node<NQ, true>(g, b, cur, T, V, inv_tau, par, rank, walk_q + tid, sh, br);
+        off = e.child < 0;
     }
     if (!e.mine) return;
     // one wave is left: the result is written through before the count moves
     int n = 0;
     if (l == 0) {
         if (!off) __hip_atomic_store(mine + cur, e.child > 0 ? e.child : -1 - e.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
+        written_through();
         n = __hip_atomic_fetch_add(mine + DONE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (__builtin_amdgcn_readfirstlane(n) != T - 1) return;
@@ -857,6 +886,7 @@ __global__ __launch_bounds__(NT) void k_accept_nodes(TreeTables tt, int T, int D
         g.next_token[b] = -1 - __builtin_amdgcn_readlane(st, at);
         g.accept_len[b] = a;
         __hip_atomic_store(mine + DONE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(br.dead, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (l < T) __hip_atomic_store(mine + l, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -887,10 +917,12 @@ void accept_sample(hipStream_t st, const TreeTables &tt, int T, int D, int V, fl
                    int32_t *accept_path, int32_t *next_token, int batch) {
     const float it = 1.0f / temperature;
     const WalkArgs g{tree_tokens, target_logits, draft_logits, u_accept, u_resample, accept_len, accept_path, next_token};
-    // Up to sixteen nodes a compute unit, as far as measured: 60 nodes of 32000 tokens, one workgroup a node against one a
-    // sequence, us at 1 / 8 / 16 / 32 / 64 sequences: 26 / 43 / 44 / 57 / 80 against 81 / 88 / 88 / 92 / 99; 4000 tokens
-    // 11 / 13 / 16 / 18 / 24 against 24 / 30 / 30 / 30 / 29.  Beyond, the nodes that the path leaves out would fill the chip.
-    const bool nodes = T > 1 && (long)batch * T <= 16L * n_cu;
+    // Up to eight nodes a compute unit.  60 nodes of 32000 tokens, one workgroup a node against one a sequence, us at 1 / 8 / 16 /
+    // 32 / 64 sequences: 21 / 35 / 49 / 58 / 74 against 81 / 81 / 94 / 98 / 100 where a target is near its draft, 38 / 45 / 45 /
+    // 46 / 62 against 37 / 38 / 38 / 38 / 38 where every child of the root is turned down; 4000 tokens 10 / 14 / 15 / 19 / 25
+    // against 21 / 29 / 29 / 29 / 29 and 14 / 17 / 18 / 20 / 25 against 13.  Beyond, nodes that the path leaves out cost a path
+    // that ends at once more than they gain a long one.
+    const bool nodes = T > 1 && (long)batch * T <= 8L * n_cu;
 #define KOALA_WALK(NQ)                                                                                                  \
     {                                                                                                                  \
         static OncePerDevice once[2];                                                                                  \

@@ -144,17 +144,19 @@ def test_grouped_heads(depth, batch):
         assert err.max().item() < 2e-3, (j, err)
 
 
-@pytest.mark.parametrize("V, batch", [(100, 1), (100, 11), (300, 12), (4099, 40), (300, 186), (300, 187), (16385, 14)])
-def test_acceptance_of_a_batch_equals_that_of_its_sequences(V, batch):
-    """22 nodes a sequence, all at once in up to 4096 workgroups (186 sequences), the first 256 of which (11 sequences) look at
-    no other node's outcome, and in turn beyond.  Whichever way, the outcome of a sequence is its own, bit for bit, and a call
-    leaves nothing behind for the next."""
+@pytest.mark.parametrize("V, batch", [(100, 1), (100, 11), (300, 12), (4099, 40), (300, 93), (300, 94), (300, 186), (300, 187), (16385, 14)])
+@pytest.mark.parametrize("near", [True, False])
+def test_acceptance_of_a_batch_equals_that_of_its_sequences(V, batch, near):
+    """22 nodes a sequence, all at once in up to 2048 workgroups (93 sequences), the first 256 of which (11 sequences) start
+    without a look at what other nodes have told, and in turn beyond.  near: target distributions near their draft's, whose
+    paths go down the tree; else unrelated ones, where nodes are told that their branch was turned down while they are under
+    way.  Whichever way, the outcome of a sequence is its own, bit for bit, and a call leaves nothing behind for the next."""
     import torch
     tree, temperature = make_tree([5, 3, 2], [1, 5, 9, 7]), 0.8
     c, g, _, _ = _context(V, tree, batch)
     T, D = tree.n_nodes, tree.depth
     d = 3.0 * torch.randn(batch, T, V, generator=g, device="cuda")
-    q = d + 1.5 * torch.randn(batch, T, V, generator=g, device="cuda")
+    q = (d if near else 0.0) + 1.5 * torch.randn(batch, T, V, generator=g, device="cuda")
     tok = torch.zeros(batch, T, dtype=torch.int32, device="cuda")
     top = torch.topk(d, 5, dim=2).indices.to(torch.int32)
     for i in range(1, T):
@@ -177,7 +179,7 @@ def test_acceptance_of_a_batch_equals_that_of_its_sequences(V, batch):
             assert torch.equal(x[0], y[b]), b
     acc = whole[0][0]
     if batch > 8:
-        assert int(acc.min()) == 0 and int(acc.max()) >= 2   # rejections at once, and paths
+        assert int(acc.min()) == 0 and (int(acc.max()) >= 2 if near else float(acc.float().mean()) < 0.5)   # rejections at once, and paths
 
 
 def test_acceptance_along_a_chain_of_64_nodes():
