@@ -867,15 +867,47 @@ int x3_tiles(int M) {
     const int tiles = (M + 15) / 16, nmb = (tiles + 7) / 8, mt = (tiles + nmb - 1) / nmb;
     return mt <= 2 ? 2 : mt <= 4 ? mt : mt <= 6 ? 6 : 8;
 }
-// K splits that take the least time, with partial sums that fit `room` floats (none: one split, straight into C).  In units
-// of a stage: rounds of workgroups on the chip's compute units, a start and an end of a workgroup (about four stages), the
-// partial sums written and read (1 MB each way is about a third of a stage).
-int x3_splits(int M, int N, int K, size_t room) {
-    const long mt = x3_tiles(M), tiles = (long)((N + 127) / 128) * ((M + 16 * mt - 1) / (16 * mt)), nst = (K + 63) / 64;
+// The microseconds that a product in S splits takes in either form, up to what the choice does not depend on, as fitted to 10000
+// of them (4 to 300 rows, 64 to 32000 columns, 64 to 32000 terms, 1 to 32 splits: within a tenth of most).  An n tile's
+// workgroups are all on one die of 32 compute units, so the die with the most of them counts.
+//   k_gemm_x3: a start, the chunks of a split at no less than a round trip each, at a workgroup's share of its compute unit;
+//   k_stream_x3: rounds of one workgroup a compute unit, each a start and its stages.
+// Where P is k-contiguous a die takes in 0.68 MB of it a microsecond; the rest counts a tenth there, and orders what is equal.
+// Above the start, splits of at least two stages (k_gemm_x3 up to 32 rows: four chunks), else no such form: 1e30.
+struct Shape { int M, N, K, S; bool ks; };
+double with_stream(const Shape &p, int cols, double t) {
+    return (p.ks ? t : std::max(t, 3.0 + (double)(((p.N + cols - 1) / cols + 7) / 8) * cols * p.K * 4 / 0.68e6)) + t / 10;
+}
+double x3_time(const Shape &p) {
+    const int bm = p.M <= 32 ? 32 : p.M <= 64 ? 64 : 128, nch = (p.K + X3_BK - 1) / X3_BK;
+    if (p.S > 1 && nch < (bm == 32 ? 4 : 2) * p.S) return 1e30;
+    static const double fit[2][3][4] = {   // start, round trip, chunk, the end of a workgroup
+        {{2.7, 0.59, 0.43, 0.33}, {2.0, 0.82, 0.62, 1.6}, {2.1, 1.36, 0.96, 1.9}},
+        {{2.3, 0.85, 0.54, 0.31}, {1.3, 1.14, 0.76, 1.6}, {1.7, 1.66, 1.09, 2.0}}};
+    const double *f = fit[p.ks][bm / 64];
+    const long die = (long)((p.N + X3_BN - 1) / X3_BN + 7) / 8 * ((p.M + bm - 1) / bm) * p.S;
+    const double unit = (double)((die + 31) / 32);
+    return with_stream(p, X3_BN, f[0] + (nch + p.S - 1) / p.S * std::max(f[1], unit * f[2]) + unit * f[3]);
+}
+double stream_time(const Shape &p) {
+    const int mt = x3_tiles(p.M), nst = (p.K + 63) / 64;
+    if (p.N < 32 || p.K < 64 || p.N >= 1 << 23 || p.K >= 1 << 23 || (p.S > 1 && nst < 2 * p.S)) return 1e30;   // see k_stream_x3
+    static const double fit[2][5][2] = {   // stage, start
+        {{0.93, 6.0}, {1.05, 6.7}, {1.10, 7.3}, {1.42, 8.2}, {1.84, 9.2}},
+        {{0.95, 5.1}, {1.14, 6.0}, {1.24, 6.8}, {1.50, 8.2}, {1.92, 9.3}}};
+    const double *f = fit[p.ks][mt <= 4 ? mt - 2 : mt == 6 ? 3 : 4];
+    const long die = (long)((p.N + 127) / 128 + 7) / 8 * ((p.M + 16 * mt - 1) / (16 * mt)) * p.S;
+    return with_stream(p, 128, (double)((die + 31) / 32) * ((nst + p.S - 1) / p.S * f[0] + f[1]));
+}
+bool streamed(const Shape &p) { return stream_time(p) < x3_time(p); }
+// K splits that take the least time, with partial sums that fit `room` floats (none: one split, straight into C) and are read
+// back at 4 MB a microsecond
+int x3_splits(int M, int N, int K, size_t room, bool ks) {
     double best = 1e300;
     int S = 1;
-    for (int s = 1; s <= 32 && (s == 1 || (s * 2 <= nst && (size_t)s * M * N <= room)); ++s) {
-        const double t = (double)((tiles * s + 255) / 256) * ((nst + s - 1) / s + 4) + (s > 1 ? 0.66 * s * M * N * 4.0 / 1e6 : 0.0);
+    for (int s = 1; s <= 32 && (s == 1 || (size_t)s * M * N <= room); ++s) {
+        const Shape p{M, N, K, s, ks};
+        const double t = std::min(x3_time(p), stream_time(p)) + (s > 1 ? 1.0 + 1e-6 * s * M * N : 0.0);
         if (t < best) { best = t; S = s; }
     }
     return S;
@@ -913,11 +945,11 @@ template <bool KS>
 void gemm_weights(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K, const Join &join) {
     float *out = S > 1 ? part : C;
     const long ldp = KS ? N : K;
-    // What k_stream_x3 does not take, and workgroups of up to four stages, which are over before its loads ahead are worth
-    // their start (a head step of 10 rows at 512 x 4000: 125 us all streamed, 115 so; discriminator step of 4 rows 81 and 75;
-    // of 290 rows at 512 x 32000 805 and 785; up to eight stages: 90 rows at 512 x 32000 377 and 412 us).
-    if (N < 32 || K < 64 || N >= 1 << 23 || K >= 1 << 23 || (K + 63) / 64 <= 4 * S)
-        return gemm_x3<KS>(st, W, ldp, X, K, out, S, M, N, K, join);
+    // The faster form: k_stream_x3 gains with many stages and with many rows, k_gemm_x3's smaller workgroups where either is
+    // few.  Against more than four stages a workgroup streamed, and splits priced as the streamed form's: forward pass of a head
+    // of 512 x 4000 at 20 rows 22.5 -> 20.5 us, at 200 36.0 -> 33.3; discriminator step of 512 x 32000 x 1500, three layers, at
+    // ten positions 264 -> 246, at 200 1216 -> 1076; of 4096 x 32000 x 1024 at 20 the same.
+    if (!streamed(Shape{M, N, K, S, KS})) return gemm_x3<KS>(st, W, ldp, X, K, out, S, M, N, K, join);
 #define KOALA_STREAM(MT) return K % 64 ? launch_stream<MT, KS, true>(st, W, ldp, X, out, S, M, N, K, join) : launch_stream<MT, KS, false>(st, W, ldp, X, out, S, M, N, K, join)
     switch (x3_tiles(M)) {
         case 2: KOALA_STREAM(2);
@@ -1213,7 +1245,7 @@ inline int fc_out(const koala_disc_shape &s, int k) { return k == s.n_fc - 1 ? 1
 void disc_join(hipStream_t st, const koala_disc_shape &s, const koala_disc_params &p, const DiscWs &w, int n, const float *h,
                const float *la, const float *lb) {
     const long nV = (long)n * s.vocab;
-    const int S = x3_splits(n, s.vocab, s.hidden, (size_t)2 * nV);
+    const int S = x3_splits(n, s.vocab, s.hidden, (size_t)2 * nV, false);
     if (S == 1) return gemm_nt(st, h, p.w_lin, w.u, nullptr, 1, n, s.vocab, s.hidden, Join{la, lb, nV});
     gemm_nt(st, h, p.w_lin, nullptr, w.u, 2, n, s.vocab, s.hidden);
     k_join<<<blocks(nV), 256, 0, st>>>(w.u, w.u + nV, la, lb, w.u, nV);
@@ -1225,7 +1257,7 @@ void disc_forward(hipStream_t st, const koala_disc_shape &s, const koala_disc_pa
     const int last = s.n_fc - 1;   // width 1 (bias added where the score is used)
     if (last == 0) k_row_dot<<<rows, 256, 0, st>>>(w.a[0], p.w_fc[0], w.s, s.vocab);
     for (int k = 0; k < last; ++k) {
-        const int in = fc_in(s, k), out = fc_out(s, k), S = x3_splits(rows, out, in, (size_t)2 * n * s.vocab);
+        const int in = fc_in(s, k), out = fc_out(s, k), S = x3_splits(rows, out, in, (size_t)2 * n * s.vocab, false);
         gemm_nt(st, w.a[k], p.w_fc[k], w.pre[k], w.g[0], S, rows, out, in);
         const float *part = S > 1 ? w.g[0] : w.pre[k];
         if (k + 1 < last) sum_parts<SUM_RELU>(st, part, S, rows, out, p.b_fc[k], w.pre[k], w.a[k + 1]);
@@ -1246,7 +1278,7 @@ void disc_backward(hipStream_t st, const koala_disc_shape &s, const koala_disc_p
             const int nb = (in + 255) / 256;
             k_score_outer<<<rows * nb + 1, 256, 0, st>>>(w.s, p.b_fc[k], w.ds, t, p.w_fc[k], pre, w.g[k], rows, in, nb);
         } else {
-            const int S = x3_splits(rows, in, out, (size_t)n * s.vocab);
+            const int S = x3_splits(rows, in, out, (size_t)n * s.vocab, true);
             gemm_nn(st, gout, p.w_fc[k], w.g[k], w.z, S, rows, in, out);
             const float *part = S > 1 ? w.z : w.g[k];
             if (pre) sum_parts<SUM_MASK>(st, part, S, rows, in, pre, w.g[k], nullptr);
@@ -1260,6 +1292,12 @@ void disc_backward(hipStream_t st, const koala_disc_shape &s, const koala_disc_p
 }  // namespace
 
 extern "C" {
+
+// For tests: whether a product [rows, cols] of `terms` terms is streamed, with the splits that `room` floats of partial sums allow
+int kt_product_form(int rows, int cols, int terms, int strided, size_t room, int *splits) {
+    *splits = x3_splits(rows, cols, terms, room, strided != 0);
+    return streamed(Shape{rows, cols, terms, *splits, strided != 0});
+}
 
 koala_status koala_train_workspace_bytes(const koala_disc_shape *shape, int n_rows, size_t *out) {
     if (!shape || !out) return KOALA_E_NULL;
@@ -1353,7 +1391,7 @@ static MedWs med_carve(int n, int H, int K, const float *h, void *workspace, siz
 }
 
 static void medusa_forward(hipStream_t st, int n, int H, int K, float *const *blocks_w, const MedWs &w) {
-    const int S = x3_splits(n, H, H, w.room);
+    const int S = x3_splits(n, H, H, w.room, false);
     for (int k = 0; k < K; ++k) {
         gemm_nt(st, w.x[k], blocks_w[k], w.y[k], w.part, S, n, H, H);
         sum_parts<SUM_SILU>(st, S > 1 ? w.part : w.y[k], S, n, H, w.x[k], w.y[k], w.x[k + 1]);
@@ -1378,7 +1416,7 @@ koala_status koala_train_medusa_head_forward(void *hip_stream, int n_rows, int h
     hipStream_t st = (hipStream_t)hip_stream;
     const MedWs w = med_carve(n_rows, hidden, K, h, workspace, workspace_bytes);
     medusa_forward(st, n_rows, hidden, K, blocks_w, w);
-    const int S = x3_splits(n_rows, vocab, hidden, w.room);
+    const int S = x3_splits(n_rows, vocab, hidden, w.room, false);
     gemm_nt(st, w.x[K], w_lm, d_logits, w.part, S, n_rows, vocab, hidden);
     if (S > 1) sum_parts<SUM_ONLY>(st, w.part, S, n_rows, vocab, nullptr, d_logits, nullptr);
     return hipGetLastError() == hipSuccess ? KOALA_OK : KOALA_E_DEVICE;
@@ -1394,7 +1432,7 @@ koala_status koala_train_medusa_head_step(void *hip_stream, int n_rows, int hidd
     const int n = n_rows, H = hidden, V = vocab;
     MedWs w = med_carve(n, H, K, h, workspace, workspace_bytes);
     medusa_forward(st, n, H, K, blocks_w, w);
-    const int Sv = x3_splits(n, H, V, w.room), Sh = x3_splits(n, H, H, w.room);
+    const int Sv = x3_splits(n, H, V, w.room, true), Sh = x3_splits(n, H, H, w.room, true);
     gemm_nn(st, grad_d, w_lm, w.gx, w.part, Sv, n, H, V);                 // gx = grad_d W_lm, gy = gx * SiLU'(y)
     sum_parts<SUM_BACK>(st, Sv > 1 ? w.part : w.gx, Sv, n, H, w.y[K - 1], w.gx, w.gy);
     for (int k = K - 1; k >= 0; --k) {
