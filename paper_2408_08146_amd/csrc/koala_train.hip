@@ -1293,10 +1293,11 @@ void disc_backward(hipStream_t st, const koala_disc_shape &s, const koala_disc_p
 
 extern "C" {
 
-// For tests: whether a product [rows, cols] of `terms` terms is streamed, with the splits that `room` floats of partial sums allow
+// For tests: the row tiles of a workgroup where a product [rows, cols] of `terms` terms is streamed, else 0, and its splits where
+// partial sums have `room` floats
 int kt_product_form(int rows, int cols, int terms, int strided, size_t room, int *splits) {
     *splits = x3_splits(rows, cols, terms, room, strided != 0);
-    return streamed(Shape{rows, cols, terms, *splits, strided != 0});
+    return streamed(Shape{rows, cols, terms, *splits, strided != 0}) ? x3_tiles(rows) : 0;
 }
 
 koala_status koala_train_workspace_bytes(const koala_disc_shape *shape, int n_rows, size_t *out) {

@@ -8,6 +8,8 @@ sums by themselves are held to that bound itself further down."""
 import numpy as np
 import pytest
 
+from test_train_forms import form
+
 pytestmark = pytest.mark.gpu
 
 TOL = 3.3e-6
@@ -90,12 +92,13 @@ def test_sums_are_as_exact_as_fp32_chains(form, terms, scale):
     assert _rel(got, want) < 1.15 * 2.53e-8 * np.sqrt((terms + 1) / 2)
 
 
-@pytest.mark.parametrize("n,V,H", [(1, 32, 64), (32, 31, 64), (33, 33, 63), (48, 127, 65), (49, 128, 127), (64, 129, 128), (65, 160, 192),
-                                   (96, 161, 193), (97, 64, 320), (128, 65, 1000), (129, 1000, 96), (200, 515, 449), (20, 4099, 640)])
-def test_products_at_the_edges_of_a_streamed_tile(n, V, H):
+def _room(n, H):   # floats that a head's workspace has for partial sums: eight slots of n x H in whole 256 bytes
+    return 8 * ((n * H * 4 + 255) // 256 * 64)
+
+
+def _both_products(n, V, H):
     """d = h w_lm^T and g w_lm, set up and bounded as above, where V and H are both the length of the sums and the number of
-    columns: a wave's 32 columns and a stage's 64 terms that the matrix does not fill, one row tile up to eight, several
-    blocks of them, fewer columns or terms than a wave or a stage."""
+    columns"""
     import torch
     import paper_2408_08146_amd as KO
     rng = np.random.default_rng(n + V + H)
@@ -109,6 +112,78 @@ def test_products_at_the_edges_of_a_streamed_tile(n, V, H):
     m = min(n, H)
     KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(np.eye(n, H)), dev(g), 2.0)   # W = -(g w_lm)^T / 2 * 2 [identity]
     assert _rel(-w.T[:m], g[:m].astype(np.float64) @ w_lm.astype(np.float64)) < bound(V)
+
+
+@pytest.mark.parametrize("n,V,H", [(1, 32, 64), (32, 31, 64), (33, 33, 63), (48, 127, 65), (49, 128, 127), (64, 129, 128), (65, 160, 192),
+                                   (96, 161, 193), (97, 64, 320), (128, 65, 1000), (129, 1000, 96), (200, 515, 449), (20, 4099, 640)])
+def test_products_of_few_columns_or_terms(n, V, H):
+    """Matrices around 32 columns and 64 terms, one row tile up to several blocks of them"""
+    _both_products(n, V, H)
+
+
+@pytest.mark.parametrize("n,tiles", [(1, 2), (20, 2), (33, 3), (60, 4), (90, 6), (128, 8), (129, 6), (200, 8), (300, 8)])
+@pytest.mark.parametrize("V,H", [(4099, 1001), (5056, 1024)])
+def test_products_at_the_edges_of_a_streamed_tile(n, tiles, V, H):
+    """Both forms streamed, with each count of row tiles and several blocks of them; 4099 x 1001: the last columns' and the last
+    stage's loads are moved back into what the one before has taken, as columns and as terms; 5056 x 1024: whole stages."""
+    assert form(n, V, H, False, _room(n, H))[0] == tiles and form(n, H, V, True, _room(n, H))[0] == tiles
+    _both_products(n, V, H)
+
+
+def _forward_and_update(h, w_lm, g, lr=1.0):
+    """d = h w_lm^T, and W = -(g w_lm / 2)^T h from a zero W"""
+    import torch
+    import paper_2408_08146_amd as KO
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    n, (V, H) = len(h), w_lm.shape
+    d, w = torch.zeros(n, V, device="cuda"), torch.zeros(H, H, device="cuda")
+    KO.MedusaHeadTrainer([w], dev(w_lm)).forward(dev(h), d)
+    w.zero_()
+    KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(h), dev(g), lr)
+    return d.double().cpu().numpy(), w.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("n", [20, 33, 60, 90, 128, 200])
+def test_infinities_in_a_streamed_product(n):
+    """One infinite weight among the columns and the terms that the last loads take a second time, in both forms: its column of
+    the result is infinite, the rest, the other tiles' and its own, what it would be without (bound as for sums, over what the
+    update behind the input gradient adds)."""
+    V, H, v0, j0 = 4099, 1001, 4080, 948   # terms 937 .. 959 of 1001 and 4035 .. 4095 of 4099 are in two stages
+    assert form(n, V, H, False, _room(n, H))[0] and form(n, H, V, True, _room(n, H))[0]
+    rng = np.random.default_rng(n)
+    h, g = (np.abs(rng.normal(size=s)).astype(np.float32) for s in ((n, H), (n, V)))
+    w_lm = rng.normal(size=(V, H)).astype(np.float32)
+    d_ref = h.astype(np.float64) @ w_lm.T
+    w_ref = -(g.astype(np.float64) @ w_lm / 2).T @ h
+    w_lm[v0, j0] = np.inf
+    d, w = _forward_and_update(h, w_lm, g)
+    assert (d[:, v0] == np.inf).all() and (w[j0] == -np.inf).all()
+    for got, ref, at in ((d, d_ref, (slice(None), v0)), (w, w_ref, (j0, slice(None)))):
+        got[at] = ref[at] = 0.0
+        assert np.isfinite(got).all()
+        assert np.linalg.norm(got - ref) < 5e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n", [20, 60, 128, 200])
+@pytest.mark.parametrize("weights", [True, False])
+def test_small_operands_of_a_streamed_product(n, weights):
+    """One operand in units of 2^-118, where low bits are below the smallest normal bfloat16, the other in units of 2^60: the
+    weights or the activations, in both forms.  An identity for h makes the update a copy of the input gradient."""
+    import torch
+    import paper_2408_08146_amd as KO
+    V, H = 4099, 1001
+    assert form(n, V, H, False, _room(n, H))[0] and form(n, H, V, True, _room(n, H))[0]
+    rng = np.random.default_rng(n)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    scale = (60, -118) if weights else (-118, 60)
+    f32 = lambda e, *s: rng.normal(size=s).astype(np.float32) * np.float32(2.0 ** e)
+    h, g, w_lm = f32(scale[0], n, H), f32(scale[0], n, V), f32(scale[1], V, H)
+    bound = lambda terms: 1.15 * 2.53e-8 * np.sqrt((terms + 1) / 2)
+    d, w = torch.zeros(n, V, device="cuda"), dev(np.zeros((H, H)))
+    KO.MedusaHeadTrainer([w], dev(w_lm)).forward(dev(h), d)
+    assert _rel(d, h.astype(np.float64) @ w_lm.T.astype(np.float64)) < bound(H)
+    KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(np.eye(n, H)), dev(g), 2.0)
+    assert _rel(-w.T[:n], g.astype(np.float64) @ w_lm.astype(np.float64)) < bound(V)
 
 
 @pytest.mark.parametrize("rows,H", [(1, 1), (33, 1), (32, 2), (31, 63), (32, 65), (33, 64), (64, 127), (97, 128), (127, 129), (128, 193), (129, 130),
@@ -180,6 +255,18 @@ def test_head_results_do_not_depend_on_earlier_calls():
 
 @pytest.mark.parametrize("n,H,V,DH,n_fc", [(1, 64, 100, 0, 1), (16, 33, 1030, 40, 2), (17, 256, 2000, 64, 3), (65, 300, 700, 129, 3)])
 def test_discriminator_products(n, H, V, DH, n_fc):
+    _discriminator_products(n, H, V, DH, n_fc)
+
+
+@pytest.mark.parametrize("n,H,V,DH,n_fc", [(20, 300, 16387, 40, 2), (64, 300, 16387, 0, 1), (40, 300, 16387, 33, 3)])
+def test_logits_joined_to_a_streamed_product(n, H, V, DH, n_fc):
+    """The mapped hidden state streamed in one split, so that the product itself adds both sets of logits, in rows whose length is
+    no multiple of four"""
+    assert form(n, V, H, False, 2 * n * V) == (max(2, -(-n // 16)), 1)
+    _discriminator_products(n, H, V, DH, n_fc)
+
+
+def _discriminator_products(n, H, V, DH, n_fc):
     import torch
     import paper_2408_08146_amd as KO
     from oracle import train as T
@@ -222,12 +309,13 @@ def test_infinite_operand_stays_infinite():
     assert abs(loss.item() - np.log(2.0)) < 1e-6
 
 
-@pytest.mark.parametrize("H,rows", [(1, 3), (63, 8), (130, 9), (257, 16), (515, 24), (1030, 25), (260, 32), (260, 33), (4900, 33),
-                                    (4901, 41), (4903, 48), (4900, 49)])
+@pytest.mark.parametrize("H,rows", [(1, 3), (63, 8), (65, 9), (127, 16), (128, 24), (129, 31), (257, 32), (257, 33), (515, 48),
+                                    (1030, 128), (1030, 129)])
 def test_update_by_few_rows(H, rows):
-    """-g^T h at widths that leave columns of a wave and rows of a panel over, at each count of row groups, and on both sides of
-    the rule for more than 32 rows (24 million elements), at the error of an fp32 chain: on average as above, and every
-    element within rows * 2^-24 of the sum of its terms' magnitudes (a single element has no average)."""
+    """-g^T h on both sides of the 32 rows up to which an update takes its operands in one piece and of the 128 that others take at
+    a time, at widths around its tiles of 64 and 128 and with columns of a wave left over, at the error of an fp32 chain: on
+    average as above, and every element within rows * 2^-24 of the sum of its terms' magnitudes (a single element has no
+    average)."""
     import torch
     import paper_2408_08146_amd as KO
     gen = torch.Generator(device="cuda").manual_seed(H + rows)
@@ -272,6 +360,57 @@ def test_infinities_in_every_form(form, n):
     assert np.isinf(got[where]).all() and (np.sign(got[where]) == (1 if form == "forward" else -1)).all()
     got[where] = want[where] = 0.0
     assert np.linalg.norm(got - want) < TOL * np.linalg.norm(want)
+
+
+def _one_layer(n, H, V, w, bias, h, q, d, w_lin, lr):
+    """One discriminator step with a single layer: the new w_lin, and float64's change of it per lr"""
+    import torch
+    import paper_2408_08146_amd as KO
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    out, loss = dev(w_lin), torch.zeros(1, device="cuda")
+    KO.Discriminator(out, [dev(w[None])], [dev(np.array([bias]))]).step(dev(h), dev(q), dev(d), lr, loss)
+    h, q, d, w, w_lin = (a.astype(np.float64) for a in (h, q, d, w, w_lin))
+    with np.errstate(all="ignore"):
+        z = h @ w_lin.T
+        sd, sq = (z + d) @ w + bias, (z + q) @ w + bias
+        ds = (1 / (1 + np.exp(-sd)) - 1 / (1 + np.exp(sq))) / n
+    return out.double().cpu().numpy(), ds, w, h
+
+
+@pytest.mark.parametrize("n", [1, 20, 32, 33])
+def test_two_halves_of_a_gradient_where_pieces_do_not_hold(n):
+    """Up to 32 positions the update of the mapping adds the draft's and the target's gradients itself.  Weights in units of 2^-112
+    make gradients around 2^-118, where low bits are below the smallest normal bfloat16 but nothing is below the smallest normal
+    float (a bias keeps the halves from cancelling); the hidden states in units of 2^60.  Each element within (n + 10) roundings
+    of its terms' magnitudes: n + 2 as for other updates, eight for two sigmoids and their factors."""
+    H, V, bias = 130, 70, np.float32(2.0)
+    rng = np.random.default_rng(n)
+    w = rng.normal(size=V).astype(np.float32) * np.float32(2.0 ** -112)
+    h = rng.normal(size=(n, H)).astype(np.float32) * np.float32(2.0 ** 60)
+    zero = np.zeros((n, V), np.float32)
+    got, ds, w, h = _one_layer(n, H, V, w, bias, h, zero, zero, np.zeros((V, H), np.float32), 1.0)
+    want = -w[:, None] * (ds @ h)
+    assert (np.abs(got - want) <= (n + 10) * 2.0 ** -24 * np.abs(w)[:, None] * (np.abs(ds) @ np.abs(h))).all()
+
+
+@pytest.mark.parametrize("n", [2, 20, 32, 33])
+def test_two_halves_of_a_gradient_and_an_infinite_hidden_state(n):
+    """One infinite element of h: the draft's row has a gradient (1 / n), the target's, whose score is infinite as well, none.
+    That unit's column of the mapping goes to minus infinity, the rest is as without it."""
+    H, V, j0 = 130, 70, 67
+    rng = np.random.default_rng(n)
+    pos = lambda *s: (np.abs(rng.normal(size=s)) + 0.1).astype(np.float32)
+    h, w, w_lin = pos(n, H) * np.float32(0.05), pos(V) * np.float32(0.1), pos(V, H) * np.float32(0.1)
+    q, d = (rng.normal(size=(n, V)).astype(np.float32) for _ in range(2))
+    h[1, j0] = np.inf
+    got, ds, w, h = _one_layer(n, H, V, w, np.float32(-2.0), h, q, d, w_lin, 1.0)
+    assert ds[1] == 1.0 / n and (got[:, j0] == -np.inf).all()
+    keep = np.arange(H) != j0
+    change = -w[:, None] * (ds @ h[:, keep])
+    off = np.abs(got[:, keep] - w_lin[:, keep] - change)
+    # 2^-24 of the stored weight, and of the change 3e-6: a sum over 70 x 130 terms behind a sigmoid
+    assert np.isfinite(got[:, keep]).all()
+    assert (off <= 2.0 ** -24 * np.abs(got[:, keep]) + 3e-6 * np.abs(w)[:, None] * (np.abs(ds) @ h[:, keep])).all()
 
 
 @pytest.mark.parametrize("V", [1, 1023, 1025, 32768, 33001])

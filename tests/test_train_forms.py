@@ -7,11 +7,12 @@ import paper_2408_08146_amd as K
 
 
 def form(rows, cols, terms, strided=False, room=1 << 30):
-    """(streamed, splits), as the library's own rule gives them"""
+    """(row tiles of a workgroup, 0 where the product is not streamed; splits), as the library's own rule gives them"""
     f = C.CDLL(K.library_path()).kt_product_form
     f.argtypes, f.restype = [C.c_int] * 4 + [C.c_size_t, C.POINTER(C.c_int)], C.c_int
     splits = C.c_int()
-    return bool(f(rows, cols, terms, int(strided), room, C.byref(splits))), splits.value
+    tiles = f(rows, cols, terms, int(strided), room, C.byref(splits))
+    return tiles, splits.value
 
 
 @pytest.fixture(autouse=True)
@@ -26,13 +27,13 @@ def test_few_stages_over_few_columns_are_not_streamed():
     """One split over 4000 columns of 512 terms, the logits of a small head: 20.1 us for the forward pass against 22.3
     streamed."""
     for rows in (1, 4, 10, 20, 32):
-        assert form(rows, 4000, 512, room=0) == (False, 1)
-        assert form(rows, 300, 64, room=0) == (False, 1)
+        assert form(rows, 4000, 512, room=0) == (0, 1)
+        assert form(rows, 300, 64, room=0) == (0, 1)
 
 
 def test_large_products_are_streamed():
     for rows in (1, 20, 64, 128, 300):
-        assert form(rows, 32000, 4096, room=0) == (True, 1)
+        assert form(rows, 32000, 4096, room=0) == (min(8, max(2, -(-rows // 16))), 1)
         assert form(rows, 1024, 32000)[0]
         assert form(rows, 4096, 32000, strided=True)[0]
 
