@@ -92,6 +92,12 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t &h, uint32_t &
 // pass: their pieces are some as well.
 __device__ __forceinline__ bool pieces_hold(float top) { return top < 0x1.ffp127f && (top >= 0x1p-102f || top == 0.f); }
 
+// The smaller of `least` and the magnitudes of a and b, as whole numbers in which zero is the largest of all
+__device__ __forceinline__ uint32_t least2(float a, float b, uint32_t least) {
+    return min(min((__float_as_uint(a) << 1) - 1, (__float_as_uint(b) << 1) - 1), least);
+}
+constexpr uint32_t LEAST_EXACT = (25u << 24) - 1;   // 2^-102 so
+
 // One operand's share of a chunk in a thread's registers, and its way into LDS.  T rows (32, 64 or 128).
 template <int T, bool KS, int DEPTH>
 struct X3Loader {
@@ -622,13 +628,19 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
 // chunk's products (FEW, up to 32 rows: with the operands).  Registers and LDS for three workgroups a compute unit: one's
 // products and cutting run beside the others' memory.  Tiles go by rows of W, and each die has an eighth of them that is
 // contiguous in memory.
+// No less exact than a chain of fp32 multiply-adds, at any number of rows: 2.53e-8 of a sum of random terms at one row (both; with
+// six products of pieces 2.60e-8, and the largest error 1.7 times a rounding), 2.6e-8 against 3.1e-8 at two, 3.9e-8 against
+// 1.03e-7 at 32 (2-norm).  For it FEW keeps eight of the nine products (33 rows and more round oftener than the other two would
+// weigh), a tile whose sums overflow, as products of first pieces may where the whole does not, is summed anew on the fp32 pipe,
+// and so is, EXACT, one with a value below 2^-102 beside larger ones.  EXACT up to UPD_EXACT rows, where memory bounds all sizes: it costs
+// 1 to 2 %.
 // Measured, 32000 x 4096 by 20 rows: 188 us (5.6 TB/s), a kernel of plain multiply-adds with the rows of W dealt to all dies
 // 227; by 60 rows 222, both operands through LDS and W in pieces of 256 B 478; by 300 rows 615 and 1446; 4096 x 4096 by 128
 // rows 41 and 90; 1024 x 32000 by 40 rows 65 and 84; 4000 x 1000 by 4 rows 9.6 and 9.3.  Two workgroups a compute unit
 // with X two chunks ahead: 277 us at 32000 x 4096 by 60 rows, 49 at 4096 x 4096 by 128.
 // ---------------------------------------------------------------------------------------------
-enum { UPD_FEW = 32 };
-template <bool FEW>
+enum { UPD_FEW = 32, UPD_EXACT = 48 };
+template <bool FEW, bool EXACT>
 __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ G, const float *__restrict__ G2, const float *__restrict__ X,
                                                       float *W, float *bias, int M, int N, int rows, float alpha) {
     constexpr int BM = 64, BN = 128, TM = BM / 16, TN = 2, PL = TM * 64, LDO = BN + 4, NC = FEW ? 1 : 4;
@@ -647,6 +659,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     const bool edge = n0 + BN > N, whole = !edge && m0 + BM <= M, second = nx > nl;
     f32x2 xv[8];
     float gtop = 0.f, xtop = 0.f, gsum = 0.f;   // largest magnitudes, this thread's share of its column's sum
+    uint32_t gleast = ~0u, xleast = ~0u;         // EXACT: smallest
     auto load_x = [&](int r0) __attribute__((always_inline)) {
         if (r0 + 32 <= rows && N > 1 && N < 1 << 25) {
             unsigned off = 4u * (8u * lg * (unsigned)N + nl);
@@ -674,6 +687,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
             for (int e = 0; e < 4; ++e) {
                 uint32_t h, m, w;
                 split3(xv[2 * e][t], xv[2 * e + 1][t], h, m, w, xtop);
+                if (EXACT) xleast = least2(xv[2 * e][t], xv[2 * e + 1][t], xleast);
                 a[0][t][e] = h; a[1][t][e] = m; a[2][t][e] = w;
             }
     };
@@ -694,7 +708,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
             const int pq = 2 - f % 3, j = f / 3;
             if (f + 3 < 3 * TM) b[(f + 3) & 3] = read(f + 3);
 #pragma unroll
-            for (int pp = 2 - pq; pp >= 0; --pp)
+            for (int pp = FEW ? min(3 - pq, 2) : 2 - pq; pp >= 0; --pp)
 #pragma unroll
                 for (int t = 0; t < TN; ++t) {
                     f32x4 &sum = pq + pp == 0 ? acc[t][j] : low[t][j];
@@ -768,6 +782,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
                 for (int e = 0; e < 4; ++e) {
                     uint32_t p, q, r;
                     split3(gv[i][2 * e], gv[i][2 * e + 1], p, q, r, gtop);
+                    if (EXACT) gleast = least2(gv[i][2 * e], gv[i][2 * e + 1], gleast);
                     h[e] = p; m[e] = q; w[e] = r;
                 }
                 u32x4 *dst = gs + i * 3 * PL + (l >> 4) * 64 + 16 * wave + li;
@@ -804,6 +819,17 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
 #pragma unroll
             for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
                 acc[t][j][r] += fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f;
+    bool finite = true;
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) finite &= fabsf(acc[t][j][r]) < INFINITY;
+    if (EXACT) {
+        if (gleast < LEAST_EXACT) gtop = INFINITY;
+        if (xleast < LEAST_EXACT) xtop = INFINITY;
+    }
     // the largest magnitudes of G's columns and of this wave's columns of X
     for (int o = 32; o > 0; o >>= 1) { gtop = fmaxf(gtop, __shfl_xor(gtop, o)); xtop = fmaxf(xtop, __shfl_xor(xtop, o)); }
     if (l == 0) tops[wave] = gtop;
@@ -811,7 +837,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     __syncthreads();
     if (bias && n0 == 0 && wave == 0 && m0 + l < M) bias[m0 + l] += alpha * ((bsum[0][l] + bsum[1][l]) + (bsum[2][l] + bsum[3][l]));
     gtop = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
-    if (!pieces_hold(gtop) || !pieces_hold(xtop)) {
+    if (!pieces_hold(gtop) || !pieces_hold(xtop) || !__all(finite)) {
         // once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds r = g of column i), four r a step
 #pragma unroll
         for (int t = 0; t < TN; ++t)
@@ -972,8 +998,9 @@ void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M
                  const float *G2 = nullptr) {
     const long tiles = (long)((M + 63) / 64) * ((N + 127) / 128);
     const int grid = (int)((tiles + 7) / 8 * 8);
-    if (rows <= UPD_FEW) k_update_x3<true><<<grid, 256, 0, st>>>(G, G2, X, W, bias, M, N, rows, -lr);
-    else k_update_x3<false><<<grid, 256, 0, st>>>(G, nullptr, X, W, bias, M, N, rows, -lr);
+    if (rows <= UPD_FEW) k_update_x3<true, true><<<grid, 256, 0, st>>>(G, G2, X, W, bias, M, N, rows, -lr);
+    else if (rows <= UPD_EXACT) k_update_x3<false, true><<<grid, 256, 0, st>>>(G, nullptr, X, W, bias, M, N, rows, -lr);
+    else k_update_x3<false, false><<<grid, 256, 0, st>>>(G, nullptr, X, W, bias, M, N, rows, -lr);
 }
 
 // The S split sums of element i added in split order, and the element-wise step that follows the product:

@@ -377,6 +377,57 @@ def _one_layer(n, H, V, w, bias, h, q, d, w_lin, lr):
     return out.double().cpu().numpy(), ds, w, h
 
 
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+@pytest.mark.parametrize("H", [64, 257, 1030])
+def test_update_by_few_rows_to_the_last_bit(H, rows):
+    """A chain of fp32 multiply-adds rounds each term and each sum of several once: every element within rows roundings of 2^-24
+    of its terms' magnitudes, which is 2 at two rows, where the matrix pipe, which cuts off what its sums do not hold, needs three.
+    2^-6 of that on top: products of pieces are added among themselves first, at 2^-8 of the whole.  In the 2-norm a chain's
+    rounding of a single term, 2.53e-8, and less than a chain's from two on."""
+    import torch
+    import paper_2408_08146_amd as KO
+    gen = torch.Generator(device="cuda").manual_seed(H + rows)
+    h, g = (torch.randn(rows, H, generator=gen, device="cuda") for _ in range(2))
+    w = torch.zeros(H, H, device="cuda")
+    KO.MedusaHeadTrainer([w], 2 * torch.eye(H, device="cuda")).step(h, g, 1.0)
+    want = g.double().T @ h.double()
+    off = (w.double() + want).abs()
+    assert (off <= (1 + 2.0 ** -6) * max(rows, 3 * (rows > 1)) * 2.0 ** -24 * (g.double().abs().T @ h.double().abs())).all()
+    assert H < 1000 or (off.norm() / want.norm()).item() < 2.56e-8 * (1.0, 1.03, 1.05, 1.07)[rows - 1]
+
+
+@pytest.mark.parametrize("n", [1, 4, 20, 32])
+@pytest.mark.parametrize("small", [-112, -140])
+def test_update_by_few_rows_of_small_beside_large_values(n, small):
+    """Every second gradient and every third hidden state in units of 2^small, beside others in the same tile that are 2^40 and 2^30:
+    elements are no less exact for it, also where a factor is below the smallest normal float.  Within (n + 10) roundings of the
+    terms' magnitudes as below (weights too small to be normal floats are rounded by their sigmoids' factors at 2^-149: twelve
+    times that)."""
+    H, V = 260, 130
+    rng = np.random.default_rng(n)
+    w = (rng.normal(size=V) * np.where(np.arange(V) % 2, 2.0 ** 40, 2.0 ** small)).astype(np.float32)
+    h = (rng.normal(size=(n, H)) * np.where(np.arange(H) % 3, 2.0 ** 30, 2.0 ** small)).astype(np.float32)
+    zero = np.zeros((n, V), np.float32)
+    got, ds, w, h = _one_layer(n, H, V, w, np.float32(2.0), h, zero, zero, np.zeros((V, H), np.float32), 1.0)
+    want = -w[:, None] * (ds @ h)
+    rounded = (n + 10) * 2.0 ** -24 * np.abs(w)[:, None] * (np.abs(ds) @ np.abs(h)) + 12 * 2.0 ** -149 * (1 + np.abs(h).sum(0))
+    assert (np.abs(got - want) <= rounded).all()
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 100])
+def test_update_near_overflow(rows):
+    """Products of 0.998 of the largest float, whose first pieces alone, rounded up, are past it"""
+    import torch
+    import paper_2408_08146_amd as KO
+    H = 200
+    g, h = torch.zeros(rows, H, device="cuda"), torch.zeros(rows, H, device="cuda")
+    g[-1], h[-1] = 1.998, 0.9999 * 2.0 ** 127
+    w = torch.zeros(H, H, device="cuda")
+    KO.MedusaHeadTrainer([w], 2 * torch.eye(H, device="cuda")).step(h, g, 1.0)
+    want = -g[-1, 0].double() * h[-1, 0].double()
+    assert ((w.double() / want - 1).abs() <= 2.0 ** -23).all()
+
+
 @pytest.mark.parametrize("n", [1, 20, 32, 33])
 def test_two_halves_of_a_gradient_where_pieces_do_not_hold(n):
     """Up to 32 positions the update of the mapping adds the draft's and the target's gradients itself.  Weights in units of 2^-112
