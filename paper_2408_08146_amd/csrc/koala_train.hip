@@ -636,7 +636,7 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
 // 1 to 2 %.
 // Measured, 32000 x 4096 by 20 rows: 188 us (5.6 TB/s), a kernel of plain multiply-adds with the rows of W dealt to all dies
 // 227; by 60 rows 222, both operands through LDS and W in pieces of 256 B 478; by 300 rows 615 and 1446; 4096 x 4096 by 128
-// rows 41 and 90; 1024 x 32000 by 40 rows 65 and 84; 4000 x 1000 by 4 rows 9.6 and 9.3.  Two workgroups a compute unit
+// rows 41 and 90; 1024 x 32000 by 40 rows 65 and 84.  Two workgroups a compute unit
 // with X two chunks ahead: 277 us at 32000 x 4096 by 60 rows, 49 at 4096 x 4096 by 128.
 // ---------------------------------------------------------------------------------------------
 enum { UPD_FEW = 32, UPD_EXACT = 48 };
@@ -888,6 +888,83 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same update of a small matrix by few rows (gemm_update), as plain fp32 multiply-adds in row order: no cutting, no way of the sums
+// through LDS, and pieces of any size for a workgroup, where the form above has a chain of latencies a tile and few tiles.  A wave
+// takes rows of W in pieces of 256 columns (1 KiB, PF of them under way) and holds its columns of X in registers; a workgroup's
+// four waves take the rows of its panel in turn and share the panel of G, transposed, in LDS, where a row's KP factors are
+// broadcast reads.
+// grid: x = column blocks, y = panels of mr rows.
+// ---------------------------------------------------------------------------------------------
+enum { UPD_MR = 128 };
+template <int KP>
+__global__ __launch_bounds__(256) void k_update_rows(const float *__restrict__ G, const float *__restrict__ G2, const float *__restrict__ X,
+                                                     float *W, float *bias, int M, int N, int rows, int mr, float alpha) {
+    constexpr int PF = 8;
+    __shared__ f32x4 gs[UPD_MR][KP / 4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int m0 = blockIdx.y * mr, n = (blockIdx.x * 64 + l) * 4, cnt = N - n;   // columns of this lane: four, or cnt of them
+    for (int i = threadIdx.x; i < mr * KP; i += 256) {
+        const int m = i % mr, r = i / mr;
+        float g = 0.f;
+        if (r < rows && m0 + m < M) {
+            g = G[(size_t)r * M + m0 + m];
+            if (G2) g += G2[(size_t)r * M + m0 + m];
+        }
+        ((float *)gs[m])[r] = g;
+    }
+    auto load = [&](const float *p) {
+        if (cnt >= 4) return (f32x4)*(const f32x4_a4 *)p;
+        f32x4 w = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < cnt) w[e] = p[e];
+        return w;
+    };
+    f32x4 x[KP], w[PF];
+#pragma unroll
+    for (int r = 0; r < KP; ++r) x[r] = r < rows ? load(X + (size_t)r * N + n) : (f32x4){0.f, 0.f, 0.f, 0.f};
+    // rows m0 + wave, + 4, ..
+    const int nrow = (min(mr, M - m0) - wave + 3) / 4;
+    float *row = W + (size_t)(m0 + wave) * N + n;
+    const size_t step = (size_t)4 * N;
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+        if (p < nrow) w[p] = load(row + p * step);
+    __syncthreads();
+    if (bias && blockIdx.x == 0 && (int)threadIdx.x < min(mr, M - m0)) {
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < KP; ++r) sum += gs[threadIdx.x][r / 4][r % 4];
+        bias[m0 + threadIdx.x] += alpha * sum;
+    }
+    for (int i = 0; i < nrow; i += PF) {
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+            if (i + p >= nrow) continue;
+            const f32x4 old = w[p];
+            float *o = row + (size_t)(i + p) * step;
+            if (i + p + PF < nrow) w[p] = load(o + PF * step);
+            f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < KP / 4; ++q) {
+                const f32x4 g = gs[wave + 4 * (i + p)][q];
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t[e] = fmaf(g[z], x[4 * q + z][e], t[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] = fmaf(alpha, t[e], old[e]);
+            if (cnt >= 4) *(f32x4_a4 *)o = t;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < cnt) o[e] = t[e];
+        }
+    }
+}
+
 // row tiles of a workgroup of k_stream_x3: those of all rows, or of equal blocks of up to eight
 int x3_tiles(int M) {
     const int tiles = (M + 15) / 16, nmb = (tiles + 7) / 8, mt = (tiles + nmb - 1) / nmb;
@@ -992,10 +1069,30 @@ void gemm_nt(hipStream_t st, const float *X, const float *W, float *C, float *pa
 void gemm_nn(hipStream_t st, const float *X, const float *W, float *C, float *part, int S, int M, int N, int K) {
     gemm_weights<true>(st, X, W, C, part, S, M, N, K, Join{});
 }
+template <int KP>
+void launch_update(hipStream_t st, const float *G, const float *G2, const float *X, float *W, float *bias, int M, int N, int rows,
+                   float alpha) {
+    const int nb = (N + 255) / 256;
+    int mr = UPD_MR;   // panels as high as leave a workgroup a compute unit: each reads its columns of X for itself
+    while (mr > 16 && (long)nb * ((M + mr - 1) / mr) < 256) mr /= 2;
+    k_update_rows<KP><<<dim3(nb, (M + mr - 1) / mr), 256, 0, st>>>(G, G2, X, W, bias, M, N, rows, mr, alpha);
+}
 // W[M,N] -= lr * G[rows,M]^T X[rows,N] and (bias not null) bias[M] -= lr * column sums of G; G2 (up to UPD_FEW rows, may be
 // null) is added to G
 void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr, float *bias = nullptr,
                  const float *G2 = nullptr) {
+    // Plain multiply-adds up to where the matrix takes as long either way.  A head step with this update and little else, us, them
+    // and k_update_x3: 1000 x 1000 by 4 rows 19.6 and 22.6, by 16 20.8 and 22.7; 3000 x 3000 by 8 38.9 and 39.3, 4096 x 4096
+    // 52.5 and 52.3; 1500 x 1500 by 16 26.8 and 27.1, 2048 x 2048 32.4 and 31.1; by 20 27.8 and 27.3 and 34.1 and 30.8.  A
+    // matrix of few rows leaves most of a tile empty: a discriminator step of one layer, 250 x 250 at 20 positions 26.8 and 28.8.
+    const size_t size = (size_t)M * N;
+    if (rows <= 8 ? size <= 1u << 24 : rows <= 16 ? size <= 5u << 19 : rows <= 24 && M <= 16 && size <= 5u << 19) {
+        switch ((rows + 7) / 8) {
+            case 1: return launch_update<8>(st, G, G2, X, W, bias, M, N, rows, -lr);
+            case 2: return launch_update<16>(st, G, G2, X, W, bias, M, N, rows, -lr);
+            default: return launch_update<24>(st, G, G2, X, W, bias, M, N, rows, -lr);
+        }
+    }
     const long tiles = (long)((M + 63) / 64) * ((N + 127) / 128);
     const int grid = (int)((tiles + 7) / 8 * 8);
     if (rows <= UPD_FEW) k_update_x3<true, true><<<grid, 256, 0, st>>>(G, G2, X, W, bias, M, N, rows, -lr);
