@@ -242,32 +242,46 @@ void rows_to_frags(koala_ctx *c, hipStream_t st, const float *a, int lda, int ro
     kb::fold(st, const_cast<float *>(a), lda, nullptr, 0, 0, 0, 0, rows, K, nullptr, c->xf, MT, nullptr, 0);
 }
 
+// The candidates of a row where an LM head finishes its logits in the GEMM, with its launch shape from 128 activation rows on; 0
+// where it takes partial sums instead, whose top-k pass costs 5 to 70 us more.
+// Many rows: partial sums let K be split freely, where a join in the kernel hands accumulators over (10 to 14 us a hand-over).  With
+// less than a round of workgroups (one layer, partial sums and joined, us): 240 rows, 4096 columns, 8000 tokens in three splits
+// 212 and 236, 16000 234 and 265; 512 rows, 4096 columns, 8000 tokens in two 292 and 325, 2048 columns, 12000 tokens 185 and
+// 175; whole K, 132 rows, 512 columns, 1000 tokens (12 workgroups) 77 and 79, 240 rows and 4000 tokens (42) 84 and 82.  20000
+// tokens and more: joined at 512 to 6656 columns, by 1 to 15 %.
+// Up to 64 rows every workgroup takes in all of them, and with 33 and more of many columns that is the longer way where the
+// vocabulary makes few workgroups: 64 rows, 4000 tokens (63 workgroups) 50 and 46 at 512 columns, 77 and 72 at 2048, 104
+// and 106 at 4096, 167 and 175 at 6656; 8000 tokens (125) 111 and 109 at 4096, 176 and 179 at 6656.
+int head_groups(int Npad, int H, int rows, int MT, int n_cu, size_t room, int n_cnt, kb::BigShape *b) {
+    if (MT >= 8) {
+        if (!big_fits32(Npad, H, MT) || !big_gemm_enabled()) return 0;
+        *b = kb::big_shape(Npad, H, rows, n_cu, true, room, n_cnt);
+        const int n = kb::big_groups(Npad, *b);
+        const long wgs = (long)n * b->n_pm;
+        const bool joined = wgs >= n_cu || (b->S == 1 ? 7 * wgs >= n_cu : b->S == 2 && Npad >= 12000);
+        return joined && n <= 1024 ? n : 0;   // k_topk_stage2 takes 1024
+    }
+    const int n = kb::rows_logits_groups(Npad, n_cu);
+    return MT == 4 && (long)H * (n_cu - n) > 2600L * n_cu ? 0 : n;
+}
+
 // LM head whose logits are finished in the GEMM, on the fragments in c->xf: to `logits` (may be null) and, if wanted, the
-// candidates for kb::best_logit.  Returns the candidates of a row, 0 where the vocabulary or the number of rows is one that
-// takes partial sums instead (bf_gemm, then kb::logits_topk).
+// candidates for kb::best_logit.  Returns the candidates of a row, 0 where it takes partial sums instead (bf_gemm, then
+// kb::logits_topk).
 int bf_head_logits(koala_ctx *c, hipStream_t st, int rows, int MT, const kb::NormScale &ns, float *logits, bool best) {
     const int V = c->shape.vocab, H = c->shape.hidden, Npad = kb::pad64(V);
     float *val = best ? c->cand_val : nullptr;
     int *idx = best ? c->cand_idx : nullptr;
-    if (MT >= 8 && big_fits32(Npad, H, MT) && big_gemm_enabled()) {
-        const kb::BigShape b = kb::big_shape(Npad, H, rows, c->n_cu, true, c->part_bytes, c->max_batch * c->shape.n_heads * 4);
-        const int n = kb::big_groups(Npad, b);
-        if (n > 1024) return 0;   // more than k_topk_stage2 takes
-        const LaunchEvents ev = timed_launch(c, (double)Npad * H * 2.0);
+    kb::BigShape b{};
+    const int n = head_groups(Npad, H, rows, MT, c->n_cu, c->part_bytes, c->max_batch * c->shape.n_heads * 4, &b);
+    if (!n) return 0;
+    const LaunchEvents ev = timed_launch(c, (double)Npad * H * 2.0);
+    if (MT >= 8)
         kb::gemm_big_logits(st, c->w.lm_head, c->xf, H, MT, b, ns, rows, logits, V, val, idx, c->part, c->part_bytes, c->attn_cnt,
                             ev.start, ev.stop);
-        return n;
-    }
-    // Every workgroup takes in all of the rows: with 33 rows and more of many columns that is the longer way where the vocabulary
-    // makes few workgroups (64 rows, one layer at 4096 columns: 4000 tokens, 63 workgroups, 106 us against 102 with K split over
-    // the chip; 8000 tokens 107 and 110, 512 columns and 4000 tokens 46 and 50; 26 rows at 4096 columns and 4000 tokens 83 and 86).
-    const int n = MT <= 4 ? kb::rows_logits_groups(Npad, c->n_cu) : 0;
-    if (n && !(MT == 4 && H >= 2048 && 8 * n < 3 * c->n_cu)) {
-        const LaunchEvents ev = timed_launch(c, (double)Npad * H * 2.0);
+    else
         kb::gemm_rows_logits(st, c->w.lm_head, c->xf, H, MT, ns, rows, logits, V, val, idx, c->n_cu, ev.start, ev.stop);
-        return n;
-    }
-    return 0;
+    return n;
 }
 
 // bf16 decoder layer.  On entry c->pend_* may describe partial sums still to be folded into x, or c->frags_ready says that
@@ -401,6 +415,14 @@ koala_status check_call(koala_ctx *c, int batch) {
 }  // namespace
 
 extern "C" {
+
+// For tests: head_groups of a context with `heads` heads in all its sequences and room for four splits of the head's sums
+int kt_head_groups(int vocab, int hidden, int rows, int heads, int n_cu) {
+    const int Npad = kb::pad64(vocab), MT = kb::mt_of(rows);
+    kb::BigShape b{};
+    return head_groups(Npad, hidden, rows, MT, n_cu, (size_t)4 * Npad * MT * 16 * sizeof(float), heads * 4, &b);
+}
+
 
 koala_status koala_create(const koala_shape *shape, const koala_draft_shape *draft, const koala_tree *tree,
                           int max_batch, koala_ctx **out) {
