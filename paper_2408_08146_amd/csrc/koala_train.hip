@@ -18,7 +18,6 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 struct __attribute__((packed, aligned(4))) f32x4_any { float x, y, z, w; };   // 16 bytes at a 4-byte aligned address
-struct __attribute__((packed, aligned(4))) f32x2_any { float x, y; };
 typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4_a4;   // as vectors: loaded, kept and used as one
 typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 
@@ -37,12 +36,12 @@ typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 // as fast as in fp32.
 //
 // Workgroup of 256 threads on a tile of 64 n x BM m; K in chunks of 32.  Both operands of a chunk go from memory to
-// registers (two chunks ahead, so that about 50 KB a compute unit are under way), are cut into their three planes there
-// and put into LDS as MFMA fragments, double-buffered with one barrier a chunk.  P is the MFMA's row operand: a lane then
-// holds four consecutive n of one m, a 16-byte piece of a row of C.
+// registers (up to 64 rows four chunks ahead, else two), are cut into their three planes there and put into LDS as MFMA
+// fragments, double-buffered with one barrier a chunk.  P is the MFMA's row operand: a lane then holds four consecutive n of
+// one m, a 16-byte piece of a row of C.
 //   k-contiguous (KS false; Q is): element (i, k) at i * ld + k;  8 threads x 16 B cover 128 B of a row
-//   k-strided    (KS true):        element (i, k) at k * ld + i;  a thread takes 8 consecutive k of one or two i, the
-//                                  eight values of a fragment lane
+//   k-strided    (KS true):        element (i, k) at k * ld + i;  a thread takes 8 consecutive k of one i, the eight values
+//                                  of a fragment lane
 // LDS plane of a 16-row tile: 64 slots of 16 B, lane (i, g = k/8) in slot (i ^ 4 g) + 16 g: the 8-byte stores of 32 lanes of
 // the k-contiguous form (four rows, all g) then fall into different banks.
 // Rows past the end re-read the last one (never stored); k past the end is zero in both operands.  Where pieces do not stand
@@ -51,9 +50,10 @@ typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 // are off by up to 2^-125.
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  A
 // split's sums go to out[split][M][N], for k_sum_parts where there are several.
-// The products of all but the smallest matrices are k_stream_x3's, the updates k_update_x3's (both below).
-// Registers for four workgroups a compute unit up to 32 rows (three: 158 instead of 132 us for the 20 rows above, by
-// themselves), two beyond (three spill: 54 -> 95 us for the 40 rows).
+// Its products are the small ones, of few chunks or few tiles (gemm_weights), and what bounds them is latency: a start, and a
+// round trip a chunk.  The others are k_stream_x3's, the updates k_update_x3's and k_update_rows' (all below).
+// Registers for four workgroups a compute unit up to 32 rows (room for three is as fast: forward pass of a head of 512 x 4000 at 20
+// rows 20.6 us and 20.4), two beyond (three spill with 128 rows: 256 x 1000 at 100 rows 21 -> 36 us).
 // ---------------------------------------------------------------------------------------------
 enum { X3_BN = 64, X3_BK = 32 };
 
@@ -101,7 +101,8 @@ constexpr uint32_t LEAST_EXACT = (25u << 24) - 1;   // 2^-102 so
 // One operand's share of a chunk in a thread's registers, and its way into LDS.  T rows (32, 64 or 128).
 template <int T, bool KS, int DEPTH>
 struct X3Loader {
-    static constexpr int PER = KS && T == 32 ? 8 : T * X3_BK / 256;   // floats per thread (KS, 32 rows: of half of them)
+    static_assert(!KS || T == 64, "k-strided: a wave per eight k");
+    static constexpr int PER = T * X3_BK / 256;              // floats per thread
     static constexpr int TILE = 64;                          // 16-byte units of a plane of one 16-row tile
     const float *p;
     long ld;
@@ -129,25 +130,12 @@ struct X3Loader {
                 }
             }
         } else {
-            constexpr int W = T / 64 > 0 ? T / 64 : 1;       // consecutive i per thread
-            const int g = t / (T / W), i = (t % (T / W)) * W;
-            if (T / W * 4 < 256 && g > 3) return;            // T = 32: half of the threads
-            const bool whole = i0 + T <= rows;
+            const int g = t >> 6, i = min(i0 + (t & 63), rows - 1);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = k0 + 8 * g + e;
-                const float *src = p + (long)min(k, K - 1) * ld;
-                if (W == 2 && whole) {
-                    const f32x2_any w = *(const f32x2_any *)(src + i0 + i);
-                    d[e] = k < K ? w.x : 0.f;
-                    d[(W - 1) * 8 + e] = k < K ? w.y : 0.f;
-                } else {
-#pragma unroll
-                    for (int w = 0; w < W; ++w) {
-                        const float x = src[min(i0 + i + w, rows - 1)];
-                        d[w * 8 + e] = k < K ? x : 0.f;
-                    }
-                }
+                const float x = p[(long)min(k, K - 1) * ld + i];
+                d[e] = k < K ? x : 0.f;
             }
         }
     }
@@ -170,19 +158,14 @@ struct X3Loader {
                 *(u32x2 *)(dst + 2 * PL) = (u32x2){l[0], l[1]};
             }
         } else {
-            constexpr int W = T / 64 > 0 ? T / 64 : 1;
-            const int g = t / (T / W), i = (t % (T / W)) * W;
-            if (T / W * 4 < 256 && g > 3) return;
+            const int g = t >> 6, i = t & 63;
+            uint32_t h[4], m[4], l[4];
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                uint32_t h[4], m[4], l[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) split3(d[w * 8 + 2 * e], d[w * 8 + 2 * e + 1], h[e], m[e], l[e], top);
-                u32x4 *dst = lds + ((i + w) >> 4) * TILE + (((i + w) & 15) ^ (4 * g)) + 16 * g;
-                dst[0] = (u32x4){h[0], h[1], h[2], h[3]};
-                dst[(T / 16) * TILE] = (u32x4){m[0], m[1], m[2], m[3]};
-                dst[2 * (T / 16) * TILE] = (u32x4){l[0], l[1], l[2], l[3]};
-            }
+            for (int e = 0; e < 4; ++e) split3(d[2 * e], d[2 * e + 1], h[e], m[e], l[e], top);
+            u32x4 *dst = lds + (i >> 4) * TILE + ((i & 15) ^ (4 * g)) + 16 * g;
+            dst[0] = (u32x4){h[0], h[1], h[2], h[3]};
+            dst[(T / 16) * TILE] = (u32x4){m[0], m[1], m[2], m[3]};
+            dst[2 * (T / 16) * TILE] = (u32x4){l[0], l[1], l[2], l[3]};
         }
     }
 };
