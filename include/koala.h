@@ -238,7 +238,11 @@ koala_status koala_draft_expand_sample(koala_ctx *ctx, void *hip_stream, int bat
  *   target_logits device fp32 [batch, n_nodes, vocab]: logits_out of koala_tree_verify;
  *   draft_logits  device fp32 [batch, n_nodes, vocab]: from koala_draft_expand_sample;
  *   u_accept, u_resample device fp32 [batch, n_nodes]: uniforms in [0,1);
- *   outputs and commit as in koala_accept_prefix. */
+ *   outputs and commit as in koala_accept_prefix.
+ * Scratch: up to 32768 tokens 80 whole numbers a sequence in the workspace, by which the nodes of a tree
+ * tell each other what has become of them; koala_bind clears them and every call that has run to its end
+ * leaves them clear (after one that the device has broken off, bind again).  Beyond, two rows of the
+ * vocabulary a sequence, which need not be clear. */
 koala_status koala_accept_sample(koala_ctx *ctx, void *hip_stream, int batch,
                                  const int32_t *tree_tokens, const float *target_logits,
                                  const float *draft_logits, const float *u_accept,
@@ -250,7 +254,9 @@ koala_status koala_accept_sample(koala_ctx *ctx, void *hip_stream, int batch,
  * koala_accept_sample (same kernels, same results bit for bit) except that where the walk keeps the two
  * vocabulary-sized distributions of a sequence in memory, which it does for vocabularies above 32768, they
  * are held in a fixed array inside the library (2 MiB of device memory per GPU, present from the moment the
- * library is loaded until the process ends) instead of the workspace.  The call allocates nothing.
+ * library is loaded until the process ends) instead of the workspace.  Up to 32768 tokens it uses the same
+ * whole numbers in the workspace as koala_accept_sample, in the same way, so the two calls on one context
+ * are to be ordered like any others.  The call allocates nothing.
  *   Limit, at every vocabulary: batch * vocab <= 262144, else KOALA_E_CAPACITY (nothing is launched).
  *   The array is shared by every context and every call on the same GPU: two calls that use it and overlap
  *   on one GPU (different streams or threads) race; calls on one stream are ordered.  Nothing in the

@@ -64,7 +64,7 @@ struct koala_ctx {
     int n_cu;                      // compute units of the device the context is bound on
     int attn_ns;                   // key splits of the attention kernels (fixed at create)
     float *med_logits;                                   // [D * max_batch][V] per-depth logits of Medusa-style heads (sampled drafting)
-    int *acc_state;                                      // [max_batch][ks::ACCEPT_STATE] zero between calls
+    int *acc_state;                                      // [max_batch][ks::ACCEPT_STATE] cleared by koala_bind, left clear by every call
     float *acc_q, *acc_d;                                // [max_batch][V] distributions of the stochastic acceptance walk (rows in memory)
     // bf16 path: GEMM input as fp16 MFMA fragments, and the split-K partial sums
     void *xf, *xf2;   // xf2: input of the down projection (written by the gate/up projection's epilogue)
