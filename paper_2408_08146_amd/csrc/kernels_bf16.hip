@@ -1994,9 +1994,12 @@ __global__ __launch_bounds__(64 * NWV) void k_attn_tree(const u32x4 *qf_in, cons
     }
     __syncthreads();
     // Two row tiles of heads of 128: one workgroup fits a compute unit anyway, so a wave has the registers to keep the query
-    // fragments (eight sequences of the 33B shape: 1799 -> 1790 us for two layers).  Heads of 64 would lose their second
-    // workgroup; a single row tile has few reads to save, and passes of a few rows few steps (EAGLE-style drafting at 7B
-    // with it: 0.5 % slower).
+    // fragments.  Whole passes, read from LDS with every step and kept, us, in two rounds of alternating runs: eight sequences of
+    // 60 nodes over 8000 keys (7B, two layers) 1156, 1155 -> 1148, 1145 (runs of one side within 0.3 %), four over 2000 to 4000
+    // 658, 659 -> 654, 659, eight of four heads 417, 422 -> 414, 419; one of 26 nodes over 8000 keys 515, 515 -> 514, 513, over
+    // 1024 438 -> 437; one of 60 over 4096 (13B) 406 -> 405; eight of 26 nodes 1538, 1518 and 1544, 1523 (runs within 1.1 %).
+    // Heads of 64 would lose their second workgroup; a single row tile has few reads to save, and passes of a few rows few
+    // steps (EAGLE-style drafting at 7B with it: 0.5 % slower).
     constexpr bool QREG = DH == 128 && MT == 2;
     auto query = [&](int mt, int ks, int z) { return __builtin_bit_cast(bf16x8, qf[((mt * KS + ks) * 2 + z) * 64 + l]); };
     bf16x8 qr[QREG ? MT : 1][QREG ? KS : 1][2];

@@ -331,9 +331,11 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
 // in Q; where a weight there is infinite the tile is summed anew below), stages past the last re-read it.
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die, y = K splits.
 // N >= 32, K >= 64, ldp and ldq < 2^23 (32-bit offsets).
-// Measured against the form above (both operands through LDS): 20 x 32000 from K = 4096 147 -> 117 us (4.6 TB/s), 40 x 1024
-// from K = 32000 59 -> 40, 40 x 32000 from K = 1024 (KS) 61 -> 33, 128 x 32000 from K = 4096 300 -> 187 us (six products of pieces:
-// 1.08 PFLOP/s in bfloat16, about what a large product reaches here), 128 x 4096 from K = 32000 (KS) 306 -> 167.
+// Measured within training steps, by kernel trace, against the form above (both operands through LDS): 20 x 32000 from K = 4096
+// 115 (in two splits, joined by a further launch) -> 97 us (5.4 TB/s), and where the step before has just updated that matrix
+// 137 -> 127 (4.1 TB/s); 40 x 1024 from K = 32000 53 -> 41; 40 x 32000 from K = 1024 (KS) 54 -> 34; 128 x 32000 from K = 4096
+// 273 -> 181 (six products of pieces: 1.11 PFLOP/s in bfloat16, what a large product reaches here); 128 x 4096 from K = 32000 (KS)
+// 299 -> 186.
 // The stream bounds up to 64 rows (without its MFMAs the kernel takes as long), the matrix pipe beyond.
 // ---------------------------------------------------------------------------------------------
 template <int MT, bool KS, bool KT>
@@ -617,10 +619,10 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
 // weigh), a tile whose sums overflow, as products of first pieces may where the whole does not, is summed anew on the fp32 pipe,
 // and so is, EXACT, one with a value below 2^-102 beside larger ones.  EXACT up to UPD_EXACT rows, where memory bounds all sizes: it costs
 // 1 to 2 %.
-// Measured, 32000 x 4096 by 20 rows: 188 us (5.6 TB/s), a kernel of plain multiply-adds with the rows of W dealt to all dies
-// 227; by 60 rows 222, both operands through LDS and W in pieces of 256 B 478; by 300 rows 615 and 1446; 4096 x 4096 by 128
-// rows 41 and 90; 1024 x 32000 by 40 rows 65 and 84.  Two workgroups a compute unit
-// with X two chunks ahead: 277 us at 32000 x 4096 by 60 rows, 49 at 4096 x 4096 by 128.
+// Measured within training steps, by kernel trace: 32000 x 4096 by 20 rows 188 us (5.6 TB/s), plain multiply-adds with the rows of W
+// dealt to all dies 216; by 60 rows 223, both operands through LDS and W in pieces of 256 B 470; by 300 rows 606 and 1451;
+// 4096 x 4096 by 20 rows 30 and 34, by 128 rows 46 and 85; 1024 x 32000 by 40 rows 66 and 76.  Two workgroups a compute unit with X
+// two chunks ahead, by themselves: 277 us at 32000 x 4096 by 60 rows and 49 at 4096 x 4096 by 128, with three 222 and 41.
 // ---------------------------------------------------------------------------------------------
 enum { UPD_FEW = 32, UPD_EXACT = 48 };
 template <bool FEW, bool EXACT>
