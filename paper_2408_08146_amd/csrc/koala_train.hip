@@ -92,12 +92,6 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t &h, uint32_t &
 // pass: their pieces are some as well.
 __device__ __forceinline__ bool pieces_hold(float top) { return top < 0x1.ffp127f && (top >= 0x1p-102f || top == 0.f); }
 
-// The smaller of `least` and the magnitudes of a and b, as whole numbers in which zero is the largest of all
-__device__ __forceinline__ uint32_t least2(float a, float b, uint32_t least) {
-    return min(min((__float_as_uint(a) << 1) - 1, (__float_as_uint(b) << 1) - 1), least);
-}
-constexpr uint32_t LEAST_EXACT = (25u << 24) - 1;   // 2^-102 so
-
 // One operand's share of a chunk in a thread's registers, and its way into LDS.  T rows (32, 64 or 128).
 template <int T, bool KS, int DEPTH>
 struct X3Loader {
@@ -616,9 +610,10 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
 // No less exact than a chain of fp32 multiply-adds, at any number of rows: 2.53e-8 of a sum of random terms at one row (both; with
 // six products of pieces 2.60e-8, and the largest error 1.7 times a rounding), 2.6e-8 against 3.1e-8 at two, 3.9e-8 against
 // 1.03e-7 at 32 (2-norm).  For it FEW keeps eight of the nine products (33 rows and more round oftener than the other two would
-// weigh), a tile whose sums overflow, as products of first pieces may where the whole does not, is summed anew on the fp32 pipe,
-// and so is, EXACT, one with a value below 2^-102 beside larger ones.  EXACT up to UPD_EXACT rows, where memory bounds all sizes: it costs
-// 1 to 2 %.
+// weigh), EXACT takes both operands times 2^24, so that pieces stand for values of any size, and a tile whose sums overflow, as they
+// may where the whole does not, is summed anew on the fp32 pipe.  EXACT up to UPD_EXACT rows, where memory bounds all sizes: with
+// the eight products it costs 1 to 2 %.  (Tiles with a value below 2^-102 beside larger ones summed anew instead: gradients of a
+// discriminator that no longer errs are such, and the update of 32000 x 4096 by 20 rows took 271 us, that of 1024 x 32000 by 40 88.)
 // Measured within training steps, by kernel trace: 32000 x 4096 by 20 rows 188 us (5.6 TB/s), plain multiply-adds with the rows of W
 // dealt to all dies 216; by 60 rows 223, both operands through LDS and W in pieces of 256 B 470; by 300 rows 606 and 1451;
 // 4096 x 4096 by 20 rows 30 and 34, by 128 rows 46 and 85; 1024 x 32000 by 40 rows 66 and 76.  Two workgroups a compute unit with X
@@ -644,7 +639,10 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     const bool edge = n0 + BN > N, whole = !edge && m0 + BM <= M, second = nx > nl;
     f32x2 xv[8];
     float gtop = 0.f, xtop = 0.f, gsum = 0.f;   // largest magnitudes, this thread's share of its column's sum
-    uint32_t gleast = ~0u, xleast = ~0u;         // EXACT: smallest
+    // EXACT: both operands times 2^24.  Every float is then a multiple of 2^-125, and so are its pieces: none is below the smallest
+    // normal bfloat16.
+    constexpr float UP = EXACT ? 0x1p24f : 1.f, DOWN = EXACT ? 0x1p-48f : 1.f;
+    auto holds = [](float top) { return EXACT ? top < 0x1.ffp127f : pieces_hold(top); };
     auto load_x = [&](int r0) __attribute__((always_inline)) {
         if (r0 + 32 <= rows && N > 1 && N < 1 << 25) {
             unsigned off = 4u * (8u * lg * (unsigned)N + nl);
@@ -671,8 +669,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 uint32_t h, m, w;
-                split3(xv[2 * e][t], xv[2 * e + 1][t], h, m, w, xtop);
-                if (EXACT) xleast = least2(xv[2 * e][t], xv[2 * e + 1][t], xleast);
+                split3(UP * xv[2 * e][t], UP * xv[2 * e + 1][t], h, m, w, xtop);
                 a[0][t][e] = h; a[1][t][e] = m; a[2][t][e] = w;
             }
     };
@@ -766,8 +763,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     uint32_t p, q, r;
-                    split3(gv[i][2 * e], gv[i][2 * e + 1], p, q, r, gtop);
-                    if (EXACT) gleast = least2(gv[i][2 * e], gv[i][2 * e + 1], gleast);
+                    split3(UP * gv[i][2 * e], UP * gv[i][2 * e + 1], p, q, r, gtop);
                     h[e] = p; m[e] = q; w[e] = r;
                 }
                 u32x4 *dst = gs + i * 3 * PL + (l >> 4) * 64 + 16 * wave + li;
@@ -803,7 +799,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
         for (int j = 0; j < TM; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
-                acc[t][j][r] += fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f;
+                acc[t][j][r] = (acc[t][j][r] + (fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f)) * DOWN;
     bool finite = true;
 #pragma unroll
     for (int t = 0; t < TN; ++t)
@@ -811,10 +807,6 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
         for (int j = 0; j < TM; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) finite &= fabsf(acc[t][j][r]) < INFINITY;
-    if (EXACT) {
-        if (gleast < LEAST_EXACT) gtop = INFINITY;
-        if (xleast < LEAST_EXACT) xtop = INFINITY;
-    }
     // the largest magnitudes of G's columns and of this wave's columns of X
     for (int o = 32; o > 0; o >>= 1) { gtop = fmaxf(gtop, __shfl_xor(gtop, o)); xtop = fmaxf(xtop, __shfl_xor(xtop, o)); }
     if (l == 0) tops[wave] = gtop;
@@ -822,7 +814,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     __syncthreads();
     if (bias && n0 == 0 && wave == 0 && m0 + l < M) bias[m0 + l] += alpha * ((bsum[0][l] + bsum[1][l]) + (bsum[2][l] + bsum[3][l]));
     gtop = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
-    if (!pieces_hold(gtop) || !pieces_hold(xtop) || !__all(finite)) {
+    if (!holds(gtop) || !holds(xtop) || !__all(finite)) {
         // once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds r = g of column i), four r a step
 #pragma unroll
         for (int t = 0; t < TN; ++t)

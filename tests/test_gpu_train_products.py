@@ -423,7 +423,7 @@ def test_update_by_few_rows_to_the_last_bit(H, rows):
     assert (off.norm() / want.norm()).item() < 2.56e-8 * (1.0, 1.03, 1.05, 1.07)[rows - 1]
 
 
-@pytest.mark.parametrize("n", [1, 4, 20, 32])
+@pytest.mark.parametrize("n", [1, 4, 20, 32, 40])
 @pytest.mark.parametrize("small", [-112, -140])
 def test_update_by_few_rows_of_small_beside_large_values(n, small):
     """Every second gradient and every third hidden state in units of 2^small, beside others in the same tile that are 2^40 and 2^30:
@@ -441,14 +441,16 @@ def test_update_by_few_rows_of_small_beside_large_values(n, small):
     assert (np.abs(got - want) <= rounded).all()
 
 
-@pytest.mark.parametrize("rows", [1, 32, 33, 100])
-def test_update_near_overflow(rows):
-    """Products of 0.998 of the largest float, whose first pieces alone, rounded up, are past it"""
+@pytest.mark.parametrize("rows", [1, 20, 32, 33, 48, 49, 100])
+@pytest.mark.parametrize("gv,hv", [(1.998, 0.9999 * 2.0 ** 127), (1.3 * 2.0 ** 60, 1.7 * 2.0 ** 40), (1.3 * 2.0 ** 110, 1.7 * 2.0 ** -60)])
+def test_update_near_overflow(rows, gv, hv):
+    """Products of 0.998 of the largest float, whose first pieces alone, rounded up, are past it; products and factors that are
+    not near it but would be past it times 2^48 and 2^24"""
     import torch
     import paper_2408_08146_amd as KO
     H = 200
     g, h = torch.zeros(rows, H, device="cuda"), torch.zeros(rows, H, device="cuda")
-    g[-1], h[-1] = 1.998, 0.9999 * 2.0 ** 127
+    g[-1], h[-1] = gv, hv
     w = torch.zeros(H, H, device="cuda")
     KO.MedusaHeadTrainer([w], 2 * torch.eye(H, device="cuda")).step(h, g, 1.0)
     want = -g[-1, 0].double() * h[-1, 0].double()
