@@ -408,9 +408,9 @@ def test_discriminator_updates_of_small_matrices(n, H, V, DH, n_fc):
 @pytest.mark.parametrize("H", [4100])
 def test_update_by_few_rows_to_the_last_bit(H, rows):
     """A chain of fp32 multiply-adds rounds each term and each sum of several once: every element within rows roundings of 2^-24
-    of its terms' magnitudes, which is 2 at two rows, where the matrix pipe, which cuts off what its sums do not hold, needs three.
-    2^-6 of that on top: products of pieces are added among themselves first, at 2^-8 of the whole.  In the 2-norm a chain's
-    rounding of a single term, 2.53e-8, and less than a chain's from two on."""
+    of its terms' magnitudes (the matrix pipe, which cuts off what its sums do not hold, would need three at two rows).  2^-6 of
+    that on top: products of pieces are added among themselves first, at 2^-8 of the whole.  In the 2-norm a chain's rounding of
+    a single term, 2.53e-8, and that times the root of 1.5 at two rows, which are such a chain; less than a chain's beyond."""
     import torch
     import paper_2408_08146_amd as KO
     gen = torch.Generator(device="cuda").manual_seed(H + rows)
@@ -419,8 +419,8 @@ def test_update_by_few_rows_to_the_last_bit(H, rows):
     KO.MedusaHeadTrainer([w], 2 * torch.eye(H, device="cuda")).step(h, g, 1.0)
     want = g.double().T @ h.double()
     off = (w.double() + want).abs()
-    assert (off <= (1 + 2.0 ** -6) * max(rows, 3 * (rows > 1)) * 2.0 ** -24 * (g.double().abs().T @ h.double().abs())).all()
-    assert (off.norm() / want.norm()).item() < 2.56e-8 * (1.0, 1.03, 1.05, 1.07)[rows - 1]
+    assert (off <= (1 + 2.0 ** -6) * rows * 2.0 ** -24 * (g.double().abs().T @ h.double().abs())).all()
+    assert (off.norm() / want.norm()).item() < 2.56e-8 * (1.0, 1.5 ** 0.5, 1.05, 1.07)[rows - 1]
 
 
 @pytest.mark.parametrize("n", [1, 4, 20, 32, 40])
