@@ -350,10 +350,10 @@ koala_status koala_profile_end(koala_ctx *ctx, double *gemm_ms, int *gemm_launch
  * others are at most 2^-24 of a product; updates by up to 32 rows keep eight), or as plain fp32
  * multiply-adds.  The error of a sum, measured against that of a chain of fp32 multiply-adds, is 1.03 times
  * as large at a single term and 0.85 at two (updates: as large at either), a half at eight and a third at 64
- * terms and more.  Infinities and not-a-numbers come out as in fp32; forward products and input gradients
- * may be infinite where a product of two factors is within 2^-7 of overflow.  Their operand values below
- * 2^-102 beside larger ones of the same 32 to 128 rows are taken to within 2^-125, and those of updates by
- * more than 48 rows.
+ * terms and more.  Infinities and not-a-numbers come out as in fp32; forward products may be infinite where
+ * a product of two factors is within 2^-7 of overflow.  Values below 2^-102 beside larger ones of the same 32
+ * to 128 rows are taken to within 2^-125 in forward products and in updates by more than 48 rows, and the
+ * weights' in input gradients.
  *
  * The discriminator D (section 3.2: a linear layer followed by fully connected layers, as many as the
  * draft head has layers) scores a row of token logits together with the target model's last hidden

@@ -47,7 +47,9 @@ typedef float __attribute__((ext_vector_type(2), aligned(4))) f32x2_a4;
 // Rows past the end re-read the last one (never stored); k past the end is zero in both operands.  Where pieces do not stand
 // for an operand of the tile (an infinity, or all of it below 2^-102: the MFMA takes pieces below 2^-126 as zero) the tile is
 // summed again on the fp32 pipe, so that it comes out as it does there.  Values below 2^-102 beside larger ones
-// are off by up to 2^-125.
+// are off by up to 2^-125.  In input gradients (KS) Q is taken times 2^24 instead, and pieces stand for all of its values: the
+// gradients of a discriminator that no longer errs are such, and summing again took 109 us instead of 28 (40 x 32000 from K = 1024).
+// Sums that overflow for it are summed again.
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die (indices 8 apart), y = K splits.  A
 // split's sums go to out[split][M][N], for k_sum_parts where there are several.
 // Its products are the small ones, of few chunks or few tiles (gemm_weights), and what bounds them is latency: a start, and a
@@ -90,10 +92,14 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t &h, uint32_t &
 // whether pieces stand for an operand of this largest magnitude: not where one is infinite or rounds to infinity in bfloat16,
 // nor where all are so small (but not zero) that their last pieces are below 2^-126, which the MFMA takes as zero.  Not-a-numbers
 // pass: their pieces are some as well.
-__device__ __forceinline__ bool pieces_hold(float top) { return top < 0x1.ffp127f && (top >= 0x1p-102f || top == 0.f); }
+// up: of the operand times 2^24.  Every float is then a multiple of 2^-125, and so are its pieces: none is below the smallest
+// normal bfloat16.
+constexpr float x3_up(bool up) { return up ? 0x1p24f : 1.f; }
+constexpr float x3_down(bool up) { return up ? 0x1p-24f : 1.f; }
+__device__ __forceinline__ bool pieces_hold(float top, bool up) { return top < 0x1.ffp127f && (up || top >= 0x1p-102f || top == 0.f); }
 
 // One operand's share of a chunk in a thread's registers, and its way into LDS.  T rows (32, 64 or 128).
-template <int T, bool KS, int DEPTH>
+template <int T, bool KS, int DEPTH, bool UP>
 struct X3Loader {
     static_assert(!KS || T == 64, "k-strided: a wave per eight k");
     static constexpr int PER = T * X3_BK / 256;              // floats per thread
@@ -144,7 +150,7 @@ struct X3Loader {
                 const int i = (t >> 3) + 32 * q;
                 uint32_t h[2], m[2], l[2];
 #pragma unroll
-                for (int e = 0; e < 2; ++e) split3(d[4 * q + 2 * e], d[4 * q + 2 * e + 1], h[e], m[e], l[e], top);
+                for (int e = 0; e < 2; ++e) split3(x3_up(UP) * d[4 * q + 2 * e], x3_up(UP) * d[4 * q + 2 * e + 1], h[e], m[e], l[e], top);
                 unsigned char *dst = (unsigned char *)(lds + (i >> 4) * TILE + ((i & 15) ^ (4 * g)) + 16 * g) + 8 * (t & 1);
                 constexpr int PL = (T / 16) * TILE * 16;
                 *(u32x2 *)dst = (u32x2){h[0], h[1]};
@@ -180,8 +186,8 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
     const int n0 = nt * X3_BN, m0 = mb * BM;
     const int nch = (K + X3_BK - 1) / X3_BK, S = gridDim.y;
     const int c0 = (int)((unsigned)(blockIdx.y * nch) / (unsigned)S), c1 = (int)((unsigned)((blockIdx.y + 1) * nch) / (unsigned)S);
-    X3Loader<X3_BN, PKS, DEPTH> lp;
-    X3Loader<BM, false, DEPTH> lq;
+    X3Loader<X3_BN, PKS, DEPTH, false> lp;
+    X3Loader<BM, false, DEPTH, PKS> lq;
     lp.init(P, ldp, N, n0, K);
     lq.init(Q, ldq, M, m0, K);
     // the products of the first pieces, and all the others, which are 2^-8 of them: small as they are, the second sum's
@@ -254,7 +260,15 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
         for (int j = 0; j < TM; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
-                acc[i][j][r] += fabsf(acc[i][j][r]) < INFINITY ? low[i][j][r] : 0.f;
+                acc[i][j][r] = (acc[i][j][r] + (fabsf(acc[i][j][r]) < INFINITY ? low[i][j][r] : 0.f)) * x3_down(PKS);
+    bool finite = true;
+    if (PKS)
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) finite &= fabsf(acc[i][j][r]) < INFINITY;
     // every thread has cut up its share of both operands: the tile's largest magnitudes
     __shared__ float tops[2][4];
     for (int o = 32; o > 0; o >>= 1) { ptop = fmaxf(ptop, __shfl_xor(ptop, o)); qtop = fmaxf(qtop, __shfl_xor(qtop, o)); }
@@ -262,7 +276,7 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
     __syncthreads();
     ptop = fmaxf(fmaxf(tops[0][0], tops[0][1]), fmaxf(tops[0][2], tops[0][3]));
     qtop = fmaxf(fmaxf(tops[1][0], tops[1][1]), fmaxf(tops[1][2], tops[1][3]));
-    if (!pieces_hold(ptop) || !pieces_hold(qtop)) {
+    if (!pieces_hold(ptop, false) || !pieces_hold(qtop, PKS) || !__all(finite)) {
         // the tile once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds k = g of row i), sixteen k a step
         const int kend = min(K, c1 * X3_BK);
 #pragma unroll
@@ -326,10 +340,10 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
 // grid: x = n tiles x m blocks, the m blocks of an n tile on one die, y = K splits.
 // N >= 32, K >= 64, ldp and ldq < 2^23 (32-bit offsets).
 // Measured within training steps, by kernel trace, against the form above (both operands through LDS): 20 x 32000 from K = 4096
-// 115 (in two splits, joined by a further launch) -> 97 us (5.4 TB/s), and where the step before has just updated that matrix
-// 137 -> 127 (4.1 TB/s); 40 x 1024 from K = 32000 53 -> 41; 40 x 32000 from K = 1024 (KS) 54 -> 34; 128 x 32000 from K = 4096
-// 273 -> 181 (six products of pieces: 1.11 PFLOP/s in bfloat16, what a large product reaches here); 128 x 4096 from K = 32000 (KS)
-// 299 -> 186.
+// 115 (in two splits, joined by a further launch) -> 97 us (5.4 TB/s), where the step before has just updated that matrix
+// 137 -> 127 (4.1 TB/s), with three models in turn 172 -> 153; 40 x 1024 from K = 32000 53 -> 41; 40 x 32000 from K = 1024 (KS)
+// 54 -> 34; 128 x 32000 from K = 4096 273 -> 181 (six products of pieces: 1.11 PFLOP/s in bfloat16, what a large product reaches
+// here); 128 x 4096 from K = 32000 (KS) 299 -> 186.
 // The stream bounds up to 64 rows (without its MFMAs the kernel takes as long), the matrix pipe beyond.
 // ---------------------------------------------------------------------------------------------
 template <int MT, bool KS, bool KT>
@@ -423,7 +437,7 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
         for (int i = 0; i < NQ; ++i) {
             uint32_t h[2], m[2], w[2];
 #pragma unroll
-            for (int e = 0; e < 2; ++e) split3(d[i][2 * e], d[i][2 * e + 1], h[e], m[e], w[e], qtop);
+            for (int e = 0; e < 2; ++e) split3(x3_up(KS) * d[i][2 * e], x3_up(KS) * d[i][2 * e + 1], h[e], m[e], w[e], qtop);
             unsigned char *dst = base + i * 2048;   // 32 rows on
             *(u32x2 *)dst = (u32x2){h[0], h[1]};
             *(u32x2 *)(dst + PL * 16) = (u32x2){m[0], m[1]};
@@ -538,7 +552,15 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
         for (int j = 0; j < MT; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
-                acc[t][j][r] += fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f;
+                acc[t][j][r] = (acc[t][j][r] + (fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f)) * x3_down(KS);
+    bool finite = true;
+    if (KS)
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) finite &= fabsf(acc[t][j][r]) < INFINITY;
     // the largest magnitudes of Q's rows and of this wave's share of P
     for (int o = 32; o > 0; o >>= 1) { ptop = fmaxf(ptop, __shfl_xor(ptop, o)); qtop = fmaxf(qtop, __shfl_xor(qtop, o)); }
     if ((tid2 & 63) == 0) tops[wave] = qtop;
@@ -546,7 +568,7 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
     qtop = tops[0];
 #pragma unroll
     for (int w = 1; w < 8; ++w) qtop = fmaxf(qtop, tops[w]);
-    if (!pieces_hold(ptop) || !pieces_hold(qtop)) {
+    if (!pieces_hold(ptop, false) || !pieces_hold(qtop, KS) || !__all(finite)) {
         // this wave's k once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds k = g of row i), four k a step
 #pragma unroll
         for (int t = 0; t < TN; ++t)
@@ -639,10 +661,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     const bool edge = n0 + BN > N, whole = !edge && m0 + BM <= M, second = nx > nl;
     f32x2 xv[8];
     float gtop = 0.f, xtop = 0.f, gsum = 0.f;   // largest magnitudes, this thread's share of its column's sum
-    // EXACT: both operands times 2^24.  Every float is then a multiple of 2^-125, and so are its pieces: none is below the smallest
-    // normal bfloat16.
-    constexpr float UP = EXACT ? 0x1p24f : 1.f, DOWN = EXACT ? 0x1p-48f : 1.f;
-    auto holds = [](float top) { return EXACT ? top < 0x1.ffp127f : pieces_hold(top); };
+    constexpr float UP = x3_up(EXACT), DOWN = x3_down(EXACT) * x3_down(EXACT);
     auto load_x = [&](int r0) __attribute__((always_inline)) {
         if (r0 + 32 <= rows && N > 1 && N < 1 << 25) {
             unsigned off = 4u * (8u * lg * (unsigned)N + nl);
@@ -814,7 +833,7 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     __syncthreads();
     if (bias && n0 == 0 && wave == 0 && m0 + l < M) bias[m0 + l] += alpha * ((bsum[0][l] + bsum[1][l]) + (bsum[2][l] + bsum[3][l]));
     gtop = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
-    if (!holds(gtop) || !holds(xtop) || !__all(finite)) {
+    if (!pieces_hold(gtop, EXACT) || !pieces_hold(xtop, EXACT) || !__all(finite)) {
         // once more on the fp32 matrix pipe (16x16x4: lane (i, g) holds r = g of column i), four r a step
 #pragma unroll
         for (int t = 0; t < TN; ++t)

@@ -186,6 +186,47 @@ def test_small_operands_of_a_streamed_product(n, weights):
     assert _rel(-w.T[:n], g.astype(np.float64) @ w_lm.astype(np.float64)) < bound(V)
 
 
+@pytest.mark.parametrize("n,V,H,streams", [(20, 4099, 1001, True), (40, 4099, 1001, True), (48, 5056, 1024, True), (20, 300, 64, False),
+                                          (40, 300, 130, False)])
+@pytest.mark.parametrize("small", [-110, -125, -140])
+def test_input_gradients_of_values_of_any_size(n, V, H, streams, small):
+    """Gradients of which every second row is in units of 2^small, beside rows around 2^20 in the same tile: each row as exact as
+    by itself.  Bound as for sums, and for results below the smallest normal float, whole multiples of 2^-149, half of one for
+    each split of a sum and one for the product with SiLU'(0) = 1/2, which the learning rate doubles.  An identity for h makes the
+    update, by up to 48 rows, a copy of the input gradient."""
+    import torch
+    import paper_2408_08146_amd as KO
+    tiles, splits = form(n, H, V, True, _room(n, H))
+    assert bool(tiles) == streams
+    rng = np.random.default_rng(n)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    g = (rng.normal(size=(n, V)) * np.where(np.arange(n) % 2, 2.0 ** 20, 2.0 ** small)[:, None]).astype(np.float32)
+    w_lm = rng.normal(size=(V, H)).astype(np.float32)
+    m, w = min(n, H), dev(np.zeros((H, H)))
+    KO.MedusaHeadTrainer([w], dev(w_lm)).step(dev(np.eye(n, H)), dev(g), 2.0)
+    got, want = -w.T[:m].double().cpu().numpy(), (g.astype(np.float64) @ w_lm.astype(np.float64))[:m]
+    bound = 1.15 * 2.53e-8 * np.sqrt((V + 1) / 2)
+    off = np.linalg.norm(got - want, axis=1)
+    assert (off <= bound * np.linalg.norm(want, axis=1) + np.sqrt(H) * (splits / 2 + 1) * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("n,V,H,streams", [(20, 4099, 1001, True), (200, 5056, 1024, True), (20, 300, 64, False), (100, 300, 130, False)])
+@pytest.mark.parametrize("gv,wv", [(1.998, 0.9999 * 2.0 ** 127), (1.3 * 2.0 ** 60, 1.7 * 2.0 ** 50), (1.3 * 2.0 ** 110, 1.7 * 2.0 ** -60)])
+def test_input_gradients_near_overflow(n, V, H, streams, gv, wv):
+    """A product of 0.998 of the largest float, whose first pieces alone, rounded up, are past it, and products and factors that
+    would be past it times 2^24"""
+    import torch
+    import paper_2408_08146_amd as KO
+    assert bool(form(n, H, V, True, _room(n, H))[0]) == streams
+    g, w_lm = torch.zeros(n, V, device="cuda"), torch.zeros(V, H, device="cuda")
+    g[:, V - 2], w_lm[V - 2] = gv, wv
+    w = torch.zeros(H, H, device="cuda")
+    KO.MedusaHeadTrainer([w], w_lm).step(torch.eye(n, H, device="cuda"), g, 1.0)
+    want = g[0, V - 2].double() * w_lm[V - 2, 0].double() / 2   # SiLU'(0)
+    m = min(n, H)
+    assert ((w.double().T[:m] / -want - 1).abs() <= 2.0 ** -23).all()
+
+
 @pytest.mark.parametrize("rows,H", [(1, 1), (33, 1), (32, 2), (31, 63), (32, 65), (33, 64), (64, 127), (97, 128), (127, 129), (128, 193), (129, 130),
                                     (160, 191), (256, 66), (257, 515), (20, 1030)])
 @pytest.mark.parametrize("scale", [0, -118])
