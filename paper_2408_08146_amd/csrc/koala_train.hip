@@ -254,21 +254,20 @@ __global__ __launch_bounds__(256, BM == 32 ? 4 : 2) void k_gemm_x3(const float *
             if (c + 3 < c1) chunk(c + 3, std::integral_constant<int, 3>{});
         }
     }
+    bool finite = true;   // PKS: every sum
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
-                acc[i][j][r] = (acc[i][j][r] + (fabsf(acc[i][j][r]) < INFINITY ? low[i][j][r] : 0.f)) * x3_down(PKS);
-    bool finite = true;
-    if (PKS)
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) finite &= fabsf(acc[i][j][r]) < INFINITY;
+            for (int r = 0; r < 4; ++r) {
+                f32x4 &sum = acc[i][j];
+                if (PKS) {   // one that has overflowed is taken anew below, whatever the small terms make of it
+                    sum[r] = (sum[r] + low[i][j][r]) * x3_down(PKS);
+                    finite &= fabsf(sum[r]) < INFINITY;
+                } else         // it stays as it is: the small terms may be of the other sign
+                    sum[r] += fabsf(sum[r]) < INFINITY ? low[i][j][r] : 0.f;
+            }
     // every thread has cut up its share of both operands: the tile's largest magnitudes
     __shared__ float tops[2][4];
     for (int o = 32; o > 0; o >>= 1) { ptop = fmaxf(ptop, __shfl_xor(ptop, o)); qtop = fmaxf(qtop, __shfl_xor(qtop, o)); }
@@ -546,21 +545,20 @@ __global__ __launch_bounds__(512, 2) void k_stream_x3(const float *__restrict__ 
     int tid2 = threadIdx.x;
     asm volatile("" : "+v"(tid2));
     const int li2 = tid2 & 15, lg2 = (tid2 & 63) >> 4;
+    bool finite = true;   // KS: every sum
 #pragma unroll
     for (int t = 0; t < TN; ++t)
 #pragma unroll
         for (int j = 0; j < MT; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
-                acc[t][j][r] = (acc[t][j][r] + (fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f)) * x3_down(KS);
-    bool finite = true;
-    if (KS)
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-            for (int j = 0; j < MT; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) finite &= fabsf(acc[t][j][r]) < INFINITY;
+            for (int r = 0; r < 4; ++r) {
+                f32x4 &sum = acc[t][j];
+                if (KS) {   // one that has overflowed is taken anew below, whatever the small terms make of it
+                    sum[r] = (sum[r] + low[t][j][r]) * x3_down(KS);
+                    finite &= fabsf(sum[r]) < INFINITY;
+                } else         // it stays as it is: the small terms may be of the other sign
+                    sum[r] += fabsf(sum[r]) < INFINITY ? low[t][j][r] : 0.f;
+            }
     // the largest magnitudes of Q's rows and of this wave's share of P
     for (int o = 32; o > 0; o >>= 1) { ptop = fmaxf(ptop, __shfl_xor(ptop, o)); qtop = fmaxf(qtop, __shfl_xor(qtop, o)); }
     if ((tid2 & 63) == 0) tops[wave] = qtop;
@@ -812,20 +810,15 @@ __global__ __launch_bounds__(256, 3) void k_update_x3(const float *__restrict__ 
     if (!FEW) load_old();
     __builtin_amdgcn_sched_barrier(0);
     multiply(nck - 1);
+    bool finite = true;   // every sum; one that has overflowed is taken anew below, whatever the small terms make of it
 #pragma unroll
     for (int t = 0; t < TN; ++t)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)   // a sum that has overflowed stays as it is: the small terms may be of the other sign
-                acc[t][j][r] = (acc[t][j][r] + (fabsf(acc[t][j][r]) < INFINITY ? low[t][j][r] : 0.f)) * DOWN;
-    bool finite = true;
-#pragma unroll
-    for (int t = 0; t < TN; ++t)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
+        for (int j = 0; j < TM; ++j) {
+            acc[t][j] = (acc[t][j] + low[t][j]) * DOWN;
 #pragma unroll
             for (int r = 0; r < 4; ++r) finite &= fabsf(acc[t][j][r]) < INFINITY;
+        }
     // the largest magnitudes of G's columns and of this wave's columns of X
     for (int o = 32; o > 0; o >>= 1) { gtop = fmaxf(gtop, __shfl_xor(gtop, o)); xtop = fmaxf(xtop, __shfl_xor(xtop, o)); }
     if (l == 0) tops[wave] = gtop;
