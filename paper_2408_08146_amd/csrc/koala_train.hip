@@ -1071,13 +1071,15 @@ void launch_update(hipStream_t st, const float *G, const float *G2, const float 
 void gemm_update(hipStream_t st, const float *G, const float *X, float *W, int M, int N, int rows, float lr, float *bias = nullptr,
                  const float *G2 = nullptr) {
     // Plain multiply-adds up to where the matrix takes as long either way.  A head step with this update and little else, us, them
-    // and k_update_x3: 1000 x 1000 by 4 rows 19.6 and 22.6, by 16 20.8 and 22.7; 3000 x 3000 by 8 38.9 and 39.3, 4096 x 4096
-    // 52.5 and 52.3; 1500 x 1500 by 16 26.8 and 27.1, 2048 x 2048 32.4 and 31.1; by 20 27.8 and 27.3 and 34.1 and 30.8.  A
-    // matrix of few rows leaves most of a tile empty: a discriminator step of one layer, 250 x 250 at 20 positions 26.8 and 28.8.
+    // and k_update_x3, on one matrix / on so many in turn that each comes from memory: by 4 rows 1000 x 1000 22.6 / 22.3 and
+    // 23.8 / 24.0, 1500 x 1500 25.0 / 26.2 and 26.6 / 28.5; by 8 2048 x 2048 29.7 / 31.9 and 30.2 / 32.5, 3000 x 3000 38.7 / 43.9 and
+    // 38.1 / 43.7, 4096 x 4096 55.8 / 65.7 and 50.3 / 60.1; by 16 1250 x 1250 25.8 / 26.5 and 26.0 / 28.8, 1500 x 1500 26.0 / 27.5
+    // and 26.5 / 28.6; by 20 (one matrix) 1500 x 1500 27.8 and 27.3, 2048 x 2048 34.1 and 30.8.  A matrix of few rows leaves most
+    // of a tile empty: a discriminator step of one layer, 250 x 250 at 20 positions 26.8 and 28.8.
     // Two rows at any size: the largest error of an element is 1.97 roundings of its terms' magnitudes then and 2.77 on the matrix
     // pipe, whose sums are cut off (at three rows 2.81 and 2.70); such a step at 4096 x 32000 takes 370 us instead of 356.
     const size_t size = (size_t)M * N;
-    if (rows == 2 || (rows <= 8 ? size <= 1u << 24 : rows <= 16 ? size <= 5u << 19 : rows <= 24 && M <= 16 && size <= 5u << 19)) {
+    if (rows == 2 || (rows <= 8 ? size <= 1u << 23 : rows <= 16 ? size <= 5u << 19 : rows <= 24 && M <= 16 && size <= 5u << 19)) {
         switch ((rows + 7) / 8) {
             case 1: return launch_update<8>(st, G, G2, X, W, bias, M, N, rows, -lr);
             case 2: return launch_update<16>(st, G, G2, X, W, bias, M, N, rows, -lr);

@@ -418,7 +418,7 @@ def _one_layer(n, H, V, w, bias, h, q, d, w_lin, lr):
     return out.double().cpu().numpy(), ds, w, h
 
 
-@pytest.mark.parametrize("rows,H", [(1, 1), (1, 255), (7, 256), (8, 257), (8, 4096), (8, 4100), (9, 130), (15, 1030), (16, 1619), (16, 1620),
+@pytest.mark.parametrize("rows,H", [(1, 1), (1, 255), (7, 256), (8, 257), (8, 2896), (8, 2897), (9, 130), (15, 1030), (16, 1619), (16, 1620),
                                     (17, 1000), (24, 515)])
 def test_update_of_a_small_or_large_matrix(rows, H):
     """-g^T h on both sides of the sizes up to which an update by 8 and 16 rows is plain multiply-adds, with columns of a wave of
@@ -471,7 +471,7 @@ def test_update_by_few_rows_of_small_beside_large_values(n, small):
     elements are no less exact for it, also where a factor is below the smallest normal float.  Within (n + 10) roundings of the
     terms' magnitudes as below (weights too small to be normal floats are rounded by their sigmoids' factors at 2^-149: twelve
     times that)."""
-    H, V = 4200, 4100   # more than 2^24 elements: the matrix pipe's form
+    H, V = 4200, 4100   # more than 2^23 elements: the matrix pipe's form
     rng = np.random.default_rng(n)
     w = (rng.normal(size=V) * np.where(np.arange(V) % 2, 2.0 ** 40, 2.0 ** small)).astype(np.float32)
     h = (rng.normal(size=(n, H)) * np.where(np.arange(H) % 3, 2.0 ** 30, 2.0 ** small)).astype(np.float32)
